@@ -50,6 +50,9 @@ extern "C" size_t fbq_packed_bytes(const fbq_desc *d)
 // for the sets): the sets take about 2 + sets x (2.2 + 0.165 MC), the GEMM 30 + 0.135 MC + 1.5 K / 1024 (with INT3
 // and INT4 alike).  Examples, sets / GEMM: 8192 -> 28672 at 32 tokens 84 / 71, at 64 160 / 83; 28672 -> 8192 at 32
 // tokens 80 / 101, at 48 122 / 101; 4096 -> 11008 at 64 tokens 35 / 41; 13824 -> 5120 at 48 tokens 50 / 62.
+// The GEMM has become faster since (28 us at 64 tokens of 4096 -> 11008, 40 at 48 of 13824 -> 5120), the line has not moved:
+// the sets multiply the codes exactly, the GEMM rounds the weights to fp16 (relative error of y 2.2e-4 and 2.9e-4), and a
+// call that has had the smaller error keeps it.
 static bool sets_beat_gemm(int M, int N, int K)
 {
     const int sets = (M + kDecodeMaxM - 1) / kDecodeMaxM;

@@ -3,39 +3,39 @@
 //   y[M,N] = x[M,K] . Wq[N,K]^T + t[M,r] . B[r,N],   t = x . A
 //
 // Three launches (two without a sub-branch): the down-projection t = x.A as a small MFMA GEMM over K slices
-// ("requires relatively minimal time" in the paper's words; its blocks also write the re-ordered copy of x the
-// fused kernel wants), the slices' sums as t_hi | t_lo, and the fused kernel, which de-quantizes in registers,
+// ("requires relatively minimal time" in the paper's words; its blocks also write the re-ordered copies of x and of the
+// scales the fused kernel wants), the slices' sums as t_hi | t_lo, and the fused kernel, which de-quantizes in registers,
 // multiplies on the matrix cores and folds the up-projection into the same accumulators as 2r extra K columns,
-// so y is written once.  Three super-steps of K are under way at any time (one multiplied, two on their way from
-// memory), and the loads of the one after next are issued a few at a time between the matrix instructions of the
-// current one: a wave that asks for all fourteen at the top of a round waits in the queue of the CU's address unit
-// behind the other seven waves' requests with the matrix pipe idle (measured on 4096 -> 11008 at 1024 tokens: of
-// 135 us, 46 went when the rounds issued no loads at all; row-scattered loads - one row per lane - are the
-// expensive kind, whatever their width).  Tiles are 64, 96 or 128 rows high, whichever fills the compute units most evenly; a layer with at
-// most one tile per CU runs blocks of eight waves, two groups that split K and meet in LDS; only a layer with
-// fewer tiles than half the CUs (256 tokens into a few thousand outputs) still splits K over blocks, through fp32
-// partial results and a small summing launch.
+// so y is written once.  Where there are too few tiles for the CUs, K is split over blocks through fp32 partial results
+// and a small summing launch.
 //
-// Fused kernel.  Block = 4 waves (or two groups of 4) side by side along N; block tile (32 TM) x 256, TM = 2, 3
-// or 4; a wave owns TM x 2 tiles of v_mfma_f32_32x32x16_f16.
-// K advances in super-steps of 128 (one quantization group):
+// Fused kernel.  Four waves side by side along N, block tile (32 TM) x 256, TM = 2, 3, 4, 6 or 8; a wave owns TM x 2
+// tiles of v_mfma_f32_32x32x16_f16.  With TM of 6 or 8 that is one wave per SIMD with up to 256 accumulator registers;
+// with less the block has eight waves, two groups that split K and meet in LDS.
+// K advances in steps of 64, half a quantization group, and everything a step reads comes out of LDS, copied there three
+// steps ahead by buffer_load ... lds (no registers): the activations, the packed words, and scale and zero.  With the
+// packed words loaded into registers instead - 32 rows per load, waited for by the compiler's count - the look-ahead
+// was worth a step less and the registers it took kept a wave from owning more than 96 rows.
 //   * activations: a small pre-pass rewrites x once into the order the kernel wants (see below);
-//     from there a (32 TM) x 128 fp16 tile per super-step is copied straight into LDS by
-//     global_load_lds_dwordx4 (no registers, three buffers); every wave reads all of it
-//     (TM fragments per K step of 16);
-//   * weights never touch LDS: lane (n = lane % 32, h = lane / 32) loads, for each half c of the
-//     super-step, the 32 codes k = 128u + 64c + 32h .. +31 of row n (INT4: one 16-byte load, INT3:
-//     one 12-byte load) and turns them into the 8 x fp16 operands of four K steps in registers.  The MFMA only
+//   * weights: lane (n = lane % 32, h = lane / 32) takes the 32 codes k = 64v + 32h .. +31 of row n (INT4: 16 bytes,
+//     INT3: 12) from LDS and turns them into the 8 x fp16 operands of four K steps of 16 in registers.  The MFMA only
 //     needs both operands to agree on which k sits in which slot, so the pre-pass puts the
 //     activations in the order the code extraction produces (pairs (c, c+4) for INT4, (f, f+5) for
-//     INT3), and it XORs the position of each 16-byte chunk within its 256-byte row segment with
-//     m % 16, so that the un-padded LDS rows are read without bank conflicts.
+//     INT3), and it XORs the position of each 16-byte piece within its 128-byte row segment with a key of
+//     the row, so that the un-padded LDS rows are read without bank conflicts.
 //   * de-quantization: one v_and_or_b32 puts a code into the mantissa of 1024.0 (or 1024 + 16c,
 //     1024 + 8c, 1024 + 64c for fields at higher bit offsets); one exact packed add or fma recovers
 //     the code minus the integer zi nearest to the zero point, d = q - zi; the weight is
 //     fma(d, s, c) with c = fp16((zi - z) s): one rounding of the weight (2^-11 relative) and one of
 //     c, which is at most 2^-12 of a quantization step.
 // The sub-branch enters as t = t_hi + t_lo (two fp16 halves, ~22 bits) against B^T rows.
+//
+// What bounds it: the matrix cores at the clock they leave.  2048 tokens into 8192 x 8192 (INT4, no sub-branch, us per
+// call): 256-row tiles 252; with the de-quantization left out 230, without copies 241, without reading activations 248,
+// with nothing but matrix instructions 209 (they alone draw the clock down to 1.9 - 2.0 GHz).  By tile height, us per CU
+// and step of 64: 256 rows 1.8, 192 rows 1.43, 128 rows 0.97, 96 rows 0.77, 64 rows 0.59: a step costs about 0.1 and
+// each 32 rows 0.21.  The loop before this one (packed words in registers, compiler waits of vmcnt(0) at the top of every
+// round) took 977 us for 2048 tokens of 8192 -> 28672 without a sub-branch where this takes 870.
 #include <hip/hip_fp16.h>
 
 #include <type_traits>
@@ -52,32 +52,59 @@ typedef uint32_t uint4v_t __attribute__((ext_vector_type(4)));
 typedef uint32_t uint3v_t __attribute__((ext_vector_type(3)));
 
 constexpr int kTN = 2;               // 32-column MFMA tiles per wave along N
-constexpr int kWavesN = 4;           // waves per block, side by side along N
+constexpr int kWavesN = 4;           // waves side by side along N
 constexpr int kBN = kWavesN * kTN * 32;   // 256
-constexpr int kBK = 128;             // K per super-step: one quantization group
-constexpr int kLdsRow = 256;         // bytes per activation row in LDS: 16 chunks of 8 fp16, chunk l at l ^ (m % 16)
+constexpr int kStepK = 64;           // K per step: half a quantization group
+constexpr int kXRow = 128;           // bytes per activation row and step in LDS: 8 pieces of 8 fp16, piece l at l ^ piece_key(row)
 constexpr int kXcds = 8;             // accelerator dies, each with its own L2
-constexpr int kStages = 3;           // super-steps in flight: the one worked on and the next two on their way from memory
-constexpr int kRowPad = 128;         // the arranged copy of x has its row count rounded up to this, plus one more (a 96-row tiling overshoots a multiple of 128)
+constexpr int kStages = 3;           // steps in LDS: the one worked on and the next two on their way from memory
+
+// Sixteen bytes per lane from global memory straight into LDS, `lane_off` + `row_off` bytes behind the descriptor's
+// base (row_off the same for all lanes): lane l's go to `dst` + 16 l, dst wave-uniform.  Written as an instruction and
+// not with the builtin, because the compiler waits for EVERY load in flight before the first LDS read behind a builtin
+// copy - it cannot tell the buffer being read from the ones being filled - which undoes any look-ahead: in an earlier
+// form of the fused kernel every round began with vmcnt(0).  The instruction has no destination register; whoever reads
+// a copy waits for it by count and passes a barrier (both with a memory clobber).  The compiler's own counted waits only
+// get stricter by the copies it does not know of.  Nothing else in these kernels uses M0.
+__device__ __forceinline__ uint32_t lds_offset(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p; }
+__device__ __forceinline__ void copy16_to_lds(__amdgpu_buffer_rsrc_t buf, int lane_off, int row_off, uint32_t dst)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(lane_off), "s"(buf), "s"(row_off));
+}
+__device__ __forceinline__ void copy12_to_lds(__amdgpu_buffer_rsrc_t buf, int lane_off, int row_off, uint32_t dst)   // (12 bytes per lane, but 16 l apart in LDS)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx3 %1, %2, %3 offen lds" ::"s"(dst), "v"(lane_off), "s"(buf), "s"(row_off));
+}
+__device__ __forceinline__ void copy4_to_lds(__amdgpu_buffer_rsrc_t buf, int lane_off, int row_off, uint32_t dst)    // (4 bytes: dst + 4 l)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(dst), "v"(lane_off), "s"(buf), "s"(row_off));
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, long bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+
+// Piece c (16 bytes) of a row is stored at position c ^ piece_key(row): 8 or 16 consecutive rows reading the same c touch
+// every bank once, whether the LDS serves 128 or 256 bytes per clock.
+__host__ __device__ __forceinline__ constexpr int piece_key(int row) { return ((row >> 1) & 7) ^ ((row & 1) << 2); }
 
 __device__ __forceinline__ half2_t h2_of(uint32_t v) { return __builtin_bit_cast(half2_t, v); }
 __device__ __forceinline__ half2_t h2_splat(half_t v) { return half2_t{v, v}; }
 
 struct PrefillParams {
     const uint32_t *qw;
-    const uint16_t *scales;
-    const uint16_t *zeros;
+    const uint32_t *sz;    // [G][Np] scale (low half) and zero (high half) by group, written by the pre-pass
     const uint16_t *Bt;    // [N][r]
-    const uint16_t *xp;    // [M rounded up to kRowPad][K], arranged by fbq_arrange_x_kernel
+    const uint16_t *xp;    // [M][K], arranged by the pre-pass
     const uint16_t *thl;   // [M][2r]: t_hi | t_lo
     uint16_t *y;           // [M][N]
     int M, N, K, r;
-    int row_words, G;
+    int row_words, G, Np;  // Np: N rounded up to kBN
     int row_blocks;        // ceil(M / block tile rows)
     int full_slots;        // tiles per XCD that belong to column blocks this XCD has to itself: (column blocks / 8) * row_blocks
     int full_cols;         // column blocks dealt out whole, eight at a time: (column blocks / 8) * 8
     int rem_tiles;         // tiles of the column blocks left over, dealt out singly over the XCDs
-    int ksplit;            // blocks that split K for the same tile (1: none; more only where there are too few tiles for half the CUs)
+    int ksplit;            // blocks that split K for the same tile (1: none)
     float *ypart;          // ksplit > 1 only: [ksplit][M][N] fp32 partial results, added up by fbq_sum_parts_kernel
 };
 
@@ -95,21 +122,21 @@ __device__ __forceinline__ constexpr int slot_source(int s)
     return 10 * w + (t / 2) + 5 * (t % 2);
 }
 
-// The lane's 32 codes of one super-step as 16 fp16 pairs s * (q - z), in slot order.
+// The lane's 32 codes of one step as 16 fp16 pairs s * (q - z), in slot order, four pairs (one matrix operand) at a time.
 template <int BITS>
 struct WeightRegs {
     static constexpr int kWords = BITS == 4 ? 4 : 3;
+    static constexpr int kRowBytes = 2 * kWords * 4;    // bytes of a weight row per step: two blocks of 32 codes ...
+    static constexpr int kLdsRow = 32;                  // ... in LDS 16 bytes apart, used up or not
     uint32_t w[kWords];
 
-    // The 32 codes at byte offset `off` of the packed buffer: exactly one load instruction (the kernel counts the
-    // loads it has in flight).
-    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t qbuf, int off)
+    __device__ __forceinline__ void read(const unsigned char *lds)
     {
         if constexpr (BITS == 4) {
-            const uint4v_t q = __builtin_amdgcn_raw_buffer_load_b128(qbuf, off, 0, 0);
+            const uint4v_t q = *reinterpret_cast<const uint4v_t *>(lds);
             w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
         } else {
-            const uint3v_t q = __builtin_amdgcn_raw_buffer_load_b96(qbuf, off, 0, 0);
+            const uint3v_t q = *reinterpret_cast<const uint3v_t *>(lds);   // (16-byte aligned)
             w[0] = q.x; w[1] = q.y; w[2] = q.z;
         }
     }
@@ -129,10 +156,10 @@ struct WeightRegs {
         half2_t k0;   // -(1024 + zi): field at bit 0
         half2_t k1;   // INT4: -(64 + zi), field at bit 4;  INT3: -(128 + zi), field at bit 3
         half2_t k2;   // INT3: -(16 + zi), field at bit 6
-        __device__ __forceinline__ Affine(uint32_t s_bits, uint32_t z_bits)
+        __device__ __forceinline__ void set(uint32_t sz)
         {
-            const float sf = (float)__builtin_bit_cast(half_t, (uint16_t)s_bits);
-            const float zf = (float)__builtin_bit_cast(half_t, (uint16_t)z_bits);
+            const float sf = (float)__builtin_bit_cast(half_t, (uint16_t)sz);
+            const float zf = (float)__builtin_bit_cast(half_t, (uint16_t)(sz >> 16));
             const float zi = __builtin_rintf(zf);
             s = h2_splat((half_t)sf);
             c = h2_splat((half_t)((zi - zf) * sf));
@@ -142,65 +169,62 @@ struct WeightRegs {
         }
     };
 
-    // INT4: word j alone gives the four pairs of K step j.
-    __device__ __forceinline__ void dequant_word(int j, const Affine &f, uint32_t k6400, half2_t (&out)[4]) const
+    // pair p of 16
+    __device__ __forceinline__ half2_t pair(int p, const Affine &f, uint32_t k6400) const
     {
-        const half2_t r16 = h2_splat((half_t)0.0625f);
-        const uint32_t a = w[j], b = w[j] >> 8;
-        const half2_t d0 = field(a, 0x000F000Fu, k6400) + f.k0;
-        const half2_t d1 = field(a, 0x00F000F0u, k6400) * r16 + f.k1;
-        const half2_t d2 = field(b, 0x000F000Fu, k6400) + f.k0;
-        const half2_t d3 = field(b, 0x00F000F0u, k6400) * r16 + f.k1;
-        out[0] = d0 * f.s + f.c;
-        out[1] = d1 * f.s + f.c;
-        out[2] = d2 * f.s + f.c;
-        out[3] = d3 * f.s + f.c;
-    }
-
-    // INT3: all 32 codes of the block, 16 pairs in slot order.
-    __device__ __forceinline__ void dequant(const Affine &f, uint32_t k6400, half2_t (&out)[16]) const
-    {
-        const half2_t r8 = h2_splat((half_t)0.125f), r64 = h2_splat((half_t)0.015625f);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const uint32_t a = w[j], b = w[j] >> 9;
-            const half2_t d0 = field(a, 0x00070007u, k6400) + f.k0;
-            const half2_t d1 = field(a, 0x00380038u, k6400) * r8 + f.k1;
-            const half2_t d2 = field(a, 0x01C001C0u, k6400) * r64 + f.k2;
-            const half2_t d3 = field(b, 0x00070007u, k6400) + f.k0;
-            const half2_t d4 = field(b, 0x00380038u, k6400) * r8 + f.k1;
-            out[5 * j + 0] = d0 * f.s + f.c;
-            out[5 * j + 1] = d1 * f.s + f.c;
-            out[5 * j + 2] = d2 * f.s + f.c;
-            out[5 * j + 3] = d3 * f.s + f.c;
-            out[5 * j + 4] = d4 * f.s + f.c;
+        half2_t d;
+        if constexpr (BITS == 4) {                      // word p / 4: fields at bits 0, 4, 8, 12 of its halves
+            const uint32_t a = p % 4 < 2 ? w[p / 4] : w[p / 4] >> 8;
+            if (p % 2 == 0) d = field(a, 0x000F000Fu, k6400) + f.k0;
+            else d = field(a, 0x00F000F0u, k6400) * h2_splat((half_t)0.0625f) + f.k1;
+        } else if (p == 15) {                           // the two codes spread over bits 15 and 31 of the words
+            const uint32_t e = ((w[0] >> 15) & 0x00010001u) | ((w[1] >> 14) & 0x00020002u) | ((w[2] >> 13) & 0x00040004u);
+            d = h2_of(e | 0x64006400u) + f.k0;
+        } else {                                        // word p / 5: fields at bits 0, 3, 6, 9, 12 of its halves
+            const uint32_t a = p % 5 < 3 ? w[p / 5] : w[p / 5] >> 9;
+            if (p % 5 % 3 == 0) d = field(a, 0x00070007u, k6400) + f.k0;
+            else if (p % 5 % 3 == 1) d = field(a, 0x00380038u, k6400) * h2_splat((half_t)0.125f) + f.k1;
+            else d = field(a, 0x01C001C0u, k6400) * h2_splat((half_t)0.015625f) + f.k2;
         }
-        const uint32_t e = ((w[0] >> 15) & 0x00010001u) | ((w[1] >> 14) & 0x00020002u) | ((w[2] >> 13) & 0x00040004u);
-        out[15] = (h2_of(e | 0x64006400u) + f.k0) * f.s + f.c;
+        return d * f.s + f.c;
+    }
+    __device__ __forceinline__ half8_t operand(int i, const Affine &f, uint32_t k6400) const
+    {
+        const half2_t a = pair(4 * i, f, k6400), b = pair(4 * i + 1, f, k6400), c = pair(4 * i + 2, f, k6400), d = pair(4 * i + 3, f, k6400);
+        return half8_t{a.x, a.y, b.x, b.y, c.x, c.y, d.x, d.y};
     }
 };
 
-__device__ __forceinline__ half8_t pack8(half2_t a, half2_t b, half2_t c, half2_t d)
-{
-    return half8_t{a.x, a.y, b.x, b.y, c.x, c.y, d.x, d.y};
-}
+// TM: 32-row tiles of a wave and of the block.  KG: groups of four waves that split K for the same tile inside one block
+// (1 or 2): the groups take consecutive ranges of K, and group 1 hands its accumulators to group 0 through LDS at the
+// end, so nothing but y is ever written.  One block per CU either way: with TM of 6 or 8 a wave has a SIMD, and its 512
+// registers, to itself; with less, two waves share one.
+template <int BITS, int TM, int KG>
+struct GemmTile {
+    static constexpr int kBM = 32 * TM;
+    static constexpr int kThreads = 64 * kWavesN * KG;
+    static constexpr int kXBytes = kBM * kXRow, kQBytes = kBN * WeightRegs<BITS>::kLdsRow;
+    static constexpr int kStepBytes = kXBytes + kQBytes;                // one step of one K group
+    static constexpr int kSzBytes = kWavesN * KG * 2 * 256;        // two groups' scales and zeros per wave
+    static constexpr int kOutRow = 64 * 2 + 16;                         // a wave's output rows in LDS: 64 fp16, 144 bytes apart
+    static constexpr int kMain = KG * kStages * kStepBytes + kSzBytes;
+    static constexpr int kUp = kBN * 128 + kBM * 256;                   // 64 taps of the block's rows of B^T and of t_hi | t_lo
+    static constexpr int kHand = KG > 1 ? TM * kTN * 16 * 64 * 4 * kWavesN : 0;
+    static constexpr int kOut = kWavesN * 32 * kOutRow;
+    static constexpr int kLds = std::max(std::max(kMain, kUp), std::max(kHand, kOut));
+    static_assert(kLds <= 160 * 1024, "a block's buffers must fit the CU's LDS");
+};
 
-// KG: groups of four waves that split K for the same tile inside one block (1 or 2).  A layer with too few tiles
-// to give every CU two blocks of four waves runs one block of eight waves per CU instead: the groups take
-// alternate halves of K and group 1 hands its accumulators to group 0 through LDS at the end, so nothing but y
-// is ever written.
-// PAIRS: the number of groups per row is even, so scale and zero of six consecutive super-steps are three aligned dwords.
-template <int BITS, int TM, int KG, bool PAIRS>
-__global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))) void fbq_gemm_kernel(const PrefillParams p)
+template <int BITS, int TM, int KG>
+__global__ __launch_bounds__((GemmTile<BITS, TM, KG>::kThreads)) __attribute__((amdgpu_waves_per_eu(TM > 4 ? 1 : 2, TM > 4 ? 1 : 2))) void fbq_gemm_kernel(const PrefillParams p)
 {
-    constexpr int kBM = 32 * TM;
-    constexpr int kCopies = kBM / 16;                   // 1 KiB wave copies (4 rows each) per wave and super-step
-    __shared__ __attribute__((aligned(1024))) unsigned char lds_all[KG][kStages][kBM * kLdsRow];
-    static_assert(sizeof(lds_all) <= 160 * 1024, "a block's activation buffers must fit the CU's LDS");
+    using T = GemmTile<BITS, TM, KG>;
+    constexpr int kBM = T::kBM;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[T::kLds];   // [KG][kStages][x tile | packed words], then [wave][2][64] scale | zero
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int kg = __builtin_amdgcn_readfirstlane(tid >> 8);       // K group of this wave
-    const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);   // its position along N
+    const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = wave_all / kWavesN, wave = wave_all % kWavesN;   // K group of this wave, position along N
     const int col = lane & 31, h = lane >> 5;
     // Workgroups go to the eight XCDs round-robin by linear id, and each XCD has its own L2.  Give
     // every XCD its own column blocks (all row blocks of one column block run on the same XCD, one
@@ -220,25 +244,54 @@ __global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))
         bm = q % p.row_blocks;
         bn = p.full_cols + q / p.row_blocks;
     }
-    const int m0 = bm * kBM;
-    const int nw = bn * kBN + wave * (kTN * 32);
-    const int U_all = p.K / kBK;
-    const int shares = KG * p.ksplit;                   // K is shared out over the groups of a block and, for a layer with very few tiles, over blocks
-    int U_part = (U_all + shares - 1) / shares;
-    if (PAIRS) U_part = (U_part + 1) & ~1;              // an even first super-step: scale and zero come as aligned dwords
-    const int u0 = (part * KG + kg) * U_part, U = min(U_all, u0 + U_part);   // this group's super-steps: u0 .. U - 1 (at most U_part)
+    const int m0 = bm * kBM, n0 = bn * kBN;
+    const int nw = n0 + wave * (kTN * 32);
+    const int shares = KG * p.ksplit;                   // K is shared out over the groups of a block and, for a layer with few tiles, over blocks
+    const int U_part = (p.G + shares - 1) / shares;     // quantization groups per share
+    const int u0 = min((part * KG + kg) * U_part, p.G - 1);         // this wave's groups: u0 .. u0 + U - 1 (the last shares may have none)
+    const int U = max(0, min(U_part, p.G - (part * KG + kg) * U_part));
 
-    // this lane's weight rows (clamped: columns past N are computed on a valid row and never stored)
-    int nrow[kTN];
-#pragma unroll
-    for (int tn = 0; tn < kTN; ++tn) nrow[tn] = min(nw + tn * 32 + col, p.N - 1);
-
-    // activation tile: wave w copies rows [w kBM/4, (w+1) kBM/4) of the tile, four rows (1 KiB) per
-    // instruction; lane l moves chunk l % 16 of row l / 16 and the hardware puts it at LDS base + 16 l.
-    const uint16_t *xsrc = p.xp + (size_t)(m0 + wave * (kBM / 4) + (lane >> 4)) * p.K + (lane & 15) * 8;
-    // this lane's fragment address within a tile for K step 0 of row block 0; K step s = 4 c + i is
-    // logical chunk 8 c + 4 h + i, stored at that index ^ (row % 16)
-    const uint32_t a_lane = col * kLdsRow + (((4 * h) ^ (col & 15)) << 4);
+    // Everything the loop reads comes out of LDS, copied there without passing registers:
+    //   x      rows of 128 bytes, eight per copy;  rows past M are outside the descriptor
+    //   words  rows of 32 (24) bytes, the blocks of 32 codes side by side, 32 rows per copy;  rows past N likewise
+    //   sz     the wave's 64 rows' scale | zero of one group, one copy per group
+    const __amdgpu_buffer_rsrc_t xbuf = buffer_of(p.xp + (size_t)m0 * p.K, (long)min(kBM, p.M - m0) * p.K * 2);
+    const __amdgpu_buffer_rsrc_t qbuf = buffer_of(p.qw + (size_t)n0 * p.row_words, (long)min(kBN, p.N - n0) * p.row_words * 4);
+    const __amdgpu_buffer_rsrc_t sbuf = buffer_of(p.sz, (long)p.G * p.Np * 4);
+    constexpr int kPiece = WeightRegs<BITS>::kWords * 4;
+    const int xoff = (lane >> 3) * p.K * 2 + (lane & 7) * 16;
+    const int qoff = (lane >> 1) * p.row_words * 4 + (lane & 1) * kPiece;
+    const int soff = (nw + lane) * 4;
+    const uint32_t lds0 = lds_offset(lds);
+    const uint32_t ring0 = lds0 + kg * (kStages * T::kStepBytes);   // the group's ring of steps
+    const int sz_at = KG * kStages * T::kStepBytes + wave_all * 512; // the wave's two slots
+    constexpr int kLoadsX = TM, kLoadsQ = 2;       // copies per wave and step; one more, scale and zero, in the first step of a group
+    constexpr int kLoads = kLoadsX + kLoadsQ;
+    // copy j of step `st` (of this share: group st / 2, half st % 2), into stage `buf`.  Past the share's end: its last
+    // group again, never used - every wave issues the same number of copies, so that they can be waited for by count
+    auto issue_one = [&](int st, bool first_half, int buf, int j) __attribute__((always_inline)) {
+        const int u = min(u0 + (st >> 1), p.G - 1), half = first_half ? 0 : 1;
+        const uint32_t stage = ring0 + buf * T::kStepBytes;
+        if (j < kLoadsX) {
+            const int rows = (wave * kLoadsX + j) * 8;
+            copy16_to_lds(xbuf, xoff, rows * p.K * 2 + (2 * u + half) * kXRow, stage + rows * kXRow);
+        } else if (j < kLoads) {
+            const int rows = (wave * kLoadsQ + j - kLoadsX) * 32;
+            const int off = rows * p.row_words * 4 + (2 * u + half) * WeightRegs<BITS>::kRowBytes;
+            const uint32_t dst = stage + T::kXBytes + rows * WeightRegs<BITS>::kLdsRow;
+            if constexpr (BITS == 4) copy16_to_lds(qbuf, qoff, off, dst);
+            else copy12_to_lds(qbuf, qoff, off, dst);
+        } else if (j == kLoads && first_half) {
+            copy4_to_lds(sbuf, soff, u * p.Np * 4, lds0 + sz_at + ((st >> 1) & 1) * 256);
+        }
+    };
+    // What has to be complete at a barrier is waited for explicitly in front of it: __syncthreads() would wait for every
+    // copy in flight.  At most n of this wave's copies may still be on their way.
+    auto wait_and_meet = [&](auto N) __attribute__((always_inline)) {
+        constexpr int n = decltype(N)::value;
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(n) : "memory");
+    };
+    auto block_barrier = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
     float16_t acc[TM][kTN];
 #pragma unroll
@@ -248,211 +301,115 @@ __global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[tm][tn][v] = 0.0f;
 
-    // The packed words of one super-step (two code blocks, the k halves, per N tile), and scale and zero as fp16 bits.
-    // Scale and zero are loads of 32 different rows, as expensive for the load path as the 16-byte weight loads
-    // however few bytes they fetch (measured: a quarter of the kernel's time went into them when every second
-    // super-step fetched a dword of each).  With an even number of groups per row, six consecutive groups of a row
-    // from an even one on are three aligned dwords: one 12-byte load per row, array and six super-steps - the six
-    // rounds of the unrolled loop.  With an odd number of groups, one 2-byte load per super-step.
-    struct StepRegs {
-        WeightRegs<BITS> w[kTN][2];
-    };
-    struct SzRegs {
-        uint32_t s[kTN][3], z[kTN][3];                  // (single loads: element 0 only)
-    };
-    constexpr bool pairs = PAIRS;
-    const __amdgpu_buffer_rsrc_t qbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.qw), 0, (int)((size_t)p.N * p.row_words * 4), 0x00020000);
-    const int sz_bytes = (p.N * p.G * 2 + 3) & ~3;      // whole dwords: the range check is per dword
-    const __amdgpu_buffer_rsrc_t sbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.scales), 0, sz_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t zbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.zeros), 0, sz_bytes, 0x00020000);
-    int woff[kTN], goff[kTN];
-#pragma unroll
-    for (int tn = 0; tn < kTN; ++tn) {
-        woff[tn] = nrow[tn] * p.row_words * 4 + h * WeightRegs<BITS>::kWords * 4;
-        goff[tn] = nrow[tn] * p.G * 2;
-    }
-    // loads per super-step, each one instruction: the wait before a barrier names how many younger loads may stay in flight
-    constexpr int kLoadsW = kTN * 2, kLoadsSZ = kTN * 2, kLoadsX = kBM / 16;
     uint32_t k6400 = 0x64006400u;
     asm volatile("" : "+v"(k6400));                     // keep the constant in a VGPR for v_and_or_b32
 
-    // one super-step: eight K steps of 16 on the tile in lds[buf].  The activation fragments of K step
-    // i + 1 are fetched from LDS before the matrix instructions of step i are issued.
-    // (q, gi: the registers that hold scale and zero, and which of their six fp16 it is)
-    auto compute = [&](const StepRegs &sr, const SzRegs &q, int gi, int buf, auto &&loads_of_step) __attribute__((always_inline)) {
-        const int half_shift = 16 * (gi & 1);
-        const typename WeightRegs<BITS>::Affine aff[kTN] = {{(q.s[0][gi / 2] >> half_shift) & 0xFFFFu, (q.z[0][gi / 2] >> half_shift) & 0xFFFFu},
-                                                            {(q.s[1][gi / 2] >> half_shift) & 0xFFFFu, (q.z[1][gi / 2] >> half_shift) & 0xFFFFu}};
-        auto a_frag = [&](int tm, int step) __attribute__((always_inline)) {
-            const uint32_t off = a_lane ^ (uint32_t)((8 * (step / 4) + (step % 4)) << 4);
-            return *reinterpret_cast<const half8_t *>(&lds_all[kg][buf][off + tm * (32 * kLdsRow)]);
-        };
-        half2_t wv3[kTN][16];                           // INT3 only
-        auto b_frag = [&](int tn, int step) __attribute__((always_inline)) {
-            const int c = step / 4, i = step % 4;
-            if constexpr (BITS == 4) {
-                half2_t o[4];
-                sr.w[tn][c].dequant_word(i, aff[tn], k6400, o);
-                return pack8(o[0], o[1], o[2], o[3]);
+    // this lane's fragment of K step i (16 values of k) of the step in stage `buf`, row tile tm: piece 4 h + i of its row
+    const int a_lane = col * kXRow + (((4 * h) ^ piece_key(col & 15)) << 4);
+    const int q_lane = T::kXBytes + (wave * kTN * 32 + col) * WeightRegs<BITS>::kLdsRow + h * 16;
+    auto a_frag = [&](int buf, int i, int tm) __attribute__((always_inline)) {
+        return *reinterpret_cast<const half8_t *>(lds + (kg * kStages + buf) * T::kStepBytes + (a_lane ^ (i << 4)) + tm * (32 * kXRow));
+    };
+    WeightRegs<BITS> w[2][kTN];                         // packed words of the step worked on and of the next one
+    typename WeightRegs<BITS>::Affine aff[kTN];
+    auto read_words = [&](WeightRegs<BITS> (&dst)[kTN], int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int tn = 0; tn < kTN; ++tn) dst[tn].read(lds + (kg * kStages + buf) * T::kStepBytes + q_lane + tn * 32 * WeightRegs<BITS>::kLdsRow);
+    };
+    uint32_t szw[kTN];
+    auto read_sz = [&](int parity) __attribute__((always_inline)) {
+#pragma unroll
+        for (int tn = 0; tn < kTN; ++tn) szw[tn] = *reinterpret_cast<const uint32_t *>(lds + sz_at + parity * 256 + (tn * 32 + col) * 4);
+    };
+
+    half8_t af[2][TM], b0, b1;
+    // One step: four K steps of 16.  A K step is two phases of TM matrix instructions, one per column tile: during the
+    // first the second tile's weights of this K step are de-quantized and the activation fragments of the next one are
+    // read from LDS, during the second the first tile's weights of the next K step are de-quantized.  One or two copies of
+    // the step after next go out per K step, between the matrix instructions (all at once, they would hold the wave up in
+    // the queue of the CU's address unit).  In front of the last K step the waves meet: the next step has landed, and
+    // this one's stage has been read by everybody and may be filled again.
+    // the copies of a step go out in eight portions, one per phase: copy j of n with portion 8 j / n
+    auto issue_portion = [&](int st, auto FIRST, int buf, int portion) __attribute__((always_inline)) {
+        constexpr int n = kLoads + (decltype(FIRST)::value ? 1 : 0);
+#pragma unroll
+        for (int j = 0; j < n; ++j)
+            if (8 * j / n == portion) issue_one(st, decltype(FIRST)::value, buf, j);
+    };
+    auto do_step = [&](auto HALF, int st, int buf, int buf1, int buf2) __attribute__((always_inline)) {
+        constexpr int half = decltype(HALF)::value;     // of the group
+        constexpr std::integral_constant<bool, half == 0> next_first{};   // step st + 2 begins a group if this one does
+        constexpr std::integral_constant<bool, half == 1> next_second{};  // ... and st + 3 if this one does not
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int cur = i & 1, nxt = cur ^ 1;
+            __builtin_amdgcn_sched_barrier(0);
+            if (i == 3) {
+                wait_and_meet(std::integral_constant<int, kLoads + (half == 0 ? 1 : 0)>{});
+                issue_portion(st + 3, next_second, buf, 0);
+                if (half == 1) read_sz(((st + 1) >> 1) & 1);
+                read_words(w[half ^ 1], buf1);
             } else {
-                if (i == 0) sr.w[tn][c].dequant(aff[tn], k6400, wv3[tn]);
-                return pack8(wv3[tn][4 * i], wv3[tn][4 * i + 1], wv3[tn][4 * i + 2], wv3[tn][4 * i + 3]);
+                issue_portion(st + 2, next_first, buf2, 2 + 2 * i);
             }
-        };
-        // Order of issue, fixed with scheduling fences and groups.  A K step is two phases of TM matrix
-        // instructions, one per column tile.  While the first phase's instructions run, the second
-        // tile's weights of this step are de-quantized; during the second phase the first tile's
-        // weights of the NEXT step are, and each activation fragment is re-read from LDS for the
-        // next step right after its last use.  Vector, LDS and matrix instructions alternate, so
-        // the matrix pipe stays fed whatever the other wave of the SIMD is doing.
-        static_assert(kTN == 2, "the issue order below is written for two column tiles per wave");
-        constexpr int kValu = BITS == 4 ? (TM == 4 ? 4 : TM == 3 ? 6 : 7) : (TM == 4 ? 5 : TM == 3 ? 7 : 9);   // vector ops per matrix instruction
-        // Activation fragments have two register sets: those of K step i + 1 are asked for during the FIRST phase
-        // of step i, a whole K step of matrix work before they are needed (asked for right after their last use,
-        // three matrix instructions ahead, every K step began with a wait for LDS).
-        half8_t af[2][TM], b0, b1;
-#pragma unroll
-        for (int tm = 0; tm < TM; ++tm) af[0][tm] = a_frag(tm, 0);
-        b0 = b_frag(0, 0);
-#pragma unroll
-        for (int step = 0; step < 8; ++step) {
-            const int cur = step & 1, nxt = cur ^ 1;
             __builtin_amdgcn_sched_barrier(0);
-            // this K step's share of the loads of the round after next: asked for here, between the matrix
-            // instructions, the load path works them off in the background; asked for all at once at the top of a
-            // round they kept every wave of the CU waiting in the queue of the address unit, with the matrix pipe idle
-            loads_of_step(step);
-            __builtin_amdgcn_sched_barrier(0);
-            b1 = b_frag(1, step);
+            b1 = w[half][1].operand(i, aff[1], k6400);
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm) {
                 acc[tm][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[cur][tm], b0, acc[tm][0], 0, 0, 0);
-                if (step < 7) af[nxt][tm] = a_frag(tm, step + 1);
+                af[nxt][tm] = i < 3 ? a_frag(buf, i + 1, tm) : a_frag(buf1, 0, tm);
             }
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (step < 7) b0 = b_frag(0, step + 1);
+            if (i == 3) issue_portion(st + 3, next_second, buf, 1);
+            else issue_portion(st + 2, next_first, buf2, 3 + 2 * i);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i == 3 && half == 1) {
+                aff[0].set(szw[0]);
+                aff[1].set(szw[1]);
+            }
+            b0 = i < 3 ? w[half][0].operand(i + 1, aff[0], k6400) : w[half ^ 1][0].operand(0, aff[0], k6400);
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm) acc[tm][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[cur][tm], b1, acc[tm][1], 0, 0, 0);
-#pragma unroll
-            for (int tm = 0; tm < TM; ++tm) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
-            }
         }
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // Three super-steps are under way at any time: the one being multiplied and the next two on their way from
-    // memory (weights into registers, activations into LDS).  One super-step of matrix work is shorter than a trip
-    // to memory, so with a single step of look-ahead every round ended in a wait of a microsecond or more.  The loop
-    // is unrolled six times so that register set (round % 3), scale/zero set and parity are compile-time: registers
-    // with a load in flight are never moved.
-    StepRegs wr[kStages];
-    SzRegs sz[kStages];
-    // The barrier alone: __syncthreads() comes with a fence that waits for every load in flight, which is exactly
-    // what the look-ahead must not do.  What has to be complete at a barrier is waited for explicitly in front of it
-    // (this wave's copies into LDS, by count); the LDS reads of the round just finished have been consumed by the
-    // matrix instructions.  The memory clobber keeps the compiler from moving LDS accesses across it.
-    auto block_barrier = [&]() __attribute__((always_inline)) {
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    };
-    // Load j of round `it` (super-step u): first the copies of the activation tile into LDS, then the packed words,
-    // then scale and zero (the six-group loads: in the first of the six rounds only; they go to set 0 before the
-    // loop and to set 1, the one in waiting, inside it).  Every round issues exactly loads_in(it) loads, in this order.
-    auto loads_in = [](int it) constexpr { return kLoadsX + kLoadsW + (pairs && it % 6 != 0 ? 0 : kLoadsSZ); };
-    auto issue_one = [&](auto IT, auto FIRST, int u, int j) __attribute__((always_inline)) {
-        constexpr int it = decltype(IT)::value;
-        if (j < kLoadsX) {
-            __builtin_amdgcn_global_load_lds(xsrc + (size_t)(4 * j) * p.K + u * kBK,
-                                             (__attribute__((address_space(3))) void *)&lds_all[kg][it % 3][(wave * (kBM / 4) + 4 * j) * kLdsRow],
-                                             16, 0, 0);
-        } else if (j < kLoadsX + kLoadsW) {
-            const int tn = (j - kLoadsX) / 2, c = (j - kLoadsX) % 2;
-            wr[it % 3].w[tn][c].load(qbuf, woff[tn] + (4 * u + 2 * c) * (WeightRegs<BITS>::kWords * 4));
-        } else {
-            const int tn = (j - kLoadsX - kLoadsW) / 2, which = (j - kLoadsX - kLoadsW) % 2;
-            if constexpr (pairs) {                      // u even (past the end: whatever, rounded down to a dword; never used)
-                SzRegs &r = sz[decltype(FIRST)::value ? 0 : 1];
-                const uint3v_t v = __builtin_amdgcn_raw_buffer_load_b96(which == 0 ? sbuf : zbuf, (goff[tn] + u * 2) & ~3, 0, 0);
-                if (which == 0) { r.s[tn][0] = v.x; r.s[tn][1] = v.y; r.s[tn][2] = v.z; }
-                else { r.z[tn][0] = v.x; r.z[tn][1] = v.y; r.z[tn][2] = v.z; }
-            } else {                                    // (the load zero-extends)
-                SzRegs &r = sz[it % 3];
-                if (which == 0) r.s[tn][0] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(sbuf, goff[tn] + u * 2, 0, 0);
-                else r.z[tn][0] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(zbuf, goff[tn] + u * 2, 0, 0);
-            }
-        }
-    };
-    // all loads of round `it` at once
-    auto issue = [&](auto IT, auto FIRST, int u) __attribute__((always_inline)) {
-        constexpr int it = decltype(IT)::value;
+    // Start: steps 0 and 1, and the first two portions of step 2 (the others go out in step 0).
 #pragma unroll
-        for (int j = 0; j < loads_in(it); ++j) issue_one(IT, FIRST, u, j);
-    };
-    // the share of K step `step` (0..7) of them: load j goes with step 8 j / loads_in(it)
-    auto issue_share = [&](auto IT, int u, int step) __attribute__((always_inline)) {
-        constexpr int it = decltype(IT)::value;
+    for (int j = 0; j <= kLoads; ++j) issue_one(0, true, 0, j);
 #pragma unroll
-        for (int j = 0; j < loads_in(it); ++j)
-            if (8 * j / loads_in(it) == step) issue_one(IT, std::false_type{}, u, j);
-    };
-    // wait until at most the loads of round `it` are in flight
-    auto wait_older_than = [&](auto IT) __attribute__((always_inline)) {
-        constexpr int n = loads_in(decltype(IT)::value);
-        __builtin_amdgcn_s_waitcnt((n & 15) | ((n >> 4) << 14) | 0x0F70);
-    };
-    // The loads of a round are issued whether or not the super-step exists (past the end: the last one again, never
-    // used): with a branch around them the compiler can no longer count the loads in flight and waits for all of them.
-    const int u_last = U_all - 1;
-    auto do_round = [&](auto IT, int i6) __attribute__((always_inline)) {
-        constexpr int it = decltype(IT)::value;           // round within the unrolled six
-        const int u = u0 + i6 + it;
-        const int un = min(u + 2, u_last);
-        if (u < U) {                                    // group-uniform; both sides issue the same loads
-            compute(wr[it % 3], sz[pairs ? 0 : it % 3], pairs ? it : 0, it % 3,
-                    [&](int step) __attribute__((always_inline)) { issue_share(std::integral_constant<int, (it + 2) % 6>{}, un, step); });
-        } else {
-            issue(std::integral_constant<int, (it + 2) % 6>{}, std::false_type{}, un);
-        }
-        // the next round's operands must have landed (and, through the barrier, everybody's copies into LDS)
-        wait_older_than(std::integral_constant<int, (it + 2) % 6>{});
-        block_barrier();
-    };
-    issue(std::integral_constant<int, 0>{}, std::true_type{}, min(u0, u_last));
-    issue(std::integral_constant<int, 1>{}, std::true_type{}, min(u0 + 1, u_last));
-    wait_older_than(std::integral_constant<int, 1>{});
-    block_barrier();
-    // every group runs the same number of rounds so that the block's barriers match; a group whose share of K is
-    // shorter sits its last rounds out
-    for (int i6 = 0; i6 < U_part; i6 += 6) {
-        if (pairs && i6 > 0) sz[0] = sz[1];             // the set that was in waiting (requested two rounds ago: landed before the last barrier)
-        do_round(std::integral_constant<int, 0>{}, i6);
-        if (i6 + 1 >= U_part) break;
-        do_round(std::integral_constant<int, 1>{}, i6);
-        if (i6 + 2 >= U_part) break;
-        do_round(std::integral_constant<int, 2>{}, i6);
-        if (i6 + 3 >= U_part) break;
-        do_round(std::integral_constant<int, 3>{}, i6);
-        if (i6 + 4 >= U_part) break;
-        do_round(std::integral_constant<int, 4>{}, i6);
-        if (i6 + 5 >= U_part) break;
-        do_round(std::integral_constant<int, 5>{}, i6);
+    for (int j = 0; j < kLoads; ++j) issue_one(1, false, 1, j);
+    issue_portion(2, std::true_type{}, 2, 0);
+    issue_portion(2, std::true_type{}, 2, 1);
+    constexpr int kStarted = (2 * (kLoads + 1) + 7) / 8;            // copies j of kLoads + 1 with 8 j / (kLoads + 1) < 2
+    wait_and_meet(std::integral_constant<int, kLoads + kStarted>{});
+    read_sz(0);
+    read_words(w[0], 0);
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) af[0][tm] = a_frag(0, 0, tm);
+    aff[0].set(szw[0]);
+    aff[1].set(szw[1]);
+    b0 = w[0][0].operand(0, aff[0], k6400);
+    int buf = 0;
+    for (int u = 0; u < U; ++u) {
+        const int buf1 = buf == 2 ? 0 : buf + 1, buf2 = buf == 0 ? 2 : buf - 1;
+        do_step(std::integral_constant<int, 0>{}, 2 * u, buf, buf1, buf2);
+        do_step(std::integral_constant<int, 1>{}, 2 * u + 1, buf1, buf2, buf);
+        buf = buf2;
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);                 // the loads issued past the end have landed too: LDS is free
-    block_barrier();
+    if (KG > 1)                                         // a group of waves with a shorter share of K meets the other one at its barriers
+        for (int u = U; u < U_part; ++u) { block_barrier(); block_barrier(); }
+    wait_and_meet(std::integral_constant<int, 0>{});    // the copies issued past the end have landed too, and everybody is done: LDS is free
 
-    // the K groups meet: group 1 leaves its accumulators in LDS (the activation buffers are free now: one wave's
-    // tiles take exactly one group's share of them), group 0 adds them to its own
+    // the K groups meet: group 1 leaves its accumulators in LDS, group 0 adds them to its own
     if constexpr (KG > 1) {
         static_assert(KG <= 2, "the hand-over below is written for two K groups");
-        static_assert(sizeof(float) * TM * kTN * 16 * 64 * kWavesN <= sizeof(lds_all), "accumulators must fit the activation buffers");
-        float *hand = reinterpret_cast<float *>(&lds_all[0][0][0]) + (size_t)wave * (TM * kTN * 16 * 64);
+        float *hand = reinterpret_cast<float *>(lds) + (size_t)wave * (TM * kTN * 16 * 64);
         if (kg == 1) {
 #pragma unroll
             for (int tm = 0; tm < TM; ++tm)
@@ -472,35 +429,33 @@ __global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 
     // up-projection: 2r extra K columns, t_hi and t_lo against the same B^T rows
-    if (p.r > 0 && part == 0 && p.r % 64 == 0) {
-        // 64 taps at a time through LDS (the activation buffers are free now).  Every lane fetching its own 16 bytes of
+    if (p.r > 0 && part == 0) {
+        // 64 taps at a time through LDS.  Every lane fetching its own 16 bytes of
         // its own row - 32 rows per load, some forty loads per wave, all at once - kept the address unit busy for
         // microseconds at the end of every block; copied into LDS, a load moves 1 KiB of whole rows (eight lanes per
         // 128-byte row of B^T, sixteen per 256-byte row of t_hi | t_lo), and the operands come out of LDS.  Rows are
         // stored with the position of each 16-byte piece XOR-ed with the row number, as the activation tiles are.
-        static_assert(sizeof(lds_all) >= kBN * 128 + kBM * 256, "the activation buffers must hold 64 taps of the block's rows of B^T and of t");
-        unsigned char *const lds_b = &lds_all[0][0][0];     // [256 rows][8 pieces]
-        unsigned char *const lds_t = lds_b + kBN * 128;     // [kBM rows][16 pieces: 8 of t_hi, 8 of t_lo]
+        // Taps past r, rows past N and tokens past M lie beyond the descriptors or are aimed there: zeros.
+        const __amdgpu_buffer_rsrc_t bbuf = buffer_of(p.Bt + (size_t)n0 * p.r, (long)min(kBN, p.N - n0) * p.r * 2);
+        const __amdgpu_buffer_rsrc_t tbuf = buffer_of(p.thl + (size_t)m0 * (2 * p.r), (long)min(kBM, p.M - m0) * p.r * 4);
+        constexpr int kNowhere = 0x40000000;            // beyond every buffer
+        unsigned char *const lds_b = lds;               // [256 rows][8 pieces]
+        unsigned char *const lds_t = lds_b + kBN * 128; // [kBM rows][16 pieces: 8 of t_hi, 8 of t_lo]
         for (int c0 = 0; c0 < p.r; c0 += 64) {
             block_barrier();                            // everybody is done with what LDS held before
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const int row = (wave * 8 + i) * 8 + (lane >> 3), piece = (lane & 7) ^ (row & 7);
-                const int n = min(bn * kBN + row, p.N - 1);
-                __builtin_amdgcn_global_load_lds(p.Bt + (size_t)n * p.r + c0 + piece * 8,
-                                                 (__attribute__((address_space(3))) void *)(lds_b + (wave * 8 + i) * 1024), 16, 0, 0);
+                const int first = (wave * 8 + i) * 8, row = first + (lane >> 3), tap = c0 + ((lane & 7) ^ (row & 7)) * 8;
+                copy16_to_lds(bbuf, tap < p.r ? (row * p.r + tap) * 2 : kNowhere, 0, lds0 + first * 128);
             }
 #pragma unroll
-            for (int j = 0; j < kCopies; ++j) {
-                const int row = wave * (kBM / 4) + 4 * j + (lane >> 4), piece = (lane & 15) ^ (row & 15);
-                const int m = min(m0 + row, p.M - 1);
-                const uint16_t *src = p.thl + (size_t)m * (2 * p.r) + (piece < 8 ? c0 + piece * 8 : p.r + c0 + (piece - 8) * 8);
-                __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)(lds_t + (wave * (kBM / 4) + 4 * j) * 256), 16, 0, 0);
+            for (int j = 0; j < 2 * TM; ++j) {
+                const int first = (wave * 2 * TM + j) * 4, row = first + (lane >> 4), piece = (lane & 15) ^ (row & 15), tap = c0 + (piece & 7) * 8;
+                copy16_to_lds(tbuf, tap < p.r ? (row * 2 * p.r + (piece < 8 ? tap : p.r + tap)) * 2 : kNowhere, 0, lds0 + kBN * 128 + first * 256);
             }
-            __builtin_amdgcn_s_waitcnt(0x0F70);         // vmcnt(0): this wave's copies have landed
-            block_barrier();
-#pragma unroll
-            for (int st = 0; st < 4; ++st) {
+            wait_and_meet(std::integral_constant<int, 0>{});
+            const int steps = min(4, (p.r - c0 + 15) / 16);
+            for (int st = 0; st < steps; ++st) {
                 half8_t bf[kTN];
 #pragma unroll
                 for (int tn = 0; tn < kTN; ++tn) {
@@ -512,42 +467,11 @@ __global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
                     for (int tm = 0; tm < TM; ++tm) {
                         const int row = tm * 32 + col;
-                        const half8_t af = *reinterpret_cast<const half8_t *>(lds_t + row * 256 + (((8 * half + 2 * st + h) ^ (row & 15)) << 4));
+                        const half8_t t8 = *reinterpret_cast<const half8_t *>(lds_t + row * 256 + (((8 * half + 2 * st + h) ^ (row & 15)) << 4));
 #pragma unroll
                         for (int tn = 0; tn < kTN; ++tn)
-                            acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, bf[tn], acc[tm][tn], 0, 0, 0);
+                            acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_f16(t8, bf[tn], acc[tm][tn], 0, 0, 0);
                     }
-            }
-        }
-    } else if (p.r > 0 && part == 0) {
-        // (the operands of four steps are requested before the first of them is multiplied: step by step, every step
-        // would be a round trip to memory)
-        const int steps = (2 * p.r) / 16;
-        constexpr int kUp = 4;
-        for (int st0 = 0; st0 < steps; st0 += kUp) {
-            half8_t bf[kUp][kTN], af[kUp][TM];
-#pragma unroll
-            for (int i = 0; i < kUp; ++i) {
-                const int st = min(st0 + i, steps - 1);
-                const int jj = st * 16 + h * 8;         // column of [t_hi | t_lo]
-                const int jb = jj >= p.r ? jj - p.r : jj;   // tap of B
-#pragma unroll
-                for (int tn = 0; tn < kTN; ++tn) bf[i][tn] = *reinterpret_cast<const half8_t *>(p.Bt + (size_t)nrow[tn] * p.r + jb);
-#pragma unroll
-                for (int tm = 0; tm < TM; ++tm) {
-                    const int m = min(m0 + tm * 32 + col, p.M - 1);
-                    af[i][tm] = *reinterpret_cast<const half8_t *>(p.thl + (size_t)m * (2 * p.r) + jj);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < kUp; ++i) {
-                if (st0 + i < steps) {                  // uniform
-#pragma unroll
-                    for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                        for (int tn = 0; tn < kTN; ++tn)
-                            acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[i][tm], bf[i][tn], acc[tm][tn], 0, 0, 0);
-                }
             }
         }
     }
@@ -555,30 +479,28 @@ __global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))
     // store of y: accumulator register v of a lane holds row 8*(v/4) + 4*h + v%4, column `col`
     if (p.ksplit == 1 && p.N % 8 == 0) {
         // Stored straight from the accumulators, an instruction writes two 64-byte pieces of two rows, ninety-six such
-        // instructions per wave, and the address unit is the busy one again.  Each wave turns its tile round in LDS
-        // instead (its own 32*TM rows of 64 fp16, 144 bytes apart so that the two halves of the wave fall on different
+        // instructions per wave, and the address unit is the busy one again.  Each wave turns 32 rows at a time round in LDS
+        // instead (64 fp16 a row, 144 bytes apart so that the two halves of the wave fall on different
         // banks) and writes whole 128-byte row pieces, 16 bytes per lane, eight rows per instruction.
-        constexpr int kOutRow = 64 * 2 + 16;
-        static_assert(kWavesN * kBM * kOutRow <= (int)sizeof(lds_all), "the waves' output tiles must fit the activation buffers");
+        static_assert(kBN == kPrefillColumns, "the rule that cuts a layer into blocks counts column blocks of this width");
         static_assert(kTN == 2, "a wave's output rows are 64 columns wide");
-        unsigned char *const out = &lds_all[0][0][0] + wave * (kBM * kOutRow);
+        unsigned char *const out = lds + wave * (32 * T::kOutRow);
         block_barrier();                                // everybody is done with what LDS held before
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm)
+        for (int tm = 0; tm < TM; ++tm) {
 #pragma unroll
             for (int tn = 0; tn < kTN; ++tn)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = tm * 32 + 8 * (v / 4) + 4 * h + (v % 4);
-                    *reinterpret_cast<half_t *>(out + row * kOutRow + (tn * 32 + col) * 2) = (half_t)acc[tm][tn][v];
-                }
-        // (the wave reads what itself wrote: LDS keeps a wave's accesses in order)
+                for (int v = 0; v < 16; ++v)
+                    *reinterpret_cast<half_t *>(out + (8 * (v / 4) + 4 * h + (v % 4)) * T::kOutRow + (tn * 32 + col) * 2) = (half_t)acc[tm][tn][v];
+            // (the wave reads what itself wrote: LDS keeps a wave's accesses in order)
 #pragma unroll
-        for (int i = 0; i < kBM / 8; ++i) {
-            const int row = i * 8 + (lane >> 3), piece = lane & 7;
-            const uint4 v = *reinterpret_cast<const uint4 *>(out + row * kOutRow + piece * 16);
-            const int m = m0 + row, n = nw + piece * 8;
-            if (m < p.M && n < p.N) *reinterpret_cast<uint4 *>(p.y + (size_t)m * p.N + n) = v;
+            for (int i = 0; i < 4; ++i) {
+                const int row = i * 8 + (lane >> 3), piece = lane & 7;
+                const uint4 v = *reinterpret_cast<const uint4 *>(out + row * T::kOutRow + piece * 16);
+                const int m = m0 + tm * 32 + row, n = nw + piece * 8;
+                if (m < p.M && n < p.N) *reinterpret_cast<uint4 *>(p.y + (size_t)m * p.N + n) = v;
+            }
         }
         return;
     }
@@ -599,9 +521,17 @@ __global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
-// y = sum of the K parts' fp32 partial results (only for layers with so few tiles that K is split over blocks).
+// y = sum of the K parts' fp32 partial results, in index order (only where K is split over blocks).
 __global__ __launch_bounds__(256) void fbq_sum_parts_kernel(const float *__restrict__ ypart, uint16_t *__restrict__ y, size_t total, int parts)
 {
+    if (total % 4 != 0) {                               // (the parts after the first are not 16-byte aligned then)
+        for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
+            float acc = ypart[i];
+            for (int pt = 1; pt < parts; ++pt) acc += ypart[(size_t)pt * total + i];
+            y[i] = __builtin_bit_cast(uint16_t, (half_t)acc);
+        }
+        return;
+    }
     for (size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4; i < total; i += (size_t)gridDim.x * 256 * 4) {
         float4 acc = *reinterpret_cast<const float4 *>(ypart + i);
         for (int pt = 1; pt < parts; ++pt) {
@@ -615,8 +545,8 @@ __global__ __launch_bounds__(256) void fbq_sum_parts_kernel(const float *__restr
 
 // ------------------------------------------------------------------ activation pre-pass
 
-// xp[m][128 u + 8 (l ^ (m % 16)) + e] = x[m][128 u + 32 (l / 4) + slot_source(8 (l % 4) + e)]
-// for chunk l = 0..15 of every 128-wide block u; one thread per 32 activations (q4: the 64 bytes of piece b of row m).
+// xp[m][64 v + 8 (l ^ piece_key(m % 16)) + e] = x[m][64 v + 32 (l / 4) + slot_source(8 (l % 4) + e)]
+// for piece l = 0..7 of every 64-wide step v; one thread per 32 activations (q4: the 64 bytes of piece b of row m).
 template <int BITS>
 __device__ __forceinline__ void arrange_store(const uint4 (&q4)[4], uint16_t *__restrict__ xp, int K, int m, int b)
 {
@@ -631,15 +561,15 @@ __device__ __forceinline__ void arrange_store(const uint4 (&q4)[4], uint16_t *__
             v[i * 8 + j * 2 + 1] = hh.y;
         }
     }
-    uint16_t *dst = xp + (size_t)m * K + (b / 4) * 128;
+    uint16_t *dst = xp + (size_t)m * K + (b / 2) * 64;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         half2_t o[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             o[j] = half2_t{v[slot_source<BITS>(i * 8 + 2 * j)], v[slot_source<BITS>(i * 8 + 2 * j + 1)]};
-        const int l = 4 * (b % 4) + i;
-        *reinterpret_cast<uint4 *>(dst + 8 * (l ^ (m & 15))) =
+        const int l = 4 * (b % 2) + i;
+        *reinterpret_cast<uint4 *>(dst + 8 * (l ^ piece_key(m & 15))) =
             make_uint4(__builtin_bit_cast(uint32_t, o[0]), __builtin_bit_cast(uint32_t, o[1]),
                        __builtin_bit_cast(uint32_t, o[2]), __builtin_bit_cast(uint32_t, o[3]));
     }
@@ -670,11 +600,55 @@ __device__ __forceinline__ void arrange_items(const uint16_t *__restrict__ x, ui
     }
 }
 
-// The whole of x, for a layer without a sub-branch (with one, the down-projection's blocks arrange what they read).
-template <int BITS>
-__global__ __launch_bounds__(256) void fbq_arrange_x_kernel(const uint16_t *__restrict__ x, uint16_t *__restrict__ xp, int M, int K)
+// Scale and zero of 64 rows and 32 groups (tile `t` of the layer's), from [N][G] each to one word per row and group,
+// [G][Np]: the fused kernel fetches a group's 256 of them as whole lines.  Rows past N become zeros.  256 threads.
+constexpr int kSzRows = 64, kSzGroups = 32;
+__device__ void arrange_scales(const uint16_t *__restrict__ scales, const uint16_t *__restrict__ zeros, uint32_t *__restrict__ sz, int N, int Np,
+                               int G, int t, uint32_t (*turn)[kSzRows + 1])
 {
-    arrange_items<BITS>(x, xp, K, 0, 0, K / 32, (long)M * (K / 32), (long)blockIdx.x * 256 + threadIdx.x, (long)gridDim.x * 256);
+    const int row_tiles = Np / kSzRows, n0 = (t % row_tiles) * kSzRows, g0 = (t / row_tiles) * kSzGroups;
+    const int tid = threadIdx.x;
+    uint32_t v[kSzRows / 8];
+#pragma unroll
+    for (int i = 0; i < kSzRows / 8; ++i) {
+        const int n = n0 + i * 8 + tid / 32, g = g0 + tid % 32;
+        const bool on = n < N && g < G;
+        const size_t at = on ? (size_t)n * G + g : 0;
+        v[i] = (uint32_t)scales[at] | ((uint32_t)zeros[at] << 16);
+        if (!on) v[i] = 0;
+    }
+#pragma unroll
+    for (int i = 0; i < kSzRows / 8; ++i) turn[tid % 32][i * 8 + tid / 32] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSzGroups / 4; ++i) {
+        const int g = g0 + i * 4 + tid / kSzRows;
+        if (g < G) sz[(size_t)g * Np + n0 + tid % kSzRows] = turn[i * 4 + tid / kSzRows][tid % kSzRows];
+    }
+}
+static int sz_tiles(int N, int G) { return ceil_div(N, kBN) * (kBN / kSzRows) * ceil_div(G, kSzGroups); }
+
+// What the pre-pass reads and writes besides the down-projection's own arguments.
+struct ArrangeParams {
+    const uint16_t *x, *scales, *zeros;
+    uint16_t *xp;
+    uint32_t *sz;
+    int M, N, K, G, Np;
+    int sz_tiles;
+};
+
+// The whole of x, for a layer without a sub-branch (with one, the down-projection's blocks arrange what they read).
+// The first sz_tiles blocks arrange scales and zeros.
+template <int BITS>
+__global__ __launch_bounds__(256) void fbq_arrange_x_kernel(const ArrangeParams a)
+{
+    __shared__ uint32_t turn[kSzGroups][kSzRows + 1];
+    if ((int)blockIdx.x < a.sz_tiles) {
+        arrange_scales(a.scales, a.zeros, a.sz, a.N, a.Np, a.G, blockIdx.x, turn);
+        return;
+    }
+    arrange_items<BITS>(a.x, a.xp, a.K, 0, 0, a.K / 32, (long)a.M * (a.K / 32), (long)(blockIdx.x - a.sz_tiles) * 256 + threadIdx.x,
+                        (long)(gridDim.x - a.sz_tiles) * 256);
 }
 
 // ------------------------------------------------------------------ down-projection (prefill)
@@ -686,7 +660,7 @@ __global__ __launch_bounds__(256) void fbq_arrange_x_kernel(const uint16_t *__re
 static int down_slice_len(int M, int K)
 {
     const int want = std::min(32, std::max(8, ceil_div(256, ceil_div(M, 32))));
-    return std::max(256, ceil_div(ceil_div(K, want), kBK) * kBK);
+    return std::max(256, ceil_div(ceil_div(K, want), kGroup) * kGroup);
 }
 static int down_slices(int M, int K) { return ceil_div(K, down_slice_len(M, K)); }
 
@@ -694,36 +668,48 @@ static int down_slices(int M, int K) { return ceil_div(K, down_slice_len(M, K));
 // columns.  RT = 32-column tiles (r <= 32 * RT).  The block also writes the arranged copy of the activations it
 // reads (its 32 rows, its K slice): one pass over x serves both, and the re-ordering needs no launch of its own.
 //
-// The slice is walked in chunks of 128: the chunk's 32 rows of x and 32 RT rows of A^T (256 bytes each) are copied
-// into LDS by global_load_lds_dwordx4 - four whole rows per instruction - while the chunk before is being worked on
-// (two buffers).  (Fetched by the lanes themselves, 16 bytes of one row per lane and instruction, the operands of a
+// The slice is walked in chunks of 64: the chunk's 32 rows of x and 32 RT rows of A^T (128 bytes each) are copied
+// into LDS, eight whole rows per copy, three chunks ahead of the one worked on (a ring of four; with two chunks of 128 and
+// a wait for everything in flight between them, every chunk was a round trip to memory: 2048 x 8192, r = 128, took 35 us and takes 25; 1024 x 4096, r = 64, 10.9 and 7.0).
+// (Fetched by the lanes themselves, 16 bytes of one row per lane and instruction, the operands of a
 // long slice kept the CU's address unit busy longer than everything else in this kernel took.)  Rows are stored
-// with the position of each 16-byte piece XOR-ed with the row number, as the fused kernel's tiles are.  Of a
-// chunk's eight K steps of 16, wave w multiplies steps 2w and 2w + 1; the four waves' tiles meet in LDS at the end.
+// with the position of each 16-byte piece XOR-ed with a key of the row, as the fused kernel's tiles are.  Of a
+// chunk's four K steps of 16, wave w multiplies step w; the four waves' tiles meet in LDS at the end.
+constexpr int kDownStages = 4;
 template <int BITS, int RT>
-__global__ __launch_bounds__(256) void fbq_down_proj_prefill_kernel(const uint16_t *__restrict__ x, const uint16_t *__restrict__ At,
-                                                                    float *__restrict__ partial, uint16_t *__restrict__ xp, int M, int K,
-                                                                    int r, int kslice)
+__global__ __launch_bounds__(256) void fbq_down_proj_prefill_kernel(const ArrangeParams a, const uint16_t *__restrict__ At, float *__restrict__ partial,
+                                                                    int r, int kslice, int slices)
 {
     constexpr int kRows = 32 + 32 * RT;                 // rows of a chunk in LDS: the tokens, then the columns of A
-    __shared__ __attribute__((aligned(1024))) unsigned char lds_down[2 * kRows * 256];   // [2][kRows][256 B]; afterwards float [32][32 RT]
-    static_assert(sizeof(lds_down) <= 160 * 1024 && sizeof(lds_down) >= 32 * 32 * RT * sizeof(float), "two chunks must fit the CU's LDS and hold the summed tile");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int kChunkBytes = kRows * 128, kCopies = kRows / 8 / 4;   // copies per wave and chunk
+    __shared__ __attribute__((aligned(1024))) unsigned char lds_down[kDownStages * kChunkBytes];   // the ring; afterwards float [4][32][32 RT]
+    static_assert(sizeof(lds_down) <= 160 * 1024 && sizeof(lds_down) >= 4 * 32 * 32 * RT * sizeof(float), "the ring must fit the CU's LDS and hold the waves' tiles");
+    static_assert(sizeof(lds_down) >= kSzGroups * (kSzRows + 1) * sizeof(uint32_t), "the ring must hold a tile of scales");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, h = lane >> 5;
+    if ((int)blockIdx.y >= slices) {                    // the rows of blocks behind the K slices arrange scales and zeros
+        const int t = ((int)blockIdx.y - slices) * gridDim.x + blockIdx.x;
+        if (t < a.sz_tiles) arrange_scales(a.scales, a.zeros, a.sz, a.N, a.Np, a.G, t, reinterpret_cast<uint32_t (*)[kSzRows + 1]>(lds_down));
+        return;
+    }
+    const int M = a.M, K = a.K;
     const int m0 = blockIdx.x * 32;
     const int k_lo = blockIdx.y * kslice, k_hi = min(K, k_lo + kslice);
-    const int chunks = (k_hi - k_lo) / kBK;             // K and the slices are whole groups of 128
+    const int chunks = (k_hi - k_lo) / kStepK;          // K and the slices are whole groups of 128
 
-    // copies of chunk c: instruction i of the block moves rows 4 i .. 4 i + 3 (lane l: piece l % 16 of row 4 i + l / 16,
-    // put at LDS position l of the instruction's 1 KiB, i.e. the piece the position stands for is position ^ row)
-    auto copy_chunk = [&](int c, int buf) __attribute__((always_inline)) {
-        unsigned char *base = lds_down + (size_t)buf * kRows * 256;
+    const __amdgpu_buffer_rsrc_t xbuf = buffer_of(a.x + (size_t)m0 * K, (long)min(32, M - m0) * K * 2);   // (tokens past M, columns past r: zeros)
+    const __amdgpu_buffer_rsrc_t abuf = buffer_of(At, (long)r * K * 2);
+    const uint32_t lds0 = lds_offset(lds_down);
+    // copy i of a chunk moves rows 8 i .. 8 i + 7 (lane l: row 8 i + l / 8, put at position l % 8 of it, i.e. piece position ^ key);
+    // the first four are the tokens', one per wave
+    const int lane_row = lane >> 3;
+    auto copy_chunk = [&](int c, int stage) __attribute__((always_inline)) {
+        const uint32_t base = lds0 + stage * kChunkBytes;
 #pragma unroll
-        for (int j = 0; j < kRows / 16; ++j) {
-            const int i = wave * (kRows / 16) + j;      // this wave's share of the kRows / 4 instructions
-            const int row = 4 * i + (lane >> 4), piece = (lane & 15) ^ (row & 15);
-            const uint16_t *src = row < 32 ? x + (size_t)min(m0 + row, M - 1) * K : At + (size_t)min(row - 32, r - 1) * K;
-            __builtin_amdgcn_global_load_lds(src + k_lo + c * kBK + piece * 8, (__attribute__((address_space(3))) void *)(base + i * 1024), 16, 0, 0);
+        for (int j = 0; j < kCopies; ++j) {
+            const int i = j * 4 + wave, row = 8 * i + lane_row;
+            const int off = ((row - (j == 0 ? 0 : 32)) * K + ((lane & 7) ^ piece_key(row & 15)) * 8) * 2, at = (k_lo + c * kStepK) * 2;
+            copy16_to_lds(j == 0 ? xbuf : abuf, off, at, base + i * 1024);
         }
     };
 
@@ -733,57 +719,59 @@ __global__ __launch_bounds__(256) void fbq_down_proj_prefill_kernel(const uint16
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[rt][v] = 0.0f;
 
-    if (chunks > 0) copy_chunk(0, 0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0)
-    __syncthreads();
+    for (int c = 0; c < min(kDownStages - 1, chunks); ++c) copy_chunk(c, c);
+    // re-ordered copy: thread t writes position t % 8 of row t / 8 of the chunk, i.e. piece l = (t % 8) ^ key of its step
+    const int arow = tid >> 3, apos = tid & 7, al = apos ^ piece_key(arow & 15);
+    uint16_t *const xp = a.xp + (size_t)(m0 + arow) * K + k_lo + apos * 8;
+    const bool astore = m0 + arow < M;
     for (int c = 0; c < chunks; ++c) {
-        const int buf = c & 1;
-        if (c + 1 < chunks) copy_chunk(c + 1, buf ^ 1);
-        const unsigned char *base = lds_down + (size_t)buf * kRows * 256;
-        // the re-ordered copy: 32 rows x 4 pieces of 32 activations, one per thread of the first two waves
-        if (tid < 128) {
-            const int i = tid >> 2, b = tid & 3;
-            if (m0 + i < M) {
-                uint4 q4[4];
+        // chunk c has landed - with every store of the copy counted as if it were one more copy in flight - and everybody is
+        // done with chunk c - 1, whose stage the next copies go to
+        if (c + kDownStages - 2 < chunks) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((kDownStages - 2) * kCopies) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (c + kDownStages - 1 < chunks) copy_chunk(c + kDownStages - 1, (c + kDownStages - 1) % kDownStages);
+        const unsigned char *base = lds_down + (c % kDownStages) * kChunkBytes;
+        const int pc = 2 * wave + h;                    // the 16-byte piece with this lane's k of the wave's step
+        const half8_t af = *reinterpret_cast<const half8_t *>(base + col * 128 + ((pc ^ piece_key(col & 15)) << 4));
 #pragma unroll
-                for (int k = 0; k < 4; ++k) q4[k] = *reinterpret_cast<const uint4 *>(base + i * 256 + (((4 * b + k) ^ (i & 15)) << 4));
-                arrange_store<BITS>(q4, xp, K, m0 + i, (k_lo + c * kBK) / 32 + b);
-            }
+        for (int rt = 0; rt < RT; ++rt) {
+            const half8_t bf = *reinterpret_cast<const half8_t *>(base + (32 + rt * 32 + col) * 128 + ((pc ^ piece_key(col & 15)) << 4));
+            acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, bf, acc[rt], 0, 0, 0);
         }
+        const unsigned char *row = base + arow * 128;
+        uint4 out;
+        if constexpr (BITS == 4) {                      // the eight activations of one piece, re-ordered among themselves
+            const uint4 q = *reinterpret_cast<const uint4 *>(row + (apos << 4));   // (piece al sits at position apos)
+            out.x = __builtin_amdgcn_perm(q.z, q.x, 0x05040100u); out.y = __builtin_amdgcn_perm(q.z, q.x, 0x07060302u);
+            out.z = __builtin_amdgcn_perm(q.w, q.y, 0x05040100u); out.w = __builtin_amdgcn_perm(q.w, q.y, 0x07060302u);
+        } else {
+            uint16_t v[8];
 #pragma unroll
-        for (int st = 0; st < 2; ++st) {
-            const int pc = 2 * (2 * wave + st) + h;     // the 16-byte piece with this lane's k of the step
-            const half8_t af = *reinterpret_cast<const half8_t *>(base + col * 256 + ((pc ^ (col & 15)) << 4));
+            for (int e = 0; e < 8; ++e) {
+                int k = 0;                              // slot_source of a piece known only at run time
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                const int row = 32 + rt * 32 + col;
-                const half8_t bf = *reinterpret_cast<const half8_t *>(base + row * 256 + ((pc ^ (row & 15)) << 4));
-                acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af, bf, acc[rt], 0, 0, 0);
+                for (int pi = 0; pi < 4; ++pi) k = (al & 3) == pi ? slot_source<BITS>(8 * pi + e) : k;
+                k += 32 * (al >> 2);
+                v[e] = *reinterpret_cast<const uint16_t *>(row + (((k >> 3) ^ piece_key(arow & 15)) << 4) + (k & 7) * 2);
             }
+            out.x = v[0] | ((uint32_t)v[1] << 16); out.y = v[2] | ((uint32_t)v[3] << 16);
+            out.z = v[4] | ((uint32_t)v[5] << 16); out.w = v[6] | ((uint32_t)v[7] << 16);
         }
-        __builtin_amdgcn_s_waitcnt(0x0F70);             // the next chunk has landed (and this chunk's stores are out)
-        __syncthreads();                                // ... everybody's part of it; and everybody is done reading this one
+        if (astore) *reinterpret_cast<uint4 *>(xp + c * kStepK) = out;
     }
 
+    __syncthreads();                                    // the ring is free
     float *sum = reinterpret_cast<float *>(lds_down);
-    const int ld = 32 * RT;
-    for (int w = 0; w < 4; ++w) {
-        if (wave == w) {
+    constexpr int ld = 32 * RT;
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int i = 8 * (v / 4) + 4 * h + (v % 4);
-                    float *dst = &sum[i * ld + rt * 32 + col];
-                    *dst = w == 0 ? acc[rt][v] : *dst + acc[rt][v];
-                }
-        }
-        __syncthreads();
-    }
+        for (int v = 0; v < 16; ++v) sum[(wave * 32 + 8 * (v / 4) + 4 * h + (v % 4)) * ld + rt * 32 + col] = acc[rt][v];
+    __syncthreads();
     float *out = partial + (size_t)blockIdx.y * M * r;
-    for (int idx = tid; idx < 32 * r; idx += 256) {
-        const int i = idx / r, j = idx - i * r;
-        if (m0 + i < M) out[(size_t)(m0 + i) * r + j] = sum[i * ld + j];
+    for (int idx = tid; idx < 32 * ld; idx += 256) {
+        const int i = idx / ld, j = idx % ld;
+        if (m0 + i < M && j < r) out[(size_t)(m0 + i) * r + j] = ((sum[i * ld + j] + sum[(32 + i) * ld + j]) + sum[(64 + i) * ld + j]) + sum[(96 + i) * ld + j];
     }
 }
 
@@ -810,56 +798,59 @@ __global__ __launch_bounds__(256) void fbq_down_proj_finish_kernel(const float *
     }
 }
 
-// workspace: the arranged copy of x ([M rounded up to kRowPad][K] fp16; rows past M are never
-// written and only feed output rows that are never stored), then [M][2r] fp16 (t_hi | t_lo), then
-// down_slices x [M][r] fp32 partial sums
-static size_t xp_bytes(int M, int K) { return ((size_t)ceil_div(M, kRowPad) + 1) * kRowPad * K * sizeof(uint16_t); }
-static size_t thl_bytes(int M, int r) { return ((size_t)M * 2 * r * sizeof(uint16_t) + 255) & ~(size_t)255; }
-
-static size_t down_partial_bytes(int M, int K, int r) { return ((size_t)down_slices(M, K) * M * r * sizeof(float) + 255) & ~(size_t)255; }
-
-// K is split over blocks only where 64-row tiles give at most half as many tiles as there are CUs (256 assumed: the
-// rule must not depend on the device, the workspace is sized without one): up to eight ways, never below four
-// super-steps per group of waves (with eight as the limit, 4096 x 4096 at 65 to 256 tokens ran on half as many blocks
-// and took 37 - 42 us instead of 33 - 37).  Such a layer (256 tokens into a few thousand outputs over a long K) would leave
-// most of the GPU idle otherwise; everywhere else the two groups of a block are all the split there is and nothing
-// but y is written.  M * N must be a multiple of 4 for the summing launch.
-constexpr int kMaxKSplit = 8;
-static int ksplit_of(int M, int N, int K)
-{
-    const long tiles = (long)ceil_div(N, kBN) * ceil_div(M, 64);
-    if (tiles > 128 || N % 4 != 0 || (K / kBK) % 2 != 0) return 1;
-    int split = (int)std::min<long>(kMaxKSplit, 256 / tiles);
-    while (split > 1 && (K / kBK) / (2 * split) < 4) --split;
-    return std::max(1, split);
-}
+// workspace: the arranged copy of x ([M][K] fp16), scale | zero by group ([G][Np] words), then [M][2r] fp16 (t_hi | t_lo),
+// then down_slices x [M][r] fp32 partial sums, then - where K is split over blocks - ksplit x [M][N] fp32 partial outputs
+static size_t pad256(size_t b) { return (b + 255) & ~(size_t)255; }
+static size_t xp_bytes(int M, int K) { return pad256((size_t)M * K * sizeof(uint16_t)); }
+static size_t sz_bytes(int N, int K) { return (size_t)(K / kGroup) * ceil_div(N, kBN) * kBN * sizeof(uint32_t); }
+static size_t thl_bytes(int M, int r) { return pad256((size_t)M * 2 * r * sizeof(uint16_t)); }
+static size_t down_partial_bytes(int M, int K, int r) { return pad256((size_t)down_slices(M, K) * M * r * sizeof(float)); }
 
 size_t prefill_workspace_bytes(int M, int N, int K, int r)
 {
-    const int split = ksplit_of(M, N, K);
-    return xp_bytes(M, K) + thl_bytes(M, r) + down_partial_bytes(M, K, r) + (split > 1 ? (size_t)split * M * N * sizeof(float) : 0);
+    const int split = prefill_cut(M, N, K).ksplit;
+    return xp_bytes(M, K) + sz_bytes(N, K) + thl_bytes(M, r) + down_partial_bytes(M, K, r) + (split > 1 ? (size_t)split * M * N * sizeof(float) : 0);
 }
 
-// Before the fused kernel: x re-ordered into the workspace and, with a sub-branch, t = x.A.  With a sub-branch two
-// launches (K slices of the down-projection, whose blocks also write the re-ordered x; then the slices' sums as
-// t_hi | t_lo); without one, the re-ordering alone.
+struct PrefillScratch {
+    uint16_t *xp;
+    uint32_t *sz;
+    uint16_t *thl;
+    float *partial, *ypart;
+};
+static PrefillScratch scratch_of(const LinearArgs &a)
+{
+    char *w = (char *)a.workspace;
+    PrefillScratch s;
+    s.xp = (uint16_t *)w;       w += xp_bytes(a.M, a.K);
+    s.sz = (uint32_t *)w;       w += sz_bytes(a.N, a.K);
+    s.thl = (uint16_t *)w;      w += thl_bytes(a.M, a.r);
+    s.partial = (float *)w;     w += down_partial_bytes(a.M, a.K, a.r);
+    s.ypart = (float *)w;
+    return s;
+}
+
+// Before the fused kernel: x and the scales re-ordered into the workspace and, with a sub-branch, t = x.A.  With a
+// sub-branch two launches (K slices of the down-projection, whose blocks also write the re-ordered x; then the slices'
+// sums as t_hi | t_lo); without one, the re-ordering alone.
 hipError_t launch_prepass_prefill(const LinearArgs &a, hipStream_t stream)
 {
-    uint16_t *xp = (uint16_t *)a.workspace;
+    const PrefillScratch s = scratch_of(a);
+    const int G = a.K / kGroup;
+    const ArrangeParams ap{a.x, a.scales, a.zeros, s.xp, s.sz, a.M, a.N, a.K, G, ceil_div(a.N, kBN) * kBN, sz_tiles(a.N, G)};
     if (a.r == 0) {
         const size_t items = (size_t)a.M * (a.K / 32);
-        const int blocks = (int)std::min<size_t>(4096, (items + 255) / 256);
-        if (a.bits == 4) hipLaunchKernelGGL(fbq_arrange_x_kernel<4>, dim3(blocks), dim3(256), 0, stream, a.x, xp, a.M, a.K);
-        else hipLaunchKernelGGL(fbq_arrange_x_kernel<3>, dim3(blocks), dim3(256), 0, stream, a.x, xp, a.M, a.K);
+        const int blocks = (int)std::min<size_t>(4096, (items + 255) / 256) + ap.sz_tiles;
+        if (a.bits == 4) hipLaunchKernelGGL(fbq_arrange_x_kernel<4>, dim3(blocks), dim3(256), 0, stream, ap);
+        else hipLaunchKernelGGL(fbq_arrange_x_kernel<3>, dim3(blocks), dim3(256), 0, stream, ap);
         return hipGetLastError();
     }
     const int kslice = down_slice_len(a.M, a.K);
     const int slices = down_slices(a.M, a.K);
-    const dim3 grid(ceil_div(a.M, 32), slices);
+    const int row_tiles = ceil_div(a.M, 32);
+    const dim3 grid(row_tiles, slices + ceil_div(ap.sz_tiles, row_tiles));
     const int rt = ceil_div(a.r, 32);
-    uint16_t *thl = (uint16_t *)((char *)a.workspace + xp_bytes(a.M, a.K));
-    float *partial = (float *)((char *)thl + thl_bytes(a.M, a.r));
-#define FBQ_DOWN(B, R) hipLaunchKernelGGL((fbq_down_proj_prefill_kernel<B, R>), grid, dim3(256), 0, stream, a.x, a.At, partial, xp, a.M, a.K, a.r, kslice)
+#define FBQ_DOWN(B, R) hipLaunchKernelGGL((fbq_down_proj_prefill_kernel<B, R>), grid, dim3(256), 0, stream, ap, a.At, s.partial, a.r, kslice, slices)
     if (a.bits == 4) {
         if (rt <= 1) FBQ_DOWN(4, 1); else if (rt <= 2) FBQ_DOWN(4, 2); else if (rt <= 4) FBQ_DOWN(4, 4); else FBQ_DOWN(4, 8);
     } else {
@@ -869,75 +860,48 @@ hipError_t launch_prepass_prefill(const LinearArgs &a, hipStream_t stream)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int blocks = std::min(1024, ceil_div(a.M * a.r, 256));
-    hipLaunchKernelGGL(fbq_down_proj_finish_kernel, dim3(blocks), dim3(256), 0, stream, partial, thl, a.M, a.r, slices);
+    hipLaunchKernelGGL(fbq_down_proj_finish_kernel, dim3(blocks), dim3(256), 0, stream, s.partial, s.thl, a.M, a.r, slices);
     return hipGetLastError();
 }
 
-static int prefill_cu_count()
+template <int BITS, int TM, int KG>
+static void launch_tile(const PrefillParams &p, dim3 grid, hipStream_t stream)
 {
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-            n = 256;
-        return n;
-    }();
-    return cus;
+    hipLaunchKernelGGL((fbq_gemm_kernel<BITS, TM, KG>), grid, dim3(GemmTile<BITS, TM, KG>::kThreads), 0, stream, p);
+}
+
+template <int BITS>
+static void launch_cut(const PrefillParams &p, const PrefillCut &c, dim3 grid, hipStream_t stream)
+{
+    switch (c.tm) {
+    case 8: launch_tile<BITS, 8, 1>(p, grid, stream); break;
+    case 6: launch_tile<BITS, 6, 1>(p, grid, stream); break;
+    case 4: launch_tile<BITS, 4, 2>(p, grid, stream); break;
+    case 3: launch_tile<BITS, 3, 2>(p, grid, stream); break;
+    default: launch_tile<BITS, 2, 2>(p, grid, stream); break;
+    }
 }
 
 hipError_t launch_gemm_prefill(const LinearArgs &a, hipStream_t stream)
 {
+    const PrefillScratch s = scratch_of(a);
+    const PrefillCut c = prefill_cut(a.M, a.N, a.K);
     PrefillParams p;
-    p.qw = a.qw; p.scales = a.scales; p.zeros = a.zeros; p.Bt = a.Bt; p.y = a.y;
-    p.xp = (const uint16_t *)a.workspace;
-    p.thl = (const uint16_t *)((const char *)a.workspace + xp_bytes(a.M, a.K));
+    p.qw = a.qw; p.sz = s.sz; p.Bt = a.Bt; p.y = a.y; p.xp = s.xp; p.thl = s.thl;
     p.M = a.M; p.N = a.N; p.K = a.K; p.r = a.r;
     p.row_words = (int)row_words(a.K, a.bits);
     p.G = a.K / kGroup;
-    // Tile height: 128 rows amortise the de-quantization best, but what counts is how evenly the tiles fill the
-    // compute units; with at most one tile per CU the block has eight waves, two groups that split K.
     const int nb = ceil_div(a.N, kBN);
-    int tm = 4, kg = 1;
-    {
-        const int cus = prefill_cu_count();
-        double best = 1e30;
-        for (int t = 4; t >= 2; --t) {
-            const long blocks = (long)nb * ceil_div(a.M, 32 * t);
-            const double rounds = blocks <= cus ? 0.55 : (double)ceil_div((int)blocks, 2 * cus);   // a block alone on its CU runs faster
-            const double cost = rounds * (t + 0.65);
-            if (cost < best - 1e-9) { best = cost; tm = t; }
-        }
-        kg = (long)nb * ceil_div(a.M, 32 * tm) <= cus && a.K / kBK >= 16 ? 2 : 1;
-        if (tm == 4) kg = 1;                            // two groups' buffers of 128 rows would not fit the LDS
-        if (p.G & 1) { tm = 2; kg = 1; }
-    }
-    p.ksplit = ksplit_of(a.M, a.N, a.K);
-    if (p.ksplit > 1) { tm = 2; kg = 2; }
-    p.ypart = (float *)((char *)a.workspace + xp_bytes(a.M, a.K) + thl_bytes(a.M, a.r) + down_partial_bytes(a.M, a.K, a.r));
-    p.row_blocks = ceil_div(a.M, 32 * tm);
+    p.Np = nb * kBN;
+    p.ksplit = c.ksplit;
+    p.ypart = s.ypart;
+    p.row_blocks = ceil_div(a.M, 32 * c.tm);
     p.full_cols = (nb / kXcds) * kXcds;
     p.full_slots = (nb / kXcds) * p.row_blocks;
     p.rem_tiles = (nb % kXcds) * p.row_blocks;
     const dim3 grid(kXcds * (p.full_slots + ceil_div(p.rem_tiles, kXcds)) * p.ksplit);
-    const dim3 block(256 * kg);
-#define FBQ_GEMM(B, T, G, P) hipLaunchKernelGGL((fbq_gemm_kernel<B, T, G, P>), grid, block, 0, stream, p)
-    if (p.G & 1) {                                      // odd group count (no benchmark shape): one plain variant
-        if (a.bits == 4) FBQ_GEMM(4, 2, 1, false);
-        else FBQ_GEMM(3, 2, 1, false);
-        return hipGetLastError();
-    }
-    switch ((a.bits == 4 ? 100 : 0) + tm * 10 + kg) {
-    case 141: FBQ_GEMM(4, 4, 1, true); break;
-    case 131: FBQ_GEMM(4, 3, 1, true); break;
-    case 132: FBQ_GEMM(4, 3, 2, true); break;
-    case 121: FBQ_GEMM(4, 2, 1, true); break;
-    case 122: FBQ_GEMM(4, 2, 2, true); break;
-    case 41: FBQ_GEMM(3, 4, 1, true); break;
-    case 31: FBQ_GEMM(3, 3, 1, true); break;
-    case 32: FBQ_GEMM(3, 3, 2, true); break;
-    case 21: FBQ_GEMM(3, 2, 1, true); break;
-    default: FBQ_GEMM(3, 2, 2, true); break;
-    }
-#undef FBQ_GEMM
+    if (a.bits == 4) launch_cut<4>(p, c, grid, stream);
+    else launch_cut<3>(p, c, grid, stream);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && p.ksplit > 1) {
         const size_t total = (size_t)a.M * a.N;

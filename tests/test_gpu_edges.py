@@ -5,7 +5,8 @@ import numpy as np
 import pytest
 
 import fbq_synth
-from helpers import framed_in_nan, make_oracle_layer
+from helpers import assert_matches_oracle, framed_in_nan, make_oracle_layer
+from oracle import fbq_oracle as orc
 
 pytestmark = pytest.mark.gpu
 
@@ -29,3 +30,54 @@ def test_quantizer_tile_edges(bits, N, K, r):
     assert np.array_equal(dev.scales.cpu().numpy().view(np.float16), L.scales)
     assert np.array_equal(dev.zeros.cpu().numpy().view(np.float16), L.zeros)
     assert np.array_equal(dev.qweight.cpu().numpy().view(np.uint32), L.words)
+
+
+# ------------------------------------------------------------------ prefill GEMM: tiles of 64, 96, 128, 192 and 256 rows x 256 columns, K split over blocks
+
+PREFILL_CASES = [
+    # N, K, r, M: the tile height the launcher takes is in the remark
+    # (the per-token bar is relative to the norm of a token's outputs: a few dozen columns, so that it is no single cancelled sum)
+    (25, 128, 8, 65),           # 64 rows, one quantization group (the second K group has none)
+    (40, 256, 40, 77),          # 64; a rank that is no multiple of 16 or 64
+    (25, 2304, 24, 65),         # 64, K split over three blocks, M N odd: the summing launch's scalar form
+    (255, 4224, 200, 77),       # 64, K split over six blocks, an odd number of groups
+    (513, 1408, 256, 66),       # 64; four tiles of taps
+    (4100, 640, 0, 300),
+    (33001, 128, 0, 65),        # 96
+    (33001, 640, 72, 96),       # 96
+    (33001, 128, 72, 97),       # 128
+    (33000, 640, 8, 128),       # 128, whole rows stored
+    (33001, 128, 16, 129),      # 192
+    (33000, 640, 40, 191),      # 192
+    (33001, 128, 40, 193),      # 256
+    (33000, 640, 64, 193),      # 256
+]
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("N,K,r,M", PREFILL_CASES)
+def test_prefill_tile_edges(bits, N, K, r, M):
+    """Weights enter the matrix cores with two fp16 roundings (2^-11 of the weight, 2^-12 of a step) and y is rounded once:
+    3.5e-4 relative; the bars are those of the other parity tests.  Output and workspace start as NaN patterns."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    spec = fbq_synth.LayerSpec("edge", N, K, r, bits)
+    rng = np.random.Generator(np.random.Philox(43))
+    codes, s, z = fbq_synth.make_random_quantized(spec, 42, 3)
+    A, B = fbq_synth.make_branch(spec, 42, 3) if r else (None, None)
+    x = rng.standard_normal((M, K)).astype(np.float16)
+    want = orc.linear(x, orc.pack(codes, bits), s, z, A, B, bits, 128)
+    p = fbq.pack(fbq.Desc(N, K, r, bits), codes, s, z, A, B)
+    dev = fbq.upload_layer(p)
+    dev = fbq.DeviceLayer(dev.desc, *[framed_in_nan(t) for t in (dev.qweight, dev.scales, dev.zeros, dev.At, dev.Bt)])
+    xd = framed_in_nan(torch.from_numpy(x).cuda())
+    y = framed_in_nan(torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda"))
+    ws = framed_in_nan(torch.full((fbq.workspace_bytes(dev.desc, M),), 0x7D, dtype=torch.uint8, device="cuda"))
+    fbq.linear(dev, xd, y, ws)
+    torch.cuda.synchronize()
+    got = y.cpu().numpy()
+    assert_matches_oracle(got, want, f"{N}x{K} r={r} M={M}", tol=1e-3)
+    y.fill_(float("nan"))
+    fbq.linear(dev, xd, y, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy(), got)
