@@ -240,6 +240,8 @@ __global__ __launch_bounds__(64 * kQuantWaves, 4) void fbq_quantize_kernel(const
         if (!(s > 0.0)) s = 1.0;
         uint16_t s16 = double_to_half_bits(s);
         if (s16 < 0x0400u) s16 = 0x0400u;
+        // (extremes that are infinite or NaN never meet the condition below, whatever the scale: straight to the last one)
+        if (!(__builtin_fabs(lo) < __builtin_inf() && __builtin_fabs(hi) < __builtin_inf()) && s16 < 0x7bffu) s16 = 0x7bffu;
         uint16_t z16;
         for (;;) {
             const double sd = half_bits_to_double(s16);
