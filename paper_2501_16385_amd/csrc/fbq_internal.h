@@ -97,32 +97,36 @@ constexpr size_t kStaticScratchBytes = (size_t)(16 + 1) * 16 * kMaxRank * 8;
 constexpr int kPrefillColumns = 256;   // columns of a block tile of the prefill GEMM
 
 // How a layer is cut into blocks: tiles of 32 tm rows (tm = 8, 6: four waves; 4, 3, 2: eight waves in two K groups), K
-// split over ksplit blocks.  One block per CU at a time, 256 CUs assumed (the workspace is sized without a device): a
-// launch takes rounds x (steps x step time + fixed part), plus the summing launch and its traffic where K is split over
-// blocks.  The constants (us) are fitted to 3100 measurements: both bit widths, 17 to 2048 tokens, eleven layers from
-// 1000 x 1408 to 28672 x 8192 and 8192 x 28672, every tile height with every split; over them the choice is 0.3 % slower
-// than the best one on average and 8 % at most.  A CU runs faster while others are idle (the clock follows the load): a
-// step of a round that fills the fraction f of the CUs takes 0.46 (1 - f) less.  Examples, the choice and the two that
+// split over ksplit blocks.  One block per CU at a time, 8 XCDs of 32 CUs assumed (the workspace is sized without a device):
+// a launch takes rounds x (steps x step time + fixed part), plus the summing launch and its traffic where K is split over
+// blocks.  Column blocks are dealt to the XCDs whole, eight at a time, the rest block by block: the fullest XCD counts.
+// The constants (us) are fitted to 2700 measurements: both bit widths, 65 to 2048 tokens, eleven layers from
+// 1000 x 1408 to 28672 x 8192 and 8192 x 28672, every tile height with every split; over them the choice is 0.6 % slower
+// than the best one on average and 14 % at most.  A CU runs faster while others are idle (the clock follows the load): a
+// step of a round that fills the fraction f of the CUs takes 0.48 (1 - f) less.  Examples, the choice and the two that
 // bracket it, us: 4096 -> 11008 at 1024 tokens 102 (256 rows), 109 (96), 118 (128); 8192 -> 28672 at 384 tokens 172 (192
 // rows), 190 (96), 202 (128); 28672 -> 8192 at 256 tokens 137 (128 rows, K split in 4), 144 (in 3), 144 (in 8).
-struct PrefillCut { int tm, ksplit; double us; };
+struct PrefillCut { int tm, ksplit; };
 
 inline PrefillCut prefill_cut(int M, int N, int K)
 {
     static constexpr struct { int tm, kg; double step, fixed; } kTiles[] = {
-        {8, 1, 1.610, 13.7}, {6, 1, 1.237, 10.1}, {4, 2, 1.722, 8.3}, {3, 2, 1.397, 6.7}, {2, 2, 1.146, 5.5}};
-    const int G = K / kGroup;
-    PrefillCut best{0, 1, 1e300};
+        {8, 1, 1.614, 16.2}, {6, 1, 1.241, 11.6}, {4, 2, 1.731, 9.4}, {3, 2, 1.402, 7.6}, {2, 2, 1.144, 6.0}};
+    const int G = K / kGroup, columns = ceil_div(N, kPrefillColumns);
+    PrefillCut best{0, 1};
+    double best_us = 1e300;
     for (const auto &t : kTiles) {
-        const double tiles = (double)ceil_div(N, kPrefillColumns) * ceil_div(M, 32 * t.tm);
+        const int rows = ceil_div(M, 32 * t.tm);
+        const double tiles = (double)columns * rows;
         for (int split = 1; split <= 8; ++split) {
             if (split > 1 && (tiles * split > 600 || G / (split * t.kg) < 2)) break;
-            const double rounds = std::ceil(tiles * split / 256.0), filled = tiles * split / (256.0 * rounds);
+            const double per_xcd = (double)(columns / 8) * rows * split + std::ceil((columns % 8) * (double)rows * split / 8.0);
+            const double rounds = std::ceil(per_xcd / 32.0), filled = tiles * split / (256.0 * rounds);
             const int steps = 2 * ceil_div(G, split * t.kg);
-            double us = rounds * (steps * t.step * (1.0 - 0.46 * (1.0 - filled)) + t.fixed);
-            if (split > 1) us += 5.0 + 1.075e-6 * M * (double)N * (split + 0.5);
+            double us = rounds * (steps * t.step * (1.0 - 0.48 * (1.0 - filled)) + t.fixed);
+            if (split > 1) us += 5.6 + 0.886e-6 * M * (double)N * (split + 0.5);
             us *= 1.0 - 0.01 * t.tm;                    // (taller tiles draw less power per product: measured, they win where this estimate is a tie)
-            if (us < best.us) best = {t.tm, split, us};
+            if (us < best_us) { best_us = us; best = {t.tm, split}; }
         }
     }
     return best;

@@ -41,6 +41,7 @@
 #include <type_traits>
 
 #include "fbq_internal.h"
+#include "fbq_lds_copy.h"
 
 namespace fbq {
 
@@ -59,35 +60,6 @@ constexpr int kXRow = 128;           // bytes per activation row and step in LDS
 constexpr int kXcds = 8;             // accelerator dies, each with its own L2
 constexpr int kStages = 3;           // steps in LDS: the one worked on and the next two on their way from memory
 
-// Sixteen bytes per lane from global memory straight into LDS, `lane_off` + `row_off` bytes behind the descriptor's
-// base (row_off the same for all lanes): lane l's go to `dst` + 16 l, dst wave-uniform.  Written as an instruction and
-// not with the builtin, because the compiler waits for EVERY load in flight before the first LDS read behind a builtin
-// copy - it cannot tell the buffer being read from the ones being filled - which undoes any look-ahead: in an earlier
-// form of the fused kernel every round began with vmcnt(0).  The instruction has no destination register; whoever reads
-// a copy waits for it by count and passes a barrier (both with a memory clobber).  The compiler's own counted waits only
-// get stricter by the copies it does not know of.  Nothing else in these kernels uses M0.
-__device__ __forceinline__ uint32_t lds_offset(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p; }
-__device__ __forceinline__ void copy16_to_lds(__amdgpu_buffer_rsrc_t buf, int lane_off, int row_off, uint32_t dst)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(lane_off), "s"(buf), "s"(row_off));
-}
-__device__ __forceinline__ void copy12_to_lds(__amdgpu_buffer_rsrc_t buf, int lane_off, int row_off, uint32_t dst)   // (12 bytes per lane, but 16 l apart in LDS)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx3 %1, %2, %3 offen lds" ::"s"(dst), "v"(lane_off), "s"(buf), "s"(row_off));
-}
-__device__ __forceinline__ void copy4_to_lds(__amdgpu_buffer_rsrc_t buf, int lane_off, int row_off, uint32_t dst)    // (4 bytes: dst + 4 l)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(dst), "v"(lane_off), "s"(buf), "s"(row_off));
-}
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, long bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
-}
-
-// Piece c (16 bytes) of a row is stored at position c ^ piece_key(row): 8 or 16 consecutive rows reading the same c touch
-// every bank once, whether the LDS serves 128 or 256 bytes per clock.
-__host__ __device__ __forceinline__ constexpr int piece_key(int row) { return ((row >> 1) & 7) ^ ((row & 1) << 2); }
-
 __device__ __forceinline__ half2_t h2_of(uint32_t v) { return __builtin_bit_cast(half2_t, v); }
 __device__ __forceinline__ half2_t h2_splat(half_t v) { return half2_t{v, v}; }
 
@@ -101,9 +73,9 @@ struct PrefillParams {
     int M, N, K, r;
     int row_words, G, Np;  // Np: N rounded up to kBN
     int row_blocks;        // ceil(M / block tile rows)
-    int full_slots;        // tiles per XCD that belong to column blocks this XCD has to itself: (column blocks / 8) * row_blocks
+    int full_slots;        // blocks per XCD that belong to column blocks this XCD has to itself: (column blocks / 8) * row_blocks * ksplit
     int full_cols;         // column blocks dealt out whole, eight at a time: (column blocks / 8) * 8
-    int rem_tiles;         // tiles of the column blocks left over, dealt out singly over the XCDs
+    int rem_blocks;        // blocks of the column blocks left over, dealt out singly over the XCDs
     int ksplit;            // blocks that split K for the same tile (1: none)
     float *ypart;          // ksplit > 1 only: [ksplit][M][N] fp32 partial results, added up by fbq_sum_parts_kernel
 };
@@ -231,16 +203,19 @@ __global__ __launch_bounds__((GemmTile<BITS, TM, KG>::kThreads)) __attribute__((
     // after the other in id order), so that a weight tile is fetched into one L2 only.
     // Where a launch would have fewer blocks than the CUs can hold, ksplit blocks share a tile and split
     // K; their fp32 partial results are added by a small launch afterwards.
-    // Column blocks are dealt out whole, eight at a time; the tiles of the ones left over (fewer than eight) go to
-    // the XCDs one by one, so that every XCD has the same number of tiles whatever the column count.
-    const int xcd = blockIdx.x % kXcds, slot = (blockIdx.x / kXcds) / p.ksplit, part = (blockIdx.x / kXcds) % p.ksplit;
-    int bm, bn;
+    // Column blocks are dealt out whole, eight at a time; the blocks of the ones left over (fewer than eight) go to
+    // the XCDs one by one, so that every XCD has the same number of them whatever the column count.
+    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+    int bm, bn, part;
     if (slot < p.full_slots) {
-        bm = slot % p.row_blocks;
-        bn = (slot / p.row_blocks) * kXcds + xcd;
+        const int q = slot / p.ksplit;
+        part = slot % p.ksplit;
+        bm = q % p.row_blocks;
+        bn = (q / p.row_blocks) * kXcds + xcd;
     } else {
-        const int q = (slot - p.full_slots) * kXcds + xcd;
-        if (q >= p.rem_tiles) return;                   // block-uniform
+        const int i = (slot - p.full_slots) * kXcds + xcd, q = i / p.ksplit;
+        if (i >= p.rem_blocks) return;                  // block-uniform
+        part = i % p.ksplit;
         bm = q % p.row_blocks;
         bn = p.full_cols + q / p.row_blocks;
     }
@@ -897,9 +872,9 @@ hipError_t launch_gemm_prefill(const LinearArgs &a, hipStream_t stream)
     p.ypart = s.ypart;
     p.row_blocks = ceil_div(a.M, 32 * c.tm);
     p.full_cols = (nb / kXcds) * kXcds;
-    p.full_slots = (nb / kXcds) * p.row_blocks;
-    p.rem_tiles = (nb % kXcds) * p.row_blocks;
-    const dim3 grid(kXcds * (p.full_slots + ceil_div(p.rem_tiles, kXcds)) * p.ksplit);
+    p.full_slots = (nb / kXcds) * p.row_blocks * p.ksplit;
+    p.rem_blocks = (nb % kXcds) * p.row_blocks * p.ksplit;
+    const dim3 grid(kXcds * (p.full_slots + ceil_div(p.rem_blocks, kXcds)));
     if (a.bits == 4) launch_cut<4>(p, c, grid, stream);
     else launch_cut<3>(p, c, grid, stream);
     hipError_t e = hipGetLastError();
