@@ -270,7 +270,7 @@ fbq_status fbq_measure_read_stream(const void *buf, size_t bytes, fbq_stream str
  *           Q(W - Sigma16) held constant; loss: one fp32 = || W X^T - W_F X^T ||_F^2 (the square:
  *           the trace form and the printed gradient are those of the squared norm), or NULL:
  *           the gradients need only products with r rows (H is symmetric, so Delta_F H At^T =
- *           Delta_F (At H)^T), the loss alone needs Delta_F H (2 N K^2 flop) and is skipped then.
+ *           Delta_F (At H)^T), the loss alone needs Delta_F^T Delta_F (N K^2 flop) and is skipped then.
  *   lr = 0 evaluates without moving the masters.  Delta_F, H and their products enter the matrix
  *   cores as fp16 with fp32 accumulation: gradients and loss carry a relative error of a few 1e-4.
  *   Nothing is allocated; everything is enqueued on `stream`.  Needs r >= 1.

@@ -12,26 +12,26 @@
 //   dL/dAt     <- -2 Q H              [r,K]    } one GEMM on the stacked                                 
 //   V^T        <- At H                [r,K]    } operand [Q; At], K split
 //   dL/dBt     <- -2 Delta_F V        [N,r]                              (GEMM, K split)
-//   L          <- sum Delta_F o (Delta_F H)    only if the caller asks   (GEMM, 2 N K^2 flop, + reduction)
-//   masters    <- masters - lr gradient                                  (update kernel)
+//   L          <- sum (Delta_F^T Delta_F) o H  only if the caller asks   (symmetric product, N K^2 flop, + reduction)
+//   masters    <- masters - lr gradient                                  (with the gradients' split sums)
 //
-// with Sigma[n,k] = sum_j Bt[n,j] At[j,k] in the device layouts At [r,K], Bt [N,r].  Multiplying
-// Delta_F H out costs 2 N K^2 flop; the gradients need only products with r rows or columns
-// (8 N K r + 4 r K^2 flop, a twentieth of that at r = 64, K = 4096) because H is symmetric:
-// Delta_F H At^T = Delta_F (At H)^T.  The loss is the one quantity that needs Delta_F H itself.
+// with Sigma[n,k] = sum_j Bt[n,j] At[j,k] in the device layouts At [r,K], Bt [N,r].  The gradients need only products with
+// r rows or columns (8 N K r + 4 r K^2 flop) because H is symmetric: Delta_F H At^T = Delta_F (At H)^T.  The loss is the one
+// quantity that needs a contraction over N and K x K, and as tr(Delta_F H Delta_F^T) = sum (Delta_F^T Delta_F) o H that is a
+// symmetric one, half the work of Delta_F H.
 //
-// One matrix-core kernel serves every contraction: C[m,n] = sum_k A[m,k] B[n,k] with both operands
-// contiguous along k (fp16 in, fp32 accumulate, v_mfma_f32_32x32x16_f16).  128x128 block tile,
-// 4 waves of 64x64, k advancing 64 at a time; both operand tiles go global -> registers -> LDS with
-// coalesced 16-byte loads (rows of 128 bytes, whole cache lines) and are read back as matrix
-// operands with ds_read_b128, the 16-byte chunks of a row XOR-swizzled so that neither side has a
-// bank conflict; the next step's global loads are in flight while the current one is multiplied.
-// Rows past the end of an operand are fetched through a bounds-checked buffer descriptor and
-// arrive as zeros.  fp16 operands carry Delta_F times 256 and H times the caller's h_scale, so
+// Two matrix-core kernels (v_mfma_f32_32x32x16_f16, fp16 in, fp32 accumulate, operands contiguous along the contraction):
+// fbq_gemm_nt_kernel for the products with r rows or columns, fbq_syrk_kernel for A A^T.  Both pass their operands through LDS
+// by buffer_load ... lds, several steps of 64 ahead; rows (128 bytes a step, whole cache lines) are stored with their 16-byte
+// pieces XOR-swizzled so that reads have no bank conflict; rows past the end of an operand are fetched through a bounds-checked
+// buffer descriptor and arrive as zeros.  fp16 operands carry Delta_F times 256 and H times the caller's h_scale, so
 // that neither leaves the normal range; the factors come out again in the epilogues.
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 #include "fbq_internal.h"
+#include "fbq_lds_copy.h"
 
 namespace fbq {
 
@@ -39,7 +39,6 @@ typedef _Float16 half_t;
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
-typedef uint32_t uint4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kStepK = 64;           // k per step: one 128-byte row segment per operand row
 constexpr float kDeltaGain = 256.0f; // Delta_F is stored as fp16(256 Delta_F)
@@ -50,74 +49,68 @@ struct GemmArgs {
     const uint16_t *B;   // [Nr][ldb] fp16
     int Mr, Nr, Kd;      // Kd a multiple of 64
     int lda, ldb;        // elements
-    // store epilogue (any of the three may be absent)
+    // store epilogue (either may be absent)
     float *C32; int ldc32; float alpha; int c32_rows;   // C32[m,n] = alpha acc for rows m < c32_rows
+    float *master; float lr;                            // with C32: master[m,n] -= lr C32[m,n] (gradient descent; laid out like C32)
     uint16_t *C16; int ldc16; float beta; int c16_row0; // C16[m - c16_row0, n] = fp16(beta acc) for rows m >= c16_row0
-    const uint16_t *D; int ldd; float *dot;      // dot[tile] = sum over the tile of acc D[m,n]  (splits == 1 only)
     // K split over `splits` blocks per tile (few tiles, long K): raw sums go to part [splits][Mr][Nr]
     // and fbq_sum_splits_kernel applies the store epilogue
     int splits; float *part;
 };
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_buffer(const void *p, long bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
-}
-
-// 16-byte chunk c (0..7) of row `row` of an operand tile sits at chunk c ^ key(row): 8 or 16
-// consecutive rows reading the same c touch every bank once, whether the LDS serves 128 or 256
-// bytes per clock.
-__device__ __forceinline__ int swizzle_key(int row) { return ((row >> 1) & 7) ^ ((row & 1) << 2); }
-
 __device__ __forceinline__ void store_result(const GemmArgs &g, int m, int n, float a)
 {
-    if (g.C32 && m < g.c32_rows) g.C32[(size_t)m * g.ldc32 + n] = g.alpha * a;
+    if (g.C32 && m < g.c32_rows) {
+        const size_t i = (size_t)m * g.ldc32 + n;
+        const float v = g.alpha * a;
+        g.C32[i] = v;
+        if (g.master) g.master[i] = g.master[i] - g.lr * v;   // masters <- masters - lr gradient (Alg. 1, the update line)
+    }
     if (g.C16 && m >= g.c16_row0) g.C16[(size_t)(m - g.c16_row0) * g.ldc16 + n] = __builtin_bit_cast(uint16_t, (half_t)(g.beta * a));
 }
 
 // WM x WN: 32x32 tiles a wave owns (rows x columns); the block's 2 x 2 waves cover 64 WM x 64 WN.
+// These products have few rows or columns (r or 2r) and read one large operand once: bound by memory.  The steps of 64 pass
+// through a ring of four stages in LDS, copied there without passing registers three steps ahead (through registers, one step
+// ahead, the three products of a 4096 x 4096 step at r = 64 took 43 us and take 34).
+constexpr int kNtStages = 4;
 template <int WM, int WN>
-__global__ __launch_bounds__(256, (WM * WN > 4 ? 1 : 2)) void fbq_gemm_nt_kernel(GemmArgs g)
+__global__ __launch_bounds__(256) void fbq_gemm_nt_kernel(GemmArgs g)
 {
-    extern __shared__ __align__(16) unsigned char lds[];   // [buffer][A rows | B rows][128 bytes]
     constexpr int BM = 64 * WM, BN = 64 * WN;
-    constexpr int kABytes = BM * kStepK * 2, kBufferBytes = (BM + BN) * kStepK * 2;
-    constexpr int LA = BM * 8 / 256, LB = BN * 8 / 256;     // 16-byte loads per thread and step
+    constexpr int kStageBytes = (BM + BN) * kStepK * 2;
+    constexpr int kCopies = (BM + BN) / 8 / 4;          // per wave and step, eight rows each
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kNtStages * kStageBytes];   // [stage][A rows | B rows][128 bytes]
 
     // Consecutive tiles (same rows of A, neighbouring rows of B) run on the same XCD and share its L2.
     const int tiles_n = (g.Nr + BN - 1) / BN, tiles_m = (g.Mr + BM - 1) / BM;
     const int total = tiles_m * tiles_n * g.splits, per_xcd = (total + kXcds - 1) / kXcds;
     const int unit = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-    if (unit >= total) return;
-    const int tile = unit / g.splits, split = unit % g.splits;
-    const int m0 = (tile / tiles_n) * BM, n0 = (tile % tiles_n) * BN;
+    if ((int)(blockIdx.x / kXcds) >= per_xcd || unit >= total) return;
+    // (wave-uniform as it is, but the divisions run on the vector unit: descriptors and copies want scalar registers)
+    const int tile = __builtin_amdgcn_readfirstlane(unit / g.splits), split = __builtin_amdgcn_readfirstlane(unit % g.splits);
+    const int m0 = __builtin_amdgcn_readfirstlane(tile / tiles_n) * BM, n0 = __builtin_amdgcn_readfirstlane(tile % tiles_n) * BN;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int col = lane & 31, h = lane >> 5;
 
-    const __amdgpu_buffer_rsrc_t abuf = rows_buffer(g.A + (size_t)m0 * g.lda, (long)min(BM, g.Mr - m0) * g.lda * 2);
-    const __amdgpu_buffer_rsrc_t bbuf = rows_buffer(g.B + (size_t)n0 * g.ldb, (long)min(BN, g.Nr - n0) * g.ldb * 2);
-
-    // thread t fetches chunk t % 8 of rows t / 8, t / 8 + 32, ...: every wave-wide load covers whole 128-byte row segments
-    const int lrow = tid >> 3, lch = tid & 7;
-    const int goff_a = lrow * g.lda * 2 + lch * 16, goff_b = lrow * g.ldb * 2 + lch * 16;
-    const int gstep_a = 32 * g.lda * 2, gstep_b = 32 * g.ldb * 2;
-    const int loff = lrow * 128 + ((lch ^ swizzle_key(lrow)) * 16);     // rows 32 apart share the key
-    uint4_t ra[LA], rb[LB];
-    auto fetch = [&](int s) {
+    const __amdgpu_buffer_rsrc_t abuf = buffer_of(g.A + (size_t)m0 * g.lda, (long)min(BM, g.Mr - m0) * g.lda * 2);   // rows past the end: zeros
+    const __amdgpu_buffer_rsrc_t bbuf = buffer_of(g.B + (size_t)n0 * g.ldb, (long)min(BN, g.Nr - n0) * g.ldb * 2);
+    const int all_steps = g.Kd / kStepK, per_split = (all_steps + g.splits - 1) / g.splits;
+    const int first = split * per_split, steps = min(all_steps, first + per_split) - first;   // >= 1: the launcher sees to it
+    const int lrow = lane >> 3;
+    const uint32_t lds0 = lds_offset(lds);
+    auto copy_step = [&](int s, int stage) __attribute__((always_inline)) {
+        const uint32_t base = lds0 + stage * kStageBytes;
 #pragma unroll
-        for (int i = 0; i < LA; ++i) ra[i] = __builtin_bit_cast(uint4_t, __builtin_amdgcn_raw_buffer_load_b128(abuf, goff_a + i * gstep_a + s * 128, 0, 0));
-#pragma unroll
-        for (int i = 0; i < LB; ++i) rb[i] = __builtin_bit_cast(uint4_t, __builtin_amdgcn_raw_buffer_load_b128(bbuf, goff_b + i * gstep_b + s * 128, 0, 0));
-    };
-    auto stash = [&](int buf) {
-        unsigned char *la = lds + buf * kBufferBytes, *lb = la + kABytes;
-#pragma unroll
-        for (int i = 0; i < LA; ++i) *reinterpret_cast<uint4_t *>(la + loff + i * 32 * 128) = ra[i];
-#pragma unroll
-        for (int i = 0; i < LB; ++i) *reinterpret_cast<uint4_t *>(lb + loff + i * 32 * 128) = rb[i];
+        for (int j = 0; j < kCopies; ++j) {
+            const int row = 8 * (4 * j + wave);         // of [A rows | B rows]; BM is a multiple of 32, so the side is the same for all waves
+            const int piece = ((lane & 7) ^ piece_key((row + lrow) & 15)) * 16;
+            if (32 * j < BM) copy16_to_lds(abuf, lrow * g.lda * 2 + piece, row * g.lda * 2 + (first + s) * 128, base + row * 128);
+            else copy16_to_lds(bbuf, lrow * g.ldb * 2 + piece, (row - BM) * g.ldb * 2 + (first + s) * 128, base + row * 128);
+        }
     };
 
     float16_t acc[WM][WN];
@@ -128,90 +121,99 @@ __global__ __launch_bounds__(256, (WM * WN > 4 ? 1 : 2)) void fbq_gemm_nt_kernel
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-    // operand rows of this lane: 32 rows apart, so they share the swizzle key
-    const int key = swizzle_key(col);
-    const int arow = (wm * 32 * WM + col) * 128, brow = (wn * 32 * WN + col) * 128;
-    auto multiply = [&](int buf) {
-        const unsigned char *la = lds + buf * kBufferBytes, *lb = la + kABytes;
+    // operand rows of this lane: 32 rows apart, so they share the key
+    const int key = piece_key(col & 15);
+    const int arow = (wm * 32 * WM + col) * 128, brow = (BM + wn * 32 * WN + col) * 128;
+    for (int s = 0; s < min(kNtStages - 1, steps); ++s) copy_step(s, s);
+    for (int s = 0; s < steps; ++s) {
+        // step s has landed, and everybody is done with step s - 1, whose stage the next copies go to
+        if (s + kNtStages - 2 < steps) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((kNtStages - 2) * kCopies) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (s + kNtStages - 1 < steps) copy_step(s + kNtStages - 1, (s + kNtStages - 1) % kNtStages);
+        const unsigned char *base = lds + (s % kNtStages) * kStageBytes;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
             const int chunk = ((kk * 2 + h) ^ key) * 16;
             half8_t af[WM], bf[WN];
 #pragma unroll
-            for (int i = 0; i < WM; ++i) af[i] = *reinterpret_cast<const half8_t *>(la + arow + i * 32 * 128 + chunk);
+            for (int i = 0; i < WM; ++i) af[i] = *reinterpret_cast<const half8_t *>(base + arow + i * 32 * 128 + chunk);
 #pragma unroll
-            for (int j = 0; j < WN; ++j) bf[j] = *reinterpret_cast<const half8_t *>(lb + brow + j * 32 * 128 + chunk);
+            for (int j = 0; j < WN; ++j) bf[j] = *reinterpret_cast<const half8_t *>(base + brow + j * 32 * 128 + chunk);
 #pragma unroll
             for (int i = 0; i < WM; ++i)
 #pragma unroll
                 for (int j = 0; j < WN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[i], bf[j], acc[i][j], 0, 0, 0);
         }
-    };
-
-    const int all_steps = g.Kd / kStepK, per_split = (all_steps + g.splits - 1) / g.splits;
-    const int first = split * per_split, steps = min(all_steps, first + per_split) - first;   // >= 1: the launcher sees to it
-    fetch(first);
-    stash(0);
-    __syncthreads();
-    for (int s = 0; s < steps; ++s) {
-        if (s + 1 < steps) fetch(first + s + 1);
-        multiply(s & 1);
-        if (s + 1 < steps) stash((s + 1) & 1);   // the other buffer: every wave finished reading it before the last barrier
-        __syncthreads();
     }
 
     // accumulator register v of a lane: row 8 (v / 4) + 4 h + v % 4 of the 32x32 tile, column `col`
-    {
-        float dot = 0.0f;
 #pragma unroll
-        for (int i = 0; i < WM; ++i)
+    for (int i = 0; i < WM; ++i)
 #pragma unroll
-            for (int j = 0; j < WN; ++j) {
-                const int n = n0 + (wn * WN + j) * 32 + col;
+        for (int j = 0; j < WN; ++j) {
+            const int n = n0 + (wn * WN + j) * 32 + col;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int m = m0 + (wm * WM + i) * 32 + 8 * (v / 4) + 4 * h + (v % 4);
-                    if (m >= g.Mr || n >= g.Nr) continue;
-                    const float a = acc[i][j][v];
-                    if (g.splits > 1) {
-                        g.part[((size_t)split * g.Mr + m) * g.Nr + n] = a;
-                        continue;
-                    }
-                    store_result(g, m, n, a);
-                    if (g.D) dot = fmaf(a, (float)__builtin_bit_cast(half_t, g.D[(size_t)m * g.ldd + n]), dot);
-                }
+            for (int v = 0; v < 16; ++v) {
+                const int m = m0 + (wm * WM + i) * 32 + 8 * (v / 4) + 4 * h + (v % 4);
+                if (m >= g.Mr || n >= g.Nr) continue;
+                if (g.splits > 1) g.part[((size_t)split * g.Mr + m) * g.Nr + n] = acc[i][j][v];
+                else store_result(g, m, n, acc[i][j][v]);
             }
-        if (g.dot) {
-            // fixed order: lanes by xor-shuffles, then the four waves in turn
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 64);
-            float *wsum = reinterpret_cast<float *>(lds);
-            if (lane == 0) wsum[wave] = dot;
-            __syncthreads();
-            if (tid == 0) g.dot[tile] = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
         }
-    }
 }
 
-// The store epilogue over the sum of the K splits' partial results, splits in index order.
-__global__ __launch_bounds__(256) void fbq_sum_splits_kernel(GemmArgs g)
+// loss = scale x (sum of the tiles' partial sums, in index order), by one block.
+struct LossArgs { const float *part; int n; float scale; float *out; };
+__device__ void sum_loss(const LossArgs &l)
 {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x, count = (size_t)g.Mr * g.Nr;
-    if (i >= count) return;
-    float a = 0.0f;
-    for (int sp = 0; sp < g.splits; ++sp) a += g.part[(size_t)sp * count + i];
-    store_result(g, (int)(i / g.Nr), (int)(i % g.Nr), a);
+    __shared__ double s[256];
+    double a = 0.0;
+    for (int i = threadIdx.x; i < l.n; i += 256) a += (double)l.part[i];
+    s[threadIdx.x] = a;
+    __syncthreads();
+    for (int off = 128; off > 0; off >>= 1) {
+        if ((int)threadIdx.x < off) s[threadIdx.x] += s[threadIdx.x + off];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *l.out = (float)(s[0] * (double)l.scale);
 }
 
-// Tile shapes: 128 x 128 in general, 64 rows or 64 columns where an operand has no more than that (the
-// r-row products at r <= 64).  Larger tiles (256 x 128 at one block per CU: 4096^3 at 547 instead of
-// 650 TFLOP/s; 256 x 256: spills) were measured and dropped: with a single block per CU nothing runs
-// while its waves wait at the barrier.  K steps of 32 with up to four blocks per CU: 594 instead of 624 TFLOP/s.
+// The store epilogue over the sum of the K splits' partial results, splits in index order; four results per thread (Nr is a
+// multiple of 4).  With loss.part the last block adds up the loss instead.
+__global__ __launch_bounds__(256) void fbq_sum_splits_kernel(GemmArgs g, LossArgs loss)
+{
+    if (loss.part && blockIdx.x == gridDim.x - 1) {
+        sum_loss(loss);
+        return;
+    }
+    const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4, count = (size_t)g.Mr * g.Nr;
+    if (i >= count) return;
+    float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int s0 = 0; s0 < g.splits; s0 += 8) {          // eight splits per round trip to memory
+        float4 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = *reinterpret_cast<const float4 *>(g.part + (size_t)min(s0 + k, g.splits - 1) * count + i);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (s0 + k < g.splits) { a.x += v[k].x; a.y += v[k].y; a.z += v[k].z; a.w += v[k].w; }
+    }
+    const int m = (int)(i / g.Nr), n = (int)(i % g.Nr);
+    store_result(g, m, n, a.x);
+    store_result(g, m, n + 1, a.y);
+    store_result(g, m, n + 2, a.z);
+    store_result(g, m, n + 3, a.w);
+}
+
+// Tile shapes: 64 rows or columns where an operand has no more, and 64 of the other one, so that there are as many tiles, as few
+// K splits and as little traffic of partial results as possible (4096 x 4096, r = 64, us with 64 x 64 and 128 x 64 tiles / 64 x 128
+// and 128 x 128: B^T Delta 9.7 / 11.0, [Q; At] H 14.2 / 16.7, Delta V 9.7 / 11.6).  Half as many splits: 0.3 to 1 us slower.
 struct TileShape { int wm, wn; };
 static TileShape tile_for(int Mr, int Nr)
 {
-    if (Mr <= 64) return {1, 2};
-    if (Nr <= 64) return {2, 1};
+    if (Mr <= 64) return {1, 1};
+    if (Mr <= 128) return {2, 1};
+    if (Nr <= 64) return {1, 1};
+    if (Nr <= 128) return {1, 2};
     return {2, 2};
 }
 static int tiles_of(int Mr, int Nr)
@@ -239,23 +241,23 @@ static size_t split_scratch_bytes(int Mr, int Nr, int Kd)
 template <int WM, int WN>
 static void launch_gemm_tile(const GemmArgs &g, dim3 grid, hipStream_t stream)
 {
-    constexpr int bytes = 2 * (64 * WM + 64 * WN) * kStepK * 2;
-    static_assert(bytes <= 65536, "more LDS than a launch may ask for without raising the function's limit");
-    hipLaunchKernelGGL((fbq_gemm_nt_kernel<WM, WN>), grid, dim3(256), bytes, stream, g);
+    hipLaunchKernelGGL((fbq_gemm_nt_kernel<WM, WN>), grid, dim3(256), 0, stream, g);
 }
 
-static hipError_t launch_gemm(GemmArgs g, float *split_scratch, hipStream_t stream)
+static hipError_t launch_gemm(GemmArgs g, float *split_scratch, hipStream_t stream, const LossArgs &loss = LossArgs{})
 {
-    g.splits = (!g.dot && split_scratch) ? splits_for(g.Mr, g.Nr, g.Kd) : 1;
+    g.splits = splits_for(g.Mr, g.Nr, g.Kd);
     g.part = split_scratch;
     const TileShape t = tile_for(g.Mr, g.Nr);
     const int units = tiles_of(g.Mr, g.Nr) * g.splits;
     const dim3 grid(ceil_div(units, kXcds) * kXcds);
-    if (t.wm == 1) launch_gemm_tile<1, 2>(g, grid, stream);
+    if (t.wm == 1 && t.wn == 1) launch_gemm_tile<1, 1>(g, grid, stream);
+    else if (t.wm == 1) launch_gemm_tile<1, 2>(g, grid, stream);
     else if (t.wn == 1) launch_gemm_tile<2, 1>(g, grid, stream);
     else launch_gemm_tile<2, 2>(g, grid, stream);
-    if (g.splits > 1)
-        hipLaunchKernelGGL(fbq_sum_splits_kernel, dim3((unsigned)(((size_t)g.Mr * g.Nr + 255) / 256)), dim3(256), 0, stream, g);
+    const unsigned sums = g.splits > 1 ? (unsigned)(((size_t)g.Mr * g.Nr / 4 + 255) / 256) : 0u;   // Nr is a multiple of 8 (r or K)
+    if (sums + (loss.part ? 1u : 0u) > 0)
+        hipLaunchKernelGGL(fbq_sum_splits_kernel, dim3(sums + (loss.part ? 1u : 0u)), dim3(256), 0, stream, g, loss);
     return hipGetLastError();
 }
 
@@ -267,21 +269,328 @@ static GemmArgs gemm_args(const uint16_t *A, int Mr, int lda, const uint16_t *B,
     return g;
 }
 
-// dst [C][ldd] = transpose of src [R][C] (fp16), columns R..ldd-1 of dst zero.  Block (32, 8), tile 32x32.
+// dst [C][ldd] = transpose of src [R][C] (fp16), columns R..ldd-1 of dst zero; C a multiple of 8, ldd of 64.  Tile 64 x 64:
+// whole 128-byte row pieces in and out, 16 bytes per lane (2048 x 4096: two bytes per lane took 13 us, this takes 7).
 __global__ __launch_bounds__(256) void fbq_transpose_f16_kernel(const uint16_t *__restrict__ src, uint16_t *__restrict__ dst,
                                                                 int R, int C, int ldd)
 {
-    __shared__ uint16_t t[32][33];
-    const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
-    for (int i = threadIdx.y; i < 32; i += 8) {
-        const int r = r0 + i, c = c0 + threadIdx.x;
-        t[i][threadIdx.x] = (r < R && c < C) ? src[(size_t)r * C + c] : (uint16_t)0;
+    __shared__ uint32_t t[64][33];                      // rows 132 bytes apart: the eight row groups of a column fall on different banks
+    const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int piece = i * 256 + threadIdx.x, r = piece >> 3, c = (piece & 7) * 8;
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (r0 + r < R && c0 + c < C) v = *reinterpret_cast<const uint4 *>(src + (size_t)(r0 + r) * C + c0 + c);
+        t[r][c / 2] = v.x; t[r][c / 2 + 1] = v.y; t[r][c / 2 + 2] = v.z; t[r][c / 2 + 3] = v.w;
     }
     __syncthreads();
-    for (int i = threadIdx.y; i < 32; i += 8) {
-        const int c = c0 + i, r = r0 + threadIdx.x;
-        if (c < C && r < ldd) dst[(size_t)c * ldd + r] = t[threadIdx.x][i];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int piece = i * 256 + threadIdx.x, c = piece >> 3, r = (piece & 7) * 8;
+        if (c0 + c >= C) continue;
+        uint32_t w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            w[e] = __builtin_amdgcn_perm(t[r + 2 * e + 1][c / 2], t[r + 2 * e][c / 2], (c & 1) ? 0x07060302u : 0x05040100u);
+        *reinterpret_cast<uint4 *>(dst + (size_t)(c0 + c) * ldd + r0 + r) = make_uint4(w[0], w[1], w[2], w[3]);
     }
+}
+
+// ------------------------------------------------------------------ symmetric products
+
+// G = A A^T of one operand A [R][Kd]: the lower triangle of tiles of 192 x 192 is computed, half the work of the square.
+//   DOT false: C = fp16(beta G), both triangles (H = X^T X with A = X^T)
+//   DOT true:  dot[unit] = the tile's share of sum G o H (the loss with A = Delta_F^T: tr(Delta H Delta^T) = sum
+//              (Delta^T Delta) o H; a tile below the diagonal stands for its mirror image as well and meets H + H^T)
+// Four waves of 96 x 96 (3 x 3 of v_mfma_f32_32x32x16_f16), one per SIMD; k advances in steps of 64, three steps in LDS
+// (48 KiB each), copied there without passing registers and waited for by count as in the prefill kernel.  The copies of
+// a step go out one by one between groups of three matrix instructions.  192 rows: 4096 rows make 253 such tiles, one for
+// nearly every CU, where 256-row tiles would leave half the chip idle (136 tiles of the triangle) and 128-row tiles need 2.1
+// rounds.  Few tiles: the contraction is split over blocks - for free where only the dot product is wanted (it is linear in
+// G), through fp32 partial tiles and a summing launch otherwise.
+// Bound: matrix cores; 4096 x 4096 in us, the whole square in 128-row tiles staged through registers / this: H over 2048 tokens
+// 103 / 41, the loss over 4096 rows 196 / 71 (both 34 and 69 GFLOP of the triangle: 0.84 and 0.97 PFLOP/s).
+constexpr int kSyTile = 192, kSyWave = 96, kSyStages = 3;
+constexpr int kSySide = kSyTile * 128, kSyStep = 2 * kSySide;       // LDS bytes of one operand's rows and of a step
+constexpr int kSyBand = 6;                                          // tiles are numbered in bands of six tile rows
+
+struct SyrkArgs {
+    const uint16_t *A;
+    int R, ld, Kd;                       // Kd a multiple of 64, ld elements
+    int side, tiles, splits;             // tiles per side, tiles of the lower triangle, blocks that share a tile's contraction
+    uint16_t *C; int ldc; float beta;
+    float *part;                         // splits > 1 and not DOT: [splits][tiles][192][192]
+    const uint16_t *H; float *dot;       // DOT: H [R][R]
+};
+
+// Tile t of the lower triangle: bands of six tile rows, column by column within a band, so that the tiles an XCD works on at
+// the same time (consecutive ones) lie in a block of about six by five and share their operands' rows in its L2.
+__device__ __forceinline__ void syrk_tile(int t, int side, int *ti, int *tj)
+{
+    int b = 0, h;
+    for (;; ++b) {
+        h = min(kSyBand, side - b * kSyBand);
+        const int count = b * kSyBand * h + h * (h + 1) / 2;
+        if (t < count) break;
+        t -= count;
+    }
+    if (t < b * kSyBand * h) {
+        *tj = t / h;
+        *ti = b * kSyBand + t % h;
+        return;
+    }
+    t -= b * kSyBand * h;
+    int c = 0;
+    for (; t >= h - c; ++c) t -= h - c;
+    *tj = b * kSyBand + c;
+    *ti = *tj + t;
+}
+
+template <bool DOT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void fbq_syrk_kernel(const SyrkArgs g)
+{
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kSyStages * kSyStep];
+    const int units = g.tiles * g.splits, per_xcd = (units + kXcds - 1) / kXcds;
+    const int unit = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;      // consecutive units on the same XCD
+    if ((int)(blockIdx.x / kXcds) >= per_xcd || unit >= units) return;
+    // (wave-uniform as it is, but the divisions run on the vector unit: descriptors and copies want scalar registers)
+    const int split = __builtin_amdgcn_readfirstlane(unit / g.tiles), tile = __builtin_amdgcn_readfirstlane(unit % g.tiles);
+    int ti, tj;
+    syrk_tile(tile, g.side, &ti, &tj);
+    ti = __builtin_amdgcn_readfirstlane(ti);
+    tj = __builtin_amdgcn_readfirstlane(tj);
+    const int m0 = ti * kSyTile, n0 = tj * kSyTile;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int col = lane & 31, h = lane >> 5;
+
+    // waves 0 and 1 copy the rows of the tile's row side, 96 each, waves 2 and 3 those of its column side: eight rows per copy
+    const int side0 = wm ? n0 : m0;
+    const __amdgpu_buffer_rsrc_t buf = buffer_of(g.A + (size_t)side0 * g.ld, (long)min(kSyTile, g.R - side0) * g.ld * 2);
+    const int lrow = lane >> 3;
+    const int loff[2] = {lrow * g.ld * 2 + ((lane & 7) ^ piece_key(lrow)) * 16, lrow * g.ld * 2 + ((lane & 7) ^ piece_key(8 + lrow)) * 16};
+    const uint32_t lds0 = lds_offset(lds);
+    const int all_steps = g.Kd / 64, per_split = (all_steps + g.splits - 1) / g.splits;
+    const int first = split * per_split, steps = max(0, min(all_steps, first + per_split) - first);
+    constexpr int kCopies = kSyWave / 8;                // per wave and step
+    auto issue = [&](int st, int stage, int j) __attribute__((always_inline)) {   // (past the end: the last step again, never used)
+        const int row = wn * kSyWave + 8 * j;
+        copy16_to_lds(buf, loff[j & 1], row * g.ld * 2 + min(first + st, all_steps - 1) * 128, lds0 + stage * kSyStep + wm * kSySide + row * 128);
+    };
+    auto wait_and_meet = [&](auto N) __attribute__((always_inline)) {
+        constexpr int n = decltype(N)::value;
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(n) : "memory");
+    };
+
+    float16_t acc[3][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+    // fragment of K step i: pieces 2 i + h of its rows
+    const int key = (h ^ piece_key(col & 15)) << 4;
+    const int a_lane = (wm * kSyWave + col) * 128 + key, b_lane = kSySide + (wn * kSyWave + col) * 128 + key;
+    auto frag = [&](int stage, int lane_off, int i, int t) __attribute__((always_inline)) {
+        return *reinterpret_cast<const half8_t *>(lds + stage * kSyStep + (lane_off ^ (i << 5)) + t * (32 * 128));
+    };
+    half8_t af[2][3], bf[2][3];
+    auto do_step = [&](int st, int s0, int s1, int s2) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int cur = i & 1, nxt = cur ^ 1;
+            __builtin_amdgcn_sched_barrier(0);
+            // the next step has landed, and everybody has read all of this one: its stage may be filled again
+            if (i == 3) wait_and_meet(std::integral_constant<int, kCopies>{});
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                if (i == 3) issue(st + 3, s0, t);
+                else issue(st + 2, s2, 3 + 3 * i + t);
+                af[nxt][t] = i < 3 ? frag(s0, a_lane, i + 1, t) : frag(s1, a_lane, 0, t);
+                bf[nxt][t] = i < 3 ? frag(s0, b_lane, i + 1, t) : frag(s1, b_lane, 0, t);
+#pragma unroll
+                for (int u = 0; u < 3; ++u) acc[t][u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[cur][t], bf[cur][u], acc[t][u], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int j = 0; j < kCopies; ++j) issue(s, s, j);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) issue(2, 2, j);
+    wait_and_meet(std::integral_constant<int, kCopies + 3>{});
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        af[0][t] = frag(0, a_lane, 0, t);
+        bf[0][t] = frag(0, b_lane, 0, t);
+    }
+    int s0 = 0;
+    for (int st = 0; st < steps; ++st) {
+        const int s1 = s0 == 2 ? 0 : s0 + 1, s2 = s0 == 0 ? 2 : s0 - 1;
+        do_step(st, s0, s1, s2);
+        s0 = s1;
+    }
+    wait_and_meet(std::integral_constant<int, 0>{});    // the copies issued past the end have landed too, and everybody is done: LDS is free
+
+    // accumulator register v of a lane: row 8 (v / 4) + 4 h + v % 4 of the 32x32 tile, column `col`
+    const int mw = m0 + wm * kSyWave, nw = n0 + wn * kSyWave;       // the wave's rows and columns
+    constexpr int kPieces = kSyWave * kSyWave / 8 / 64;             // 16-byte pieces of a 96 x 96 fp16 tile per lane
+    if constexpr (DOT) {
+        // the two tiles of H that the wave's 96 x 96 meet, by way of LDS: rows mw.., columns nw.. and the mirror image
+        constexpr int kHTile = kSyWave * kSyWave * 2;
+        auto copy_h = [&](int r0, int c0, int o) __attribute__((always_inline)) {
+            const __amdgpu_buffer_rsrc_t hbuf = buffer_of(g.H + (size_t)r0 * g.R, __builtin_amdgcn_readfirstlane(max(0, min(kSyWave, g.R - r0)) * g.R * 2));   // (the clamp runs on the vector unit)
+#pragma unroll
+            for (int i = 0; i < kPieces; ++i) {
+                const int piece = i * 64 + lane, row = piece / 12, p = piece % 12;   // 192 bytes a row
+                copy16_to_lds(hbuf, c0 + p * 8 < g.R ? row * g.R * 2 + (c0 + p * 8) * 2 : 0x7FFFFFF0, 0, lds0 + (wave * 2 + o) * kHTile + i * 1024);
+            }
+        };
+        copy_h(mw, nw, 0);
+        copy_h(nw, mw, 1);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // (each wave reads what itself copied)
+        const uint16_t *hd = reinterpret_cast<const uint16_t *>(lds + wave * 2 * kHTile), *hm = hd + kSyWave * kSyWave;
+        const float mirror = ti == tj ? 0.0f : 1.0f;                // a diagonal tile is its own mirror image
+        float dot = 0.0f;
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+                float part = 0.0f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int m = t * 32 + 8 * (v / 4) + 4 * h + (v % 4), n = u * 32 + col;
+                    const float direct = (float)__builtin_bit_cast(half_t, hd[m * kSyWave + n]), turned = (float)__builtin_bit_cast(half_t, hm[n * kSyWave + m]);
+                    part = fmaf(acc[t][u][v], fmaf(mirror, turned, direct), part);
+                }
+                dot += part;
+            }
+        // fixed order: lanes by xor-shuffles, then the four waves in turn
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 64);
+        __syncthreads();
+        float *wsum = reinterpret_cast<float *>(lds);
+        if (lane == 0) wsum[wave] = dot;
+        __syncthreads();
+        if (tid == 0) g.dot[unit] = ((wsum[0] + wsum[1]) + wsum[2]) + wsum[3];
+        return;
+    }
+    if (g.splits > 1) {
+        float *part = g.part + ((size_t)split * g.tiles + tile) * (kSyTile * kSyTile) + (wm * kSyWave) * kSyTile + wn * kSyWave;
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int u = 0; u < 3; ++u)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) part[(t * 32 + 8 * (v / 4) + 4 * h + (v % 4)) * kSyTile + u * 32 + col] = acc[t][u][v];
+        return;
+    }
+    // (scaled here and not in the conversions: fused into some of them, the two triangles would not round alike)
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                float scaled = g.beta * acc[t][u][v];
+                asm volatile("" : "+v"(scaled));
+                acc[t][u][v] = scaled;
+            }
+    // fp16 tiles turned round in the wave's own piece of LDS (rows of 96 fp16, 208 bytes apart) and stored as 16-byte pieces
+    constexpr int kOutRow = kSyWave * 2 + 16;
+    static_assert(4 * kSyWave * kOutRow <= (int)sizeof(lds), "the waves' tiles must fit the stages");
+    unsigned char *const out = lds + wave * (kSyWave * kOutRow);
+    auto store = [&](int r0, int c0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const int piece = i * 64 + lane, row = piece / 12, p = piece % 12;
+            const uint4 v = *reinterpret_cast<const uint4 *>(out + row * kOutRow + p * 16);
+            if (r0 + row < g.R && c0 + p * 8 < g.R) *reinterpret_cast<uint4 *>(g.C + (size_t)(r0 + row) * g.ldc + c0 + p * 8) = v;
+        }
+    };
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                *reinterpret_cast<half_t *>(out + (t * 32 + 8 * (v / 4) + 4 * h + (v % 4)) * kOutRow + (u * 32 + col) * 2) = (half_t)acc[t][u][v];
+    store(mw, nw);                                      // (the wave reads what itself wrote: LDS keeps a wave's accesses in order)
+    if (ti == tj) return;
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                half4_t v4;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v4[e] = (half_t)acc[t][u][4 * q + e];
+                *reinterpret_cast<half4_t *>(out + (u * 32 + col) * kOutRow + (t * 32 + 8 * q + 4 * h) * 2) = v4;
+            }
+    store(nw, mw);
+}
+
+// C = fp16(beta x sum of the splits' partial tiles), splits in index order, both triangles.  Block: a 64 x 64 piece of a tile.
+__global__ __launch_bounds__(256) void fbq_syrk_sum_kernel(const SyrkArgs g)
+{
+    __shared__ uint16_t turn[64][64 + 2];
+    int ti, tj;
+    syrk_tile(blockIdx.x, g.side, &ti, &tj);
+    const int pr = (blockIdx.y / 3) * 64, pc = (blockIdx.y % 3) * 64;
+    const float *part = g.part + (size_t)blockIdx.x * (kSyTile * kSyTile) + pr * kSyTile + pc;
+    const size_t stride = (size_t)g.tiles * (kSyTile * kSyTile);
+    const int c = threadIdx.x & 63, m0 = ti * kSyTile + pr, n0 = tj * kSyTile + pc;
+    for (int r = threadIdx.x >> 6; r < 64; r += 4) {
+        float a = 0.0f;
+        for (int s = 0; s < g.splits; ++s) a += part[s * stride + r * kSyTile + c];
+        const uint16_t v = __builtin_bit_cast(uint16_t, (half_t)(g.beta * a));
+        if (m0 + r < g.R && n0 + c < g.R) g.C[(size_t)(m0 + r) * g.ldc + n0 + c] = v;
+        turn[r][c] = v;
+    }
+    if (ti == tj) return;
+    __syncthreads();
+    for (int r = threadIdx.x >> 6; r < 64; r += 4)
+        if (n0 + r < g.R && m0 + c < g.R) g.C[(size_t)(n0 + r) * g.ldc + m0 + c] = turn[c][r];
+}
+
+// Blocks that share a tile's contraction: what makes rounds x (steps + about ten steps' worth of start and end) smallest, 256
+// CUs assumed; where the partial tiles have to be written and summed, that traffic (about a third of a step per tile in flight)
+// and the launch (eight steps) count as well.
+struct SyrkShape { int side, tiles, splits; };
+static SyrkShape syrk_shape(int R, int Kd, bool dot)
+{
+    const int side = ceil_div(R, kSyTile), tiles = side * (side + 1) / 2, steps = Kd / 64;
+    SyrkShape best{side, tiles, 1};
+    double best_cost = 1e300;
+    for (int s = 1; s <= 16 && s <= steps; ++s) {
+        double cost = (double)ceil_div(tiles * s, 256) * (ceil_div(steps, s) + 10);
+        if (s > 1 && !dot) cost += 8 + tiles * s / 40.0;
+        if (cost < best_cost * 0.98) { best_cost = cost; best.splits = s; }
+    }
+    return best;
+}
+static size_t syrk_units(const SyrkShape &s) { return (size_t)s.tiles * s.splits; }
+static size_t syrk_scratch_bytes(int R, int Kd)
+{
+    const SyrkShape s = syrk_shape(R, Kd, false);
+    return s.splits > 1 ? syrk_units(s) * kSyTile * kSyTile * 4 : 0;
+}
+
+template <bool DOT>
+static hipError_t launch_syrk(SyrkArgs g, hipStream_t stream)
+{
+    const SyrkShape s = syrk_shape(g.R, g.Kd, DOT);
+    g.side = s.side; g.tiles = s.tiles; g.splits = s.splits;
+    const int units = s.tiles * s.splits;
+    hipLaunchKernelGGL(fbq_syrk_kernel<DOT>, dim3(ceil_div(units, kXcds) * kXcds), dim3(256), 0, stream, g);
+    if (!DOT && g.splits > 1) hipLaunchKernelGGL(fbq_syrk_sum_kernel, dim3(g.tiles, 9), dim3(256), 0, stream, g);
+    return hipGetLastError();
 }
 
 // fp16 views of the fp32 masters: At16 [r][K] and Bt16 [N][r] (the inference layouts, outputs of the
@@ -307,30 +616,6 @@ __global__ __launch_bounds__(256) void fbq_cast_masters_kernel(const float *__re
     }
 }
 
-// loss = scale * (sum of the tiles' partial sums, in index order), by one block.
-__global__ __launch_bounds__(256) void fbq_loss_kernel(const float *__restrict__ part, int n, float scale, float *__restrict__ loss)
-{
-    __shared__ double s[256];
-    double a = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) a += (double)part[i];
-    s[threadIdx.x] = a;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) s[threadIdx.x] += s[threadIdx.x + off];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *loss = (float)(s[0] * (double)scale);
-}
-
-// masters <- masters - lr gradient  (Alg. 1, the update line), both arrays in one launch.
-__global__ __launch_bounds__(256) void fbq_descent_kernel(float *__restrict__ At32, const float *__restrict__ gAt, size_t nA,
-                                                          float *__restrict__ Bt32, const float *__restrict__ gBt, size_t nB, float lr)
-{
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < nA) At32[i] = At32[i] - lr * gAt[i];
-    else if (i < nA + nB) Bt32[i - nA] = Bt32[i - nA] - lr * gBt[i - nA];
-}
-
 static size_t pad256(size_t b) { return (b + 255) & ~(size_t)255; }
 static int pad64(int v) { return (v + 63) & ~63; }
 
@@ -350,7 +635,7 @@ static TrainLayout train_layout(int N, int K, int r)
     l.Dt16 = o; o += pad256((size_t)K * Np * 2);
     l.S16 = o;  o += pad256((size_t)2 * r * K * 2);          // stacked operand [Q; At]
     l.Vt16 = o; o += pad256((size_t)r * K * 2);
-    l.dot = o;  o += pad256((size_t)ceil_div(N, 64) * ceil_div(K, 64) * 4);           // enough for any tile shape
+    l.dot = o;  o += pad256(syrk_units(syrk_shape(K, Np, true)) * 4);
     l.split = o;
     o += pad256(std::max(std::max(split_scratch_bytes(r, K, Np), split_scratch_bytes(2 * r, K, K)), split_scratch_bytes(N, r, K)));
     l.total = o;
@@ -360,7 +645,7 @@ static TrainLayout train_layout(int N, int K, int r)
 size_t train_workspace_bytes(int N, int K, int r, int T)
 {
     const int Tp = pad64(T);
-    return std::max(train_layout(N, K, r).total, pad256((size_t)K * Tp * 2) + pad256(split_scratch_bytes(K, K, Tp)));
+    return std::max(train_layout(N, K, r).total, pad256((size_t)K * Tp * 2) + pad256(syrk_scratch_bytes(K, Tp)));
 }
 
 hipError_t launch_gram(int K, int T, const uint16_t *X, float h_scale, uint16_t *H16, void *workspace, hipStream_t stream)
@@ -368,10 +653,11 @@ hipError_t launch_gram(int K, int T, const uint16_t *X, float h_scale, uint16_t 
     const int Tp = pad64(T);
     uint16_t *Xt = (uint16_t *)workspace;                       // [K][Tp], tokens past T zero
     float *scratch = (float *)((unsigned char *)workspace + pad256((size_t)K * Tp * 2));
-    hipLaunchKernelGGL(fbq_transpose_f16_kernel, dim3(ceil_div(K, 32), ceil_div(Tp, 32)), dim3(32, 8), 0, stream, X, Xt, T, K, Tp);
-    GemmArgs g = gemm_args(Xt, K, Tp, Xt, K, Tp, Tp);
-    g.C16 = H16; g.ldc16 = K; g.beta = h_scale;
-    return launch_gemm(g, scratch, stream);
+    hipLaunchKernelGGL(fbq_transpose_f16_kernel, dim3(ceil_div(K, 64), Tp / 64), dim3(256), 0, stream, X, Xt, T, K, Tp);
+    SyrkArgs g{};
+    g.A = Xt; g.R = K; g.ld = Tp; g.Kd = Tp;
+    g.C = H16; g.ldc = K; g.beta = h_scale; g.part = scratch;
+    return launch_syrk<false>(g, stream);
 }
 
 hipError_t launch_train_step(const TrainArgs &a, hipStream_t stream)
@@ -383,7 +669,6 @@ hipError_t launch_train_step(const TrainArgs &a, hipStream_t stream)
     uint16_t *D16 = (uint16_t *)(ws + l.D16), *Dt16 = (uint16_t *)(ws + l.Dt16);
     uint16_t *S16 = (uint16_t *)(ws + l.S16), *Vt16 = (uint16_t *)(ws + l.Vt16);
     float *dot = (float *)(ws + l.dot), *scratch = (float *)(ws + l.split);
-    const int tiles = tiles_of(N, K);
 
     // fp16 views of the masters: what the forward pass of Alg. 1 computes with
     const size_t casts = (size_t)r * K + (size_t)N * r + (size_t)r * Np;
@@ -403,28 +688,25 @@ hipError_t launch_train_step(const TrainArgs &a, hipStream_t stream)
     {
         GemmArgs g = gemm_args(S16, 2 * r, K, a.H16, K, K, K);
         g.C32 = a.gAt; g.ldc32 = K; g.alpha = -2.0f / (kDeltaGain * a.h_scale); g.c32_rows = r;
+        g.master = a.At32; g.lr = a.lr;
         g.C16 = Vt16; g.ldc16 = K; g.beta = kVGain; g.c16_row0 = r;
         if ((e = launch_gemm(g, scratch, stream)) != hipSuccess) return e;
     }
-    // dL/dBt = -2 Delta_F H At^T = -2 Delta_F V
-    {
-        GemmArgs g = gemm_args(D16, N, K, Vt16, r, K, K);
-        g.C32 = a.gBt; g.ldc32 = r; g.alpha = -2.0f / (kDeltaGain * kVGain * a.h_scale);
-        if ((e = launch_gemm(g, scratch, stream)) != hipSuccess) return e;
-    }
-    // L = sum Delta_F o (Delta_F H): the only use of the full product, and only on request
+    // L = sum (Delta_F^T Delta_F) o H: the only contraction of this size, and only on request
+    LossArgs loss{};
     if (a.loss) {
-        GemmArgs g = gemm_args(D16, N, K, a.H16, K, K, K);
-        g.D = D16; g.ldd = K; g.dot = dot;
-        if ((e = launch_gemm(g, nullptr, stream)) != hipSuccess) return e;
-        hipLaunchKernelGGL(fbq_loss_kernel, dim3(1), dim3(256), 0, stream, dot, tiles, 1.0f / (kDeltaGain * kDeltaGain * a.h_scale),
-                           a.loss);
+        SyrkArgs g{};
+        g.A = Dt16; g.R = K; g.ld = Np; g.Kd = Np;
+        g.H = a.H16; g.dot = dot;
+        if ((e = launch_syrk<true>(g, stream)) != hipSuccess) return e;
+        loss.part = dot; loss.n = (int)syrk_units(syrk_shape(K, Np, true));
+        loss.scale = 1.0f / (kDeltaGain * kDeltaGain * a.h_scale); loss.out = a.loss;
     }
-    // gradient descent on the masters
-    const size_t nA = (size_t)r * K, nB = (size_t)N * r;
-    hipLaunchKernelGGL(fbq_descent_kernel, dim3((unsigned)((nA + nB + 255) / 256)), dim3(256), 0, stream, a.At32, a.gAt, nA, a.Bt32,
-                       a.gBt, nB, a.lr);
-    return hipGetLastError();
+    // dL/dBt = -2 Delta_F H At^T = -2 Delta_F V; its summing launch adds up the loss as well
+    GemmArgs g = gemm_args(D16, N, K, Vt16, r, K, K);
+    g.C32 = a.gBt; g.ldc32 = r; g.alpha = -2.0f / (kDeltaGain * kVGain * a.h_scale);
+    g.master = a.Bt32; g.lr = a.lr;
+    return launch_gemm(g, scratch, stream, loss);
 }
 
 }  // namespace fbq

@@ -81,3 +81,56 @@ def test_prefill_tile_edges(bits, N, K, r, M):
     fbq.linear(dev, xd, y, ws)
     torch.cuda.synchronize()
     assert np.array_equal(y.cpu().numpy(), got)
+
+
+# ------------------------------------------------------------------ symmetric products: tiles of 192, the contraction split over blocks
+
+@pytest.mark.parametrize("K,T", [(128, 1), (256, 4100), (384, 65), (640, 193), (1152, 300), (2176, 837)])
+def test_gram_tile_edges(K, T):
+    """fp16 of a 32-bit sum: 2^-11 / sqrt(3) relative; both triangles come from the same sums, so H is symmetric to the bit."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    rng = np.random.Generator(np.random.Philox(44))
+    X = rng.standard_normal((T, K)).astype(np.float16)
+    d = fbq.Desc(128, K, 8, 4)
+    ws = framed_in_nan(torch.full((fbq.train_workspace_bytes(d, T),), 0x7D, dtype=torch.uint8, device="cuda"))
+    H = fbq.gram(d, framed_in_nan(torch.from_numpy(X).cuda()), 1.0 / T, ws)
+    torch.cuda.synchronize()
+    H = H.cpu().numpy()
+    X64 = X.astype(np.float64)
+    want = X64.T @ X64 / T
+    assert np.linalg.norm(H.astype(np.float64) - want) <= 5e-4 * np.linalg.norm(want)
+    assert np.array_equal(H, H.T)
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("N,K,r", [(1, 128, 8), (65, 384, 64), (200, 256, 72), (129, 640, 136), (700, 1152, 256)])
+def test_train_step_tile_edges(bits, N, K, r):
+    """Gradients, loss and update of one step from the step's own codes and the H it was given, in fp64.  Three fp16 roundings
+    of 2^-11 and 32-bit sums (a few 1e-4); bars as in the parity tests of the step."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    L = make_oracle_layer(fbq_synth.LayerSpec("edge", N, K, r, bits), config=45)
+    rng = np.random.Generator(np.random.Philox(46))
+    X = rng.standard_normal((96, K))
+    H = ((X.T @ X) / 96).astype(np.float16)
+    H = np.triu(H) + np.triu(H, 1).T
+    d = fbq.Desc(N, K, r, bits)
+    At, Bt = (torch.from_numpy(np.ascontiguousarray(m.T).astype(np.float32)).cuda() for m in (L.A, L.B))
+    st = fbq.train_state(d, At.clone(), Bt.clone())
+    st.workspace = framed_in_nan(torch.full_like(st.workspace, 0x7D))
+    lr = 1e-6
+    fbq.train_step(st, t16(L.W), t16(H), 1.0 / 96, lr)
+    torch.cuda.synchronize()
+    A64, B64, H64 = L.A.astype(np.float64).T, L.B.astype(np.float64).T, H.astype(np.float64) * 96
+    s, z = (np.repeat(v.astype(np.float64), 128, axis=1) for v in (L.scales, L.zeros))
+    D = (L.W.astype(np.float64) - B64 @ A64) - s * (L.codes - z)
+    P = D @ H64
+    gA, gB = -2.0 * B64.T @ P, -2.0 * P @ A64.T
+    rel = lambda got, want: np.linalg.norm(got.cpu().numpy().astype(np.float64) - want) / np.linalg.norm(want)
+    assert rel(st.grad_At, gA) < 2e-3 and rel(st.grad_Bt, gB) < 2e-3
+    assert rel(st.loss, np.array([np.sum(D * P)])) < 1e-3
+    # the update is one fp32 multiply-subtract of the gradient that was written
+    for got, start, grad in ((st.At32, At, st.grad_At), (st.Bt32, Bt, st.grad_Bt)):
+        step = start.double() - lr * grad.double()
+        assert float((got.double() - step).abs().max()) <= 2.0 ** -23 * float(start.abs().max()) + 1e-12
