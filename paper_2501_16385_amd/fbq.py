@@ -130,20 +130,34 @@ def _np_ptr(a: Optional[np.ndarray]):
     return None if a is None else ctypes.c_void_p(a.ctypes.data)
 
 
-def _dev_ptr(t) -> Optional[ctypes.c_void_p]:
+def _dev_ptr(t) -> Optional[int]:
     if t is None:
         return None
     if not t.is_cuda:
         raise ValueError("expected a device tensor")
     if not t.is_contiguous():
         raise ValueError("expected a contiguous tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream=None) -> ctypes.c_void_p:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+_current_raw_stream = None      # () -> hipStream_t of the current stream of the current device
+
+
+def _stream(stream=None) -> int:
+    """The stream as the number the library takes.  torch.cuda.current_stream() builds a Stream object (3 us, more than a
+    quarter of a one-token call); torch hands the number out directly."""
+    global _current_raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is None:
+        import torch
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is None or device is None:
+            _current_raw_stream = lambda: torch.cuda.current_stream().cuda_stream
+        else:
+            torch.cuda.init()
+            _current_raw_stream = lambda: raw(device())
+    return _current_raw_stream()
 
 
 @dataclass
@@ -204,14 +218,15 @@ def upload_layer(p: PackedLayer, device="cuda") -> DeviceLayer:
 
 def linear(layer: DeviceLayer, x, y=None, workspace=None, stream=None):
     """fbq_linear: x [M, K] fp16 device tensor -> y [M, N] fp16 device tensor."""
-    import torch
     d = layer.desc
     M = int(x.shape[0])
-    if y is None:
-        y = torch.empty((M, d.N), dtype=torch.float16, device=x.device)
-    need = workspace_bytes(d, M)
-    if workspace is None and need:
-        workspace = torch.zeros(need, dtype=torch.uint8, device=x.device)
+    if y is None or workspace is None:
+        import torch
+        if y is None:
+            y = torch.empty((M, d.N), dtype=torch.float16, device=x.device)
+        need = 0 if workspace is not None else workspace_bytes(d, M)   # (a workspace that is given is checked by the library)
+        if need:
+            workspace = torch.zeros(need, dtype=torch.uint8, device=x.device)
     wbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     rc = load().fbq_linear(ctypes.byref(d.c()), M, _dev_ptr(x), _dev_ptr(layer.qweight), _dev_ptr(layer.scales),
                            _dev_ptr(layer.zeros), _dev_ptr(layer.At), _dev_ptr(layer.Bt), _dev_ptr(y), _dev_ptr(workspace),
