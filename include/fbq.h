@@ -190,6 +190,26 @@ typedef struct {
  */
 fbq_status fbq_linear_group(const fbq_layer_call *calls, int n, int M, fbq_stream stream);
 
+/* A second tensor to average a layer's result with: out[m,n] = (with[m,n] + y[m,n]) / 2, fp16, rounded once from the
+ * rounded y.  with, out device [M, N] fp16; out NULL: none. */
+typedef struct {
+    const void *with;
+    void *out;
+} fbq_mix;
+
+/*
+ * fbq_linear_group_mix - fbq_linear_group for layers whose result is averaged with another tensor (the residual of
+ * the decoder loop): y is written as fbq_linear_group writes it, and mix[i].out with it, by the same launch up to 16
+ * tokens (and, at one or two tokens, an even N), by a launch of its own otherwise.
+ *   mix host array of n entries (read during the call only); an out may be no layer's x, y or `with`.
+ * Errors: those of fbq_linear_group; FBQ_ERR_NULL (out without with), FBQ_ERR_ALIGN, before ANY launch.
+ */
+fbq_status fbq_linear_group_mix(const fbq_layer_call *calls, const fbq_mix *mix, int n, int M, fbq_stream stream);
+
+/* fbq_silu_mul - out = silu(gate) * up over count fp16 values, silu rounded to fp16 in between (the gate of a decoder
+ * MLP, as two element-wise kernels would compute it).  Errors: FBQ_ERR_NULL, _SHAPE (count 0), _ALIGN before the launch; FBQ_ERR_HIP. */
+fbq_status fbq_silu_mul(const void *gate, const void *up, void *out, size_t count, fbq_stream stream);
+
 /*
  * fbq_reconstruct - validation.  W_hat[n,k] = s*(q - z) + sum_j At[j,k]*Bt[n,j], the paper's
  * W_F = Q(W - Sigma) + Sigma (Sec. 4.1), as fp32.   W_hat device [N, K] fp32, overwritten.

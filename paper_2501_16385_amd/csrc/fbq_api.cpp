@@ -183,6 +183,7 @@ fbq_status check_layer(const fbq_desc *d, int M, const void *x, const void *qwei
     a->y = (uint16_t *)y;
     a->workspace = workspace;
     a->M = M; a->N = d->N; a->K = d->K; a->r = d->r; a->bits = d->bits;
+    a->mix_with = nullptr; a->mix_out = nullptr;
     return FBQ_OK;
 }
 
@@ -257,7 +258,7 @@ extern "C" fbq_status fbq_linear(const fbq_desc *d, int M, const void *x, const 
     return hip_status(launch_one(a, s));
 }
 
-extern "C" fbq_status fbq_linear_group(const fbq_layer_call *calls, int n, int M, fbq_stream stream)
+fbq_status fbq::linear_group(const fbq_layer_call *calls, const fbq_mix *mix, int n, int M, hipStream_t s)
 {
     constexpr int kMaxCalls = 64;
     if (!calls) return FBQ_ERR_NULL;
@@ -268,6 +269,13 @@ extern "C" fbq_status fbq_linear_group(const fbq_layer_call *calls, int n, int M
         const fbq_status st = check_layer(&c.desc, M, c.x, c.qweight, c.scales, c.zeros, c.At, c.Bt, c.y, c.workspace,
                                           c.workspace_bytes, &args[i]);
         if (st != FBQ_OK) return st;
+        if (!mix || !mix[i].out) continue;
+        if (!mix[i].with) return FBQ_ERR_NULL;
+        if (misaligned(mix[i].with) || misaligned(mix[i].out)) return FBQ_ERR_ALIGN;
+        if (mix_in_kernel(M, c.desc.N)) {
+            args[i].mix_with = (const uint16_t *)mix[i].with;
+            args[i].mix_out = (uint16_t *)mix[i].out;
+        }
     }
     // Layers that share a launch carry the same launch tag: two of them writing their hand-over words into the same
     // memory would accept each other's t.  Workspaces must not overlap.
@@ -281,7 +289,6 @@ extern "C" fbq_status fbq_linear_group(const fbq_layer_call *calls, int n, int M
             if (nj && ai < aj + nj && aj < ai + ni) return FBQ_ERR_WORKSPACE;
         }
     }
-    hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipSuccess;
     if (M > kDecodeMaxM) {
         for (int i = 0; i < n && e == hipSuccess; ++i) e = launch_one(args[i], s);
@@ -305,6 +312,11 @@ extern "C" fbq_status fbq_linear_group(const fbq_layer_call *calls, int n, int M
         e = few ? launch_gemv_small_m(batch, nb, s) : launch_gemv_decode(batch, nb, s);
     }
     return hip_status(e);
+}
+
+extern "C" fbq_status fbq_linear_group(const fbq_layer_call *calls, int n, int M, fbq_stream stream)
+{
+    return linear_group(calls, nullptr, n, M, (hipStream_t)stream);
 }
 
 extern "C" fbq_status fbq_reconstruct(const fbq_desc *d, const void *qweight, const void *scales, const void *zeros,

@@ -197,6 +197,8 @@ struct LayerParams {
     int tslices;          // K slices of the down-projection = waves of a block that split K (1, 2 or 4); consumers add the partial sums
     int blocks;           // blocks of this layer
     int spin_limit;       // polls for t before a wave computes it itself; negative: at once (test hook)
+    const uint16_t *mix_with;   // [M][N], N even, or null: see LinearArgs
+    uint16_t *mix_out;
 };
 
 struct GemvGroup {
@@ -546,6 +548,15 @@ __global__ __launch_bounds__(256) void fbq_gemv_kernel(const GemvGroup g)
 
     // Second half of a tile: up-projection into the same accumulators (the K-slice-0 wave of each row
     // set only), sum over the wave (and over the K slices), one store per row.
+    // The rows of the tensor to average with: wave-uniform, so they come by scalar loads, which the counted waits of the
+    // weight stream do not see; asked for when the trip that finishes their tile begins.
+    uint32_t mixw[ROWS / 2];
+    auto request_mix = [&](int tile) __attribute__((always_inline)) {
+        if (!p.mix_out) return;
+        const auto *w = reinterpret_cast<const __attribute__((address_space(4))) uint32_t *>((uintptr_t)p.mix_with);
+#pragma unroll
+        for (int i = 0; i < ROWS / 2; ++i) mixw[i] = w[((size_t)m * p.N + min(tile * ROWS + 2 * i, p.N - 2)) / 2];
+    };
     auto finish = [&](float (&acc)[ROWS], const uint32_t (&bt)[ROWS][kRI], int tile) __attribute__((always_inline)) {
         if (RI > 0 && ks == 0) {
 #pragma unroll
@@ -575,8 +586,17 @@ __global__ __launch_bounds__(256) void fbq_gemv_kernel(const GemvGroup g)
             }
         }
         const int n0 = tile * ROWS;
-        if (ks == 0 && lane < ROWS && tile < ntiles && n0 + lane < p.N)
-            p.y[(size_t)m * p.N + n0 + lane] = __builtin_bit_cast(uint16_t, (half_t)out);
+        if (ks == 0 && lane < ROWS && tile < ntiles && n0 + lane < p.N) {
+            const half_t y = (half_t)out;
+            p.y[(size_t)m * p.N + n0 + lane] = __builtin_bit_cast(uint16_t, y);
+            if (p.mix_out) {
+                uint32_t w = mixw[0];
+#pragma unroll
+                for (int i = 1; i < ROWS / 2; ++i) w = lane / 2 == i ? mixw[i] : w;
+                const float with = (float)__builtin_bit_cast(half_t, (uint16_t)((lane & 1) ? w >> 16 : w));
+                p.mix_out[(size_t)m * p.N + n0 + lane] = __builtin_bit_cast(uint16_t, (half_t)((float)y - ((float)y - with) * 0.5f));
+            }
+        }
     };
 
     // One trip.  The tile's registers are refilled (with the tile two trips ahead, or with nothing) as
@@ -590,6 +610,8 @@ __global__ __launch_bounds__(256) void fbq_gemv_kernel(const GemvGroup g)
     auto step = [&](RowTile<BITS, CPW, ROWS> &T, float (&acc)[ROWS], float (&acc_prev)[ROWS], uint32_t (&bt_mine)[ROWS][kRI],
                     uint32_t (&bt_prev)[ROWS][kRI], int j, int tile) __attribute__((always_inline)) {
         // main path: de-quantize and multiply; clamped lanes hold zero activations and add nothing
+        if (RI == 0) request_mix(tile);
+        else if (j > 0) request_mix(tile - tstride);
 #pragma unroll
         for (int i = 0; i < ROWS; ++i) {
             // t is asked for as late as possible - when the tile's first row has arrived and its arithmetic
@@ -641,6 +663,7 @@ __global__ __launch_bounds__(256) void fbq_gemv_kernel(const GemvGroup g)
         tile += tstride;
     }
     if (RI > 0) {                                       // the last trip's second half
+        request_mix(tile - tstride);
         if (!have_t) take_t();
         if (trips & 1) finish(acc0, bt0, tile - tstride);
         else finish(acc1, bt1, tile - tstride);
@@ -769,6 +792,7 @@ hipError_t launch_gemv_decode(const LinearArgs *layers, int n_layers, hipStream_
         p.G = a.K / kGroup;
         p.tslices = v.ks;
         p.spin_limit = spin_limit();
+        p.mix_with = a.mix_with; p.mix_out = a.mix_out;
         const int max_blocks = ceil_div(ceil_div(a.N, rows), row_sets);
         const int share = (int)(budget * ((double)a.N * a.K / total_work));
         if (inline_job) {

@@ -93,6 +93,8 @@ struct SmallParams {
     int sum_blocks;        // ... and the blocks after them that add the slices up (16 columns each)
     int tiles_per_block;   // 16-row tiles a consumer block owns
     int spin_limit;        // polls for t before a wave computes it itself; negative: at once (test hook)
+    const uint16_t *mix_with;   // [M][N] or null: see LinearArgs
+    uint16_t *mix_out;
 };
 
 // Layers that share their activations (q/k/v, gate/up) share the launch.  In the grid y is the layer
@@ -585,6 +587,16 @@ __global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const Smal
     // K split: every wave leaves its tiles in LDS; wave ti adds them up for tile ti and stores.
 #pragma unroll
     for (int ti = 0; ti < T; ++ti) red[wave][ti][lane] = acc[ti];
+    // the values to average with, on their way while the waves meet (wave ti stores tile ti)
+    static_assert(T <= kMainWaves, "a wave stores at most one tile");
+    uint16_t with[4] = {0, 0, 0, 0};
+    if (p.mix_out && wave < T) {                        // wave-uniform
+        const __amdgpu_buffer_rsrc_t mbuf = buffer_of(p.mix_with, (long)p.M * p.N * 2);
+        const int n = (tile0 + wave) * 16 + c;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            with[v] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(mbuf, n < p.N && 4 * q + v < p.M ? ((4 * q + v) * p.N + n) * 2 : kNowhere, 0, 0);
+    }
     __syncthreads();
     for (int ti = wave; ti < T; ti += kMainWaves) {     // wave-uniform
         if (tile0 + ti >= ntiles) break;
@@ -597,7 +609,14 @@ __global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const Smal
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int m = 4 * q + v;
-                if (m < p.M) p.y[(size_t)m * p.N + n] = __builtin_bit_cast(uint16_t, (half_t)sum[v]);
+                if (m < p.M) {
+                    const half_t y = (half_t)sum[v];
+                    p.y[(size_t)m * p.N + n] = __builtin_bit_cast(uint16_t, y);
+                    if (p.mix_out) {
+                        const float w = (float)__builtin_bit_cast(half_t, with[v]);
+                        p.mix_out[(size_t)m * p.N + n] = __builtin_bit_cast(uint16_t, (half_t)((float)y - ((float)y - w) * 0.5f));
+                    }
+                }
             }
         }
     }
@@ -728,6 +747,7 @@ hipError_t launch_gemv_small_m(const LinearArgs *layers, int n_layers, hipStream
         p.sum_blocks = a.r > 0 ? ceil_div(a.r, 16) : 0;
         p.tiles_per_block = tpb;
         p.spin_limit = spin_limit();
+        p.mix_with = a.mix_with; p.mix_out = a.mix_out;
         row_blocks = std::max(row_blocks, p.down_blocks + p.sum_blocks + ceil_div(ceil_div(a.N, 16), tpb));
     }
     for (int i = n_layers; i < kMaxSmallGroup; ++i) g.layer[i] = g.layer[0];   // never indexed: grid.y stops at n_layers

@@ -15,7 +15,7 @@ least that keeps the data flow of a decoder layer and the values bounded:
     g, u    = h Wg, h Wu               one grouped launch
     x'      = (h + (silu(g) * u) Wd) / 2
 
-Four fused launches and four element-wise kernels (two lerp, silu, mul) per layer.  Weights are random packed words (speed
+Five launches per layer: four fused ones, two of which write the averages as well, and silu(g) * u.  Weights are random packed words (speed
 does not depend on the values) unless a list of quantized layers is passed in.  Prints one JSON line.
 """
 from __future__ import annotations
@@ -70,10 +70,15 @@ class DecoderStack:
         need = fbq.workspace_bytes(desc, self.batch)
         return torch.zeros(need, dtype=torch.uint8, device="cuda") if need else None
 
-    def _group(self, li, names, xs, ys, stream_ptr):
+    def _group(self, li, names, xs, ys, stream_ptr, mix=None):
+        """One grouped call; mix = (with, out): the last layer's result averaged with another tensor."""
         l, ws = self.layers[li], self.ws[li]
         arr = fbq.make_group([l[n] for n in names], xs, ys, [ws[n] for n in names])
-        rc = self.lib.fbq_linear_group(arr, len(names), self.batch, stream_ptr)
+        if mix is None:
+            rc = self.lib.fbq_linear_group(arr, len(names), self.batch, stream_ptr)
+        else:
+            none = [None] * (len(names) - 1)
+            rc = self.lib.fbq_linear_group_mix(arr, fbq.make_mix(none + [mix[0]], none + [mix[1]]), len(names), self.batch, stream_ptr)
         if rc:
             raise RuntimeError(f"fbq_linear_group: {fbq.status_string(rc)}")
 
@@ -87,12 +92,10 @@ class DecoderStack:
             if len(self.buf) > 1:
                 b["x_in"].copy_(x)                      # kept for inspection only
             self._group(li, ("q", "k", "v"), [x, x, x], [b["q"], b["k"], b["v"]], sp)
-            self._group(li, ("o",), [b["v"]], [b["o"]], sp)
-            torch.lerp(x, b["o"], 0.5, out=b["h"])      # (x + o) / 2
+            self._group(li, ("o",), [b["v"]], [b["o"]], sp, mix=(x, b["h"]))                 # h = (x + o) / 2
             self._group(li, ("gate", "up"), [b["h"], b["h"]], [b["gate"], b["up"]], sp)
-            torch.mul(torch.nn.functional.silu(b["gate"]), b["up"], out=b["act"])
-            self._group(li, ("down",), [b["act"]], [b["down"]], sp)
-            torch.lerp(b["h"], b["down"], 0.5, out=x)   # (h + down) / 2
+            fbq.silu_mul(b["gate"], b["up"], b["act"], stream)
+            self._group(li, ("down",), [b["act"]], [b["down"]], sp, mix=(b["h"], x))         # x = (h + down) / 2
         return x
 
     def capture(self):

@@ -18,7 +18,7 @@ _LIB_PATH = os.path.join(_HERE, "libfbq.so")
 _lib: Optional[ctypes.CDLL] = None
 
 EXPORTED_SYMBOLS = ["fbq_status_string", "fbq_check_desc", "fbq_packed_bytes", "fbq_workspace_bytes", "fbq_pack",
-                    "fbq_linear", "fbq_linear_static", "fbq_linear_unfused", "fbq_linear_group", "fbq_reconstruct", "fbq_unpack_codes", "fbq_quantize_feedback",
+                    "fbq_linear", "fbq_linear_static", "fbq_linear_unfused", "fbq_linear_group", "fbq_linear_group_mix", "fbq_silu_mul", "fbq_reconstruct", "fbq_unpack_codes", "fbq_quantize_feedback",
                     "fbq_train_workspace_bytes", "fbq_gram", "fbq_train_step", "fbq_test_set_spin_limit",
                     "fbq_measure_read_stream"]
 
@@ -38,6 +38,10 @@ class _CLayerCall(ctypes.Structure):
     _fields_ = [("desc", _CDesc), ("x", ctypes.c_void_p), ("qweight", ctypes.c_void_p), ("scales", ctypes.c_void_p),
                 ("zeros", ctypes.c_void_p), ("At", ctypes.c_void_p), ("Bt", ctypes.c_void_p), ("y", ctypes.c_void_p),
                 ("workspace", ctypes.c_void_p), ("workspace_bytes", ctypes.c_size_t)]
+
+
+class _CMix(ctypes.Structure):
+    _fields_ = [("with_", ctypes.c_void_p), ("out", ctypes.c_void_p)]
 
 
 @dataclass(frozen=True)
@@ -92,6 +96,10 @@ def load() -> ctypes.CDLL:
         lib.fbq_test_set_spin_limit.argtypes = [i32]
         lib.fbq_linear_group.restype = i32
         lib.fbq_linear_group.argtypes = [ctypes.POINTER(_CLayerCall), i32, i32, vp]
+        lib.fbq_linear_group_mix.restype = i32
+        lib.fbq_linear_group_mix.argtypes = [ctypes.POINTER(_CLayerCall), ctypes.POINTER(_CMix), i32, i32, vp]
+        lib.fbq_silu_mul.restype = i32
+        lib.fbq_silu_mul.argtypes = [vp, vp, vp, sz, vp]
         lib.fbq_reconstruct.restype = i32
         lib.fbq_reconstruct.argtypes = [dp] + [vp] * 7
         lib.fbq_unpack_codes.restype = i32
@@ -292,6 +300,22 @@ def linear_group(layers, xs, ys=None, workspaces=None, stream=None):
     arr = make_group(layers, xs, ys, workspaces)
     _check(load().fbq_linear_group(arr, len(layers), M, _stream(stream)), "fbq_linear_group")
     return ys
+
+
+def make_mix(withs, outs):
+    """Marshals the tensors to average with and the averages (None: none) into the array fbq_linear_group_mix takes (reusable)."""
+    arr = (_CMix * len(outs))()
+    for i, (w, o) in enumerate(zip(withs, outs)):
+        arr[i] = _CMix(_dev_ptr(w), _dev_ptr(o))
+    return arr
+
+
+def silu_mul(gate, up, out, stream=None):
+    """fbq_silu_mul: out = silu(gate) * up, fp16 device tensors of one shape."""
+    if gate.shape != up.shape or gate.shape != out.shape:
+        raise ValueError("shape mismatch")
+    _check(load().fbq_silu_mul(_dev_ptr(gate), _dev_ptr(up), _dev_ptr(out), out.numel(), _stream(stream)), "fbq_silu_mul")
+    return out
 
 
 def reconstruct(layer: DeviceLayer, stream=None):

@@ -134,3 +134,45 @@ def test_train_step_tile_edges(bits, N, K, r):
     for got, start, grad in ((st.At32, At, st.grad_At), (st.Bt32, Bt, st.grad_Bt)):
         step = start.double() - lr * grad.double()
         assert float((got.double() - step).abs().max()) <= 2.0 ** -23 * float(start.abs().max()) + 1e-12
+
+
+# ------------------------------------------------------------------ averages written with the result, silu(gate) * up
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("M", [1, 2, 5, 16, 40, 70])
+@pytest.mark.parametrize("N,K,r", [(1, 128, 0), (33, 384, 8), (130, 256, 16), (4098, 128, 0), (2050, 8320, 24)])
+def test_group_mix_equals_result_then_average(bits, M, N, K, r):
+    """Every way the averages are written (GEMV trips even and odd, matrix-core tiles, a launch of its own): y bit for bit that of
+    the plain call, the average bit for bit the element-wise one."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    g = torch.Generator(device="cuda")
+    g.manual_seed(47 + M + N)
+    from paper_2501_16385_amd.random_layers import random_layer
+    layers = [random_layer(fbq.Desc(N, K, r, bits), g, gain=1.0) for _ in range(2)]
+    x = torch.randn(M, K, device="cuda", generator=g).half()
+    with_ = framed_in_nan(torch.randn(M, N, device="cuda", generator=g).half())
+    want = fbq.linear_group(layers, [x, x])
+    ys, out = [torch.empty_like(w) for w in want], framed_in_nan(torch.empty(M, N, dtype=torch.float16, device="cuda"))
+    need = fbq.workspace_bytes(layers[0].desc, M)
+    wss = [torch.zeros(need, dtype=torch.uint8, device="cuda") if need else None for _ in layers]
+    arr = fbq.make_group(layers, [x, x], ys, wss)
+    stream = torch.cuda.current_stream().cuda_stream
+    assert fbq.load().fbq_linear_group_mix(arr, fbq.make_mix([None, with_], [None, out]), 2, M, stream) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0], want[0]) and torch.equal(ys[1], want[1])
+    assert torch.equal(out, torch.lerp(with_, want[1], 0.5))
+
+
+@pytest.mark.parametrize("count", [1, 7, 8, 2047, 2049, 5 * 11008])
+def test_silu_mul_equals_two_element_wise_kernels(count):
+    """silu rounded to fp16, then the product: one ulp where the exponential differs in its last place."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    g = torch.Generator(device="cuda")
+    g.manual_seed(count)
+    gate, up = (framed_in_nan((torch.randn(count, device="cuda", generator=g) * 3).half()) for _ in range(2))
+    out = fbq.silu_mul(gate, up, framed_in_nan(torch.empty(count, dtype=torch.float16, device="cuda")))
+    want = torch.nn.functional.silu(gate) * up
+    torch.cuda.synchronize()
+    assert float(((out.double() - want.double()).abs() - 2.0 ** -9 * want.double().abs()).max()) <= 2.0 ** -24
