@@ -113,27 +113,44 @@ constexpr int kPrefillColumns = 256;   // columns of a block tile of the prefill
 // step of a round that fills the fraction f of the CUs takes 0.48 (1 - f) less.  Examples, the choice and the two that
 // bracket it, us: 4096 -> 11008 at 1024 tokens 102 (256 rows), 109 (96), 118 (128); 8192 -> 28672 at 384 tokens 172 (192
 // rows), 190 (96), 202 (128); 28672 -> 8192 at 256 tokens 137 (128 rows, K split in 4), 144 (in 3), 144 (in 8).
-struct PrefillCut { int tm, ksplit; };
+//
+// Columns left over by full rounds: where the last round would leave many CUs idle, the column blocks that fill whole rounds are
+// one launch and the others a second one in tiles of their own height (4 us for the launch).  8192 -> 28672 at 2048 tokens,
+// INT4, r = 128, us: four rounds of 256-row tiles, the last half empty, 896; three rounds, and the rest as 256 tiles of 128 rows, 844.
+struct PrefillCut { int tm, ksplit, columns, tail_tm; };   // columns: column blocks of the first launch; tail_tm: tile height of the second, 0: none
 
 inline PrefillCut prefill_cut(int M, int N, int K)
 {
     static constexpr struct { int tm, kg; double step, fixed; } kTiles[] = {
         {8, 1, 1.614, 16.2}, {6, 1, 1.241, 11.6}, {4, 2, 1.731, 9.4}, {3, 2, 1.402, 7.6}, {2, 2, 1.144, 6.0}};
     const int G = K / kGroup, columns = ceil_div(N, kPrefillColumns);
-    PrefillCut best{0, 1};
-    double best_us = 1e300;
-    for (const auto &t : kTiles) {
+    auto launch_us = [&](int tile, int cols, int split) {
+        const auto &t = kTiles[tile];
         const int rows = ceil_div(M, 32 * t.tm);
-        const double tiles = (double)columns * rows;
+        const double per_xcd = (double)(cols / 8) * rows * split + std::ceil((cols % 8) * (double)rows * split / 8.0);
+        const double rounds = std::ceil(per_xcd / 32.0), filled = (double)cols * rows * split / (256.0 * rounds);
+        const int steps = 2 * ceil_div(G, split * t.kg);
+        const double us = rounds * (steps * t.step * (1.0 - 0.48 * (1.0 - filled)) + t.fixed) +
+                          (split > 1 ? 5.6 + 0.886e-6 * M * (double)N * (split + 0.5) : 0.0);
+        return us * (1.0 - 0.01 * t.tm);                // (taller tiles draw less power per product: measured, they win where this estimate is a tie)
+    };
+    PrefillCut best{0, 1, columns, 0};
+    double best_us = 1e300;
+    for (int i = 0; i < 5; ++i) {
+        const double tiles = (double)columns * ceil_div(M, 32 * kTiles[i].tm);
         for (int split = 1; split <= 8; ++split) {
-            if (split > 1 && (tiles * split > 600 || G / (split * t.kg) < 2)) break;
-            const double per_xcd = (double)(columns / 8) * rows * split + std::ceil((columns % 8) * (double)rows * split / 8.0);
-            const double rounds = std::ceil(per_xcd / 32.0), filled = tiles * split / (256.0 * rounds);
-            const int steps = 2 * ceil_div(G, split * t.kg);
-            double us = rounds * (steps * t.step * (1.0 - 0.48 * (1.0 - filled)) + t.fixed);
-            if (split > 1) us += 5.6 + 0.886e-6 * M * (double)N * (split + 0.5);
-            us *= 1.0 - 0.01 * t.tm;                    // (taller tiles draw less power per product: measured, they win where this estimate is a tie)
-            if (us < best_us) { best_us = us; best = {t.tm, split}; }
+            if (split > 1 && (tiles * split > 600 || G / (split * kTiles[i].kg) < 2)) break;
+            const double us = launch_us(i, columns, split);
+            if (us < best_us) { best_us = us; best = {kTiles[i].tm, split, columns, 0}; }
+        }
+    }
+    for (int i = 0; i < 5; ++i) {
+        const int rows = ceil_div(M, 32 * kTiles[i].tm);
+        const int whole = (int)((double)columns * rows / 256.0) * 256 / rows / 8 * 8;   // column blocks, in eights, that fill whole rounds
+        if (whole < 8 || whole >= columns) continue;
+        for (int j = 0; j < 5; ++j) {
+            const double us = launch_us(i, whole, 1) + launch_us(j, columns - whole, 1) + 4.0;
+            if (us < 0.98 * best_us) { best_us = us; best = {kTiles[i].tm, 1, whole, kTiles[j].tm}; }
         }
     }
     return best;

@@ -76,6 +76,7 @@ struct PrefillParams {
     int full_slots;        // blocks per XCD that belong to column blocks this XCD has to itself: (column blocks / 8) * row_blocks * ksplit
     int full_cols;         // column blocks dealt out whole, eight at a time: (column blocks / 8) * 8
     int rem_blocks;        // blocks of the column blocks left over, dealt out singly over the XCDs
+    int col0;              // first column block of this launch
     int ksplit;            // blocks that split K for the same tile (1: none)
     float *ypart;          // ksplit > 1 only: [ksplit][M][N] fp32 partial results, added up by fbq_sum_parts_kernel
 };
@@ -219,7 +220,7 @@ __global__ __launch_bounds__((GemmTile<BITS, TM, KG>::kThreads)) __attribute__((
         bm = q % p.row_blocks;
         bn = p.full_cols + q / p.row_blocks;
     }
-    const int m0 = bm * kBM, n0 = bn * kBN;
+    const int m0 = bm * kBM, n0 = (p.col0 + bn) * kBN;
     const int nw = n0 + wave * (kTN * 32);
     const int shares = KG * p.ksplit;                   // K is shared out over the groups of a block and, for a layer with few tiles, over blocks
     const int U_part = (p.G + shares - 1) / shares;     // quantization groups per share
@@ -845,16 +846,23 @@ static void launch_tile(const PrefillParams &p, dim3 grid, hipStream_t stream)
     hipLaunchKernelGGL((fbq_gemm_kernel<BITS, TM, KG>), grid, dim3(GemmTile<BITS, TM, KG>::kThreads), 0, stream, p);
 }
 
+// `columns` column blocks from p.col0 on, in tiles of 32 tm rows
 template <int BITS>
-static void launch_cut(const PrefillParams &p, const PrefillCut &c, dim3 grid, hipStream_t stream)
+static hipError_t launch_columns(PrefillParams p, int tm, int columns, hipStream_t stream)
 {
-    switch (c.tm) {
+    p.row_blocks = ceil_div(p.M, 32 * tm);
+    p.full_cols = (columns / kXcds) * kXcds;
+    p.full_slots = (columns / kXcds) * p.row_blocks * p.ksplit;
+    p.rem_blocks = (columns % kXcds) * p.row_blocks * p.ksplit;
+    const dim3 grid(kXcds * (p.full_slots + ceil_div(p.rem_blocks, kXcds)));
+    switch (tm) {
     case 8: launch_tile<BITS, 8, 1>(p, grid, stream); break;
     case 6: launch_tile<BITS, 6, 1>(p, grid, stream); break;
     case 4: launch_tile<BITS, 4, 2>(p, grid, stream); break;
     case 3: launch_tile<BITS, 3, 2>(p, grid, stream); break;
     default: launch_tile<BITS, 2, 2>(p, grid, stream); break;
     }
+    return hipGetLastError();
 }
 
 hipError_t launch_gemm_prefill(const LinearArgs &a, hipStream_t stream)
@@ -870,14 +878,12 @@ hipError_t launch_gemm_prefill(const LinearArgs &a, hipStream_t stream)
     p.Np = nb * kBN;
     p.ksplit = c.ksplit;
     p.ypart = s.ypart;
-    p.row_blocks = ceil_div(a.M, 32 * c.tm);
-    p.full_cols = (nb / kXcds) * kXcds;
-    p.full_slots = (nb / kXcds) * p.row_blocks * p.ksplit;
-    p.rem_blocks = (nb % kXcds) * p.row_blocks * p.ksplit;
-    const dim3 grid(kXcds * (p.full_slots + ceil_div(p.rem_blocks, kXcds)));
-    if (a.bits == 4) launch_cut<4>(p, c, grid, stream);
-    else launch_cut<3>(p, c, grid, stream);
-    hipError_t e = hipGetLastError();
+    p.col0 = 0;
+    hipError_t e = a.bits == 4 ? launch_columns<4>(p, c.tm, c.columns, stream) : launch_columns<3>(p, c.tm, c.columns, stream);
+    if (e == hipSuccess && c.tail_tm) {
+        p.col0 = c.columns;
+        e = a.bits == 4 ? launch_columns<4>(p, c.tail_tm, nb - c.columns, stream) : launch_columns<3>(p, c.tail_tm, nb - c.columns, stream);
+    }
     if (e == hipSuccess && p.ksplit > 1) {
         const size_t total = (size_t)a.M * a.N;
         hipLaunchKernelGGL(fbq_sum_parts_kernel, dim3((unsigned)std::min<size_t>(2048, (total / 4 + 255) / 256)), dim3(256), 0, stream,

@@ -51,6 +51,10 @@ PREFILL_CASES = [
     (33000, 640, 40, 191),      # 192
     (33001, 128, 40, 193),      # 256
     (33000, 640, 64, 193),      # 256
+    # the columns past the last full round in lower tiles, a second launch (several groups per row: with a single one, millions of
+    # outputs include small ones of rows with a scale far above the average, which the bound on single outputs is relative to)
+    (32957, 640, 24, 583),      # 256, then 128
+    (26297, 640, 8, 546),       # 192, then 64
 ]
 
 
