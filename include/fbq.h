@@ -199,8 +199,9 @@ typedef struct {
 
 /*
  * fbq_linear_group_mix - fbq_linear_group for layers whose result is averaged with another tensor (the residual of
- * the decoder loop): y is written as fbq_linear_group writes it, and mix[i].out with it, by the same launch up to 16
- * tokens (and, at one or two tokens, an even N), by a launch of its own otherwise.
+ * the decoder loop): y is written as fbq_linear_group writes it, and mix[i].out with it: by the same launch up to 16
+ * tokens where the kernel has an instance that does both (not for an odd N at one or two tokens, an odd number of scales at
+ * 3..16, or INT4 with rank above 128 and K in 6145..8192, 12289..16384 or 24577..32768 at one or two), by a launch of its own otherwise.
  *   mix host array of n entries (read during the call only); an out may be no layer's x, y or `with`.
  * Errors: those of fbq_linear_group; FBQ_ERR_NULL (out without with), FBQ_ERR_ALIGN, before ANY launch.
  */

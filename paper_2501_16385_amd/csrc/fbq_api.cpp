@@ -258,7 +258,8 @@ extern "C" fbq_status fbq_linear(const fbq_desc *d, int M, const void *x, const 
     return hip_status(launch_one(a, s));
 }
 
-fbq_status fbq::linear_group(const fbq_layer_call *calls, const fbq_mix *mix, int n, int M, hipStream_t s)
+// mix: null or n entries
+static fbq_status linear_group(const fbq_layer_call *calls, const fbq_mix *mix, int n, int M, hipStream_t s)
 {
     constexpr int kMaxCalls = 64;
     if (!calls) return FBQ_ERR_NULL;
@@ -272,10 +273,8 @@ fbq_status fbq::linear_group(const fbq_layer_call *calls, const fbq_mix *mix, in
         if (!mix || !mix[i].out) continue;
         if (!mix[i].with) return FBQ_ERR_NULL;
         if (misaligned(mix[i].with) || misaligned(mix[i].out)) return FBQ_ERR_ALIGN;
-        if (mix_in_kernel(M, c.desc.N)) {
-            args[i].mix_with = (const uint16_t *)mix[i].with;
-            args[i].mix_out = (uint16_t *)mix[i].out;
-        }
+        args[i].mix_with = (const uint16_t *)mix[i].with;
+        args[i].mix_out = (uint16_t *)mix[i].out;
     }
     // Layers that share a launch carry the same launch tag: two of them writing their hand-over words into the same
     // memory would accept each other's t.  Workspaces must not overlap.
@@ -291,7 +290,12 @@ fbq_status fbq::linear_group(const fbq_layer_call *calls, const fbq_mix *mix, in
     }
     hipError_t e = hipSuccess;
     if (M > kDecodeMaxM) {
-        for (int i = 0; i < n && e == hipSuccess; ++i) e = launch_one(args[i], s);
+        for (int i = 0; i < n && e == hipSuccess; ++i) {
+            LinearArgs plain = args[i];
+            plain.mix_with = nullptr; plain.mix_out = nullptr;
+            e = launch_one(plain, s);
+            if (e == hipSuccess && args[i].mix_out) e = launch_mix(args[i], s);
+        }
         return hip_status(e);
     }
     // Decode: layers that fit one launch (the same kernel instance; for 4..16 tokens also the same
@@ -317,6 +321,20 @@ fbq_status fbq::linear_group(const fbq_layer_call *calls, const fbq_mix *mix, in
 extern "C" fbq_status fbq_linear_group(const fbq_layer_call *calls, int n, int M, fbq_stream stream)
 {
     return linear_group(calls, nullptr, n, M, (hipStream_t)stream);
+}
+
+extern "C" fbq_status fbq_linear_group_mix(const fbq_layer_call *calls, const fbq_mix *mix, int n, int M, fbq_stream stream)
+{
+    if (!mix) return FBQ_ERR_NULL;
+    return linear_group(calls, mix, n, M, (hipStream_t)stream);
+}
+
+extern "C" fbq_status fbq_silu_mul(const void *gate, const void *up, void *out, size_t count, fbq_stream stream)
+{
+    if (!gate || !up || !out) return FBQ_ERR_NULL;
+    if (count < 1) return FBQ_ERR_SHAPE;
+    if (misaligned(gate) || misaligned(up) || misaligned(out)) return FBQ_ERR_ALIGN;
+    return hip_status(launch_silu_mul(gate, up, out, count, (hipStream_t)stream));
 }
 
 extern "C" fbq_status fbq_reconstruct(const fbq_desc *d, const void *qweight, const void *scales, const void *zeros,

@@ -197,12 +197,21 @@ struct LayerParams {
     int tslices;          // K slices of the down-projection = waves of a block that split K (1, 2 or 4); consumers add the partial sums
     int blocks;           // blocks of this layer
     int spin_limit;       // polls for t before a wave computes it itself; negative: at once (test hook)
-    const uint16_t *mix_with;   // [M][N], N even, or null: see LinearArgs
-    uint16_t *mix_out;
 };
 
+// The averages a layer's result is also written into, only in the arguments of the instances that do it: see kGemvMixes
+struct MixParams {
+    const uint16_t *with;   // [M][N], N even
+    uint16_t *out;          // null: none
+};
+
+template <bool MIX>
 struct GemvGroup {
     LayerParams layer[kMaxGroup];
+};
+template <>
+struct GemvGroup<true> : GemvGroup<false> {
+    MixParams mix[kMaxGroup];
 };
 
 constexpr int kNowhere = 1 << 30;     // a byte offset beyond any buffer a layer has
@@ -323,9 +332,11 @@ __device__ __forceinline__ void job_only_block(const LayerParams &p, int m, int 
 }
 
 // BITS: 3 or 4.  CPW: chunks (of 2048 codes) per wave.  KS: waves of a block that split K.
-// ROWS: rows per tile.  RI: ceil(r/128), 0 = branch-free twin.
-template <int BITS, int CPW, int KS, int ROWS, int RI>
-__global__ __launch_bounds__(256) void fbq_gemv_kernel(const GemvGroup g)
+// ROWS: rows per tile.  RI: ceil(r/128), 0 = branch-free twin.  MIX: averages are written with the results; instances of
+// their own, because the averaging costs every instance that has it four to eight vector registers and spilled scalar ones, whether a
+// call averages or not (<4, 4, 1, 2, 2>: 253 registers and two waves per SIMD without, 257 and one wave with).
+template <int BITS, int CPW, int KS, int ROWS, int RI, bool MIX>
+__global__ __launch_bounds__(256) void fbq_gemv_kernel(const GemvGroup<MIX> g)
 {
     constexpr int kWaves = 4;
     constexpr int kRowSets = kWaves / KS;               // row sets per block
@@ -342,6 +353,8 @@ __global__ __launch_bounds__(256) void fbq_gemv_kernel(const GemvGroup g)
     // one of the group leave the surplus blocks at once.
     const int m = blockIdx.z;
     const LayerParams p = g.layer[blockIdx.x];
+    MixParams mix{};
+    if constexpr (MIX) mix = g.mix[blockIdx.x];
     // (all of them before the first branch: left alone, the compiler fetches only what the branch needs first)
     asm volatile("" :: "s"(p.qw), "s"(p.scales), "s"(p.zeros), "s"(p.x), "s"(p.y), "s"(p.N), "s"(p.K), "s"(p.row_words), "s"(p.G));
     if (RI > 0) asm volatile("" :: "s"(p.At), "s"(p.Bt), "s"(p.ttag), "s"(p.r), "s"(p.tslices), "s"(p.spin_limit));
@@ -552,8 +565,8 @@ __global__ __launch_bounds__(256) void fbq_gemv_kernel(const GemvGroup g)
     // weight stream do not see; asked for when the trip that finishes their tile begins.
     uint32_t mixw[ROWS / 2];
     auto request_mix = [&](int tile) __attribute__((always_inline)) {
-        if (!p.mix_out) return;
-        const auto *w = reinterpret_cast<const __attribute__((address_space(4))) uint32_t *>((uintptr_t)p.mix_with);
+        if (!MIX || !mix.out) return;
+        const auto *w = reinterpret_cast<const __attribute__((address_space(4))) uint32_t *>((uintptr_t)mix.with);
 #pragma unroll
         for (int i = 0; i < ROWS / 2; ++i) mixw[i] = w[((size_t)m * p.N + min(tile * ROWS + 2 * i, p.N - 2)) / 2];
     };
@@ -589,12 +602,12 @@ __global__ __launch_bounds__(256) void fbq_gemv_kernel(const GemvGroup g)
         if (ks == 0 && lane < ROWS && tile < ntiles && n0 + lane < p.N) {
             const half_t y = (half_t)out;
             p.y[(size_t)m * p.N + n0 + lane] = __builtin_bit_cast(uint16_t, y);
-            if (p.mix_out) {
+            if (MIX && mix.out) {
                 uint32_t w = mixw[0];
 #pragma unroll
                 for (int i = 1; i < ROWS / 2; ++i) w = lane / 2 == i ? mixw[i] : w;
                 const float with = (float)__builtin_bit_cast(half_t, (uint16_t)((lane & 1) ? w >> 16 : w));
-                p.mix_out[(size_t)m * p.N + n0 + lane] = __builtin_bit_cast(uint16_t, (half_t)((float)y - ((float)y - with) * 0.5f));
+                mix.out[(size_t)m * p.N + n0 + lane] = __builtin_bit_cast(uint16_t, (half_t)((float)y - ((float)y - with) * 0.5f));
             }
         }
     };
@@ -700,38 +713,54 @@ static Variant variant_of(int K, int bits, int r)
     return v;
 }
 
+// Whether there is an instance that averages.  Not where it would pass 256 registers (257 and 258): the launcher counts on
+// two blocks per CU.
+static constexpr bool gemv_mixes(int bits, int cpw, int ri) { return !(bits == 4 && cpw == 4 && ri >= 2); }
+
+template <int BITS, int CPW, int KS, int ROWS, int RI>
+static void launch_instance(const GemvGroup<true> &g, bool mix, dim3 grid, hipStream_t stream)
+{
+    if constexpr (gemv_mixes(BITS, CPW, RI)) {
+        if (mix) {
+            hipLaunchKernelGGL((fbq_gemv_kernel<BITS, CPW, KS, ROWS, RI, true>), grid, dim3(256), 0, stream, g);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((fbq_gemv_kernel<BITS, CPW, KS, ROWS, RI, false>), grid, dim3(256), 0, stream, static_cast<const GemvGroup<false> &>(g));
+}
+
 template <int BITS, int CPW, int KS, int ROWS>
-static hipError_t launch_ri(const GemvGroup &g, int ri, dim3 grid, hipStream_t stream)
+static hipError_t launch_ri(const GemvGroup<true> &g, bool mix, int ri, dim3 grid, hipStream_t stream)
 {
     switch (ri) {
-    case 0: hipLaunchKernelGGL((fbq_gemv_kernel<BITS, CPW, KS, ROWS, 0>), grid, dim3(256), 0, stream, g); break;
-    case 1: hipLaunchKernelGGL((fbq_gemv_kernel<BITS, CPW, KS, ROWS, 1>), grid, dim3(256), 0, stream, g); break;
-    default: hipLaunchKernelGGL((fbq_gemv_kernel<BITS, CPW, KS, ROWS, 2>), grid, dim3(256), 0, stream, g); break;
+    case 0: launch_instance<BITS, CPW, KS, ROWS, 0>(g, mix, grid, stream); break;
+    case 1: launch_instance<BITS, CPW, KS, ROWS, 1>(g, mix, grid, stream); break;
+    default: launch_instance<BITS, CPW, KS, ROWS, 2>(g, mix, grid, stream); break;
     }
     return hipGetLastError();
 }
 
 template <int BITS, int CPW, int KS>
-static hipError_t launch_rows(const GemvGroup &g, int rows, int ri, dim3 grid, hipStream_t stream)
+static hipError_t launch_rows(const GemvGroup<true> &g, bool mix, int rows, int ri, dim3 grid, hipStream_t stream)
 {
     if constexpr (CPW == 1) {                           // wider tiles only where a row is a single chunk
-        if (rows == 4) return launch_ri<BITS, CPW, KS, 4>(g, ri, grid, stream);
+        if (rows == 4) return launch_ri<BITS, CPW, KS, 4>(g, mix, ri, grid, stream);
     }
-    return launch_ri<BITS, CPW, KS, 2>(g, ri, grid, stream);
+    return launch_ri<BITS, CPW, KS, 2>(g, mix, ri, grid, stream);
 }
 
 template <int BITS>
-static hipError_t launch_bits(const GemvGroup &g, const Variant &v, int rows, dim3 grid, hipStream_t stream)
+static hipError_t launch_bits(const GemvGroup<true> &g, bool mix, const Variant &v, int rows, dim3 grid, hipStream_t stream)
 {
     switch (v.ks * 10 + v.cpw) {
-    case 11: return launch_rows<BITS, 1, 1>(g, rows, v.ri, grid, stream);
-    case 12: return launch_rows<BITS, 2, 1>(g, rows, v.ri, grid, stream);
-    case 13: return launch_rows<BITS, 3, 1>(g, rows, v.ri, grid, stream);
-    case 14: return launch_rows<BITS, 4, 1>(g, rows, v.ri, grid, stream);
-    case 23: return launch_rows<BITS, 3, 2>(g, rows, v.ri, grid, stream);
-    case 24: return launch_rows<BITS, 4, 2>(g, rows, v.ri, grid, stream);
-    case 43: return launch_rows<BITS, 3, 4>(g, rows, v.ri, grid, stream);
-    case 44: return launch_rows<BITS, 4, 4>(g, rows, v.ri, grid, stream);
+    case 11: return launch_rows<BITS, 1, 1>(g, mix, rows, v.ri, grid, stream);
+    case 12: return launch_rows<BITS, 2, 1>(g, mix, rows, v.ri, grid, stream);
+    case 13: return launch_rows<BITS, 3, 1>(g, mix, rows, v.ri, grid, stream);
+    case 14: return launch_rows<BITS, 4, 1>(g, mix, rows, v.ri, grid, stream);
+    case 23: return launch_rows<BITS, 3, 2>(g, mix, rows, v.ri, grid, stream);
+    case 24: return launch_rows<BITS, 4, 2>(g, mix, rows, v.ri, grid, stream);
+    case 43: return launch_rows<BITS, 3, 4>(g, mix, rows, v.ri, grid, stream);
+    case 44: return launch_rows<BITS, 4, 4>(g, mix, rows, v.ri, grid, stream);
     }
     return hipErrorInvalidValue;   // K > 32768: rejected by the caller's shape check
 }
@@ -780,7 +809,15 @@ hipError_t launch_gemv_decode(const LinearArgs *layers, int n_layers, hipStream_
         for (int i = 0; i < n_layers; ++i) job_blocks += ceil_div(layers[i].r, row_sets);
         budget = std::max(budget / 2, budget - job_blocks);
     }
-    GemvGroup g;
+    // averages (see fbq_linear_group_mix): with the results where an instance does it and every layer's rows come in pairs,
+    // by launches of their own behind this one otherwise
+    bool mixes = false, mix_inside = gemv_mixes(v.bits, v.cpw, v.ri);
+    for (int i = 0; i < n_layers; ++i) {
+        if (!layers[i].mix_out) continue;
+        mixes = true;
+        mix_inside = mix_inside && layers[i].N % 2 == 0;
+    }
+    GemvGroup<true> g;
     int widest = 0;
     for (int i = 0; i < n_layers; ++i) {
         const LinearArgs &a = layers[i];
@@ -792,7 +829,7 @@ hipError_t launch_gemv_decode(const LinearArgs *layers, int n_layers, hipStream_
         p.G = a.K / kGroup;
         p.tslices = v.ks;
         p.spin_limit = spin_limit();
-        p.mix_with = a.mix_with; p.mix_out = a.mix_out;
+        g.mix[i] = {a.mix_with, a.mix_out};
         const int max_blocks = ceil_div(ceil_div(a.N, rows), row_sets);
         const int share = (int)(budget * ((double)a.N * a.K / total_work));
         if (inline_job) {
@@ -804,9 +841,13 @@ hipError_t launch_gemv_decode(const LinearArgs *layers, int n_layers, hipStream_
             widest = std::max(widest, p.blocks + ceil_div(a.r, row_sets));  // blocks in front that only do the down-projection
         }
     }
-    for (int i = n_layers; i < kMaxGroup; ++i) g.layer[i] = g.layer[0];   // never indexed: grid.x stops at n_layers
+    for (int i = n_layers; i < kMaxGroup; ++i) { g.layer[i] = g.layer[0]; g.mix[i] = g.mix[0]; }   // never indexed: grid.x stops at n_layers
     const dim3 grid(n_layers, widest, M);
-    return v.bits == 4 ? launch_bits<4>(g, v, rows, grid, stream) : launch_bits<3>(g, v, rows, grid, stream);
+    const bool mix = mixes && mix_inside;
+    hipError_t e = v.bits == 4 ? launch_bits<4>(g, mix, v, rows, grid, stream) : launch_bits<3>(g, mix, v, rows, grid, stream);
+    for (int i = 0; i < n_layers && e == hipSuccess && !mix; ++i)
+        if (layers[i].mix_out) e = launch_mix(layers[i], stream);
+    return e;
 }
 
 }  // namespace fbq

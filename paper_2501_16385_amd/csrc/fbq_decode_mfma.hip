@@ -93,8 +93,6 @@ struct SmallParams {
     int sum_blocks;        // ... and the blocks after them that add the slices up (16 columns each)
     int tiles_per_block;   // 16-row tiles a consumer block owns
     int spin_limit;        // polls for t before a wave computes it itself; negative: at once (test hook)
-    const uint16_t *mix_with;   // [M][N] or null: see LinearArgs
-    uint16_t *mix_out;
 };
 
 // Layers that share their activations (q/k/v, gate/up) share the launch.  In the grid y is the layer
@@ -102,9 +100,19 @@ struct SmallParams {
 // they are fetched in one go with the rest of the kernel arguments (a second, dependent round trip
 // to them costs more than half a microsecond).  Surplus blocks of rows with fewer blocks than the
 // widest leave at once.
+template <bool MIX>
 struct SmallGroup {
     int n_layers;
     SmallParams layer[kMaxSmallGroup];
+};
+// ... and, only in the arguments of the instances that write averages with the results, what to average with
+struct SmallMix {
+    const uint16_t *with;   // [M][N]
+    uint16_t *out;          // null: none
+};
+template <>
+struct SmallGroup<true> : SmallGroup<false> {
+    SmallMix mix[kMaxSmallGroup];
 };
 
 // What the weight field of pair p (0..15, in extraction order) is multiplied by; the activation that meets it is divided by it.
@@ -338,8 +346,9 @@ __device__ __forceinline__ uint32_t small_m_launch_tag()
 
 // BITS: 3 or 4.  T: 16-row tiles per block.  BRANCH: r > 0.
 // TAIL: some layer of the launch has an odd number of scales (N G odd): see where scale and zero are taken.
-template <int BITS, int T, bool BRANCH, bool TAIL>
-__global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const SmallGroup g)
+// MIX: averages are written with the results; instances of their own for the same reason.
+template <int BITS, int T, bool BRANCH, bool TAIL, bool MIX>
+__global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const SmallGroup<MIX> g)
 {
     constexpr int kPiece = BITS == 4 ? 16 : 12;         // bytes of 32 codes
     __shared__ float4_t red[kMainWaves][T][64];
@@ -349,6 +358,8 @@ __global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const Smal
     float4_t (*red_prep)[64] = reinterpret_cast<float4_t (*)[64]>(&red[0][0][0]);   // [8][64], what a down-projection block needs
 
     const SmallParams p = g.layer[blockIdx.y];
+    SmallMix mix{};
+    if constexpr (MIX) mix = g.mix[blockIdx.y];
     // (all of them before the first branch: left alone, the compiler fetches only what the branch needs first)
     asm volatile("" :: "s"(p.qw), "s"(p.scales), "s"(p.zeros), "s"(p.x), "s"(p.y), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.row_words), "s"(p.G), "s"(p.tiles_per_block));
     if (BRANCH) asm volatile("" :: "s"(p.Bt), "s"(p.At), "s"(p.tpart), "s"(p.tsum), "s"(p.r), "s"(p.slices), "s"(p.kslice), "s"(p.down_blocks), "s"(p.sum_blocks), "s"(p.spin_limit));
@@ -590,8 +601,8 @@ __global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const Smal
     // the values to average with, on their way while the waves meet (wave ti stores tile ti)
     static_assert(T <= kMainWaves, "a wave stores at most one tile");
     uint16_t with[4] = {0, 0, 0, 0};
-    if (p.mix_out && wave < T) {                        // wave-uniform
-        const __amdgpu_buffer_rsrc_t mbuf = buffer_of(p.mix_with, (long)p.M * p.N * 2);
+    if (MIX && mix.out && wave < T) {                   // wave-uniform
+        const __amdgpu_buffer_rsrc_t mbuf = buffer_of(mix.with, (long)p.M * p.N * 2);
         const int n = (tile0 + wave) * 16 + c;
 #pragma unroll
         for (int v = 0; v < 4; ++v)
@@ -612,9 +623,9 @@ __global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const Smal
                 if (m < p.M) {
                     const half_t y = (half_t)sum[v];
                     p.y[(size_t)m * p.N + n] = __builtin_bit_cast(uint16_t, y);
-                    if (p.mix_out) {
+                    if (MIX && mix.out) {
                         const float w = (float)__builtin_bit_cast(half_t, with[v]);
-                        p.mix_out[(size_t)m * p.N + n] = __builtin_bit_cast(uint16_t, (half_t)((float)y - ((float)y - w) * 0.5f));
+                        mix.out[(size_t)m * p.N + n] = __builtin_bit_cast(uint16_t, (half_t)((float)y - ((float)y - w) * 0.5f));
                     }
                 }
             }
@@ -633,36 +644,46 @@ static int cu_count()
     return cus;
 }
 
+template <int BITS, int T, bool BRANCH, bool TAIL>
+static void launch_instance(const SmallGroup<true> &g, bool mix, dim3 grid, hipStream_t stream)
+{
+    if constexpr (!TAIL) {
+        if (mix) {
+            hipLaunchKernelGGL((fbq_small_m_kernel<BITS, T, BRANCH, TAIL, true>), grid, dim3(64 * kMainWaves), 0, stream, g);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((fbq_small_m_kernel<BITS, T, BRANCH, TAIL, false>), grid, dim3(64 * kMainWaves), 0, stream, static_cast<const SmallGroup<false> &>(g));
+}
+
 template <int BITS, int T, bool TAIL>
-static hipError_t launch_tiles(const SmallGroup &g, bool branch, dim3 grid, hipStream_t stream)
+static hipError_t launch_tiles(const SmallGroup<true> &g, bool branch, bool mix, dim3 grid, hipStream_t stream)
 {
     // (the INT3 three- and four-tile instances without the branch come out of the compiler with spills of
     // 160 bytes and more; the ones with the branch spill nothing or 36 bytes, and with r = 0 they do the same work)
     if constexpr (BITS == 3 && T >= 3) {
-        hipLaunchKernelGGL((fbq_small_m_kernel<BITS, T, true, TAIL>), grid, dim3(64 * kMainWaves), 0, stream, g);
+        launch_instance<BITS, T, true, TAIL>(g, mix, grid, stream);
     } else {
-        if (branch) hipLaunchKernelGGL((fbq_small_m_kernel<BITS, T, true, TAIL>), grid, dim3(64 * kMainWaves), 0, stream, g);
-        else hipLaunchKernelGGL((fbq_small_m_kernel<BITS, T, false, TAIL>), grid, dim3(64 * kMainWaves), 0, stream, g);
+        if (branch) launch_instance<BITS, T, true, TAIL>(g, mix, grid, stream);
+        else launch_instance<BITS, T, false, TAIL>(g, mix, grid, stream);
     }
     return hipGetLastError();
 }
 
 template <int BITS>
-static hipError_t launch_bits(const SmallGroup &g, int row_blocks, hipStream_t stream)
+static hipError_t launch_bits(const SmallGroup<true> &g, bool tail, bool mix, int row_blocks, hipStream_t stream)
 {
     const bool branch = g.layer[0].r > 0;
     const dim3 grid(row_blocks, g.n_layers);
-    bool tail = false;                                  // a layer whose scale array ends in the middle of a dword
-    for (int i = 0; i < g.n_layers; ++i) tail = tail || (((long)g.layer[i].N * g.layer[i].G) & 1);
     switch (g.layer[0].tiles_per_block * 2 + (tail ? 1 : 0)) {
-    case 2: return launch_tiles<BITS, 1, false>(g, branch, grid, stream);
-    case 3: return launch_tiles<BITS, 1, true>(g, branch, grid, stream);
-    case 4: return launch_tiles<BITS, 2, false>(g, branch, grid, stream);
-    case 5: return launch_tiles<BITS, 2, true>(g, branch, grid, stream);
-    case 6: return launch_tiles<BITS, 3, false>(g, branch, grid, stream);
-    case 7: return launch_tiles<BITS, 3, true>(g, branch, grid, stream);
-    case 8: return launch_tiles<BITS, 4, false>(g, branch, grid, stream);
-    default: return launch_tiles<BITS, 4, true>(g, branch, grid, stream);
+    case 2: return launch_tiles<BITS, 1, false>(g, branch, mix, grid, stream);
+    case 3: return launch_tiles<BITS, 1, true>(g, branch, mix, grid, stream);
+    case 4: return launch_tiles<BITS, 2, false>(g, branch, mix, grid, stream);
+    case 5: return launch_tiles<BITS, 2, true>(g, branch, mix, grid, stream);
+    case 6: return launch_tiles<BITS, 3, false>(g, branch, mix, grid, stream);
+    case 7: return launch_tiles<BITS, 3, true>(g, branch, mix, grid, stream);
+    case 8: return launch_tiles<BITS, 4, false>(g, branch, mix, grid, stream);
+    default: return launch_tiles<BITS, 4, true>(g, branch, mix, grid, stream);
     }
 }
 
@@ -727,7 +748,7 @@ hipError_t launch_gemv_small_m(const LinearArgs *layers, int n_layers, hipStream
     for (int i = 0; i < n_layers; ++i)
         if (layers[i].r > 0) preparing += ceil_div(layers[i].r, 16) * (ceil_div(layers[i].K, slice_length(layers[i].K)) + 1);
     const int tpb = tiles_per_block_of(total_tiles, preparing, ceil_div(first.K / kGroup, kPassGroups));
-    SmallGroup g;
+    SmallGroup<true> g;
     g.n_layers = n_layers;
     int row_blocks = 0;                                  // widest row of the grid
     for (int i = 0; i < n_layers; ++i) {
@@ -747,11 +768,20 @@ hipError_t launch_gemv_small_m(const LinearArgs *layers, int n_layers, hipStream
         p.sum_blocks = a.r > 0 ? ceil_div(a.r, 16) : 0;
         p.tiles_per_block = tpb;
         p.spin_limit = spin_limit();
-        p.mix_with = a.mix_with; p.mix_out = a.mix_out;
+        g.mix[i] = {a.mix_with, a.mix_out};
         row_blocks = std::max(row_blocks, p.down_blocks + p.sum_blocks + ceil_div(ceil_div(a.N, 16), tpb));
     }
-    for (int i = n_layers; i < kMaxSmallGroup; ++i) g.layer[i] = g.layer[0];   // never indexed: grid.y stops at n_layers
-    return first.bits == 4 ? launch_bits<4>(g, row_blocks, stream) : launch_bits<3>(g, row_blocks, stream);
+    for (int i = n_layers; i < kMaxSmallGroup; ++i) { g.layer[i] = g.layer[0]; g.mix[i] = g.mix[0]; }   // never indexed: grid.y stops at n_layers
+    bool tail = false;                                  // a layer whose scale array ends in the middle of a dword
+    bool mix = false;                                   // averages to be written: with the results, or behind the launch where a layer has such a tail
+    for (int i = 0; i < n_layers; ++i) {
+        tail = tail || (((long)layers[i].N * g.layer[i].G) & 1);
+        mix = mix || layers[i].mix_out;
+    }
+    hipError_t e = first.bits == 4 ? launch_bits<4>(g, tail, mix, row_blocks, stream) : launch_bits<3>(g, tail, mix, row_blocks, stream);
+    for (int i = 0; i < n_layers && e == hipSuccess && tail; ++i)
+        if (layers[i].mix_out) e = launch_mix(layers[i], stream);
+    return e;
 }
 
 }  // namespace fbq

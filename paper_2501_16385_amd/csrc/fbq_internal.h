@@ -46,12 +46,9 @@ struct LinearArgs {
     uint16_t *y;
     void *workspace;  // see decode_workspace_bytes / small_m_workspace_bytes / prefill_workspace_bytes
     int M, N, K, r, bits;
-    const uint16_t *mix_with;   // null, or [M][N]: the kernel that writes y also writes mix_out = (mix_with + y) / 2
-    uint16_t *mix_out;          // (see mix_in_kernel; the caller sees to the other cases)
+    const uint16_t *mix_with;   // [M][N] and ...
+    uint16_t *mix_out;          // ... null, or [M][N] that the two decode launchers write y averaged with mix_with to (see launch_mix)
 };
-
-// Whether the decode kernels mix while they store (the GEMV fetches the other tensor's rows in pairs).
-inline bool mix_in_kernel(int M, int N) { return M <= kDecodeMaxM && (M > kPerTokenMaxM || N % 2 == 0); }
 
 // Launchers (validated arguments only).  Each returns the hipError_t of its launches.
 hipError_t launch_gemv_decode(const LinearArgs *layers, int n_layers, hipStream_t stream);
@@ -67,6 +64,10 @@ hipError_t launch_reconstruct(const fbq_desc &d, const uint32_t *qw, const uint1
 hipError_t launch_quantize(const fbq_desc &d, const uint16_t *W, const uint16_t *At, const uint16_t *Bt, uint32_t *qw,
                            uint16_t *scales, uint16_t *zeros, hipStream_t stream, uint16_t *D16 = nullptr,
                            uint16_t *Dt16 = nullptr, int ldt = 0, float gain = 0.0f);
+
+// a.mix_out = a.y averaged with a.mix_with, behind the launch that writes y
+hipError_t launch_mix(const LinearArgs &a, hipStream_t stream);
+hipError_t launch_silu_mul(const void *gate, const void *up, void *out, size_t count, hipStream_t stream);
 
 hipError_t launch_read_stream(const void *buf, size_t bytes, hipStream_t stream);
 // the sub-branch as two launches of its own on top of a y the main path has written (t: [M][r] fp16 scratch)
@@ -93,8 +94,6 @@ size_t train_workspace_bytes(int N, int K, int r, int T);
 fbq_status check_layer(const fbq_desc *d, int M, const void *x, const void *qweight, const void *scales, const void *zeros,
                        const void *At, const void *Bt, void *y, void *workspace, size_t workspace_bytes, LinearArgs *a);
 hipError_t launch_one(const LinearArgs &a, hipStream_t s);
-// fbq_linear_group and fbq_linear_group_mix up to the mixing that mix_in_kernel leaves to launches of its own (mix: null or n entries)
-fbq_status linear_group(const fbq_layer_call *calls, const fbq_mix *mix, int n, int M, hipStream_t s);
 fbq_status hip_status(hipError_t e);
 
 // Largest hand-over scratch any call of up to kDecodeMaxM tokens needs (r = kMaxRank): 16 K slices and their

@@ -1,6 +1,6 @@
 // The element-wise glue of a decoder layer: averaging a layer's result with another tensor, silu(gate) * up.  Launches of
 // their own cost about 2.5 us each between launches that stream weights for 4 to 12; the averaging rides on the store of
-// the decode kernels where it can (see mix_in_kernel), the gate is one launch instead of two.  Step of four 7B-shaped decoder
+// the decode kernels where they have an instance for it, the gate is one launch instead of two.  Step of four 7B-shaped decoder
 // layers, r = 64, us: INT4, one sequence, 182 with eight launches a layer and 160 with five; INT3, eight sequences, 270 and 249.
 #include <hip/hip_fp16.h>
 
@@ -46,31 +46,19 @@ __global__ __launch_bounds__(256) void fbq_silu_mul_kernel(const half_t *__restr
     }
 }
 
-}  // namespace fbq
-
-using namespace fbq;
-
-extern "C" fbq_status fbq_linear_group_mix(const fbq_layer_call *calls, const fbq_mix *mix, int n, int M, fbq_stream stream)
+hipError_t launch_mix(const LinearArgs &a, hipStream_t stream)
 {
-    if (!mix) return FBQ_ERR_NULL;
-    hipStream_t s = (hipStream_t)stream;
-    const fbq_status st = linear_group(calls, mix, n, M, s);
-    if (st != FBQ_OK) return st;
-    for (int i = 0; i < n; ++i) {
-        if (!mix[i].out || mix_in_kernel(M, calls[i].desc.N)) continue;
-        const size_t count = (size_t)M * calls[i].desc.N;
-        hipLaunchKernelGGL(fbq_mix_kernel, dim3((unsigned)((count + 2047) / 2048)), dim3(256), 0, s, (const half_t *)mix[i].with, (const half_t *)calls[i].y,
-                           (half_t *)mix[i].out, count);
-    }
-    return hip_status(hipSuccess);
+    const size_t count = (size_t)a.M * a.N;
+    hipLaunchKernelGGL(fbq_mix_kernel, dim3((unsigned)((count + 2047) / 2048)), dim3(256), 0, stream, (const half_t *)a.mix_with, (const half_t *)a.y,
+                       (half_t *)a.mix_out, count);
+    return hipGetLastError();
 }
 
-extern "C" fbq_status fbq_silu_mul(const void *gate, const void *up, void *out, size_t count, fbq_stream stream)
+hipError_t launch_silu_mul(const void *gate, const void *up, void *out, size_t count, hipStream_t stream)
 {
-    if (!gate || !up || !out) return FBQ_ERR_NULL;
-    if (count < 1) return FBQ_ERR_SHAPE;
-    if (((uintptr_t)gate | (uintptr_t)up | (uintptr_t)out) & 15u) return FBQ_ERR_ALIGN;
-    hipLaunchKernelGGL(fbq_silu_mul_kernel, dim3((unsigned)((count + 2047) / 2048)), dim3(256), 0, (hipStream_t)stream, (const half_t *)gate,
+    hipLaunchKernelGGL(fbq_silu_mul_kernel, dim3((unsigned)((count + 2047) / 2048)), dim3(256), 0, stream, (const half_t *)gate,
                        (const half_t *)up, (half_t *)out, count);
-    return hip_status(hipSuccess);
+    return hipGetLastError();
 }
+
+}  // namespace fbq

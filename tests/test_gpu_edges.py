@@ -144,7 +144,8 @@ def test_train_step_tile_edges(bits, N, K, r):
 
 @pytest.mark.parametrize("bits", [4, 3])
 @pytest.mark.parametrize("M", [1, 2, 5, 16, 40, 70])
-@pytest.mark.parametrize("N,K,r", [(1, 128, 0), (33, 384, 8), (130, 256, 16), (4098, 128, 0), (2050, 8320, 24)])
+@pytest.mark.parametrize("N,K,r", [(1, 128, 0), (33, 384, 8), (130, 256, 16), (4098, 128, 0), (2050, 8320, 24),
+                                   (130, 640, 136), (2050, 8192, 200), (514, 16384, 256)])   # two taps per lane; INT4: no instance that averages
 def test_group_mix_equals_result_then_average(bits, M, N, K, r):
     """Every way the averages are written (GEMV trips even and odd, matrix-core tiles, a launch of its own): y bit for bit that of
     the plain call, the average bit for bit the element-wise one."""

@@ -1,0 +1,48 @@
+"""What the launchers take for granted about the compiled kernels, read from the metadata of the code objects in
+libfbq.so (built here from csrc/): registers, spills and LDS of every instance."""
+import re
+import struct
+import subprocess
+
+import msgpack
+import pytest
+
+import paper_2501_16385_amd as fbq
+
+
+def _kernels():
+    """demangled name -> metadata of every kernel: the AMDGPU notes of the ELF images inside the library."""
+    data, found, pos = open(fbq.lib_path(), "rb").read(), {}, 0
+    while (i := data.find(b"\x7fELF", pos)) >= 0:
+        pos = i + 4
+        if struct.unpack_from("<H", data, i + 18)[0] != 224:        # EM_AMDGPU
+            continue
+        table, = struct.unpack_from("<Q", data, i + 40)
+        entry, count = struct.unpack_from("<HH", data, i + 58)
+        for s in range(count):
+            kind, = struct.unpack_from("<I", data, i + table + s * entry + 4)
+            offset, size = struct.unpack_from("<QQ", data, i + table + s * entry + 24)
+            p, end = i + offset, i + offset + size
+            while kind == 7 and p < end:                            # SHT_NOTE
+                name, desc, _ = struct.unpack_from("<III", data, p)
+                d = p + 12 + (name + 3 & ~3)
+                if data[p + 12:p + 12 + name] == b"AMDGPU\0":
+                    found.update((k[".name"], k) for k in msgpack.unpackb(data[d:d + desc])["amdhsa.kernels"])
+                p = d + (desc + 3 & ~3)
+    names = subprocess.run(["c++filt"], input="\n".join(found), text=True, capture_output=True, check=True).stdout.split("\n")
+    return {re.sub(r"^void |\(.*", "", n): k for n, k in zip(names, found.values())}
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    return _kernels()
+
+
+def test_two_blocks_of_the_gemv_fit_a_compute_unit(kernels):
+    """launch_gemv_decode hands out two blocks of four waves per CU with fixed tile lists and counts on all of them being
+    resident: two waves per SIMD, i.e. at most 256 of its 512 registers each, and half of the 160 KiB of LDS."""
+    gemv = {n: k for n, k in kernels.items() if "fbq_gemv_kernel<" in n}
+    assert len(gemv) >= 54                                          # 2 bit widths x 9 shapes x 3 rank classes
+    for n, k in gemv.items():
+        assert k[".vgpr_count"] <= 256 and k[".vgpr_spill_count"] == 0, n
+        assert k[".group_segment_fixed_size"] <= 80 * 1024, n
