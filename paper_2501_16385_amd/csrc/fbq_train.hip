@@ -536,41 +536,61 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     store(nw, mw);
 }
 
-// C = fp16(beta x sum of the splits' partial tiles), splits in index order, both triangles.  Block: a 64 x 64 piece of a tile.
+// C = fp16(beta x sum of the splits' partial tiles), splits in index order, both triangles.  Block: a 32 x 32 piece of a tile,
+// four values per thread; R is a multiple of 128, so a piece lies in the matrix whole or not at all.
+// Bound: the round trips over the splits, eight at a time.  (64 x 64 pieces, sixteen rows of a thread and every split one after
+// the other: the whole H of 128 features over 4096 tokens 73 us, of 1024 features 57; 17 and 28 with these pieces.)
+constexpr int kSyPiece = 32, kSyPieces = kSyTile / kSyPiece;       // pieces along a side of a tile
 __global__ __launch_bounds__(256) void fbq_syrk_sum_kernel(const SyrkArgs g)
 {
-    __shared__ uint16_t turn[64][64 + 2];
+    __shared__ uint32_t turn[kSyPiece][kSyPiece / 2 + 1];
     int ti, tj;
     syrk_tile(blockIdx.x, g.side, &ti, &tj);
-    const int pr = (blockIdx.y / 3) * 64, pc = (blockIdx.y % 3) * 64;
-    const float *part = g.part + (size_t)blockIdx.x * (kSyTile * kSyTile) + pr * kSyTile + pc;
+    const int pr = (blockIdx.y / kSyPieces) * kSyPiece, pc = (blockIdx.y % kSyPieces) * kSyPiece;
+    const int m0 = ti * kSyTile + pr, n0 = tj * kSyTile + pc;
+    if (m0 >= g.R || n0 >= g.R) return;                 // block-uniform
+    const int r = threadIdx.x >> 3, c = (threadIdx.x & 7) * 4;
+    const float *part = g.part + (size_t)blockIdx.x * (kSyTile * kSyTile) + (pr + r) * kSyTile + pc + c;
     const size_t stride = (size_t)g.tiles * (kSyTile * kSyTile);
-    const int c = threadIdx.x & 63, m0 = ti * kSyTile + pr, n0 = tj * kSyTile + pc;
-    for (int r = threadIdx.x >> 6; r < 64; r += 4) {
-        float a = 0.0f;
-        for (int s = 0; s < g.splits; ++s) a += part[s * stride + r * kSyTile + c];
-        const uint16_t v = __builtin_bit_cast(uint16_t, (half_t)(g.beta * a));
-        if (m0 + r < g.R && n0 + c < g.R) g.C[(size_t)(m0 + r) * g.ldc + n0 + c] = v;
-        turn[r][c] = v;
+    float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int s0 = 0; s0 < g.splits; s0 += 8) {          // eight splits per round trip to memory
+        float4 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = *reinterpret_cast<const float4 *>(part + (size_t)min(s0 + k, g.splits - 1) * stride);
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (s0 + k < g.splits) { a.x += v[k].x; a.y += v[k].y; a.z += v[k].z; a.w += v[k].w; }
     }
-    if (ti == tj) return;
+    // (scaled here and not in the conversions, as in the kernel above: a diagonal tile's two halves have to round alike)
+    float scaled[4] = {g.beta * a.x, g.beta * a.y, g.beta * a.z, g.beta * a.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(scaled[e]));
+    const half4_t o = half4_t{(half_t)scaled[0], (half_t)scaled[1], (half_t)scaled[2], (half_t)scaled[3]};
+    *reinterpret_cast<half4_t *>(g.C + (size_t)(m0 + r) * g.ldc + n0 + c) = o;
+    if (ti == tj) return;                               // block-uniform
+#pragma unroll
+    for (int e = 0; e < 4; ++e) reinterpret_cast<half_t *>(turn[c + e])[r] = o[e];
     __syncthreads();
-    for (int r = threadIdx.x >> 6; r < 64; r += 4)
-        if (n0 + r < g.R && m0 + c < g.R) g.C[(size_t)(n0 + r) * g.ldc + m0 + c] = turn[c][r];
+    const uint2 w = make_uint2(turn[r][c / 2], turn[r][c / 2 + 1]);
+    *reinterpret_cast<uint2 *>(g.C + (size_t)(n0 + r) * g.ldc + m0 + c) = w;
 }
 
-// Blocks that share a tile's contraction: what makes rounds x (steps + about ten steps' worth of start and end) smallest, 256
-// CUs assumed; where the partial tiles have to be written and summed, that traffic (about a third of a step per tile in flight)
-// and the launch (eight steps) count as well.
+// Blocks that share a tile's contraction: what makes the estimate in us smallest, 256 CUs assumed: rounds x (steps + 7 of
+// start and end), a step taking 0.55 and up to 0.3 more as the round fills the CUs; where the partial tiles have to be written
+// and summed, 0.3 per partial tile of a sum and 0.03 of traffic per tile in flight as well.  Fitted to H at 128 to 5120
+// features and 128 to 65536 tokens with 1 to 256 splits: where the choice itself was measured it is within 7 % of the best one.
+// Examples, us without a split / as chosen / with twice the splits: 1024 features, 4096 tokens 54 / 28 (5) / 28; 2048 features,
+// 2048 tokens 39 / 32 (2) / 40; 128 features, 4096 tokens 47 / 17 (8) / 18; 2944 features, 4096 tokens 67 (1) / 78.
 struct SyrkShape { int side, tiles, splits; };
 static SyrkShape syrk_shape(int R, int Kd, bool dot)
 {
     const int side = ceil_div(R, kSyTile), tiles = side * (side + 1) / 2, steps = Kd / 64;
     SyrkShape best{side, tiles, 1};
     double best_cost = 1e300;
-    for (int s = 1; s <= 16 && s <= steps; ++s) {
-        double cost = (double)ceil_div(tiles * s, 256) * (ceil_div(steps, s) + 10);
-        if (s > 1 && !dot) cost += 8 + tiles * s / 40.0;
+    for (int s = 1; s <= 64 && s <= steps && (s == 1 || tiles * s <= 768); ++s) {
+        const double rounds = ceil_div(tiles * s, 256), filled = tiles * s / (256.0 * rounds);
+        double cost = rounds * (ceil_div(steps, s) * (0.55 + 0.3 * filled) + 7.0);
+        if (s > 1 && !dot) cost += 0.5 + 0.3 * s + 0.03 * tiles * s;
         if (cost < best_cost * 0.98) { best_cost = cost; best.splits = s; }
     }
     return best;
@@ -589,7 +609,7 @@ static hipError_t launch_syrk(SyrkArgs g, hipStream_t stream)
     g.side = s.side; g.tiles = s.tiles; g.splits = s.splits;
     const int units = s.tiles * s.splits;
     hipLaunchKernelGGL(fbq_syrk_kernel<DOT>, dim3(ceil_div(units, kXcds) * kXcds), dim3(256), 0, stream, g);
-    if (!DOT && g.splits > 1) hipLaunchKernelGGL(fbq_syrk_sum_kernel, dim3(g.tiles, 9), dim3(256), 0, stream, g);
+    if (!DOT && g.splits > 1) hipLaunchKernelGGL(fbq_syrk_sum_kernel, dim3(g.tiles, kSyPieces * kSyPieces), dim3(256), 0, stream, g);
     return hipGetLastError();
 }
 

@@ -89,7 +89,8 @@ def test_prefill_tile_edges(bits, N, K, r, M):
 
 # ------------------------------------------------------------------ symmetric products: tiles of 192, the contraction split over blocks
 
-@pytest.mark.parametrize("K,T", [(128, 1), (256, 4100), (384, 65), (640, 193), (1152, 300), (2176, 837)])
+@pytest.mark.parametrize("K,T", [(128, 1), (256, 4100), (384, 65), (640, 193), (1152, 300), (2176, 837),
+                                 (128, 20000), (384, 5000), (1152, 1500)])     # few features: the contraction split over up to 22 blocks
 def test_gram_tile_edges(K, T):
     """fp16 of a 32-bit sum: 2^-11 / sqrt(3) relative; both triangles come from the same sums, so H is symmetric to the bit."""
     import torch
@@ -105,6 +106,30 @@ def test_gram_tile_edges(K, T):
     want = X64.T @ X64 / T
     assert np.linalg.norm(H.astype(np.float64) - want) <= 5e-4 * np.linalg.norm(want)
     assert np.array_equal(H, H.T)
+
+
+def test_gram_of_few_features_takes_no_longer_than_of_many():
+    """128 features have a sixty-fourth of the products of 1024.  Where the contraction is split over blocks, the sum of the
+    partial tiles must not take that back (read one after the other they took 73 us and 57; 18 and 28 now)."""
+    import torch
+    import paper_2501_16385_amd as fbq
+
+    def us(K, T=4096):
+        d = fbq.Desc(128, K, 8, 4)
+        X, ws = torch.randn(T, K, device="cuda").half(), torch.empty(fbq.train_workspace_bytes(d, T), dtype=torch.uint8, device="cuda")
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        times = []
+        for _ in range(7):
+            torch.cuda.synchronize()
+            e[0].record()
+            for _ in range(10):
+                fbq.gram(d, X, 1.0 / T, ws)
+            e[1].record()
+            torch.cuda.synchronize()
+            times.append(e[0].elapsed_time(e[1]) * 100)
+        return sorted(times)[3]
+
+    assert us(128) <= us(1024)
 
 
 @pytest.mark.parametrize("bits", [4, 3])
