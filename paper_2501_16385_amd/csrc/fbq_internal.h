@@ -116,6 +116,14 @@ constexpr int kPrefillColumns = 256;   // columns of a block tile of the prefill
 // Columns left over by full rounds: where the last round would leave many CUs idle, the column blocks that fill whole rounds are
 // one launch and the others a second one in tiles of their own height (4 us for the launch).  8192 -> 28672 at 2048 tokens,
 // INT4, r = 128, us: four rounds of 256-row tiles, the last half empty, 896; three rounds, and the rest as 256 tiles of 128 rows, 844.
+//
+// Short K: up to six groups a block is mostly its start and its end, and what counts is that another block works meanwhile.
+// There the low tiles have one K group, so that two (96 rows) or three (64 rows) blocks share a CU, and only these two heights
+// are used; the one whose rounds over the CUs, each its rows and 24 rows' worth of start and end, are fewer.  us with one block per
+// CU as above / like this, r = 0 where none is given: 14402 x 128 at 922 tokens, INT4, 30.1 / 21.5; 26880 x 256 at 577, r = 64,
+// 37.5 / 28.8; 20431 x 640 at 1166, r = 64, INT3, 83.9 / 65.6; 2506 x 256 at 420, INT3, 13.1 / 12.1; 6272 x 768 at 342 15.0 / 14.9;
+// from 896 on a layer with one round of blocks is faster with two K groups (5375 x 2688 at 1671 73 and, with one, 75).
+constexpr int kShortGroups = 6;
 struct PrefillCut { int tm, ksplit, columns, tail_tm; };   // columns: column blocks of the first launch; tail_tm: tile height of the second, 0: none
 
 inline PrefillCut prefill_cut(int M, int N, int K)
@@ -123,6 +131,10 @@ inline PrefillCut prefill_cut(int M, int N, int K)
     static constexpr struct { int tm, kg; double step, fixed; } kTiles[] = {
         {8, 1, 1.614, 16.2}, {6, 1, 1.241, 11.6}, {4, 2, 1.731, 9.4}, {3, 2, 1.402, 7.6}, {2, 2, 1.144, 6.0}};
     const int G = K / kGroup, columns = ceil_div(N, kPrefillColumns);
+    if (G <= kShortGroups) {
+        auto cost = [&](int tm) { return std::ceil(columns * (double)ceil_div(M, 32 * tm) / 256.0) * (32 * tm + 24); };
+        return {cost(2) <= cost(3) ? 2 : 3, 1, columns, 0};
+    }
     auto launch_us = [&](int tile, int cols, int split) {
         const auto &t = kTiles[tile];
         const int rows = ceil_div(M, 32 * t.tm);

@@ -11,7 +11,7 @@
 //
 // Fused kernel.  Four waves side by side along N, block tile (32 TM) x 256, TM = 2, 3, 4, 6 or 8; a wave owns TM x 2
 // tiles of v_mfma_f32_32x32x16_f16.  With TM of 6 or 8 that is one wave per SIMD with up to 256 accumulator registers;
-// with less the block has eight waves, two groups that split K and meet in LDS.
+// with less the block has eight waves, two groups that split K and meet in LDS (four waves and several blocks per CU where K is short).
 // K advances in steps of 64, half a quantization group, and everything a step reads comes out of LDS, copied there three
 // steps ahead by buffer_load ... lds (no registers): the activations, the packed words, and scale and zero.  With the
 // packed words loaded into registers instead - 32 rows per load, waited for by the compiler's count - the look-ahead
@@ -170,8 +170,9 @@ struct WeightRegs {
 
 // TM: 32-row tiles of a wave and of the block.  KG: groups of four waves that split K for the same tile inside one block
 // (1 or 2): the groups take consecutive ranges of K, and group 1 hands its accumulators to group 0 through LDS at the
-// end, so nothing but y is ever written.  One block per CU either way: with TM of 6 or 8 a wave has a SIMD, and its 512
-// registers, to itself; with less, two waves share one.
+// end, so nothing but y is ever written.  One block per CU: with TM of 6 or 8 a wave has a SIMD, and its 512
+// registers, to itself; with less, two waves share one - of one block with two K groups, or, where K is short (see
+// kShortGroups), of blocks with one.
 template <int BITS, int TM, int KG>
 struct GemmTile {
     static constexpr int kBM = 32 * TM;
@@ -855,6 +856,11 @@ static hipError_t launch_columns(PrefillParams p, int tm, int columns, hipStream
     p.full_slots = (columns / kXcds) * p.row_blocks * p.ksplit;
     p.rem_blocks = (columns % kXcds) * p.row_blocks * p.ksplit;
     const dim3 grid(kXcds * (p.full_slots + ceil_div(p.rem_blocks, kXcds)));
+    if (p.G <= kShortGroups) {                          // (tm is 2 or 3)
+        if (tm == 2) launch_tile<BITS, 2, 1>(p, grid, stream);
+        else launch_tile<BITS, 3, 1>(p, grid, stream);
+        return hipGetLastError();
+    }
     switch (tm) {
     case 8: launch_tile<BITS, 8, 1>(p, grid, stream); break;
     case 6: launch_tile<BITS, 6, 1>(p, grid, stream); break;

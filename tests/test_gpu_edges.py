@@ -7,6 +7,7 @@ import pytest
 import fbq_synth
 from helpers import assert_matches_oracle, framed_in_nan, make_oracle_layer
 from oracle import fbq_oracle as orc
+from prefill_cases import CUT_CASES
 
 pytestmark = pytest.mark.gpu
 
@@ -35,26 +36,26 @@ def test_quantizer_tile_edges(bits, N, K, r):
 # ------------------------------------------------------------------ prefill GEMM: tiles of 64, 96, 128, 192 and 256 rows x 256 columns, K split over blocks
 
 PREFILL_CASES = [
-    # N, K, r, M: the tile height the launcher takes is in the remark
+    # N, K, r, M (prefill_cases.py has a layer for every kind of cut; up to 768 activations the tiles have 64 or 96 rows)
     # (the per-token bar is relative to the norm of a token's outputs: a few dozen columns, so that it is no single cancelled sum)
-    (25, 128, 8, 65),           # 64 rows, one quantization group (the second K group has none)
-    (40, 256, 40, 77),          # 64; a rank that is no multiple of 16 or 64
-    (25, 2304, 24, 65),         # 64, K split over three blocks, M N odd: the summing launch's scalar form
-    (255, 4224, 200, 77),       # 64, K split over six blocks, an odd number of groups
-    (513, 1408, 256, 66),       # 64; four tiles of taps
+    (25, 128, 8, 65),           # one quantization group
+    (40, 256, 40, 77),          # a rank that is no multiple of 16 or 64
+    (25, 2304, 24, 65),         # K split over three blocks, M N odd: the summing launch's scalar form
+    (255, 4224, 200, 77),       # K split over six blocks, an odd number of groups
+    (513, 1408, 256, 66),       # four tiles of taps
     (4100, 640, 0, 300),
-    (33001, 128, 0, 65),        # 96
-    (33001, 640, 72, 96),       # 96
-    (33001, 128, 72, 97),       # 128
-    (33000, 640, 8, 128),       # 128, whole rows stored
-    (33001, 128, 16, 129),      # 192
-    (33000, 640, 40, 191),      # 192
-    (33001, 128, 40, 193),      # 256
-    (33000, 640, 64, 193),      # 256
-    # the columns past the last full round in lower tiles, a second launch (several groups per row: with a single one, millions of
+    (33001, 128, 0, 65),
+    (33001, 640, 72, 96),
+    (33001, 128, 72, 97),
+    (33000, 640, 8, 128),       # whole rows stored
+    (33001, 128, 16, 129),
+    (33000, 640, 40, 191),
+    (33001, 128, 40, 193),
+    (33000, 640, 64, 193),
+    # several row blocks of many column blocks (several groups per row: with a single one, millions of
     # outputs include small ones of rows with a scale far above the average, which the bound on single outputs is relative to)
-    (32957, 640, 24, 583),      # 256, then 128
-    (26297, 640, 8, 546),       # 192, then 64
+    (32957, 640, 24, 583),
+    (26297, 640, 8, 546),
 ]
 
 
@@ -85,6 +86,34 @@ def test_prefill_tile_edges(bits, N, K, r, M):
     fbq.linear(dev, xd, y, ws)
     torch.cuda.synchronize()
     assert np.array_equal(y.cpu().numpy(), got)
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("N,K,r,M,cut", CUT_CASES)
+def test_prefill_every_kind_of_cut(bits, N, K, r, M, cut):
+    """The bars of the test above (assert_matches_oracle's), against W_F in 64 bits from the layer's own codes on the device: these
+    layers are too large for the oracle on the host."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    from helpers import ELEMENT_SLACK, framed_layer
+    from paper_2501_16385_amd.random_layers import random_layer
+    g = torch.Generator(device="cuda")
+    g.manual_seed(48)
+    layer = framed_layer(random_layer(fbq.Desc(N, K, r, bits), g, gain=1.0))
+    x = framed_in_nan(torch.randn(M, K, device="cuda", generator=g).half())
+    y = framed_in_nan(torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda"))
+    ws = framed_in_nan(torch.full((fbq.workspace_bytes(layer.desc, M),), 0x7D, dtype=torch.uint8, device="cuda"))
+    fbq.linear(layer, x, y, ws)
+    f64 = lambda t: t.view(torch.float16).double()
+    W = ((fbq.unpack_codes(layer).view(N, K // 128, 128).double() - f64(layer.zeros)[:, :, None]) * f64(layer.scales)[:, :, None]).view(N, K)
+    want = x.double() @ W.T.contiguous()
+    if r:
+        want += (x.double() @ f64(layer.At).T.contiguous()) @ f64(layer.Bt).T.contiguous()
+    miss = (y.double() - want).abs_()
+    assert bool(torch.isfinite(miss).all())
+    per_token = miss.norm(dim=1) / want.norm(dim=1)
+    assert float(miss.norm() / want.norm()) <= 1e-3 and float(per_token.max()) <= 1e-3
+    assert float((miss - want.abs() * 2.0 ** -10 - ELEMENT_SLACK["prefill"] * want.square().mean(1, keepdim=True).sqrt()).max()) <= 0.0
 
 
 # ------------------------------------------------------------------ symmetric products: tiles of 192, the contraction split over blocks
