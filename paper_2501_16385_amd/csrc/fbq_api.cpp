@@ -182,6 +182,7 @@ fbq_status check_layer(const fbq_desc *d, int M, const void *x, const void *qwei
     a->x = (const uint16_t *)x;
     a->y = (uint16_t *)y;
     a->workspace = workspace;
+    a->workspace_need = need;
     a->M = M; a->N = d->N; a->K = d->K; a->r = d->r; a->bits = d->bits;
     a->mix_with = nullptr; a->mix_out = nullptr;
     return FBQ_OK;
@@ -279,12 +280,11 @@ static fbq_status linear_group(const fbq_layer_call *calls, const fbq_mix *mix, 
     // Layers that share a launch carry the same launch tag: two of them writing their hand-over words into the same
     // memory would accept each other's t.  Workspaces must not overlap.
     for (int i = 0; i < n; ++i) {
-        const size_t ni = fbq_workspace_bytes(&calls[i].desc, M);
-        if (!ni) continue;
-        const uintptr_t ai = (uintptr_t)calls[i].workspace;
-        for (int j = i + 1; j < n; ++j) {
-            const size_t nj = fbq_workspace_bytes(&calls[j].desc, M);
-            const uintptr_t aj = (uintptr_t)calls[j].workspace;
+        const size_t ni = args[i].workspace_need;
+        const uintptr_t ai = (uintptr_t)args[i].workspace;
+        for (int j = 0; j < i && ni; ++j) {
+            const size_t nj = args[j].workspace_need;
+            const uintptr_t aj = (uintptr_t)args[j].workspace;
             if (nj && ai < aj + nj && aj < ai + ni) return FBQ_ERR_WORKSPACE;
         }
     }

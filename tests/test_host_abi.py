@@ -94,6 +94,36 @@ def test_group_rejects_overlapping_workspaces_and_the_test_hook_clamps():
     assert lib.fbq_test_set_spin_limit(default) == default
 
 
+def test_group_check_takes_time_in_proportion_to_the_layers():
+    """Above 64 tokens a workspace size costs a search over tile heights.  The check for overlaps needs each layer's size once,
+    not once per pair of layers: 64 layers, refused for their last pair, in the time of a few hundred look-ups, not of 4000."""
+    import time
+    lib = fbq.load()
+    d, M, n, ok = fbq.Desc(4096, 4096, 8, 4), 300, 64, 0x10000
+    need = fbq.workspace_bytes(d, M)
+    step = (need + 255) // 256 * 256
+    ws = [0x10000000 + i * step for i in range(n - 1)]
+    arr = (fbq.fbq._CLayerCall * n)(*[fbq.fbq._CLayerCall(d.c(), ok, ok, ok, ok, ok, ok, ok, w, need) for w in ws + ws[-1:]])
+    c = d.c()
+
+    def best(fn):
+        times = []
+        for _ in range(9):
+            t = time.perf_counter()
+            fn()
+            times.append(time.perf_counter() - t)
+        return min(times)
+
+    def look_up():
+        for _ in range(400):
+            lib.fbq_workspace_bytes(ctypes.byref(c), M)
+
+    def group():
+        assert lib.fbq_linear_group(arr, n, M, None) == 5
+
+    assert best(group) < best(look_up)
+
+
 def test_training_argument_errors_without_launch():
     lib = fbq.load()
     d = fbq.Desc(256, 512, 16, 4)
