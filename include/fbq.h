@@ -190,8 +190,8 @@ typedef struct {
  */
 fbq_status fbq_linear_group(const fbq_layer_call *calls, int n, int M, fbq_stream stream);
 
-/* A second tensor to average a layer's result with: out[m,n] = (with[m,n] + y[m,n]) / 2, fp16, rounded once from the
- * rounded y.  with, out device [M, N] fp16; out NULL: none. */
+/* A second tensor to average a layer's result with: out[m,n] = y[m,n] - (y[m,n] - with[m,n]) / 2 in fp32 from the rounded y,
+ * rounded to fp16 (an infinite y therefore gives a NaN, as it does in a linear interpolation).  with, out device [M, N] fp16; out NULL: none. */
 typedef struct {
     const void *with;
     void *out;
@@ -202,8 +202,10 @@ typedef struct {
  * the decoder loop): y is written as fbq_linear_group writes it, and mix[i].out with it: by the same launch up to 16
  * tokens where the kernel has an instance that does both (not for an odd N at one or two tokens, an odd number of scales at
  * 3..16, or INT4 with rank above 128 and K in 6145..8192, 12289..16384 or 24577..32768 at one or two), by a launch of its own otherwise.
- *   mix host array of n entries (read during the call only); an out may be no layer's x, y or `with`.
- * Errors: those of fbq_linear_group; FBQ_ERR_NULL (out without with), FBQ_ERR_ALIGN, before ANY launch.
+ *   mix host array of n entries (read during the call only).  An out may not overlap any layer's x, y or `with` of the
+ *   call or another out, and a `with` may not overlap any layer's y.
+ * Errors: those of fbq_linear_group; FBQ_ERR_NULL (no mix, out without with), FBQ_ERR_ALIGN, FBQ_ERR_UNSUPPORTED (tensors that
+ * overlap as above), before ANY launch.
  */
 fbq_status fbq_linear_group_mix(const fbq_layer_call *calls, const fbq_mix *mix, int n, int M, fbq_stream stream);
 

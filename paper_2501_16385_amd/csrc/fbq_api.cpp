@@ -259,6 +259,29 @@ extern "C" fbq_status fbq_linear(const fbq_desc *d, int M, const void *x, const 
     return hip_status(launch_one(a, s));
 }
 
+static bool overlap(const void *a, size_t na, const void *b, size_t nb)
+{
+    return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
+// What an average is written to may be nothing that a layer of the call reads or writes, and what it is taken with may be no
+// layer's result: within a launch, and between the launches of a call, nothing orders the one against the other.
+static bool mix_tensors_overlap(const LinearArgs *args, int n)
+{
+    for (int i = 0; i < n; ++i) {
+        if (!args[i].mix_out) continue;
+        const size_t ni = (size_t)args[i].M * args[i].N * sizeof(uint16_t);
+        for (int j = 0; j < n; ++j) {
+            const LinearArgs &b = args[j];
+            const size_t nx = (size_t)b.M * b.K * sizeof(uint16_t), ny = (size_t)b.M * b.N * sizeof(uint16_t);
+            if (overlap(args[i].mix_out, ni, b.x, nx) || overlap(args[i].mix_out, ni, b.y, ny) || overlap(args[i].mix_with, ni, b.y, ny)) return true;
+            if (b.mix_out && overlap(args[i].mix_out, ni, b.mix_with, ny)) return true;
+            if (b.mix_out && j > i && overlap(args[i].mix_out, ni, b.mix_out, ny)) return true;
+        }
+    }
+    return false;
+}
+
 // mix: null or n entries
 static fbq_status linear_group(const fbq_layer_call *calls, const fbq_mix *mix, int n, int M, hipStream_t s)
 {
@@ -288,6 +311,7 @@ static fbq_status linear_group(const fbq_layer_call *calls, const fbq_mix *mix, 
             if (nj && ai < aj + nj && aj < ai + ni) return FBQ_ERR_WORKSPACE;
         }
     }
+    if (mix && mix_tensors_overlap(args, n)) return FBQ_ERR_UNSUPPORTED;
     hipError_t e = hipSuccess;
     if (M > kDecodeMaxM) {
         for (int i = 0; i < n && e == hipSuccess; ++i) {

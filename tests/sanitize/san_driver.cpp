@@ -105,6 +105,16 @@ int main()
     fbq_layer_call calls[2];
     for (auto &c : calls) c = fbq_layer_call{d, ok, ok, ok, ok, ok, ok, ok, (void *)0x20000, fbq_workspace_bytes(&d, 1)};
     REQUIRE(fbq_linear_group(calls, 2, 1, nullptr) == FBQ_ERR_WORKSPACE);     // the same workspace twice
+    calls[1].workspace = (void *)0x40000; calls[1].y = (void *)0x8000;
+    fbq_mix mix[2] = {{nullptr, nullptr}, {(void *)0x60000, ok}};
+    REQUIRE(fbq_linear_group_mix(calls, nullptr, 2, 1, nullptr) == FBQ_ERR_NULL);
+    REQUIRE(fbq_linear_group_mix(calls, mix, 2, 1, nullptr) == FBQ_ERR_UNSUPPORTED);   // the average over the layers' x
+    mix[1].out = odd;
+    REQUIRE(fbq_linear_group_mix(calls, mix, 2, 1, nullptr) == FBQ_ERR_ALIGN);
+    mix[1].with = nullptr;
+    REQUIRE(fbq_linear_group_mix(calls, mix, 2, 1, nullptr) == FBQ_ERR_NULL);
+    REQUIRE(fbq_silu_mul(ok, ok, nullptr, 8, nullptr) == FBQ_ERR_NULL && fbq_silu_mul(ok, ok, ok, 0, nullptr) == FBQ_ERR_SHAPE);
+    REQUIRE(fbq_silu_mul(ok, odd, ok, 8, nullptr) == FBQ_ERR_ALIGN);
     REQUIRE(strcmp(fbq_status_string(FBQ_OK), "ok") == 0);
     printf("sanitize ok\n");
     return 0;

@@ -94,6 +94,44 @@ def test_group_rejects_overlapping_workspaces_and_the_test_hook_clamps():
     assert lib.fbq_test_set_spin_limit(default) == default
 
 
+def test_averages_and_gate_argument_errors_without_launch():
+    lib = fbq.load()
+    M, d, d2 = 2, fbq.Desc(64, 256, 0, 4), fbq.Desc(32, 256, 0, 4)
+    ok, x, y, y2, w, out = 0x10000, 0x20000, 0x30000, 0x40000, 0x50000, 0x60000
+    layer = lambda desc, x, y: fbq.fbq._CLayerCall(desc.c(), x, ok, ok, ok, None, None, y, None, 0)
+
+    def call(mix, calls=None, M=M, n=2):
+        arr = (fbq.fbq._CLayerCall * 2)(*(calls or [layer(d, x, y), layer(d2, x, y2)]))
+        return lib.fbq_linear_group_mix(arr, None if mix is None else (fbq.fbq._CMix * 2)(*[fbq.fbq._CMix(*m) for m in mix]), n, M, None)
+
+    none = (None, None)
+    for m in (1, 2, 9, 40, 100):                                 # every kind of kernel behind the call
+        if m > 64:
+            calls = [fbq.fbq._CLayerCall(dd.c(), x, ok, ok, ok, None, None, yy, wsp, 1 << 28) for dd, yy, wsp in ((d, y, 0x100000000), (d2, y2, 0x200000000))]
+        else:
+            calls = None
+        go = lambda mix: call(mix, calls, m)
+        assert go(None) == 1                                     # no mix at all
+        assert go([none, (None, out)]) == 1                      # out without with
+        assert go([none, (w + 2, out)]) == 4 and go([(w, out + 2), none]) == 4
+        size = m * 64 * 2                                        # of the first layer's out, with and y
+        assert go([(w, x), none]) == 3                           # out over the activations
+        assert go([(w, x + m * 256 * 2 - 16), none]) == 3        # ... over their last sixteen bytes
+        assert go([(w, y), none]) == 3                           # out over the layer's own result
+        assert go([(w, y2), none]) == 3                          # ... over another layer's
+        assert go([(w, y2 - size + 16), none]) == 3
+        assert go([(w, w), none]) == 3                           # in place
+        assert go([(w, out), (out, 0x70000)]) == 3               # a with that another average writes
+        assert go([(w, out), (w, out)]) == 3                     # two averages in one place
+        assert go([(y, out), none]) == 3                         # a with that is the layer's own result
+        assert go([none, (y + 16, out)]) == 3                    # ... or another layer's
+    assert call([none, none], n=0) == 2 and call([none, none], M=0) == 2 and call([none, none], n=65) == 2
+    silu = lambda a, b, c, n: lib.fbq_silu_mul(a, b, c, n, None)
+    assert silu(None, ok, ok, 8) == 1 and silu(ok, None, ok, 8) == 1 and silu(ok, ok, None, 8) == 1
+    assert silu(ok, ok, ok, 0) == 2
+    assert silu(ok + 2, ok, ok, 8) == 4 and silu(ok, ok + 8, ok, 8) == 4 and silu(ok, ok, ok + 4, 8) == 4
+
+
 def test_group_check_takes_time_in_proportion_to_the_layers():
     """Above 64 tokens a workspace size costs a search over tile heights.  The check for overlaps needs each layer's size once,
     not once per pair of layers: 64 layers, refused for their last pair, in the time of a few hundred look-ups, not of 4000."""
