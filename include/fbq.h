@@ -294,7 +294,7 @@ fbq_status fbq_measure_read_stream(const void *buf, size_t bytes, fbq_stream str
  *           the trace form and the printed gradient are those of the squared norm), or NULL:
  *           the gradients need only products with r rows (H is symmetric, so Delta_F H At^T =
  *           Delta_F (At H)^T), the loss alone needs Delta_F^T Delta_F (N K^2 flop) and is skipped then.
- *   lr = 0 evaluates without moving the masters.  Delta_F, H and their products enter the matrix
+ *   lr = 0 evaluates without moving the masters; a call that returns an error has moved neither.  Delta_F, H and their products enter the matrix
  *   cores as fp16 with fp32 accumulation: gradients and loss carry a relative error of a few 1e-4.
  *   Nothing is allocated; everything is enqueued on `stream`.  Needs r >= 1.
  * Errors: FBQ_ERR_NULL, _SHAPE, _UNSUPPORTED, _ALIGN, _WORKSPACE before any launch; FBQ_ERR_HIP.

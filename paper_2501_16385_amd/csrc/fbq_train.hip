@@ -13,7 +13,8 @@
 //   V^T        <- At H                [r,K]    } operand [Q; At], K split
 //   dL/dBt     <- -2 Delta_F V        [N,r]                              (GEMM, K split)
 //   L          <- sum (Delta_F^T Delta_F) o H  only if the caller asks   (symmetric product, N K^2 flop, + reduction)
-//   masters    <- masters - lr gradient                                  (with the gradients' split sums)
+//   masters    <- masters - lr gradient                                  (both in the last launch, with the split sums of dL/dBt:
+//                                                                         a call that fails on the way moves neither)
 //
 // with Sigma[n,k] = sum_j Bt[n,j] At[j,k] in the device layouts At [r,K], Bt [N,r].  The gradients need only products with
 // r rows or columns (8 N K r + 4 r K^2 flop) because H is symmetric: Delta_F H At^T = Delta_F (At H)^T.  The loss is the one
@@ -51,7 +52,6 @@ struct GemmArgs {
     int lda, ldb;        // elements
     // store epilogue (either may be absent)
     float *C32; int ldc32; float alpha; int c32_rows;   // C32[m,n] = alpha acc for rows m < c32_rows
-    float *master; float lr;                            // with C32: master[m,n] -= lr C32[m,n] (gradient descent; laid out like C32)
     uint16_t *C16; int ldc16; float beta; int c16_row0; // C16[m - c16_row0, n] = fp16(beta acc) for rows m >= c16_row0
     // K split over `splits` blocks per tile (few tiles, long K): raw sums go to part [splits][Mr][Nr]
     // and fbq_sum_splits_kernel applies the store epilogue
@@ -60,12 +60,7 @@ struct GemmArgs {
 
 __device__ __forceinline__ void store_result(const GemmArgs &g, int m, int n, float a)
 {
-    if (g.C32 && m < g.c32_rows) {
-        const size_t i = (size_t)m * g.ldc32 + n;
-        const float v = g.alpha * a;
-        g.C32[i] = v;
-        if (g.master) g.master[i] = g.master[i] - g.lr * v;   // masters <- masters - lr gradient (Alg. 1, the update line)
-    }
+    if (g.C32 && m < g.c32_rows) g.C32[(size_t)m * g.ldc32 + n] = g.alpha * a;
     if (g.C16 && m >= g.c16_row0) g.C16[(size_t)(m - g.c16_row0) * g.ldc16 + n] = __builtin_bit_cast(uint16_t, (half_t)(g.beta * a));
 }
 
@@ -178,12 +173,33 @@ __device__ void sum_loss(const LossArgs &l)
     if (threadIdx.x == 0) *l.out = (float)(s[0] * (double)l.scale);
 }
 
-// The store epilogue over the sum of the K splits' partial results, splits in index order; four results per thread (Nr is a
-// multiple of 4).  With loss.part the last block adds up the loss instead.
-__global__ __launch_bounds__(256) void fbq_sum_splits_kernel(GemmArgs g, LossArgs loss)
+// What the last launch of a step does besides its split sums.
+struct LastArgs {
+    LossArgs loss;                                      // loss.part null: none
+    float *At32, *Bt32;                                 // masters <- masters - lr gradient (Alg. 1, the update line); null: not this launch
+    const float *gAt, *gBt;
+    float lr;
+    unsigned sum_blocks, a_blocks, b_blocks;            // blocks that add up splits - and move Bt32 as they go -, that move At32, and, without splits, Bt32
+    size_t nA, nB;
+};
+__device__ __forceinline__ void descend(float *__restrict__ master, const float *__restrict__ grad, float lr, size_t i, size_t n)   // n a multiple of 4
 {
-    if (loss.part && blockIdx.x == gridDim.x - 1) {
-        sum_loss(loss);
+    if (i >= n) return;
+    const float4 v = *reinterpret_cast<const float4 *>(grad + i);
+    float4 m = *reinterpret_cast<const float4 *>(master + i);
+    m.x -= lr * v.x; m.y -= lr * v.y; m.z -= lr * v.z; m.w -= lr * v.w;
+    *reinterpret_cast<float4 *>(master + i) = m;
+}
+
+// The store epilogue over the sum of the K splits' partial results, splits in index order; four results per thread (Nr is a
+// multiple of 4).
+__global__ __launch_bounds__(256) void fbq_sum_splits_kernel(GemmArgs g, LastArgs last)
+{
+    if (blockIdx.x >= last.sum_blocks) {                // block-uniform
+        const unsigned b = blockIdx.x - last.sum_blocks;
+        if (b < last.a_blocks) descend(last.At32, last.gAt, last.lr, ((size_t)b * 256 + threadIdx.x) * 4, last.nA);
+        else if (b < last.a_blocks + last.b_blocks) descend(last.Bt32, last.gBt, last.lr, ((size_t)(b - last.a_blocks) * 256 + threadIdx.x) * 4, last.nB);
+        else sum_loss(last.loss);
         return;
     }
     const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4, count = (size_t)g.Mr * g.Nr;
@@ -202,6 +218,12 @@ __global__ __launch_bounds__(256) void fbq_sum_splits_kernel(GemmArgs g, LossArg
     store_result(g, m, n + 1, a.y);
     store_result(g, m, n + 2, a.z);
     store_result(g, m, n + 3, a.w);
+    if (last.Bt32) {                                    // (g.C32 is dL/dBt, laid out like the master; the thread has just written these four)
+        const size_t at = (size_t)m * g.ldc32 + n;
+        float4 b = *reinterpret_cast<const float4 *>(last.Bt32 + at);
+        b.x -= last.lr * (g.alpha * a.x); b.y -= last.lr * (g.alpha * a.y); b.z -= last.lr * (g.alpha * a.z); b.w -= last.lr * (g.alpha * a.w);
+        *reinterpret_cast<float4 *>(last.Bt32 + at) = b;
+    }
 }
 
 // Tile shapes: 64 rows or columns where an operand has no more, and 64 of the other one, so that there are as many tiles, as few
@@ -244,7 +266,8 @@ static void launch_gemm_tile(const GemmArgs &g, dim3 grid, hipStream_t stream)
     hipLaunchKernelGGL((fbq_gemm_nt_kernel<WM, WN>), grid, dim3(256), 0, stream, g);
 }
 
-static hipError_t launch_gemm(GemmArgs g, float *split_scratch, hipStream_t stream, const LossArgs &loss = LossArgs{})
+// last: the launch that ends a step, or null
+static hipError_t launch_gemm(GemmArgs g, float *split_scratch, hipStream_t stream, const LastArgs *last = nullptr)
 {
     g.splits = splits_for(g.Mr, g.Nr, g.Kd);
     g.part = split_scratch;
@@ -255,9 +278,19 @@ static hipError_t launch_gemm(GemmArgs g, float *split_scratch, hipStream_t stre
     else if (t.wm == 1) launch_gemm_tile<1, 2>(g, grid, stream);
     else if (t.wn == 1) launch_gemm_tile<2, 1>(g, grid, stream);
     else launch_gemm_tile<2, 2>(g, grid, stream);
-    const unsigned sums = g.splits > 1 ? (unsigned)(((size_t)g.Mr * g.Nr / 4 + 255) / 256) : 0u;   // Nr is a multiple of 8 (r or K)
-    if (sums + (loss.part ? 1u : 0u) > 0)
-        hipLaunchKernelGGL(fbq_sum_splits_kernel, dim3(sums + (loss.part ? 1u : 0u)), dim3(256), 0, stream, g, loss);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const auto blocks_of = [](size_t n) { return (unsigned)((n / 4 + 255) / 256); };
+    LastArgs l{};
+    if (last) l = *last;
+    l.sum_blocks = g.splits > 1 ? blocks_of((size_t)g.Mr * g.Nr) : 0u;   // Nr is a multiple of 8 (r or K)
+    if (last) {
+        l.a_blocks = blocks_of(l.nA);
+        l.b_blocks = g.splits > 1 ? 0u : blocks_of(l.nB);
+    }
+    const unsigned blocks = l.sum_blocks + l.a_blocks + l.b_blocks + (l.loss.part ? 1u : 0u);
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(fbq_sum_splits_kernel, dim3(blocks), dim3(256), 0, stream, g, l);
     return hipGetLastError();
 }
 
@@ -694,9 +727,11 @@ hipError_t launch_train_step(const TrainArgs &a, hipStream_t stream)
     const size_t casts = (size_t)r * K + (size_t)N * r + (size_t)r * Np;
     hipLaunchKernelGGL(fbq_cast_masters_kernel, dim3((unsigned)((casts + 255) / 256)), dim3(256), 0, stream, a.At32, a.Bt32, a.At16,
                        a.Bt16, S16 + (size_t)r * K, Bc, N, K, r, Np);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     // Q(W - Sigma16), written in the inference layout, and Delta_F = (W - Sigma16) - Q(W - Sigma16), times 256,
     // in both orientations
-    hipError_t e = launch_quantize(a.d, a.W, a.At16, a.Bt16, a.qw, a.scales, a.zeros, stream, D16, Dt16, Np, kDeltaGain);
+    e = launch_quantize(a.d, a.W, a.At16, a.Bt16, a.qw, a.scales, a.zeros, stream, D16, Dt16, Np, kDeltaGain);
     if (e != hipSuccess) return e;
     // Q = Bt^T Delta_F (times 256), the upper half of the stacked operand
     {
@@ -708,25 +743,24 @@ hipError_t launch_train_step(const TrainArgs &a, hipStream_t stream)
     {
         GemmArgs g = gemm_args(S16, 2 * r, K, a.H16, K, K, K);
         g.C32 = a.gAt; g.ldc32 = K; g.alpha = -2.0f / (kDeltaGain * a.h_scale); g.c32_rows = r;
-        g.master = a.At32; g.lr = a.lr;
         g.C16 = Vt16; g.ldc16 = K; g.beta = kVGain; g.c16_row0 = r;
         if ((e = launch_gemm(g, scratch, stream)) != hipSuccess) return e;
     }
     // L = sum (Delta_F^T Delta_F) o H: the only contraction of this size, and only on request
-    LossArgs loss{};
+    LastArgs last{};
     if (a.loss) {
         SyrkArgs g{};
         g.A = Dt16; g.R = K; g.ld = Np; g.Kd = Np;
         g.H = a.H16; g.dot = dot;
         if ((e = launch_syrk<true>(g, stream)) != hipSuccess) return e;
-        loss.part = dot; loss.n = (int)syrk_units(syrk_shape(K, Np, true));
-        loss.scale = 1.0f / (kDeltaGain * kDeltaGain * a.h_scale); loss.out = a.loss;
+        last.loss = {dot, (int)syrk_units(syrk_shape(K, Np, true)), 1.0f / (kDeltaGain * kDeltaGain * a.h_scale), a.loss};
     }
-    // dL/dBt = -2 Delta_F H At^T = -2 Delta_F V; its summing launch adds up the loss as well
+    // dL/dBt = -2 Delta_F H At^T = -2 Delta_F V; its summing launch moves the masters and adds up the loss as well
     GemmArgs g = gemm_args(D16, N, K, Vt16, r, K, K);
     g.C32 = a.gBt; g.ldc32 = r; g.alpha = -2.0f / (kDeltaGain * kVGain * a.h_scale);
-    g.master = a.Bt32; g.lr = a.lr;
-    return launch_gemm(g, scratch, stream, loss);
+    last.At32 = a.At32; last.Bt32 = a.Bt32; last.gAt = a.gAt; last.gBt = a.gBt; last.lr = a.lr;
+    last.nA = (size_t)r * K; last.nB = (size_t)N * r;
+    return launch_gemm(g, scratch, stream, &last);
 }
 
 }  // namespace fbq

@@ -10,9 +10,9 @@ import pytest
 import paper_2501_16385_amd as fbq
 
 
-def _kernels():
-    """demangled name -> metadata of every kernel: the AMDGPU notes of the ELF images inside the library."""
-    data, found, pos = open(fbq.lib_path(), "rb").read(), {}, 0
+def code_objects():
+    """The metadata of every kernel: the AMDGPU notes of the ELF images inside the library."""
+    data, found, pos = open(fbq.lib_path(), "rb").read(), [], 0
     while (i := data.find(b"\x7fELF", pos)) >= 0:
         pos = i + 4
         if struct.unpack_from("<H", data, i + 18)[0] != 224:        # EM_AMDGPU
@@ -27,15 +27,16 @@ def _kernels():
                 name, desc, _ = struct.unpack_from("<III", data, p)
                 d = p + 12 + (name + 3 & ~3)
                 if data[p + 12:p + 12 + name] == b"AMDGPU\0":
-                    found.update((k[".name"], k) for k in msgpack.unpackb(data[d:d + desc])["amdhsa.kernels"])
+                    found += msgpack.unpackb(data[d:d + desc])["amdhsa.kernels"]
                 p = d + (desc + 3 & ~3)
-    names = subprocess.run(["c++filt"], input="\n".join(found), text=True, capture_output=True, check=True).stdout.split("\n")
-    return {re.sub(r"^void |\(.*", "", n): k for n, k in zip(names, found.values())}
+    return found
 
 
 @pytest.fixture(scope="module")
 def kernels():
-    return _kernels()
+    found = code_objects()
+    names = subprocess.run(["c++filt"], input="\n".join(k[".name"] for k in found), text=True, capture_output=True, check=True).stdout.split("\n")
+    return {re.sub(r"^void |\(.*", "", n): k for n, k in zip(names, found)}
 
 
 def test_two_blocks_of_the_gemv_fit_a_compute_unit(kernels):

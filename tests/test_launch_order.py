@@ -1,0 +1,73 @@
+"""What a call leaves behind when one of its launches fails, on the CPU: the process's kernel launches go to a recorder
+(tests/host/launch_recorder.cpp) that lets the n-th one fail, and nothing runs."""
+import ctypes
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+CHILD = r"""
+import ctypes, json, sys
+sys.path[:0] = [sys.argv[1], sys.argv[1] + "/tests"]
+import paper_2501_16385_amd as fbq
+from test_kernel_resources import code_objects
+lib = fbq.load()
+sizes = {k[".name"]: [a[".size"] for a in k[".args"] if not a[".value_kind"].startswith("hidden")] for k in code_objects()}
+launched, fail_at = [], [0]
+
+@ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_char_p, ctypes.POINTER(ctypes.c_void_p))
+def on_launch(name, args):
+    name = name.decode()
+    launched.append((name, [ctypes.string_at(args[i], n) for i, n in enumerate(sizes[name])]))
+    return len(launched) == fail_at[0]
+
+ctypes.CDLL(None).recorder_set_callback(on_launch)
+AT, BT = 0x7A1100000000, 0x7B2200000000          # addresses of the masters: never dereferenced, looked for in the arguments
+out = []
+for N, K, r, loss in [(700, 1152, 64, 1), (700, 1152, 64, 0), (128, 128, 8, 1), (40000, 256, 256, 0), (40000, 256, 256, 1)]:
+    d = fbq.Desc(N, K, r, 4)
+    p = lambda i: 0x100000000 * (i + 1)
+    def step():
+        launched.clear()
+        return lib.fbq_train_step(ctypes.byref(d.c()), p(0), p(1), 1.0, AT, BT, 0.1, *(p(i) for i in range(2, 9)), p(9) if loss else None,
+                                  p(10), fbq.train_workspace_bytes(d, 1), None)
+    fail_at[0] = 0
+    assert step() == 0
+    whole = list(launched)
+    for n in range(1, len(whole) + 1):
+        fail_at[0] = n
+        assert step() == 6, "a failed launch is reported"
+        assert len(launched) == n, "nothing is launched behind a failed launch"
+    has = lambda args, v: any(v.to_bytes(8, "little") in a for a in args)
+    out.append([[name, has(args, AT), has(args, BT)] for name, args in whole])
+print("RESULT " + json.dumps(out))
+"""
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    if shutil.which("g++") is None or not os.path.exists(os.path.join(ROCM, "include", "hip", "hip_runtime.h")):
+        pytest.skip("needs g++ and the HIP runtime's headers")
+    so = str(tmp_path_factory.mktemp("recorder") / "recorder.so")
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
+                    os.path.join(ROOT, "tests", "host", "launch_recorder.cpp"), "-o", so, "-ldl"], check=True)
+    return so
+
+
+def test_train_step_moves_both_masters_in_its_last_launch(recorder):
+    """A step that reports an error has moved neither master, so it can be made again.  The first launch reads both (it casts
+    them to fp16); of the others only the last may know them."""
+    import json
+    env = dict(os.environ, LD_PRELOAD=recorder)
+    res = subprocess.run([sys.executable, "-c", CHILD, ROOT], env=env, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
+    steps = json.loads(res.stdout.split("RESULT ")[1])
+    for launches in steps:
+        assert "cast_masters" in launches[0][0] and launches[0][1:] == [True, True]
+        assert launches[-1][1:] == [True, True], launches
+        assert all(l[1:] == [False, False] for l in launches[1:-1]), launches
