@@ -13,19 +13,19 @@ namespace fbq {
 // copy - it cannot tell the buffer being read from the ones being filled - which undoes any look-ahead: an earlier
 // form of the prefill kernel began every round with vmcnt(0).  The instruction has no destination register; whoever reads
 // a copy waits for it by count and passes a barrier (both with a memory clobber).  The compiler's own counted waits only
-// get stricter by the copies it does not know of.  Nothing else in these kernels uses M0.
+// get stricter by the copies it does not know of.  M0, the LDS address, is declared as overwritten: the compiler may keep a value there.
 __device__ __forceinline__ uint32_t lds_offset(const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p; }
 __device__ __forceinline__ void copy16_to_lds(__amdgpu_buffer_rsrc_t buf, int lane_off, int row_off, uint32_t dst)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(lane_off), "s"(buf), "s"(row_off));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(lane_off), "s"(buf), "s"(row_off) : "m0");
 }
 __device__ __forceinline__ void copy12_to_lds(__amdgpu_buffer_rsrc_t buf, int lane_off, int row_off, uint32_t dst)   // (12 bytes per lane, but 16 l apart in LDS)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx3 %1, %2, %3 offen lds" ::"s"(dst), "v"(lane_off), "s"(buf), "s"(row_off));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx3 %1, %2, %3 offen lds" ::"s"(dst), "v"(lane_off), "s"(buf), "s"(row_off) : "m0");
 }
 __device__ __forceinline__ void copy4_to_lds(__amdgpu_buffer_rsrc_t buf, int lane_off, int row_off, uint32_t dst)    // (4 bytes: dst + 4 l)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(dst), "v"(lane_off), "s"(buf), "s"(row_off));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(dst), "v"(lane_off), "s"(buf), "s"(row_off) : "m0");
 }
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, long bytes)
 {

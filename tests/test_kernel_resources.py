@@ -1,5 +1,6 @@
 """What the launchers take for granted about the compiled kernels, read from the metadata of the code objects in
 libfbq.so (built here from csrc/): registers, spills and LDS of every instance."""
+import os
 import re
 import struct
 import subprocess
@@ -47,3 +48,16 @@ def test_two_blocks_of_the_gemv_fit_a_compute_unit(kernels):
     for n, k in gemv.items():
         assert k[".vgpr_count"] <= 256 and k[".vgpr_spill_count"] == 0, n
         assert k[".group_segment_fixed_size"] <= 80 * 1024, n
+
+
+def test_inline_assembly_declares_the_scalar_register_it_overwrites():
+    """M0 belongs to the compiler: a statement that moves an LDS address into it without saying so would silently change
+    whatever value the compiler keeps there."""
+    csrc = os.path.join(os.path.dirname(fbq.lib_path()), "csrc")
+    found = 0
+    for name in sorted(os.listdir(csrc)):
+        for statement in re.findall(r"\basm\b[^;]*;", open(os.path.join(csrc, name)).read()):
+            if re.search(r"\bs_mov_b32 m0\b", statement):
+                found += 1
+                assert statement.rstrip(");").endswith('"m0"'), (name, statement)
+    assert found == 3
