@@ -118,24 +118,23 @@ constexpr int kPrefillColumns = 256;   // columns of a block tile of the prefill
 // one launch and the others a second one in tiles of their own height (4 us for the launch).  8192 -> 28672 at 2048 tokens,
 // INT4, r = 128, us: four rounds of 256-row tiles, the last half empty, 896; three rounds, and the rest as 256 tiles of 128 rows, 844.
 //
-// Short K: up to six groups a block is mostly its start and its end, and what counts is that another block works meanwhile.
-// There the low tiles have one K group, so that two (96 rows) or three (64 rows) blocks share a CU, and only these two heights
-// are used; the one whose rounds over the CUs, each its rows and 24 rows' worth of start and end, are fewer.  us with one block per
-// CU as above / like this, r = 0 where none is given: 14402 x 128 at 922 tokens, INT4, 30.1 / 21.5; 26880 x 256 at 577, r = 64,
-// 37.5 / 28.8; 20431 x 640 at 1166, r = 64, INT3, 83.9 / 65.6; 2506 x 256 at 420, INT3, 13.1 / 12.1; 6272 x 768 at 342 15.0 / 14.9;
-// from 896 on a layer with one round of blocks is faster with two K groups (5375 x 2688 at 1671 73 and, with one, 75).
-constexpr int kShortGroups = 6;
-struct PrefillCut { int tm, ksplit, columns, tail_tm; };   // columns: column blocks of the first launch; tail_tm: tile height of the second, 0: none
+// Low tiles of one K group: two blocks of 128 or 96 rows, three of 64, share a CU, and one works while another starts or ends.  That
+// is worth most where a block has few steps and a CU several blocks; what it lacks is the second group's help with the
+// steps.  Estimated the same way, from what a set of one, two or three blocks on a CU takes per step and at its start and end
+// (fitted to 400 layers without a sub-branch, 256 to 150000 rows, 65 to 4096 tokens), and taken up to 2048 activations where
+// the estimate is 5 % below the other one.  Further up a block's end with a sub-branch, which lower tiles have more of, undoes the
+// gain (11008 x 4096 at 1024 tokens, r = 64: 102 us in 256 rows, 105 in 96 like this).  Over 160 drawn layers of up to 2176
+// activations with a sub-branch 7 % faster on average than without these tiles, and 1 % slower at worst.  Examples, us
+// without / with: 14402 x 128 at 922 tokens, INT4, no sub-branch 30.1 / 21; 26880 x 256 at 577, r = 64, 37.5 / 28.8;
+// 50257 x 1024 at 700, r = 16, 130 / 105; 9000 x 1536 at 2000, r = 64, 94 / 81; 2434 x 256 at 148, r = 128, INT3, 20.5 / 19.7.
+constexpr int kSingleGroups = 16;
+struct PrefillCut { int tm, ksplit, columns, tail_tm; bool single; };   // columns: column blocks of the first launch; tail_tm: tile height of the second, 0: none; single: one K group though tm < 6
 
 inline PrefillCut prefill_cut(int M, int N, int K)
 {
     static constexpr struct { int tm, kg; double step, fixed; } kTiles[] = {
         {8, 1, 1.614, 16.2}, {6, 1, 1.241, 11.6}, {4, 2, 1.731, 9.4}, {3, 2, 1.402, 7.6}, {2, 2, 1.144, 6.0}};
     const int G = K / kGroup, columns = ceil_div(N, kPrefillColumns);
-    if (G <= kShortGroups) {
-        auto cost = [&](int tm) { return std::ceil(columns * (double)ceil_div(M, 32 * tm) / 256.0) * (32 * tm + 24); };
-        return {cost(2) <= cost(3) ? 2 : 3, 1, columns, 0};
-    }
     auto launch_us = [&](int tile, int cols, int split) {
         const auto &t = kTiles[tile];
         const int rows = ceil_div(M, 32 * t.tm);
@@ -146,14 +145,14 @@ inline PrefillCut prefill_cut(int M, int N, int K)
                           (split > 1 ? 5.6 + 0.886e-6 * M * (double)N * (split + 0.5) : 0.0);
         return us * (1.0 - 0.01 * t.tm);                // (taller tiles draw less power per product: measured, they win where this estimate is a tie)
     };
-    PrefillCut best{0, 1, columns, 0};
+    PrefillCut best{0, 1, columns, 0, false};
     double best_us = 1e300;
     for (int i = 0; i < 5; ++i) {
         const double tiles = (double)columns * ceil_div(M, 32 * kTiles[i].tm);
         for (int split = 1; split <= 8; ++split) {
             if (split > 1 && (tiles * split > 600 || G / (split * kTiles[i].kg) < 2)) break;
             const double us = launch_us(i, columns, split);
-            if (us < best_us) { best_us = us; best = {kTiles[i].tm, split, columns, 0}; }
+            if (us < best_us) { best_us = us; best = {kTiles[i].tm, split, columns, 0, false}; }
         }
     }
     for (int i = 0; i < 5; ++i) {
@@ -162,8 +161,21 @@ inline PrefillCut prefill_cut(int M, int N, int K)
         if (whole < 8 || whole >= columns) continue;
         for (int j = 0; j < 5; ++j) {
             const double us = launch_us(i, whole, 1) + launch_us(j, columns - whole, 1) + 4.0;
-            if (us < 0.98 * best_us) { best_us = us; best = {kTiles[i].tm, 1, whole, kTiles[j].tm}; }
+            if (us < 0.98 * best_us) { best_us = us; best = {kTiles[i].tm, 1, whole, kTiles[j].tm, false}; }
         }
+    }
+    static constexpr struct { int tm, together; double step[3], fixed[3], idle; } kSingle[] = {
+        {4, 2, {0.93, 1.65, 0}, {6.8, 8.3, 0}, 0.29}, {3, 2, {0.79, 1.32, 0}, {5.7, 6.5, 0}, 0.27}, {2, 3, {0.71, 1.07, 1.68}, {4.5, 6.3, 5.5}, 0.26}};
+    best_us *= 0.95;
+    for (int i = 0; i < 3 && G <= kSingleGroups; ++i) {
+        const auto &t = kSingle[i];
+        const int rows = ceil_div(M, 32 * t.tm);
+        const double per_cu = std::ceil(((double)(columns / 8) * rows + std::ceil((columns % 8) * (double)rows / 8.0)) / 32.0);
+        auto set_us = [&](int blocks) { return blocks ? 2 * G * t.step[blocks - 1] + t.fixed[blocks - 1] : 0.0; };
+        const double sets = std::floor(per_cu / t.together);
+        const double us = (sets * set_us(t.together) + set_us((int)(per_cu - sets * t.together))) *
+                          (1.0 - t.idle * (1.0 - (double)columns * rows / (256.0 * per_cu))) * (1.0 - 0.01 * t.tm);
+        if (us < best_us) { best_us = us; best = {t.tm, 1, columns, 0, true}; }
     }
     return best;
 }

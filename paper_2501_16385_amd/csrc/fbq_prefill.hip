@@ -11,7 +11,7 @@
 //
 // Fused kernel.  Four waves side by side along N, block tile (32 TM) x 256, TM = 2, 3, 4, 6 or 8; a wave owns TM x 2
 // tiles of v_mfma_f32_32x32x16_f16.  With TM of 6 or 8 that is one wave per SIMD with up to 256 accumulator registers;
-// with less the block has eight waves, two groups that split K and meet in LDS (four waves and several blocks per CU where K is short).
+// with less the block has eight waves, two groups that split K and meet in LDS (or four waves and several blocks per CU).
 // K advances in steps of 64, half a quantization group, and everything a step reads comes out of LDS, copied there three
 // steps ahead by buffer_load ... lds (no registers): the activations, the packed words, and scale and zero.  With the
 // packed words loaded into registers instead - 32 rows per load, waited for by the compiler's count - the look-ahead
@@ -171,8 +171,8 @@ struct WeightRegs {
 // TM: 32-row tiles of a wave and of the block.  KG: groups of four waves that split K for the same tile inside one block
 // (1 or 2): the groups take consecutive ranges of K, and group 1 hands its accumulators to group 0 through LDS at the
 // end, so nothing but y is ever written.  One block per CU: with TM of 6 or 8 a wave has a SIMD, and its 512
-// registers, to itself; with less, two waves share one - of one block with two K groups, or, where K is short (see
-// kShortGroups), of blocks with one.
+// registers, to itself; with less, two waves share one - of one block with two K groups, or of blocks
+// with one (see prefill_cut for which).
 template <int BITS, int TM, int KG>
 struct GemmTile {
     static constexpr int kBM = 32 * TM;
@@ -849,24 +849,22 @@ static void launch_tile(const PrefillParams &p, dim3 grid, hipStream_t stream)
 
 // `columns` column blocks from p.col0 on, in tiles of 32 tm rows
 template <int BITS>
-static hipError_t launch_columns(PrefillParams p, int tm, int columns, hipStream_t stream)
+static hipError_t launch_columns(PrefillParams p, int tm, bool single, int columns, hipStream_t stream)
 {
     p.row_blocks = ceil_div(p.M, 32 * tm);
     p.full_cols = (columns / kXcds) * kXcds;
     p.full_slots = (columns / kXcds) * p.row_blocks * p.ksplit;
     p.rem_blocks = (columns % kXcds) * p.row_blocks * p.ksplit;
     const dim3 grid(kXcds * (p.full_slots + ceil_div(p.rem_blocks, kXcds)));
-    if (p.G <= kShortGroups) {                          // (tm is 2 or 3)
-        if (tm == 2) launch_tile<BITS, 2, 1>(p, grid, stream);
-        else launch_tile<BITS, 3, 1>(p, grid, stream);
-        return hipGetLastError();
-    }
-    switch (tm) {
+    switch (single ? -tm : tm) {
     case 8: launch_tile<BITS, 8, 1>(p, grid, stream); break;
     case 6: launch_tile<BITS, 6, 1>(p, grid, stream); break;
     case 4: launch_tile<BITS, 4, 2>(p, grid, stream); break;
     case 3: launch_tile<BITS, 3, 2>(p, grid, stream); break;
-    default: launch_tile<BITS, 2, 2>(p, grid, stream); break;
+    case 2: launch_tile<BITS, 2, 2>(p, grid, stream); break;
+    case -4: launch_tile<BITS, 4, 1>(p, grid, stream); break;
+    case -3: launch_tile<BITS, 3, 1>(p, grid, stream); break;
+    default: launch_tile<BITS, 2, 1>(p, grid, stream); break;
     }
     return hipGetLastError();
 }
@@ -885,10 +883,10 @@ hipError_t launch_gemm_prefill(const LinearArgs &a, hipStream_t stream)
     p.ksplit = c.ksplit;
     p.ypart = s.ypart;
     p.col0 = 0;
-    hipError_t e = a.bits == 4 ? launch_columns<4>(p, c.tm, c.columns, stream) : launch_columns<3>(p, c.tm, c.columns, stream);
+    hipError_t e = a.bits == 4 ? launch_columns<4>(p, c.tm, c.single, c.columns, stream) : launch_columns<3>(p, c.tm, c.single, c.columns, stream);
     if (e == hipSuccess && c.tail_tm) {
         p.col0 = c.columns;
-        e = a.bits == 4 ? launch_columns<4>(p, c.tail_tm, nb - c.columns, stream) : launch_columns<3>(p, c.tail_tm, nb - c.columns, stream);
+        e = a.bits == 4 ? launch_columns<4>(p, c.tail_tm, false, nb - c.columns, stream) : launch_columns<3>(p, c.tail_tm, false, nb - c.columns, stream);
     }
     if (e == hipSuccess && p.ksplit > 1) {
         const size_t total = (size_t)a.M * a.N;

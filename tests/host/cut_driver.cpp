@@ -1,5 +1,5 @@
 // Prints how prefill_cut (csrc/fbq_internal.h) cuts layers into blocks, as "<rows>/<K split>" or "<rows>+<rows of the second
-// launch>" with " short" behind it where the blocks have one K group: one line for each "M N K" on stdin, then - without the
+// launch>" with " single" behind it where low tiles have one K group: one line for each "M N K" on stdin, then - without the
 // number of splits - every kind that a million calls of ordinary sizes meet, with its count.
 #include <cstdio>
 #include <map>
@@ -16,7 +16,7 @@ static std::string kind(int M, int N, int K, bool with_split)
     std::string s = std::to_string(32 * c.tm);
     if (c.tail_tm) s += "+" + std::to_string(32 * c.tail_tm);
     else if (c.ksplit > 1) s += with_split ? "/" + std::to_string(c.ksplit) : "/split";
-    return K / kGroup <= kShortGroups ? s + " short" : s;
+    return c.single ? s + " single" : s;
 }
 
 int main()

@@ -36,7 +36,7 @@ def test_quantizer_tile_edges(bits, N, K, r):
 # ------------------------------------------------------------------ prefill GEMM: tiles of 64, 96, 128, 192 and 256 rows x 256 columns, K split over blocks
 
 PREFILL_CASES = [
-    # N, K, r, M (prefill_cases.py has a layer for every kind of cut; up to 768 activations the tiles have 64 or 96 rows)
+    # N, K, r, M (prefill_cases.py has a layer for every kind of cut)
     # (the per-token bar is relative to the norm of a token's outputs: a few dozen columns, so that it is no single cancelled sum)
     (25, 128, 8, 65),           # one quantization group
     (40, 256, 40, 77),          # a rank that is no multiple of 16 or 64
