@@ -173,9 +173,15 @@ def free_read_pool():
     _POOL = None
 
 
+def train_flops(N, K, r, T):
+    """Operations of H, of the gradients and of the loss.  H and the loss's Delta^T Delta are symmetric: K (K + 1) / 2 sums of
+    T and of N products.  The gradients are products with r rows only: 8 N K r + 4 r K^2."""
+    return {"gram": float(K) * (K + 1) * T, "gradients": 8.0 * N * K * r + 4.0 * r * K * K, "loss": float(K) * (K + 1) * N}
+
+
 def time_train_step(N, K, r, bits, T, iters=20, warmup=3):
     """Times fbq_gram and fbq_train_step (with and without the loss) on synthetic W ~ N(0, 0.02), X ~ N(0, 1).
-    Flops: gram 2 K^2 T; gradients 8 N K r + 4 r K^2 (products with r rows only); the loss 2 N K^2 more."""
+    Rates are over the operations that are done: see train_flops."""
     d = fbq.Desc(N, K, r, bits)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(1)
@@ -203,13 +209,12 @@ def time_train_step(N, K, r, bits, T, iters=20, warmup=3):
     lr = 0.0        # the masters stay put: every timed iteration does the same work on the same values
     us_loss = timed(lambda: fbq.train_step(st, W, H16, hs, lr))
     us_grad = timed(lambda: fbq.train_step(st, W, H16, hs, lr, want_loss=False))
-    fl_grad = 8.0 * N * K * r + 4.0 * r * K * K
-    fl_loss = 2.0 * N * K * K
+    flops = train_flops(N, K, r, T)
     return {"N": N, "K": K, "r": r, "bits": bits, "T": T, "gram_us": round(us_gram, 1),
-            "gram_TFLOPps": round(2.0 * K * K * T / us_gram / 1e6, 1),
+            "gram_TFLOPps": round(flops["gram"] / us_gram / 1e6, 1),
             "step_us": round(us_grad, 1), "step_with_loss_us": round(us_loss, 1),
-            "loss_contraction_TFLOPps": round(fl_loss / max(us_loss - us_grad, 1e-3) / 1e6, 1),
-            "step_TFLOPps": round(fl_grad / us_grad / 1e6, 1), "loss": float(st.loss.cpu()[0])}
+            "loss_contraction_TFLOPps": round(flops["loss"] / max(us_loss - us_grad, 1e-3) / 1e6, 1),
+            "step_TFLOPps": round(flops["gradients"] / us_grad / 1e6, 1), "loss": float(st.loss.cpu()[0])}
 
 
 def main():
