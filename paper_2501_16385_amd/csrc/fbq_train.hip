@@ -17,7 +17,7 @@
 //                                                                         a call that fails on the way moves neither)
 //
 // with Sigma[n,k] = sum_j Bt[n,j] At[j,k] in the device layouts At [r,K], Bt [N,r].  The gradients need only products with
-// r rows or columns (8 N K r + 4 r K^2 flop) because H is symmetric: Delta_F H At^T = Delta_F (At H)^T.  The loss is the one
+// r rows or columns (4 N K r + 4 r K^2 flop) because H is symmetric: Delta_F H At^T = Delta_F (At H)^T.  The loss is the one
 // quantity that needs a contraction over N and K x K, and as tr(Delta_F H Delta_F^T) = sum (Delta_F^T Delta_F) o H that is a
 // symmetric one, half the work of Delta_F H.
 //

@@ -174,9 +174,9 @@ def free_read_pool():
 
 
 def train_flops(N, K, r, T):
-    """Operations of H, of the gradients and of the loss.  H and the loss's Delta^T Delta are symmetric: K (K + 1) / 2 sums of
-    T and of N products.  The gradients are products with r rows only: 8 N K r + 4 r K^2."""
-    return {"gram": float(K) * (K + 1) * T, "gradients": 8.0 * N * K * r + 4.0 * r * K * K, "loss": float(K) * (K + 1) * N}
+    """Operations of H, of a step without the loss and of the loss.  H and the loss's Delta^T Delta are symmetric: K (K + 1) / 2
+    sums of T and of N products.  A step is B A in the quantizer (2 N K r) and products with r rows (4 N K r + 4 r K^2)."""
+    return {"gram": float(K) * (K + 1) * T, "step": 6.0 * N * K * r + 4.0 * r * K * K, "loss": float(K) * (K + 1) * N}
 
 
 def time_train_step(N, K, r, bits, T, iters=20, warmup=3):
@@ -214,7 +214,7 @@ def time_train_step(N, K, r, bits, T, iters=20, warmup=3):
             "gram_TFLOPps": round(flops["gram"] / us_gram / 1e6, 1),
             "step_us": round(us_grad, 1), "step_with_loss_us": round(us_loss, 1),
             "loss_contraction_TFLOPps": round(flops["loss"] / max(us_loss - us_grad, 1e-3) / 1e6, 1),
-            "step_TFLOPps": round(flops["gradients"] / us_grad / 1e6, 1), "loss": float(st.loss.cpu()[0])}
+            "step_TFLOPps": round(flops["step"] / us_grad / 1e6, 1), "loss": float(st.loss.cpu()[0])}
 
 
 def main():

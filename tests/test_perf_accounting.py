@@ -10,5 +10,5 @@ def test_symmetric_products_count_one_triangle():
     flops = perf.train_flops(N, K, r, T)
     assert flops["gram"] == 2 * pairs * T
     assert flops["loss"] == 2 * pairs * N
-    # B^T Delta, [Q; At] H, Delta V: r x K x N, 2 r x K x K and N x r x K multiply-adds
-    assert flops["gradients"] == 2 * (r * K * N + 2 * r * K * K + N * r * K)
+    # B A, B^T Delta, [Q; At] H, Delta V: N x K x r, r x K x N, 2 r x K x K and N x r x K multiply-adds
+    assert flops["step"] == 2 * (N * K * r + r * K * N + 2 * r * K * K + N * r * K)
