@@ -33,6 +33,62 @@ def test_quantizer_tile_edges(bits, N, K, r):
     assert np.array_equal(dev.qweight.cpu().numpy().view(np.uint32), L.words)
 
 
+def quantize_group_by_the_book(R, qmax):
+    """Scale, zero and codes of one group as include/fbq.h defines them, the scale stepped through every fp16 number: extremes that
+    ignore NaN, comparisons that a NaN fails, clamping that turns a NaN into code 0."""
+    with np.errstate(all="ignore"):
+        lo, hi = np.fmin.reduce(R), np.fmax.reduce(R)
+        s = (hi - lo) / qmax
+        bits = max(int(np.float16(s if s > 0 else 1.0).view(np.uint16)), 0x0400)
+        while True:
+            sd = float(np.uint16(bits).view(np.float16))
+            z = np.float16(-lo / sd)
+            if (lo / sd + float(z) >= -0.5 and hi / sd + float(z) <= qmax + 0.5) or bits >= 0x7bff:
+                break
+            bits += 1
+        q = np.fmin(np.fmax(np.rint(R / sd + float(z)), 0.0), qmax).astype(np.uint8)
+    return bits, z, q
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("r", [0, 8])
+def test_quantizer_with_weights_that_are_no_numbers(bits, r):
+    """NaN and infinite weights: the search for a scale ends where it always ended, and nothing else of the layer changes."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    K, inf, nan = 256, np.inf, np.nan
+    rng = np.random.Generator(np.random.Philox(49))
+    W = (rng.standard_normal((17, K)) * 0.02).astype(np.float16)
+    W[1, 5] = nan                                       # one NaN
+    W[2, :128] = nan                                    # a whole group
+    W[3, 7], W[4, 130], W[5, 0], W[5, 127] = inf, -inf, inf, -inf
+    W[6, :128], W[7, :128] = inf, -inf                  # nothing else in the group
+    W[8, 3], W[8, 4] = inf, nan
+    W[9, :128] = nan
+    W[9, 64] = inf
+    W[10, 1], W[10, 2] = 65504, -65504                  # finite after all
+    W[11, :128] = 0.25                                  # constant
+    W[12, :128:2], W[12, 1:128:2] = inf, nan
+    At = (rng.standard_normal((max(r, 1), K)) * 0.01).astype(np.float16)
+    Bt = (rng.standard_normal((17, max(r, 1))) * 0.01).astype(np.float16)
+    if r:
+        Bt[13, 3], Bt[14, 2] = inf, nan                 # a branch that is no number
+    dev = fbq.quantize_feedback(fbq.Desc(17, K, r, bits), t16(W), t16(At) if r else None, t16(Bt) if r else None)
+    codes = fbq.unpack_codes(dev)
+    torch.cuda.synchronize()
+    codes, s, z = codes.cpu().numpy(), dev.scales.cpu().numpy().view(np.uint16), dev.zeros.cpu().numpy().view(np.float16)
+    with np.errstate(all="ignore"):
+        R = W.astype(np.float64) - (Bt.astype(np.float64) @ At.astype(np.float64) if r else 0.0)
+    for n in range(17):
+        for g in range(2):
+            want_s, want_z, want_q = quantize_group_by_the_book(R[n, g * 128:(g + 1) * 128], 2 ** bits - 1)
+            where = f"row {n} group {g}"
+            assert s[n, g] == want_s, where
+            # a zero that is no number is stored as an infinity, of either sign
+            assert np.isinf(z[n, g]) if np.isnan(want_z) else z[n, g] == want_z, where
+            assert np.array_equal(codes[n, g * 128:(g + 1) * 128], want_q), where
+
+
 # ------------------------------------------------------------------ prefill GEMM: tiles of 64, 96, 128, 192 and 256 rows x 256 columns, K split over blocks
 
 PREFILL_CASES = [
@@ -225,7 +281,8 @@ def test_group_mix_equals_result_then_average(bits, M, N, K, r):
 
 @pytest.mark.parametrize("count", [1, 7, 8, 2047, 2049, 5 * 11008])
 def test_silu_mul_equals_two_element_wise_kernels(count):
-    """silu rounded to fp16, then the product: one ulp where the exponential differs in its last place."""
+    """silu rounded to fp16, then the product.  Where the exponential differs in its last place, silu may round to the neighbouring
+    number (2^-10 relative at most) and the product to one more (2^-11 each side of it): 2^-9 in all, and one subnormal step."""
     import torch
     import paper_2501_16385_amd as fbq
     g = torch.Generator(device="cuda")
