@@ -43,17 +43,16 @@ extern "C" size_t fbq_packed_bytes(const fbq_desc *d)
     return (size_t)d->N * row_words(d->K, d->bits) * sizeof(uint32_t);
 }
 
-// 17..64 tokens: whether the few-token kernel, the sets of 16 tokens side by side in one launch, is expected to beat
-// the prefill GEMM.  It streams the packed words once per set, in passes of 4096 along K; the GEMM reads them once
-// but has a long start (three launches, few tiles) and a K loop per tile that few tiles cannot hide.  Fitted to
-// measurements of both at 32, 48 and 64 tokens on ten shapes (us; MC = millions of codes, K counted in whole passes
-// for the sets): the sets take about 2 + sets x (2.2 + 0.165 MC), the GEMM 30 + 0.135 MC + 1.5 K / 1024 (with INT3
-// and INT4 alike).  Examples, sets / GEMM: 8192 -> 28672 at 32 tokens 84 / 71, at 64 160 / 83; 28672 -> 8192 at 32
-// tokens 80 / 101, at 48 122 / 101; 4096 -> 11008 at 64 tokens 35 / 41; 13824 -> 5120 at 48 tokens 50 / 62.
-// The GEMM has become faster since (28 us at 64 tokens of 4096 -> 11008, 40 at 48 of 13824 -> 5120), the line has not moved:
-// the sets multiply the codes exactly, the GEMM rounds the weights to fp16 (relative error of y 2.2e-4 and 2.9e-4), and a
-// call that has had the smaller error keeps it.
-static bool sets_beat_gemm(int M, int N, int K)
+// 17..64 tokens: whether the few-token kernel, the sets of 16 tokens side by side in one launch, takes the call, or the prefill
+// GEMM.  The sets stream the packed words once per set, in passes of 4096 along K, and multiply the codes exactly (relative error
+// of y 2.2e-4); the GEMM reads the words once and rounds the weights to fp16 (2.9e-4).  The line is the cost of both, in us, that
+// was fitted to ten shapes when the GEMM was slower than it is: sets 2 + sets x (2.2 + 0.165 MC), GEMM 30 + 0.135 MC + 1.5 K / 1024
+// (MC = millions of codes, K counted in whole passes for the sets).  As an estimate of the GEMM it is obsolete; it stays as the line up
+// to which a call has the smaller error: who had it keeps it.  What that costs by now, sets / GEMM, us: nothing for
+// 4096 x 4096 (9.5 / 25 at 32 tokens, 19 / 28 at 64) and 4096 -> 11008 up to 48 tokens (26 / 30; 34 / 32 at 64); 13824 -> 5120 at 48
+// tokens INT4 47 / 41, INT3 41 / 42; 8192 -> 8192 at 48 40 / 39 and 45 / 38; 28672 -> 8192 at 32 76 / 65 and 68 / 64; 5120 -> 13824
+// at 32 42 / 36.  On the GEMM's side of the line it is the faster one throughout: 8192 -> 28672 at 17 tokens 79 / 63, at 64 155 / 68.
+static bool takes_sets(int M, int N, int K)
 {
     const int sets = (M + kDecodeMaxM - 1) / kDecodeMaxM;
     const double k_passes = 4096.0 * ((K + 4095) / 4096);
@@ -79,7 +78,7 @@ extern "C" size_t fbq_workspace_bytes(const fbq_desc *d, int M)
     // words of their own (one or two left over go through the GEMV afterwards, whose words fit the first set);
     // nothing to hand over without a sub-branch
     if (M <= kDecodeMaxM) return small_m_workspace_bytes(d->K, d->r);
-    if (M <= kChunkedMaxM && sets_beat_gemm(M, d->N, d->K))
+    if (M <= kChunkedMaxM && takes_sets(M, d->N, d->K))
         return (size_t)((M + kDecodeMaxM - 1) / kDecodeMaxM) * small_m_workspace_bytes(d->K, d->r);
     return handover_reserve(d->K, d->r) + prefill_workspace_bytes(M, d->N, d->K, d->r);      // holds the re-ordered activations even when r == 0
 }
@@ -199,14 +198,13 @@ static hipError_t launch_prefill(const LinearArgs &call, hipStream_t s)
 
 // One or two tokens: streaming GEMV, one pass per token, with the down-projection inside the launch.
 // 3..16 tokens: one pass over the packed words against a matrix-core tile of tokens.  17..64 tokens:
-// the same, 16 tokens at a time, the sets of 16 side by side in ONE launch as if they were layers of a group
-// (the prefill GEMM has too few tiles to fill the GPU there), unless the layer is so large that reading its packed words
-// three or four times costs more than the GEMM's long start.  More: the prefill GEMM.
+// the same, 16 tokens at a time, the sets of 16 side by side in ONE launch as if they were layers of a group,
+// unless the layer lies beyond the line of takes_sets.  More: the prefill GEMM.
 hipError_t launch_one(const LinearArgs &a, hipStream_t s)
 {
     if (a.M <= kPerTokenMaxM) return launch_gemv_decode(&a, 1, s);
     if (a.M <= kDecodeMaxM) return launch_gemv_small_m(&a, 1, s);
-    if (a.M <= kChunkedMaxM && sets_beat_gemm(a.M, a.N, a.K)) {
+    if (a.M <= kChunkedMaxM && takes_sets(a.M, a.N, a.K)) {
         static_assert(kChunkedMaxM <= kMaxSmallGroup * kDecodeMaxM, "the sets of 16 tokens must fit one grouped launch");
         LinearArgs set[kMaxSmallGroup], rest = a;
         const size_t ws_each = small_m_workspace_bytes(a.K, a.r);

@@ -1,5 +1,6 @@
-// Validation and preparation kernels: unpack codes, reconstruct W_F, feedback quantizer.
-// None of these is on the inference hot path; they are written for clarity, one thread per element.
+// Kernels off the inference hot path: the feedback quantizer (fp64 matrix instructions: the step before the path, and a third of
+// a reconstruction iteration), and, one thread per element or output and written for clarity, unpacking, W_F, the read-only
+// yardstick and the conventional sub-branch that the fused kernels are compared with.
 #include <hip/hip_fp16.h>
 
 #include "fbq_internal.h"
