@@ -37,7 +37,7 @@
 // once per lane and chunk:  s * (sum q.x - z * sum x).
 #include <hip/hip_fp16.h>
 
-
+#include <type_traits>
 
 #include "fbq_internal.h"
 
@@ -199,19 +199,16 @@ struct LayerParams {
     int spin_limit;       // polls for t before a wave computes it itself; negative: at once (test hook)
 };
 
-// The averages a layer's result is also written into, only in the arguments of the instances that do it: see kGemvMixes
-struct MixParams {
-    const uint16_t *with;   // [M][N], N even
-    uint16_t *out;          // null: none
+// The same with the average that a layer's result is also written into, for the instances that do it (see gemv_mixes).  Behind the
+// layer's other parameters, so that they are fetched in one go (from an array of their own: 0.2 us a launch).
+struct MixLayerParams : LayerParams {
+    const uint16_t *mix_with;   // [M][N], N even
+    uint16_t *mix_out;          // null: none
 };
 
 template <bool MIX>
 struct GemvGroup {
-    LayerParams layer[kMaxGroup];
-};
-template <>
-struct GemvGroup<true> : GemvGroup<false> {
-    MixParams mix[kMaxGroup];
+    std::conditional_t<MIX, MixLayerParams, LayerParams> layer[kMaxGroup];
 };
 
 constexpr int kNowhere = 1 << 30;     // a byte offset beyond any buffer a layer has
@@ -352,9 +349,7 @@ __global__ __launch_bounds__(256) void fbq_gemv_kernel(const GemvGroup<MIX> g)
     // arguments costs more than half a microsecond here).  Layers with fewer blocks than the widest
     // one of the group leave the surplus blocks at once.
     const int m = blockIdx.z;
-    const LayerParams p = g.layer[blockIdx.x];
-    MixParams mix{};
-    if constexpr (MIX) mix = g.mix[blockIdx.x];
+    const auto p = g.layer[blockIdx.x];
     // (all of them before the first branch: left alone, the compiler fetches only what the branch needs first)
     asm volatile("" :: "s"(p.qw), "s"(p.scales), "s"(p.zeros), "s"(p.x), "s"(p.y), "s"(p.N), "s"(p.K), "s"(p.row_words), "s"(p.G));
     if (RI > 0) asm volatile("" :: "s"(p.At), "s"(p.Bt), "s"(p.ttag), "s"(p.r), "s"(p.tslices), "s"(p.spin_limit));
@@ -565,10 +560,12 @@ __global__ __launch_bounds__(256) void fbq_gemv_kernel(const GemvGroup<MIX> g)
     // weight stream do not see; asked for when the trip that finishes their tile begins.
     uint32_t mixw[ROWS / 2];
     auto request_mix = [&](int tile) __attribute__((always_inline)) {
-        if (!MIX || !mix.out) return;
-        const auto *w = reinterpret_cast<const __attribute__((address_space(4))) uint32_t *>((uintptr_t)mix.with);
+        if constexpr (MIX) {
+            if (!p.mix_out) return;
+            const auto *w = reinterpret_cast<const __attribute__((address_space(4))) uint32_t *>((uintptr_t)p.mix_with);
 #pragma unroll
-        for (int i = 0; i < ROWS / 2; ++i) mixw[i] = w[((size_t)m * p.N + min(tile * ROWS + 2 * i, p.N - 2)) / 2];
+            for (int i = 0; i < ROWS / 2; ++i) mixw[i] = w[((size_t)m * p.N + min(tile * ROWS + 2 * i, p.N - 2)) / 2];
+        }
     };
     auto finish = [&](float (&acc)[ROWS], const uint32_t (&bt)[ROWS][kRI], int tile) __attribute__((always_inline)) {
         if (RI > 0 && ks == 0) {
@@ -602,12 +599,14 @@ __global__ __launch_bounds__(256) void fbq_gemv_kernel(const GemvGroup<MIX> g)
         if (ks == 0 && lane < ROWS && tile < ntiles && n0 + lane < p.N) {
             const half_t y = (half_t)out;
             p.y[(size_t)m * p.N + n0 + lane] = __builtin_bit_cast(uint16_t, y);
-            if (MIX && mix.out) {
-                uint32_t w = mixw[0];
+            if constexpr (MIX) {
+                if (p.mix_out) {
+                    uint32_t w = mixw[0];
 #pragma unroll
-                for (int i = 1; i < ROWS / 2; ++i) w = lane / 2 == i ? mixw[i] : w;
-                const float with = (float)__builtin_bit_cast(half_t, (uint16_t)((lane & 1) ? w >> 16 : w));
-                mix.out[(size_t)m * p.N + n0 + lane] = __builtin_bit_cast(uint16_t, (half_t)((float)y - ((float)y - with) * 0.5f));
+                    for (int i = 1; i < ROWS / 2; ++i) w = lane / 2 == i ? mixw[i] : w;
+                    const float with = (float)__builtin_bit_cast(half_t, (uint16_t)((lane & 1) ? w >> 16 : w));
+                    p.mix_out[(size_t)m * p.N + n0 + lane] = __builtin_bit_cast(uint16_t, (half_t)((float)y - ((float)y - with) * 0.5f));
+                }
             }
         }
     };
@@ -726,7 +725,9 @@ static void launch_instance(const GemvGroup<true> &g, bool mix, dim3 grid, hipSt
             return;
         }
     }
-    hipLaunchKernelGGL((fbq_gemv_kernel<BITS, CPW, KS, ROWS, RI, false>), grid, dim3(256), 0, stream, static_cast<const GemvGroup<false> &>(g));
+    GemvGroup<false> plain;
+    std::copy(g.layer, g.layer + kMaxGroup, plain.layer);
+    hipLaunchKernelGGL((fbq_gemv_kernel<BITS, CPW, KS, ROWS, RI, false>), grid, dim3(256), 0, stream, plain);
 }
 
 template <int BITS, int CPW, int KS, int ROWS>
@@ -821,7 +822,7 @@ hipError_t launch_gemv_decode(const LinearArgs *layers, int n_layers, hipStream_
     int widest = 0;
     for (int i = 0; i < n_layers; ++i) {
         const LinearArgs &a = layers[i];
-        LayerParams &p = g.layer[i];
+        MixLayerParams &p = g.layer[i];
         p.qw = a.qw; p.scales = a.scales; p.zeros = a.zeros; p.At = a.At; p.Bt = a.Bt; p.x = a.x; p.y = a.y;
         p.ttag = (uint64_t *)a.workspace;
         p.N = a.N; p.K = a.K; p.r = a.r;
@@ -829,7 +830,7 @@ hipError_t launch_gemv_decode(const LinearArgs *layers, int n_layers, hipStream_
         p.G = a.K / kGroup;
         p.tslices = v.ks;
         p.spin_limit = spin_limit();
-        g.mix[i] = {a.mix_with, a.mix_out};
+        p.mix_with = a.mix_with; p.mix_out = a.mix_out;
         const int max_blocks = ceil_div(ceil_div(a.N, rows), row_sets);
         const int share = (int)(budget * ((double)a.N * a.K / total_work));
         if (inline_job) {
@@ -841,7 +842,7 @@ hipError_t launch_gemv_decode(const LinearArgs *layers, int n_layers, hipStream_
             widest = std::max(widest, p.blocks + ceil_div(a.r, row_sets));  // blocks in front that only do the down-projection
         }
     }
-    for (int i = n_layers; i < kMaxGroup; ++i) { g.layer[i] = g.layer[0]; g.mix[i] = g.mix[0]; }   // never indexed: grid.x stops at n_layers
+    for (int i = n_layers; i < kMaxGroup; ++i) g.layer[i] = g.layer[0];   // never indexed: grid.x stops at n_layers
     const dim3 grid(n_layers, widest, M);
     const bool mix = mixes && mix_inside;
     hipError_t e = v.bits == 4 ? launch_bits<4>(g, mix, v, rows, grid, stream) : launch_bits<3>(g, mix, v, rows, grid, stream);

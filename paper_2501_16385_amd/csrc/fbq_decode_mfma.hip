@@ -43,6 +43,8 @@
 // once.  Layers that read the same activations (q/k/v, gate/up) share the launch.
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 #include "fbq_internal.h"
 
 
@@ -100,19 +102,15 @@ struct SmallParams {
 // they are fetched in one go with the rest of the kernel arguments (a second, dependent round trip
 // to them costs more than half a microsecond).  Surplus blocks of rows with fewer blocks than the
 // widest leave at once.
+// The instances that write averages with the results have what to average with behind a layer's other parameters.
+struct MixSmallParams : SmallParams {
+    const uint16_t *mix_with;   // [M][N]
+    uint16_t *mix_out;          // null: none
+};
 template <bool MIX>
 struct SmallGroup {
     int n_layers;
-    SmallParams layer[kMaxSmallGroup];
-};
-// ... and, only in the arguments of the instances that write averages with the results, what to average with
-struct SmallMix {
-    const uint16_t *with;   // [M][N]
-    uint16_t *out;          // null: none
-};
-template <>
-struct SmallGroup<true> : SmallGroup<false> {
-    SmallMix mix[kMaxSmallGroup];
+    std::conditional_t<MIX, MixSmallParams, SmallParams> layer[kMaxSmallGroup];
 };
 
 // What the weight field of pair p (0..15, in extraction order) is multiplied by; the activation that meets it is divided by it.
@@ -357,9 +355,7 @@ __global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const Smal
     __shared__ uint4_t xslab[kMainWaves][kTokens * 17];
     float4_t (*red_prep)[64] = reinterpret_cast<float4_t (*)[64]>(&red[0][0][0]);   // [8][64], what a down-projection block needs
 
-    const SmallParams p = g.layer[blockIdx.y];
-    SmallMix mix{};
-    if constexpr (MIX) mix = g.mix[blockIdx.y];
+    const auto p = g.layer[blockIdx.y];
     // (all of them before the first branch: left alone, the compiler fetches only what the branch needs first)
     asm volatile("" :: "s"(p.qw), "s"(p.scales), "s"(p.zeros), "s"(p.x), "s"(p.y), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.row_words), "s"(p.G), "s"(p.tiles_per_block));
     if (BRANCH) asm volatile("" :: "s"(p.Bt), "s"(p.At), "s"(p.tpart), "s"(p.tsum), "s"(p.r), "s"(p.slices), "s"(p.kslice), "s"(p.down_blocks), "s"(p.sum_blocks), "s"(p.spin_limit));
@@ -601,12 +597,14 @@ __global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const Smal
     // the values to average with, on their way while the waves meet (wave ti stores tile ti)
     static_assert(T <= kMainWaves, "a wave stores at most one tile");
     uint16_t with[4] = {0, 0, 0, 0};
-    if (MIX && mix.out && wave < T) {                   // wave-uniform
-        const __amdgpu_buffer_rsrc_t mbuf = buffer_of(mix.with, (long)p.M * p.N * 2);
-        const int n = (tile0 + wave) * 16 + c;
+    if constexpr (MIX) {
+        if (p.mix_out && wave < T) {                    // wave-uniform
+            const __amdgpu_buffer_rsrc_t mbuf = buffer_of(p.mix_with, (long)p.M * p.N * 2);
+            const int n = (tile0 + wave) * 16 + c;
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            with[v] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(mbuf, n < p.N && 4 * q + v < p.M ? ((4 * q + v) * p.N + n) * 2 : kNowhere, 0, 0);
+            for (int v = 0; v < 4; ++v)
+                with[v] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(mbuf, n < p.N && 4 * q + v < p.M ? ((4 * q + v) * p.N + n) * 2 : kNowhere, 0, 0);
+        }
     }
     __syncthreads();
     for (int ti = wave; ti < T; ti += kMainWaves) {     // wave-uniform
@@ -623,9 +621,11 @@ __global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const Smal
                 if (m < p.M) {
                     const half_t y = (half_t)sum[v];
                     p.y[(size_t)m * p.N + n] = __builtin_bit_cast(uint16_t, y);
-                    if (MIX && mix.out) {
-                        const float w = (float)__builtin_bit_cast(half_t, with[v]);
-                        mix.out[(size_t)m * p.N + n] = __builtin_bit_cast(uint16_t, (half_t)((float)y - ((float)y - w) * 0.5f));
+                    if constexpr (MIX) {
+                        if (p.mix_out) {
+                            const float w = (float)__builtin_bit_cast(half_t, with[v]);
+                            p.mix_out[(size_t)m * p.N + n] = __builtin_bit_cast(uint16_t, (half_t)((float)y - ((float)y - w) * 0.5f));
+                        }
                     }
                 }
             }
@@ -653,7 +653,10 @@ static void launch_instance(const SmallGroup<true> &g, bool mix, dim3 grid, hipS
             return;
         }
     }
-    hipLaunchKernelGGL((fbq_small_m_kernel<BITS, T, BRANCH, TAIL, false>), grid, dim3(64 * kMainWaves), 0, stream, static_cast<const SmallGroup<false> &>(g));
+    SmallGroup<false> plain;
+    plain.n_layers = g.n_layers;
+    std::copy(g.layer, g.layer + kMaxSmallGroup, plain.layer);
+    hipLaunchKernelGGL((fbq_small_m_kernel<BITS, T, BRANCH, TAIL, false>), grid, dim3(64 * kMainWaves), 0, stream, plain);
 }
 
 template <int BITS, int T, bool TAIL>
@@ -753,7 +756,7 @@ hipError_t launch_gemv_small_m(const LinearArgs *layers, int n_layers, hipStream
     int row_blocks = 0;                                  // widest row of the grid
     for (int i = 0; i < n_layers; ++i) {
         const LinearArgs &a = layers[i];
-        SmallParams &p = g.layer[i];
+        MixSmallParams &p = g.layer[i];
         p.qw = a.qw; p.scales = a.scales; p.zeros = a.zeros; p.At = a.At; p.Bt = a.Bt; p.x = a.x; p.y = a.y;
         p.tpart = (uint64_t *)a.workspace;               // each layer's own partial sums of t ...
         p.tsum = p.tpart + (size_t)kMaxSlices * kTokens * a.r;   // ... and their sums
@@ -768,10 +771,10 @@ hipError_t launch_gemv_small_m(const LinearArgs *layers, int n_layers, hipStream
         p.sum_blocks = a.r > 0 ? ceil_div(a.r, 16) : 0;
         p.tiles_per_block = tpb;
         p.spin_limit = spin_limit();
-        g.mix[i] = {a.mix_with, a.mix_out};
+        p.mix_with = a.mix_with; p.mix_out = a.mix_out;
         row_blocks = std::max(row_blocks, p.down_blocks + p.sum_blocks + ceil_div(ceil_div(a.N, 16), tpb));
     }
-    for (int i = n_layers; i < kMaxSmallGroup; ++i) { g.layer[i] = g.layer[0]; g.mix[i] = g.mix[0]; }   // never indexed: grid.y stops at n_layers
+    for (int i = n_layers; i < kMaxSmallGroup; ++i) g.layer[i] = g.layer[0];   // never indexed: grid.y stops at n_layers
     bool tail = false;                                  // a layer whose scale array ends in the middle of a dword
     bool mix = false;                                   // averages to be written: with the results, or behind the launch where a layer has such a tail
     for (int i = 0; i < n_layers; ++i) {
