@@ -121,16 +121,17 @@ constexpr int kPrefillColumns = 256;   // columns of a block tile of the prefill
 // Low tiles of one K group: two blocks of 128 or 96 rows, three of 64, share a CU, and one works while another starts or ends.  That
 // is worth most where a block has few steps and a CU several blocks; what it lacks is the second group's help with the
 // steps.  Estimated the same way, from what a set of one, two or three blocks on a CU takes per step and at its start and end
-// (fitted to 400 layers without a sub-branch, 256 to 150000 rows, 65 to 4096 tokens), and taken up to 2048 activations where
-// the estimate is 5 % below the other one.  Further up a block's end with a sub-branch, which lower tiles have more of, undoes the
-// gain (11008 x 4096 at 1024 tokens, r = 64: 102 us in 256 rows, 105 in 96 like this).  Over 160 drawn layers of up to 2176
-// activations with a sub-branch 7 % faster on average than without these tiles, and 1 % slower at worst.  Examples, us
+// (fitted to 400 layers without a sub-branch, 128 to 6144 activations, 256 to 150000 rows, 65 to 4096 tokens).  Without a
+// sub-branch they are taken over that range of activations up to 5 % above the other estimate; with one, up to 2048 where theirs is
+// 5 % below: a block's end with a sub-branch, which lower tiles have more of, undoes the gain (11008 x 4096 at 1024 tokens, r = 64:
+// 102 us in 256 rows, 105 in 96 like this).  Against the estimate above alone: 160 drawn layers of up to 2176 activations with a
+// sub-branch 7 % faster on average, 1 % slower at worst; 800 without one, 7 % on average.  Examples, us
 // without / with: 14402 x 128 at 922 tokens, INT4, no sub-branch 30.1 / 21; 26880 x 256 at 577, r = 64, 37.5 / 28.8;
-// 50257 x 1024 at 700, r = 16, 130 / 105; 9000 x 1536 at 2000, r = 64, 94 / 81; 2434 x 256 at 148, r = 128, INT3, 20.5 / 19.7.
-constexpr int kSingleGroups = 16;
+// 50257 x 1024 at 700, r = 16, 130 / 105; 9000 x 1536 at 2000, r = 64, 94 / 81; 18796 x 2304 at 849, INT3, no sub-branch 102 / 92.
+constexpr int kSingleGroups = 16, kSingleGroupsNoBranch = 48;
 struct PrefillCut { int tm, ksplit, columns, tail_tm; bool single; };   // columns: column blocks of the first launch; tail_tm: tile height of the second, 0: none; single: one K group though tm < 6
 
-inline PrefillCut prefill_cut(int M, int N, int K)
+inline PrefillCut prefill_cut(int M, int N, int K, int r)
 {
     static constexpr struct { int tm, kg; double step, fixed; } kTiles[] = {
         {8, 1, 1.614, 16.2}, {6, 1, 1.241, 11.6}, {4, 2, 1.731, 9.4}, {3, 2, 1.402, 7.6}, {2, 2, 1.144, 6.0}};
@@ -166,8 +167,8 @@ inline PrefillCut prefill_cut(int M, int N, int K)
     }
     static constexpr struct { int tm, together; double step[3], fixed[3], idle; } kSingle[] = {
         {4, 2, {0.93, 1.65, 0}, {6.8, 8.3, 0}, 0.29}, {3, 2, {0.79, 1.32, 0}, {5.7, 6.5, 0}, 0.27}, {2, 3, {0.71, 1.07, 1.68}, {4.5, 6.3, 5.5}, 0.26}};
-    best_us *= 0.95;
-    for (int i = 0; i < 3 && G <= kSingleGroups; ++i) {
+    best_us *= r > 0 ? 0.95 : 1.05;
+    for (int i = 0; i < 3 && G <= (r > 0 ? kSingleGroups : kSingleGroupsNoBranch); ++i) {
         const auto &t = kSingle[i];
         const int rows = ceil_div(M, 32 * t.tm);
         const double per_cu = std::ceil(((double)(columns / 8) * rows + std::ceil((columns % 8) * (double)rows / 8.0)) / 32.0);

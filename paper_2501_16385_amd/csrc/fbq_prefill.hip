@@ -785,7 +785,7 @@ static size_t down_partial_bytes(int M, int K, int r) { return pad256((size_t)do
 
 size_t prefill_workspace_bytes(int M, int N, int K, int r)
 {
-    const int split = prefill_cut(M, N, K).ksplit;
+    const int split = prefill_cut(M, N, K, r).ksplit;
     return xp_bytes(M, K) + sz_bytes(N, K) + thl_bytes(M, r) + down_partial_bytes(M, K, r) + (split > 1 ? (size_t)split * M * N * sizeof(float) : 0);
 }
 
@@ -872,7 +872,7 @@ static hipError_t launch_columns(PrefillParams p, int tm, bool single, int colum
 hipError_t launch_gemm_prefill(const LinearArgs &a, hipStream_t stream)
 {
     const PrefillScratch s = scratch_of(a);
-    const PrefillCut c = prefill_cut(a.M, a.N, a.K);
+    const PrefillCut c = prefill_cut(a.M, a.N, a.K, a.r);
     PrefillParams p;
     p.qw = a.qw; p.sz = s.sz; p.Bt = a.Bt; p.y = a.y; p.xp = s.xp; p.thl = s.thl;
     p.M = a.M; p.N = a.N; p.K = a.K; p.r = a.r;

@@ -1,5 +1,5 @@
 // Prints how prefill_cut (csrc/fbq_internal.h) cuts layers into blocks, as "<rows>/<K split>" or "<rows>+<rows of the second
-// launch>" with " single" behind it where low tiles have one K group: one line for each "M N K" on stdin, then - without the
+// launch>" with " single" behind it where low tiles have one K group: one line for each "M N K r" on stdin, then - without the
 // number of splits - every kind that a million calls of ordinary sizes meet, with its count.
 #include <cstdio>
 #include <map>
@@ -10,9 +10,9 @@
 
 using namespace fbq;
 
-static std::string kind(int M, int N, int K, bool with_split)
+static std::string kind(int M, int N, int K, int r, bool with_split)
 {
-    const PrefillCut c = prefill_cut(M, N, K);
+    const PrefillCut c = prefill_cut(M, N, K, r);
     std::string s = std::to_string(32 * c.tm);
     if (c.tail_tm) s += "+" + std::to_string(32 * c.tail_tm);
     else if (c.ksplit > 1) s += with_split ? "/" + std::to_string(c.ksplit) : "/split";
@@ -21,8 +21,8 @@ static std::string kind(int M, int N, int K, bool with_split)
 
 int main()
 {
-    int M, N, K;
-    while (scanf("%d %d %d", &M, &N, &K) == 3) printf("%s\n", kind(M, N, K, true).c_str());
+    int M, N, K, r;
+    while (scanf("%d %d %d %d", &M, &N, &K, &r) == 4) printf("%s\n", kind(M, N, K, r, true).c_str());
     std::mt19937_64 gen(1);
     auto log_uniform = [&](double lo, double hi) { return (int)std::lround(lo * std::pow(hi / lo, (double)(gen() >> 11) * 0x1p-53)); };
     std::map<std::string, long> kinds;
@@ -30,7 +30,7 @@ int main()
         M = log_uniform(65, 2048);
         N = log_uniform(500, 33000);
         K = kGroup * log_uniform(1, 224);
-        ++kinds[kind(M, N, K, false)];
+        ++kinds[kind(M, N, K, i % 2 * 64, false)];
     }
     printf("kinds\n");
     for (const auto &k : kinds) printf("%ld %s\n", k.second, k.first.c_str());

@@ -9,11 +9,12 @@ CUT_CASES = [
     (5001, 640, 72, 131, "64 single"),
     (32971, 128, 0, 65, "96 single"),
     (33011, 896, 40, 67, "96 single"),
+    (18797, 2304, 0, 849, "96 single"),
     (32771, 384, 8, 97, "128 single"),
     (8001, 1152, 200, 1001, "128 single"),
     (258, 896, 8, 65, "64"),
     (258, 1920, 40, 66, "64/3"),
-    (33579, 1408, 0, 65, "96"),
+    (32358, 2176, 0, 66, "96"),
     (6407, 3200, 72, 65, "96/5"),
     (33229, 1664, 8, 97, "128"),
     (259, 9344, 200, 1747, "128/8"),
@@ -21,13 +22,13 @@ CUT_CASES = [
     (11074, 5760, 0, 131, "192/5"),
     (32930, 2176, 64, 198, "256"),
     (10762, 8320, 136, 194, "256/5"),
-    (33363, 2176, 0, 297, "128+64"),
+    (33363, 2176, 16, 297, "128+64"),
     (22143, 3328, 8, 521, "128+96"),
     (21962, 2176, 24, 521, "192+64"),
-    (18735, 2176, 0, 773, "192+96"),
+    (18735, 2176, 8, 773, "192+96"),
     (26526, 2176, 40, 577, "192+128"),
-    (32772, 2176, 8, 390, "256+64"),
+    (33213, 2688, 0, 483, "256+64"),
     (39603, 2688, 72, 463, "256+96"),
-    (33355, 2176, 0, 581, "256+128"),
+    (33355, 2176, 72, 581, "256+128"),
     (32821, 1664, 128, 683, "256+192"),
 ]

@@ -31,7 +31,7 @@ def run_driver(exe, given):
 
 @pytest.fixture(scope="module")
 def cuts(driver):
-    return run_driver(driver, "".join(f"{M} {N} {K}\n" for N, K, _, M, _ in CUT_CASES))
+    return run_driver(driver, "".join(f"{M} {N} {K} {r}\n" for N, K, r, M, _ in CUT_CASES))
 
 
 def test_the_cases_are_cut_as_they_say(cuts):
@@ -44,7 +44,8 @@ def test_every_kind_of_cut_has_a_case(cuts):
     assert met <= covered, met - covered
 
 
-@pytest.mark.parametrize("M,N,K", [(922, 14402, 128), (577, 26880, 256), (1166, 20431, 640), (700, 50257, 1024), (65, 151936, 1024), (2000, 9000, 1536)])
-def test_many_short_blocks_share_the_compute_units(driver, M, N, K):
+@pytest.mark.parametrize("M,N,K,r", [(922, 14402, 128, 0), (577, 26880, 256, 64), (1166, 20431, 640, 64), (700, 50257, 1024, 16), (65, 151936, 1024, 64),
+                                     (2000, 9000, 1536, 64), (849, 18796, 2304, 0)])
+def test_many_short_blocks_share_the_compute_units(driver, M, N, K, r):
     """Several blocks per CU and few steps each: one block per CU took 10 to 30 % longer here."""
-    assert run_driver(driver, f"{M} {N} {K}\n")[0][0].endswith(" single")
+    assert run_driver(driver, f"{M} {N} {K} {r}\n")[0][0].endswith(" single")
