@@ -343,6 +343,8 @@ __global__ __launch_bounds__(256) void fbq_transpose_f16_kernel(const uint16_t *
 // G), through fp32 partial tiles and a summing launch otherwise.
 // Bound: matrix cores; 4096 x 4096 in us, the whole square in 128-row tiles staged through registers / this: H over 2048 tokens
 // 103 / 41, the loss over 4096 rows 196 / 71 (both 34 and 69 GFLOP of the triangle: 0.84 and 0.97 PFLOP/s).
+// Other sizes leave the last round emptier and keep the gain; H with the transpose, the square / this: 3072 features, 4096 tokens
+// 152 / 66 (136 tiles); 5120, 2048 185 / 81 (378); 8192, 512 168 / 80 (946); 11008, 4096 1362 / 493 (1711).
 constexpr int kSyTile = 192, kSyWave = 96, kSyStages = 3;
 constexpr int kSySide = kSyTile * 128, kSyStep = 2 * kSySide;       // LDS bytes of one operand's rows and of a step
 constexpr int kSyBand = 6;                                          // tiles are numbered in bands of six tile rows

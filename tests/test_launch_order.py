@@ -1,6 +1,5 @@
 """What a call leaves behind when one of its launches fails, on the CPU: the process's kernel launches go to a recorder
 (tests/host/launch_recorder.cpp) that lets the n-th one fail, and nothing runs."""
-import ctypes
 import os
 import shutil
 import subprocess
@@ -63,7 +62,7 @@ def test_train_step_moves_both_masters_in_its_last_launch(recorder):
     """A step that reports an error has moved neither master, so it can be made again.  The first launch reads both (it casts
     them to fp16); of the others only the last may know them."""
     import json
-    env = dict(os.environ, LD_PRELOAD=recorder)
+    env = dict(os.environ, LD_PRELOAD=" ".join([recorder] + os.environ.get("LD_PRELOAD", "").split()))   # (in front of what is preloaded already)
     res = subprocess.run([sys.executable, "-c", CHILD, ROOT], env=env, capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
     steps = json.loads(res.stdout.split("RESULT ")[1])
