@@ -41,42 +41,15 @@
 // k (t split into two fp16 halves: t_hi + t_lo carries 22 bits of the fp32 sum), in units of
 // (tile, 32 taps) dealt out to the waves; then the waves' partial tiles meet in LDS and y is stored
 // once.  Layers that read the same activations (q/k/v, gate/up) share the launch.
-#include <hip/hip_fp16.h>
-
 #include <type_traits>
 
-#include "fbq_internal.h"
-
+#include "fbq_few_tokens.h"
 
 namespace fbq {
 
-typedef _Float16 half_t;
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t uint2_t __attribute__((ext_vector_type(2)));
-typedef uint32_t uint3_t __attribute__((ext_vector_type(3)));
-typedef uint32_t uint4_t __attribute__((ext_vector_type(4)));
-
-constexpr int kTokens = 16;          // rows of the matrix-core tile; M is padded up to it
-constexpr int kMainWaves = 8;        // waves per block of the fused kernel; they split K
 constexpr int kWaveGroups = 4;       // consecutive quantization groups a wave takes per pass over the block's tiles
 constexpr int kPassGroups = kMainWaves * kWaveGroups;   // groups one pass covers (4096 codes)
 constexpr int kMaxTiles = 4;         // 16-row tiles per block (more would not fit the register file next to the activations)
-
-__device__ __forceinline__ half2_t h2_of(uint32_t v) { return __builtin_bit_cast(half2_t, v); }
-__device__ __forceinline__ half8_t pack8(half2_t a, half2_t b, half2_t c, half2_t d)
-{
-    return half8_t{a.x, a.y, b.x, b.y, c.x, c.y, d.x, d.y};
-}
-__device__ __forceinline__ float4_t mfma(half8_t a, half8_t b, float4_t c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, long bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
-}
 
 struct SmallParams {
     const uint32_t *qw;
@@ -112,16 +85,6 @@ struct SmallGroup {
     int n_layers;
     std::conditional_t<MIX, MixSmallParams, SmallParams> layer[kMaxSmallGroup];
 };
-
-// What the weight field of pair p (0..15, in extraction order) is multiplied by; the activation that meets it is divided by it.
-template <int BITS>
-__device__ __forceinline__ constexpr float field_gain(int p)
-{
-    if (BITS == 4) return (p & 1) ? 16.0f : 1.0f;
-    if (p == 15) return 1.0f;
-    const int f = p % 5;
-    return f == 1 || f == 4 ? 8.0f : (f == 2 ? 64.0f : 1.0f);
-}
 
 // (w & mask) | 0x6400 in both halves: the masked field lands in the mantissa of 1024.0.  Plain C on
 // purpose (it becomes one v_and_or_b32): the result feeds a matrix instruction directly, and only
@@ -188,156 +151,6 @@ __device__ __forceinline__ half_t half_at(uint3_t w, int i)
 {
     const uint32_t lo = i < 2 ? w.x : (i < 4 ? w.y : w.z);
     return __builtin_bit_cast(half_t, (uint16_t)((i & 1) ? lo >> 16 : lo));
-}
-
-// ------------------------------------------------------------------ down-projection, inside the launch
-
-constexpr int kCacheSc1 = 16 | (1 << 31);   // buffer-load policy: device scope (sc1), and volatile so that a poll is never hoisted or merged
-
-constexpr int kPrepWaves = 8;      // = kMainWaves: preparing blocks and consumers are blocks of the same launch
-
-// Down-projection for up to 16 tokens: block b = (K slice, column tile of 16); the block's eight
-// waves take an eighth of the slice each.  partial[slice][token][j] = sum over the slice of
-// x[token][k] At[j][k], stored with the launch tag in the other half of its 8-byte word; token rows
-// past M repeat the last token.  The slices only exist to put more compute units to work on this
-// short, latency-bound step; the consumers add them up.
-__device__ void down_proj_block(const SmallParams &p, int b, uint32_t tag, float4_t (*red)[64])
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int c = lane & 15, q = lane >> 4;
-    const int col_tiles = (p.r + 15) / 16;
-    const int slice = b / col_tiles, j0 = (b - slice * col_tiles) * 16;
-    const int kw = p.kslice / kPrepWaves;               // a multiple of 32
-    const int kbeg = slice * p.kslice + wave * kw;
-    const int kend = min(p.K, kbeg + kw);
-    // As in the consumers: lane l fetches the piece l % 4 of row l / 4 (a load quad reads 64 contiguous bytes
-    // of one row), and lane (c, q) then takes the words of lane 4 c + q.
-    const int ld_row = lane >> 2, ld_piece = lane & 3, from_lane = (4 * c + q) * 4;
-    const uint16_t *xr = p.x + (size_t)min(ld_row, p.M - 1) * p.K + 8 * ld_piece;
-    const uint16_t *ar = p.At + (size_t)min(j0 + ld_row, p.r - 1) * p.K + 8 * ld_piece;
-    auto to_matrix_order = [&](uint4 v) __attribute__((always_inline)) {
-        const uint4_t w = {(uint32_t)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.x), (uint32_t)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.y),
-                           (uint32_t)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.z), (uint32_t)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.w)};
-        return __builtin_bit_cast(half8_t, w);
-    };
-    float4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 4
-    for (int k = kbeg; k < kend; k += 32)
-        acc = mfma(to_matrix_order(*reinterpret_cast<const uint4 *>(xr + k)), to_matrix_order(*reinterpret_cast<const uint4 *>(ar + k)), acc);
-    red[wave][lane] = acc;
-    __syncthreads();
-    if (wave == 0) {
-        float4_t sum = red[0][lane];
-#pragma unroll
-        for (int w = 1; w < kPrepWaves; ++w) sum += red[w][lane];
-        const int j = j0 + c;                           // lane (c, q) holds column j and tokens 4 q + v
-        if (j < p.r) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float partial = sum[v];        // a scalar first: bit_cast of a vector component reads the wrong element
-                const uint64_t word = (uint64_t)__builtin_bit_cast(uint32_t, partial) | ((uint64_t)tag << 32);
-                __hip_atomic_store(p.tpart + ((size_t)slice * kTokens + 4 * q + v) * p.r + j, word, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-    }
-}
-
-// Second step of the down-projection: block b adds up the K slices of columns 16 b .. 16 b + 15 for all
-// 16 token rows (one thread per sum) as soon as their words carry this launch's tag, and passes t on
-// in the same form.  Consumers then read one word per value, whatever the number of slices.
-constexpr int kSumSlices = 16;        // = the most K slices a layer can have
-__device__ void sum_slices_block(const SmallParams &p, int b, uint32_t tag)
-{
-    const int tid = threadIdx.x;
-    if (tid >= 256) return;                             // whole waves
-    const int token = tid >> 4, j = 16 * b + (tid & 15);
-    const bool mine = j < p.r;
-    const __amdgpu_buffer_rsrc_t pb = buffer_of(p.tpart, (long)p.slices * kTokens * p.r * 8);
-    float t = 0.0f;
-    bool ready = false;
-    for (int spin = 0; spin < p.spin_limit && !ready; ++spin) {
-        bool ok = true;
-        t = 0.0f;
-        // all slices are asked for at once (one device-scope round trip per poll, not one per slice);
-        // slices the layer does not have aim past the buffer: zero, no access
-        uint2_t w[kSumSlices];
-#pragma unroll
-        for (int sl = 0; sl < kSumSlices; ++sl)
-            w[sl] = __builtin_amdgcn_raw_buffer_load_b64(pb, mine && sl < p.slices ? ((sl * kTokens + token) * p.r + j) * 8 : 0x7FFFFFF0, 0, kCacheSc1);
-#pragma unroll
-        for (int sl = 0; sl < kSumSlices; ++sl) {
-            const uint32_t v = w[sl].x;
-            t += __builtin_bit_cast(float, v);               // (zero for the slices that are not there)
-            ok = ok && (!mine || sl >= p.slices || w[sl].y == tag);
-        }
-        ready = __all(ok);
-        if (!ready) __builtin_amdgcn_s_sleep(4);
-    }
-    if (!mine) return;
-    if (!ready) {                                       // the slices never showed up: the whole sum, here
-        const uint16_t *xr = p.x + (size_t)min(token, p.M - 1) * p.K, *ar = p.At + (size_t)j * p.K;
-        t = 0.0f;
-        for (int k = 0; k < p.K; ++k) t = fmaf((float)__builtin_bit_cast(half_t, xr[k]), (float)__builtin_bit_cast(half_t, ar[k]), t);
-    }
-    const uint64_t word = (uint64_t)__builtin_bit_cast(uint32_t, t) | ((uint64_t)tag << 32);
-    __hip_atomic_store(p.tsum + (size_t)token * p.r + j, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Activation operands of one group: the lane's 32 activations (four 16-byte pieces, k ascending) become
-// the four operands that meet its weight operands, pair by pair in extraction order, each divided by
-// the gain of the weight field it meets (exact unless the quotient is subnormal).  One byte
-// permutation picks the two activations of a pair out of the 16 dwords, one packed multiply scales
-// the pairs whose field has a gain.
-template <int BITS>
-__device__ __forceinline__ void arrange_operands(const uint4_t (&raw)[4], half8_t (&ops)[4])
-{
-    uint32_t d[16];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { d[4 * i] = raw[i].x; d[4 * i + 1] = raw[i].y; d[4 * i + 2] = raw[i].z; d[4 * i + 3] = raw[i].w; }
-    half2_t pr[16];
-#pragma unroll
-    for (int pi = 0; pi < 16; ++pi) {
-        int first, second;                              // the two codes of pair pi
-        if (BITS == 4) { first = 8 * (pi / 4) + pi % 4; second = first + 4; }
-        else if (pi == 15) { first = 30; second = 31; }
-        else { first = 10 * (pi / 5) + pi % 5; second = first + 5; }
-        // result bytes 0,1 <- half `first` (bytes 0..3 of the selector's view are its dword), bytes 2,3 <- half `second`
-        const uint32_t sel = (uint32_t)(2 * (first & 1)) | ((uint32_t)(2 * (first & 1) + 1) << 8) |
-                             ((uint32_t)(4 + 2 * (second & 1)) << 16) | ((uint32_t)(4 + 2 * (second & 1) + 1) << 24);
-        const half2_t both = h2_of(__builtin_amdgcn_perm(d[second / 2], d[first / 2], sel));
-        const float gain = field_gain<BITS>(pi);
-        const half_t inv = (half_t)(1.0f / gain);
-        pr[pi] = gain == 1.0f ? both : both * half2_t{inv, inv};
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t) ops[t] = pack8(pr[4 * t], pr[4 * t + 1], pr[4 * t + 2], pr[4 * t + 3]);
-}
-
-// The gains of the eight weight fields that operand t holds: against this column the scaled
-// activations sum to X = sum x.
-template <int BITS>
-__device__ __forceinline__ half8_t gain_operand(int t)
-{
-    half8_t g;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) g[e] = (half_t)field_gain<BITS>(4 * t + e / 2);
-    return g;
-}
-
-// ------------------------------------------------------------------ hand-over inside the launch
-
-
-extern "C" __device__ unsigned long long fbq_small_m_dispatch_id(void) __asm("llvm.amdgcn.dispatch.id");
-
-// Identity of this launch, the same in every block and different for every launch (also for every
-// replay of a captured graph): never zero, so a zero-filled workspace never matches.
-__device__ __forceinline__ uint32_t small_m_launch_tag()
-{
-    const uint64_t id = fbq_small_m_dispatch_id();
-    const uint64_t q = (uint64_t)__builtin_amdgcn_queue_ptr();
-    const uint32_t tag = (uint32_t)id + (uint32_t)(q >> 6) * 0x9E3779B1u;
-    return tag ? tag : 0x80000000u;
 }
 
 // ------------------------------------------------------------------ fused kernel
@@ -633,17 +446,6 @@ __global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const Smal
     }
 }
 
-static int cu_count()
-{
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-            n = 256;
-        return n;
-    }();
-    return cus;
-}
-
 template <int BITS, int T, bool BRANCH, bool TAIL>
 static void launch_instance(const SmallGroup<true> &g, bool mix, dim3 grid, hipStream_t stream)
 {
@@ -722,7 +524,7 @@ static int tiles_per_block_of(int total_tiles, int preparing_blocks, int passes)
 static int slice_length(int K)
 {
     // slices of 1024 (they only exist to put more compute units to work on a short, latency-bound step), longer where K > 16384
-    return std::max(1024, ceil_div(ceil_div(K, kMaxSlices), 32 * kPrepWaves) * (32 * kPrepWaves));
+    return std::max(1024, ceil_div(ceil_div(K, kMaxSlices), 32 * kMainWaves) * (32 * kMainWaves));
 }
 
 // What the kernel itself needs of the layers of one launch: the same instance (a branch-free layer never joins layers
@@ -732,10 +534,10 @@ static bool same_instance(const LinearArgs &a, const LinearArgs &b)
     return a.K == b.K && a.bits == b.bits && (a.r > 0) == (b.r > 0);
 }
 
-// Layers of a grouped call share the launch when they also read the same activations.
+// Layers of a grouped call share the launch when they also read the same activations and run the same kernel.
 bool small_m_group_compatible(const LinearArgs &a, const LinearArgs &b)
 {
-    return a.x == b.x && a.M == b.M && same_instance(a, b);
+    return a.x == b.x && a.M == b.M && same_instance(a, b) && few_stream(a.N, a.K) == few_stream(b.N, b.K);
 }
 
 hipError_t launch_gemv_small_m(const LinearArgs *layers, int n_layers, hipStream_t stream)
@@ -747,6 +549,9 @@ hipError_t launch_gemv_small_m(const LinearArgs *layers, int n_layers, hipStream
         if (layers[i].M < 1 || layers[i].M > kTokens || !same_instance(first, layers[i])) return hipErrorInvalidValue;
         total_tiles += ceil_div(layers[i].N, 16);
     }
+    // sets of 16 tokens side by side have activations of their own, the layers of a group the same ones
+    const bool sets = n_layers > 1 && layers[0].x != layers[1].x;
+    if (few_stream((sets ? n_layers : 1) * (long)first.N, first.K)) return launch_few_stream(layers, n_layers, stream);
     int preparing = 0;
     for (int i = 0; i < n_layers; ++i)
         if (layers[i].r > 0) preparing += ceil_div(layers[i].r, 16) * (ceil_div(layers[i].K, slice_length(layers[i].K)) + 1);

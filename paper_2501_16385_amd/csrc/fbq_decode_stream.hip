@@ -1,0 +1,554 @@
+// Decode path for a few tokens (3 <= M <= 16) of larger layers: the fused kernel of Sec. 4.3 as a stream of packed codes that
+// every compute unit reads once from end to end, the tokens riding along as the 16 rows of a matrix-core tile.
+//
+//   y[M,N] = x[M,K] . Wq[N,K]^T + t[M,r] . B[r,N],   t = x . A
+//
+// One block per CU, one launch.  A block owns a run of rows; its eight waves split K and keep the activations of their share in
+// registers, as matrix operands, while the rows go by in tiles of 16.  What a wave needs of a tile - codes, scales and zeros,
+// a unit of 4.5 KB - is copied into a ring of LDS slots of its own, three units ahead, without passing registers; a wave waits
+// for its oldest unit by count, takes it into registers and has the slot filled again before it multiplies, so requests stay under
+// way whatever the waves do, and nobody waits for anybody but once in four tiles, when the waves' partial results meet.
+// (The other kernel for these token counts asks for a pass of a block's tiles in one burst and works on it
+// when all is there, one block after the other.)
+//
+// Products.  A code field stays where it is in the packed word, masked: as an fp16 number it is the subnormal code x gain x 2^-24,
+// which the matrix cores multiply exactly (measured); activations that meet a gain are divided by it.  So no offset rides on
+// the sums, and per two codes there is one instruction.  The zero points of a unit are one more product,
+// sums of activations [token][group] times -s z [group][row], in fp32 on the matrix core.
+//
+// Down-projection.  The first blocks of a layer do it, slices of K first and their sums behind them, and are gone after some 4 us; the
+// rows' blocks that start in their place own fewer rows.  (As a job on the rows' own blocks, which have the activations
+// anyway, t came 2 us later: 14336 x 4096, r = 64, 8 tokens 13.5 us with blocks of their own and 14.8 without.)
+//
+// What bounds it: memory, at about 6 TB/s over a long stream, and in front of it 2.7 us for the activations: launch, first round
+// trip, change of order (K up to 8192: once; beyond, once a pass and four tiles, 1.5 us each with little under way).  us, the other kernel
+// and this one: 28672 x 8192, INT4, r = 128, 16 tokens 49.6 / 30.8 (r = 0: 44.3 / 28.5, of which launch 2, activations 3.4);
+// 13824 x 5120, r = 64, 8 tokens 21 / 15.6; two layers of 11008 x 4096, INT3, r = 64, 8 tokens 19.9 / 15.3; 5120 x 13824, INT3, r = 128, 48 tokens
+// as three sets 41 / 34.6.  Tried: four waves with twice the registers (one wave per SIMD issues too slowly: 16 us where this takes 14);
+// activations by way of the ring as well (a branch more per unit and twice the code: 15.1 against 13.9); the next
+// pass's activations asked for while one is worked on (the wait for them is one for the ring behind them: 38.8 against 33.1); rows dealt
+// out in sweeps over the layer instead of runs (35.8 against 33.3).  Instances must not spill: scratch memory alone costs a launch 2 us.
+#include <type_traits>
+
+#include "fbq_few_tokens.h"
+
+namespace fbq {
+
+constexpr int kUnitGroups = 4;       // quantization groups of a unit: 16 rows x 4 groups, what one ring slot holds
+constexpr int kPassGroups = kMainWaves * kUnitGroups;
+constexpr int kRing = 3;             // ring slots per wave
+constexpr int kRoundTiles = 4;       // row tiles between two meetings of the waves
+
+constexpr int kUnitBytes = 16 * 256 + 2 * 256;               // codes (16 bytes per 32, used up or not), scales, zeros
+constexpr int kUnitLoads = 6;
+constexpr int kAreaAt = kMainWaves * kRing * kUnitBytes;         // 4 KB per wave: a group of activations changing order; partial results
+constexpr int kTapAt = kAreaAt + kMainWaves * 4096;
+constexpr int kTapBytes = kMaxRank / 32 * 2048;              // t as operands: per 32 taps 1 KB of high halves, 1 KB of low ones
+constexpr int kXSumAt = kTapAt + kTapBytes;   // [wave][group][token] sums of the activations
+constexpr int kLdsBytes = kXSumAt + kMainWaves * kUnitGroups * 64;   // (a unit's at a time)
+static_assert(kLdsBytes <= 160 * 1024, "a block's buffers must fit the CU's LDS");
+static_assert(kRoundTiles * 1024 <= 4096 && 2 * kRoundTiles == kMainWaves, "a wave's area holds its part of a round; every wave ends up with one tile of two rounds");
+
+struct StreamParams {
+    const uint32_t *qw;
+    const uint16_t *scales;
+    const uint16_t *zeros;
+    const uint16_t *At;    // [r][K]
+    const uint16_t *Bt;    // [N][r]
+    const uint16_t *x;     // [M][K]
+    uint16_t *y;           // [M][N]
+    uint64_t *tpart;       // workspace: [slices][16][r] words {fp32 partial sum of t = x.A over one K slice, launch tag}
+    uint64_t *tsum;        // workspace: [16][r] words {t, launch tag}: the slices added up
+    const uint16_t *mix_with;   // [M][N]
+    uint16_t *mix_out;          // null: none
+    int M, N, K, r;
+    int row_words, G;
+    int slices, kslice;    // down-projection: number of K slices and their length (a multiple of 256)
+    int down_blocks;       // blocks at the start of this layer's grid row that do its down-projection, slice by slice ...
+    int sum_blocks;        // ... and the blocks after them that add the slices up (16 columns each)
+    int early, rows, late_rows;   // the first blocks behind those, `early` of them, own `rows` output rows each, the others fewer
+    int passes, share;     // passes over K, and the groups a wave takes in each
+    int spin_limit;        // polls for t before a wave computes it itself; negative: at once (test hook)
+};
+struct StreamGroup {
+    StreamParams layer[kMaxSmallGroup];
+};
+
+// The four matrix operands of a lane's 32 codes: every field stays where it is, masked out, i.e. it is the subnormal fp16
+// number code x gain x 2^-24, which the matrix cores multiply exactly (measured).  Pair order (also the order of the
+// arranged activations): INT4 word j -> codes (8j+f, 8j+f+4), f = 0..3;  INT3 word j -> codes (10j+f, 10j+f+5), f = 0..4,
+// and codes (30, 31) last.
+template <int BITS>
+__device__ __forceinline__ void code_operands(const uint4_t w, half8_t (&b)[4])
+{
+    const uint32_t wd[4] = {w.x, w.y, w.z, w.w};
+    if constexpr (BITS == 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t lo = wd[j], hi = wd[j] >> 8;
+            b[j] = pack8(h2_of(lo & 0x000F000Fu), h2_of(lo & 0x00F000F0u), h2_of(hi & 0x000F000Fu), h2_of(hi & 0x00F000F0u));
+        }
+    } else {
+        half2_t d[16];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const uint32_t lo = wd[j], hi = wd[j] >> 9;
+            d[5 * j + 0] = h2_of(lo & 0x00070007u);
+            d[5 * j + 1] = h2_of(lo & 0x00380038u);
+            d[5 * j + 2] = h2_of(lo & 0x01C001C0u);
+            d[5 * j + 3] = h2_of(hi & 0x00070007u);
+            d[5 * j + 4] = h2_of(hi & 0x00380038u);
+        }
+        d[15] = h2_of(((wd[0] >> 15) & 0x00010001u) | (((wd[1] >> 14) & 0x00020002u) | ((wd[2] >> 13) & 0x00040004u)));
+#pragma unroll
+        for (int t = 0; t < 4; ++t) b[t] = pack8(d[4 * t], d[4 * t + 1], d[4 * t + 2], d[4 * t + 3]);
+    }
+}
+
+// ------------------------------------------------------------------ fused kernel
+
+// BITS: 3 or 4.  C: units of weights a wave takes per tile and pass (4 C groups).  MULTI: several passes over K.  XL: loads of four token rows a group of activations takes.
+template <int BITS, int C, int XL, bool MULTI>
+__global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void fbq_few_stream_kernel(const StreamGroup g)
+{
+    constexpr int kPiece = BITS == 4 ? 16 : 12;         // bytes of 32 codes
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kLdsBytes];
+
+    const auto p = g.layer[blockIdx.x];
+    // (all of them before the first branch: left alone, the compiler fetches only what the branch needs first)
+    asm volatile("" :: "s"(p.qw), "s"(p.scales), "s"(p.zeros), "s"(p.x), "s"(p.y), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.row_words), "s"(p.G), "s"(p.early), "s"(p.rows), "s"(p.late_rows), "s"(p.down_blocks), "s"(p.sum_blocks));
+    asm volatile("" :: "s"(p.Bt), "s"(p.At), "s"(p.tpart), "s"(p.tsum), "s"(p.r), "s"(p.passes), "s"(p.share), "s"(p.spin_limit));
+    const uint32_t tag = small_m_launch_tag();
+    // The first blocks of a grid row do the layer's down-projection.  They come first in dispatch order, so whoever waits for their
+    // words waits for blocks that are already running.
+    if ((int)blockIdx.y < p.down_blocks + p.sum_blocks) {
+        if ((int)blockIdx.y < p.down_blocks) down_proj_block(p, blockIdx.y, tag, reinterpret_cast<float4_t (*)[64]>(lds));
+        else sum_slices_block(p, blockIdx.y - p.down_blocks, tag);
+        return;
+    }
+    const int block = blockIdx.y - p.down_blocks - p.sum_blocks;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, q = lane >> 4;
+    // which eighth of a pass is the wave's: turned from block to block, so that the CUs of an XCD do not all ask for the same activations at once
+    const int kw = (wave + block + (block >> 3)) & (kMainWaves - 1);
+    const int row0 = min(block < p.early ? block * p.rows : p.early * p.rows + (block - p.early) * p.late_rows, p.N);
+    const int row_end = min(p.N, row0 + (block < p.early ? p.rows : p.late_rows));
+    const int tiles = (row_end - row0 + 15) >> 4;
+    if (tiles == 0) return;                             // a layer with fewer blocks than the widest
+    const int passes = MULTI ? p.passes : 1;
+    const int row_bytes = p.row_words * 4;
+    constexpr int kNowhere = 0x40000000;                // beyond every buffer
+    constexpr int kFar = 0x20000000;                    // beyond x and A, also on top of it
+
+    // Rows past the block's own are outside the descriptors: zeros, without a memory access.  The range check is per dword, so the
+    // counts of scales and zeros are rounded up to whole dwords (the half behind an odd-sized array is masked out below).
+    const __amdgpu_buffer_rsrc_t qbuf = buffer_of(p.qw, (long)row_end * row_bytes);
+    const __amdgpu_buffer_rsrc_t sbuf = buffer_of(p.scales, ((long)row_end * p.G * 2 + 3) & ~3L);
+    const __amdgpu_buffer_rsrc_t zbuf = buffer_of(p.zeros, ((long)row_end * p.G * 2 + 3) & ~3L);
+
+    unsigned char *const ring = lds + wave * (kRing * kUnitBytes);
+    unsigned char *const slab = lds + kAreaAt + kw * 4096;
+    float4_t *const sums = reinterpret_cast<float4_t *>(slab);
+    const uint32_t ring_lds = lds_offset(ring);
+
+    // A unit's copies.  Copy j of the codes moves rows 4 j .. 4 j + 3, 16 lanes and up to 256 contiguous bytes a row; row n's piece i
+    // (32 codes) lies at position i ^ n of it, so that the 16 rows of a matrix operand touch every bank once.  Scales and zeros: the
+    // aligned dwords that hold the four groups' halves, four lanes a row.  Groups past the wave's share aim nowhere.
+    int qoff[4], qoff_last[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int row = 4 * j + q, piece = c ^ row;
+        qoff[j] = row * row_bytes + piece * kPiece;
+        qoff_last[j] = (piece >> 2) < p.share - kUnitGroups * (C - 1) ? qoff[j] : kNowhere;
+    }
+    const int soff = (lane >> 2) * p.G, sdword = 4 * min(lane & 3, 2);
+    auto first_group = [&](int pass) __attribute__((always_inline)) { return (pass * kMainWaves + kw) * p.share; };
+    auto issue_unit = [&](int slot, int tile, int chunk, int pass) __attribute__((always_inline)) {
+        const int g0 = first_group(pass) + kUnitGroups * chunk, n0 = row0 + 16 * tile;
+        const int base = n0 * row_bytes + g0 * (4 * kPiece);
+        const uint32_t dst = ring_lds + slot * kUnitBytes;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int off = (C == 1 || chunk == C - 1 ? qoff_last[j] : qoff[j]) + base;
+            if constexpr (BITS == 4) copy16_to_lds(qbuf, off, 0, dst + j * 1024);
+            else copy12_to_lds(qbuf, off, 0, dst + j * 1024);
+        }
+        const int so = ((soff + n0 * p.G + g0) * 2 & ~3) + sdword;
+        copy4_to_lds(sbuf, so, 0, dst + 4096);
+        copy4_to_lds(zbuf, so, 0, dst + 4096 + 256);
+    };
+    // The sequence of units: rounds of kRoundTiles tiles, in each the passes over K, in each the tiles, in each the chunks of K.
+    int i_tile = 0, i_first = 0, i_end = min(kRoundTiles, tiles), i_chunk = 0, i_pass = 0, i_slot = 0;
+    int ahead = 0;                                      // units under way or landed and not yet used
+    auto issue_next = [&]() __attribute__((always_inline)) {
+        if (i_first >= tiles) return;
+        issue_unit(i_slot, i_tile, i_chunk, i_pass);
+        ++ahead;
+        i_slot = i_slot + 1 == kRing ? 0 : i_slot + 1;
+        if (++i_chunk < C) return;
+        i_chunk = 0;
+        if (++i_tile < i_end) return;
+        i_tile = i_first;
+        if (++i_pass < passes) return;
+        i_pass = 0;
+        i_first = i_tile = i_end;
+        i_end = min(i_first + kRoundTiles, tiles);
+    };
+    // The oldest unit has landed: at most the younger ones' copies are under way.  (Other loads only make the wait longer.)
+    auto wait_unit = [&]() __attribute__((always_inline)) {
+        static_assert(kRing == 3 && kUnitLoads == 6, "the counts below");
+        if (ahead >= 3) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+        else if (ahead == 2) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    auto block_barrier = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+    const int tap_steps = (p.r + 31) >> 5;
+    constexpr int kHeld = 4;             // operands of the rows of B^T of the wave's tile among the first eight, asked for early
+    half8_t ubf[kHeld];                                 // (outside the loops, where a wait for them would be one for the ring)
+    const __amdgpu_buffer_rsrc_t bbuf = buffer_of(p.Bt, (long)row_end * p.r * 2);
+    auto taps = [&](int row, int js) __attribute__((always_inline)) {
+        const int j = js * 32 + q * 8;
+        return __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(bbuf, j < p.r ? (row * p.r + j) * 2 : kNowhere, 0, 0));
+    };
+    issue_next();                                       // the first tile's weights are on their way before the activations
+#pragma unroll
+    for (int k = 0; k < kHeld; ++k) ubf[k] = half8_t{};
+    if (C == 1 && tap_steps > 0) {
+#pragma unroll
+        for (int k = 0; k < kHeld; ++k) ubf[k] = taps(row0 + wave * 16 + c, k);
+    }
+
+    const float4_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+    half8_t xa[C][kUnitGroups][4];
+    float xs[C];                                        // sums of the activations of token c and a unit's group q
+    unsigned char *const xsum = lds + kXSumAt + kw * (kUnitGroups * 64);
+    uint32_t smask[C][2];                               // which halves of a unit's scales belong to groups of the wave's share
+    int valid[C];                                       // how many of a unit's groups do
+
+    // The wave's activations of a pass: loaded a group at a time, four token rows per load (16 lanes, 256 contiguous bytes a row), passed
+    // through LDS into operand order.  kWindow groups are under way at a time.
+    const __amdgpu_buffer_rsrc_t xbuf = buffer_of(p.x, (long)p.M * p.K * 2);
+    constexpr int kWindow = C == 1 || XL < 4 ? 4 : 2;
+    uint4_t xraw[kWindow][XL];
+    // (Addresses are worked out where they are used: kept from pass to pass, they would take the registers that the operands need.)
+    auto afresh = [](int v) __attribute__((always_inline)) { asm volatile("" : "+v"(v)); return v; };
+    auto request_group = [&](int pass, int i, int c, int q) __attribute__((always_inline)) {
+        const int group = first_group(pass) + i;
+        const int at = i < p.share && group < p.G ? group * 256 + c * 16 : kFar;
+#pragma unroll
+        for (int k = 0; k < XL; ++k) xraw[i % kWindow][k] = __builtin_amdgcn_raw_buffer_load_b128(xbuf, (4 * k + q < p.M ? (4 * k + q) * p.K * 2 : kNowhere) + at, 0, 0);
+    };
+    auto request_x = [&](int pass) __attribute__((always_inline)) {
+        const int l = afresh(lane);
+#pragma unroll
+        for (int i = 0; i < kWindow; ++i) request_group(pass, i, l & 15, l >> 4);
+    };
+    auto arrange_x = [&](int pass) __attribute__((always_inline)) {
+        const int l = afresh(lane), c = l & 15, q = l >> 4;
+#pragma unroll
+        for (int ch = 0; ch < C; ++ch) {
+#pragma unroll
+            for (int gi = 0; gi < kUnitGroups; ++gi) {
+                const int n = ch * kUnitGroups + gi;
+                uint4_t mine[4];
+#pragma unroll
+                for (int i = 0; i < XL; ++i) *reinterpret_cast<uint4_t *>(slab + (4 * i + q) * 256 + ((c ^ (4 * i + q)) << 4)) = xraw[n % kWindow][i];
+                if (n + kWindow < C * kUnitGroups) request_group(pass, n + kWindow, c, q);
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int i = 0; i < 4; ++i) mine[i] = *reinterpret_cast<const uint4_t *>(slab + c * 256 + (((4 * q + i) ^ c) << 4));
+                __builtin_amdgcn_wave_barrier();
+                arrange_operands<BITS>(mine, xa[ch][gi]);
+                float4_t sx = zero4;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) sx = mfma(xa[ch][gi][t], gain_operand<BITS>(t), sx);
+                if (c == 0) *reinterpret_cast<float4_t *>(xsum + gi * 64 + q * 16) = sx * 0x1p-24f;
+            }
+            __builtin_amdgcn_wave_barrier();
+            const float4_t *const row = reinterpret_cast<const float4_t *>(xsum + q * 64 + (c & 12) * 4);   // (as it was stored: the compiler must not take these for unrelated)
+            const float4_t four = *row;
+            xs[ch] = c & 2 ? (c & 1 ? four.w : four.z) : (c & 1 ? four.y : four.x);
+            valid[ch] = min(p.share, p.G - first_group(pass)) - kUnitGroups * ch;
+            smask[ch][0] = (valid[ch] > 0 ? 0xFFFFu : 0u) | (valid[ch] > 1 ? 0xFFFF0000u : 0u);
+            smask[ch][1] = (valid[ch] > 2 ? 0xFFFFu : 0u) | (valid[ch] > 3 ? 0xFFFF0000u : 0u);
+        }
+    };
+    // Eight words {t, tag} of this wave's 32 taps.
+    const __amdgpu_buffer_rsrc_t tbuf = buffer_of(p.tsum, (long)kTokens * p.r * 8);
+    uint4_t tw[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) tw[k] = uint4_t{0, 0, 0, 0};
+    bool asked = false;
+    auto ask_t = [&]() __attribute__((always_inline)) {
+        const int l = afresh(lane), j = 32 * wave + 8 * (l >> 4);
+        const int off = (l & 15) < 4 * XL && j < p.r ? ((l & 15) * p.r + j) * 8 : kNowhere;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tw[k] = __builtin_amdgcn_raw_buffer_load_b128(tbuf, off + 16 * k, 0, kCacheSc1);
+    };
+    int u_slot = 0;
+    bool start = true;
+    float4_t mine = zero4;                              // the wave's tile: number `wave` of the eight of two rounds
+    for (int first_tile = 0;;) {
+        const int nt = min(kRoundTiles, tiles - first_tile);
+        const int eight = first_tile & ~(kMainWaves - 1);   // first tile of the eight
+        for (int pass = 0; pass < passes; ++pass) {
+            if (start || MULTI) {
+                float4_t kept[kRoundTiles];             // the area holds partial results of the passes before
+                if (MULTI && pass > 0) {
+#pragma unroll
+                    for (int ti = 0; ti < kRoundTiles; ++ti) kept[ti] = sums[ti * 64 + lane];
+                    asm volatile("" ::: "memory");  // (the same LDS under another type: the compiler keeps the order)
+                }
+                request_x(pass);
+                arrange_x(pass);
+                if (MULTI && pass > 0) {
+                    asm volatile("" ::: "memory");
+#pragma unroll
+                    for (int ti = 0; ti < kRoundTiles; ++ti) sums[ti * 64 + lane] = kept[ti];
+                }
+                start = false;
+            }
+            while (ahead < kRing && i_first < tiles) issue_next();
+            for (int ti = 0; ti < nt; ++ti) {
+                float4_t acc = zero4;
+                // the row's first half may be the upper one of its dword
+                const int odd = ((row0 + (first_tile + ti) * 16 + c) * p.G + first_group(pass)) & 1;   // (chunks are four groups apart)
+#pragma unroll
+                for (int ch = 0; ch < C; ++ch) {
+                    wait_unit();
+                    const unsigned char *const unit = ring + u_slot * kUnitBytes;
+                    uint4_t w[kUnitGroups];
+#pragma unroll
+                    for (int gi = 0; gi < kUnitGroups; ++gi) w[gi] = *reinterpret_cast<const uint4_t *>(unit + c * 256 + (((4 * gi + q) ^ c) << 4));
+                    const uint4_t s4 = *reinterpret_cast<const uint4_t *>(unit + 4096 + c * 16);
+                    const half_t sq = *reinterpret_cast<const half_t *>(unit + 4096 + c * 16 + (odd + q) * 2), zq = *reinterpret_cast<const half_t *>(unit + 4096 + 256 + c * 16 + (odd + q) * 2);
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // in registers: the slot may be filled again
+                    u_slot = u_slot + 1 == kRing ? 0 : u_slot + 1;
+                    --ahead;
+                    issue_next();
+                    if (C == 1 && ti == nt - 1 && pass == passes - 1 && first_tile + kRoundTiles >= tiles && wave < tap_steps && p.spin_limit > 0) {
+                        ask_t();                        // while the last tile is worked on
+                        asked = true;
+                    }
+                    const uint32_t s01 = __builtin_amdgcn_alignbit(s4.y, s4.x, 16 * odd) & smask[ch][0], s23 = __builtin_amdgcn_alignbit(s4.z, s4.y, 16 * odd) & smask[ch][1];
+                    // the zero points of all four groups are one more product: sums of activations [token][group] times -s z [group][row]
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[ch], q < valid[ch] ? -(float)sq * (float)zq : 0.0f, acc, 0, 0, 0);
+#pragma unroll
+                    for (int gi = 0; gi < kUnitGroups; ++gi) {
+                        half8_t b[4];
+                        code_operands<BITS>(w[gi], b);
+                        float4_t D = zero4;
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) D = mfma(xa[ch][gi][t], b[t], D);
+                        const half2_t sh = h2_of(gi < 2 ? s01 : s23);
+                        const float s = (float)(gi & 1 ? sh.y : sh.x);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[v] = fmaf(s, D[v], acc[v]);
+                    }
+                }
+                float4_t *const slot = sums + ti * 64 + lane;
+                *slot = pass == 0 ? acc * 0x1p24f : *slot + acc * 0x1p24f;
+            }
+        }
+
+        // The waves meet; tile ti of the round goes to wave ti or, in the second round of two, ti + 4.
+        const bool last = first_tile + kRoundTiles >= tiles;
+        const bool store = last || first_tile != eight;
+        // With the results to be stored: t, 32 taps a wave, lane (c, q) eight of them for token c, as two fp16 halves (22 bits) in
+        // operand order: [32 taps][hi, lo][8 taps][token].  Should the tags not turn up, the lane computes its eight values itself.
+        half8_t late[kHeld];
+        if (store && p.r > 0) {
+            const int my_row = row0 + (eight + wave) * 16 + c;
+            if (C > 1 || eight > 0) {
+#pragma unroll
+                for (int k = 0; k < kHeld; ++k) late[k] = taps(my_row, k);
+            }
+            if (wave < tap_steps) {
+                if (!asked && p.spin_limit > 0) ask_t();
+                const int l = afresh(lane), c = l & 15, j = 32 * wave + 8 * (l >> 4);
+                const bool mine_too = c < 4 * XL && j < p.r;
+                bool ready = false;
+#pragma unroll 1
+                for (int spin = 0; spin < p.spin_limit; ++spin) {
+                    bool ok = true;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) ok = ok && (!mine_too || (tw[k].y == tag && tw[k].w == tag));
+                    ready = __all(ok);
+                    if (ready) break;
+                    ask_t();
+                }
+                __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0): no load that the compiler would wait for in the tile loop
+                half8_t hi, lo;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const uint32_t word = e & 1 ? tw[e / 2].z : tw[e / 2].x;
+                    float t = __builtin_bit_cast(float, word);
+                    if (!ready && mine_too) {
+                        const uint16_t *xr = p.x + (size_t)min(c, p.M - 1) * p.K, *ar = p.At + (size_t)(j + e) * p.K;
+                        t = 0.0f;
+#pragma unroll 1
+                        for (int i = 0; i < p.K; ++i) t = fmaf((float)__builtin_bit_cast(half_t, xr[i]), (float)__builtin_bit_cast(half_t, ar[i]), t);
+                    }
+                    hi[e] = (half_t)t;
+                    lo[e] = (half_t)(t - (float)hi[e]);
+                }
+                *reinterpret_cast<half8_t *>(lds + kTapAt + wave * 2048 + l * 16) = hi;
+                *reinterpret_cast<half8_t *>(lds + kTapAt + wave * 2048 + 1024 + l * 16) = lo;
+            }
+            asked = false;
+        }
+        block_barrier();
+        const int mt = wave - (first_tile - eight);
+        if (mt >= 0 && mt < nt) {                       // wave-uniform
+            const float4_t *const part = reinterpret_cast<const float4_t *>(lds + kAreaAt) + mt * 64 + afresh(lane);
+            mine = part[0];
+#pragma unroll
+            for (int k = 1; k < kMainWaves; ++k) mine += part[k * 256];
+        }
+        if (store && eight + wave < min(tiles, first_tile + kRoundTiles)) {   // wave-uniform
+            const int l = afresh(lane), c = l & 15, q = l >> 4, my_row = row0 + (eight + wave) * 16 + c;
+            auto fold = [&](int js, half8_t bf) __attribute__((always_inline)) {
+                const unsigned char *const at = lds + kTapAt + js * 2048 + l * 16;
+                float4_t d = mfma(*reinterpret_cast<const half8_t *>(at), bf, zero4);
+                mine += mfma(*reinterpret_cast<const half8_t *>(at + 1024), bf, d);
+            };
+#pragma unroll
+            for (int k = 0; k < kHeld; ++k)
+                if (k < tap_steps) fold(k, C == 1 && eight == 0 ? ubf[k] : late[k]);
+            if (tap_steps > kHeld) {
+#pragma unroll
+                for (int k = 0; k < kHeld; ++k) late[k] = taps(my_row, kHeld + k);
+#pragma unroll
+                for (int k = 0; k < kHeld; ++k)
+                    if (kHeld + k < tap_steps) fold(kHeld + k, late[k]);
+            }
+            // lane (c, q) holds output row my_row and tokens 4 q + v
+            if (my_row < row_end) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int m = 4 * q + v;
+                    if (m < p.M) {
+                        const half_t y = (half_t)mine[v];
+                        p.y[(size_t)m * p.N + my_row] = __builtin_bit_cast(uint16_t, y);
+                        if (p.mix_out) {
+                            const float with = (float)__builtin_bit_cast(half_t, p.mix_with[(size_t)m * p.N + my_row]);
+                            p.mix_out[(size_t)m * p.N + my_row] = __builtin_bit_cast(uint16_t, (half_t)((float)y - ((float)y - with) * 0.5f));
+                        }
+                    }
+                }
+            }
+        }
+        if (last) return;
+        if (store) __builtin_amdgcn_s_waitcnt(0x0F70);
+        block_barrier();                                // (the partial results, and t, may be written again)
+        first_tile += kRoundTiles;
+    }
+}
+
+template <int BITS, int C, bool MULTI>
+static void launch_instance(const StreamGroup &g, bool half, dim3 grid, hipStream_t stream)
+{
+    if (half) hipLaunchKernelGGL((fbq_few_stream_kernel<BITS, C, 2, MULTI>), grid, dim3(64 * kMainWaves), 0, stream, g);
+    else hipLaunchKernelGGL((fbq_few_stream_kernel<BITS, C, 4, MULTI>), grid, dim3(64 * kMainWaves), 0, stream, g);
+}
+template <int BITS>
+static hipError_t launch_bits(const StreamGroup &g, int chunks, bool half, dim3 grid, hipStream_t stream)
+{
+    const bool multi = g.layer[0].passes > 1;
+    if (chunks > 1) launch_instance<BITS, 2, false>(g, half, grid, stream);
+    else if (multi) launch_instance<BITS, 1, true>(g, half, grid, stream);
+    else launch_instance<BITS, 1, false>(g, half, grid, stream);
+    return hipGetLastError();
+}
+
+// Length of a K slice of the down-projection: slices only exist to put more CUs to work on a short, latency-bound step, and every block
+// of it is a CU that starts late on its rows (28672 x 8192, r = 128, 16 tokens: up to 32 such blocks 32.7 us, 64 30.7, 128 30.8).
+constexpr int kMaxDownBlocks = 64;
+static int slice_length(int K, int r)
+{
+    constexpr int kStep = 32 * kMainWaves;
+    int len = std::max(1024, ceil_div(ceil_div(K, kSumSlices), kStep) * kStep);
+    while (ceil_div(r, 16) * ceil_div(K, len) > kMaxDownBlocks) len += kStep;
+    return len;
+}
+static int preparing_blocks(const LinearArgs &a) { return a.r > 0 ? ceil_div(a.r, 16) * (ceil_div(a.K, slice_length(a.K, a.r)) + 1) : 0; }
+
+// What a CU streams in while the blocks of a down-projection run: at 23 KB per us and CU, 5 us.
+constexpr int kLateBytes = 115000;
+
+hipError_t launch_few_stream(const LinearArgs *layers, int n_layers, hipStream_t stream)
+{
+    const LinearArgs &first = layers[0];
+    long total_rows = 0;
+    int most = 0;
+    for (int i = 0; i < n_layers; ++i) {
+        total_rows += layers[i].N;
+        most = std::max(most, layers[i].M);
+    }
+    const int G = first.K / kGroup, cus = cu_count();
+    const int chunks = G > kPassGroups && G <= 2 * kPassGroups ? 2 : 1;
+    const int passes = ceil_div(G, chunks * kPassGroups), share = ceil_div(G, kMainWaves * passes);
+    // Blocks run one per CU, in dispatch order: every layer's down-projection first, then rows.  Those that find no CU free start when
+    // the down-projection's are done; they own as many rows less as a CU streams in that time - or there are none, where that is all
+    // (two layers of 11008 x 4096 at 8 tokens, by the bytes allowed for: 40000 17.4 us, 70000 15.3, 100000 14.8, 130000 15.6).
+    int preparing = 0;
+    for (int i = 0; i < n_layers; ++i) preparing += preparing_blocks(layers[i]);
+    const int behind = std::max(1, kLateBytes / ((int)row_words(first.K, first.bits) * 4 + 4 * G));
+    auto owners = [&](const LinearArgs &a, int rows) { return ceil_div(a.N, rows); };
+    int rows = (int)((total_rows + (long)preparing * behind + cus - 1) / cus);
+    bool late = preparing > 0 && rows > behind;
+    int late_rows = rows - behind;
+    if (!late) {
+        const int free_cus = std::max(cus - preparing, cus / 2);
+        for (rows = std::max(16, (int)((total_rows + free_cus - 1) / free_cus));; ++rows) {
+            int blocks = 0;
+            for (int i = 0; i < n_layers; ++i) blocks += owners(layers[i], rows);
+            if (blocks <= std::max(free_cus, n_layers)) break;
+        }
+        if (rows > 16 && rows <= 32) rows = 32;
+        late_rows = rows;
+    }
+    // (where the activations are loaded anew for every round of four tiles: no round for a few rows)
+    const int whole = late ? 64 * ceil_div(late_rows, 64) : 0;
+    if (late && passes > 1 && rows > whole && preparing < cus) {
+        const int more = (int)((total_rows - (long)(cus - preparing) * whole + preparing - 1) / preparing);
+        if (more <= whole) { rows = whole; late_rows = std::max(more, 1); }
+    }
+    int in_order = cus;                                  // blocks of a grid row that start at once
+    for (; late && in_order > 1; --in_order) {
+        int started = 0;
+        for (int i = 0; i < n_layers; ++i) started += std::min(in_order, preparing_blocks(layers[i]) + owners(layers[i], rows));
+        if (started <= cus) break;
+    }
+    StreamGroup g;
+    int widest = 0;
+    for (int i = 0; i < n_layers; ++i) {
+        const LinearArgs &a = layers[i];
+        StreamParams &p = g.layer[i];
+        p.qw = a.qw; p.scales = a.scales; p.zeros = a.zeros; p.At = a.At; p.Bt = a.Bt; p.x = a.x; p.y = a.y;
+        p.tpart = (uint64_t *)a.workspace;               // each layer's own partial sums of t ...
+        p.tsum = p.tpart + (size_t)kSumSlices * kTokens * a.r;   // ... and their sums
+        p.mix_with = a.mix_with; p.mix_out = a.mix_out;
+        p.M = a.M; p.N = a.N; p.K = a.K; p.r = a.r;
+        p.row_words = (int)row_words(a.K, a.bits);
+        p.G = G;
+        p.kslice = slice_length(a.K, a.r);
+        p.slices = ceil_div(a.K, p.kslice);
+        p.down_blocks = a.r > 0 ? ceil_div(a.r, 16) * p.slices : 0;
+        p.sum_blocks = a.r > 0 ? ceil_div(a.r, 16) : 0;
+        p.rows = rows;
+        p.late_rows = late_rows;
+        p.early = late ? std::max(0, std::min(owners(a, rows), in_order - preparing_blocks(a))) : owners(a, rows);
+        const int left = std::max(0, a.N - p.early * rows);
+        p.passes = passes; p.share = share;
+        p.spin_limit = spin_limit();
+        widest = std::max(widest, p.down_blocks + p.sum_blocks + p.early + ceil_div(left, p.late_rows));
+    }
+    for (int i = n_layers; i < kMaxSmallGroup; ++i) g.layer[i] = g.layer[0];   // never indexed: grid.x stops at n_layers
+    const dim3 grid(n_layers, widest);
+    return first.bits == 4 ? launch_bits<4>(g, chunks, most <= 8, grid, stream) : launch_bits<3>(g, chunks, most <= 8, grid, stream);
+}
+
+}  // namespace fbq

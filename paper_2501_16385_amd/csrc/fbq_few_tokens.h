@@ -1,0 +1,218 @@
+// What the two kernels for 3 to 16 tokens share (device code): matrix-core helpers, the order of the activations, the
+// down-projection inside the launch and its hand-over.
+#ifndef FBQ_FEW_TOKENS_H
+#define FBQ_FEW_TOKENS_H
+
+#include <hip/hip_fp16.h>
+
+#include "fbq_internal.h"
+#include "fbq_lds_copy.h"
+
+namespace fbq {
+
+typedef _Float16 half_t;
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t uint2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t uint3_t __attribute__((ext_vector_type(3)));
+typedef uint32_t uint4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kTokens = 16;          // rows of the matrix-core tile; M is padded up to it
+constexpr int kMainWaves = 8;        // waves per block; they split K
+constexpr int kSumSlices = 16;       // the most K slices a layer's down-projection can have
+
+__device__ __forceinline__ half2_t h2_of(uint32_t v) { return __builtin_bit_cast(half2_t, v); }
+__device__ __forceinline__ half8_t pack8(half2_t a, half2_t b, half2_t c, half2_t d)
+{
+    return half8_t{a.x, a.y, b.x, b.y, c.x, c.y, d.x, d.y};
+}
+__device__ __forceinline__ float4_t mfma(half8_t a, half8_t b, float4_t c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+}
+
+// What the weight field of pair p (0..15, in extraction order) is multiplied by; the activation that meets it is divided by it.
+template <int BITS>
+__device__ __forceinline__ constexpr float field_gain(int p)
+{
+    if (BITS == 4) return (p & 1) ? 16.0f : 1.0f;
+    if (p == 15) return 1.0f;
+    const int f = p % 5;
+    return f == 1 || f == 4 ? 8.0f : (f == 2 ? 64.0f : 1.0f);
+}
+
+// Activation operands of one group: the lane's 32 activations (four 16-byte pieces, k ascending) become
+// the four operands that meet its weight operands, pair by pair in extraction order, each divided by
+// the gain of the weight field it meets (exact unless the quotient is subnormal).  One byte
+// permutation picks the two activations of a pair out of the 16 dwords, one packed multiply scales
+// the pairs whose field has a gain.
+template <int BITS>
+__device__ __forceinline__ void arrange_operands(const uint4_t (&raw)[4], half8_t (&ops)[4])
+{
+    uint32_t d[16];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { d[4 * i] = raw[i].x; d[4 * i + 1] = raw[i].y; d[4 * i + 2] = raw[i].z; d[4 * i + 3] = raw[i].w; }
+    half2_t pr[16];
+#pragma unroll
+    for (int pi = 0; pi < 16; ++pi) {
+        int first, second;                              // the two codes of pair pi
+        if (BITS == 4) { first = 8 * (pi / 4) + pi % 4; second = first + 4; }
+        else if (pi == 15) { first = 30; second = 31; }
+        else { first = 10 * (pi / 5) + pi % 5; second = first + 5; }
+        // result bytes 0,1 <- half `first` (bytes 0..3 of the selector's view are its dword), bytes 2,3 <- half `second`
+        const uint32_t sel = (uint32_t)(2 * (first & 1)) | ((uint32_t)(2 * (first & 1) + 1) << 8) |
+                             ((uint32_t)(4 + 2 * (second & 1)) << 16) | ((uint32_t)(4 + 2 * (second & 1) + 1) << 24);
+        const half2_t both = h2_of(__builtin_amdgcn_perm(d[second / 2], d[first / 2], sel));
+        const float gain = field_gain<BITS>(pi);
+        const half_t inv = (half_t)(1.0f / gain);
+        pr[pi] = gain == 1.0f ? both : both * half2_t{inv, inv};
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) ops[t] = pack8(pr[4 * t], pr[4 * t + 1], pr[4 * t + 2], pr[4 * t + 3]);
+}
+
+// The gains of the eight weight fields that operand t holds: against this column the scaled
+// activations sum to X = sum x.
+template <int BITS>
+__device__ __forceinline__ half8_t gain_operand(int t)
+{
+    half8_t g;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) g[e] = (half_t)field_gain<BITS>(4 * t + e / 2);
+    return g;
+}
+
+// ------------------------------------------------------------------ hand-over inside the launch
+
+extern "C" __device__ unsigned long long fbq_few_tokens_dispatch_id(void) __asm("llvm.amdgcn.dispatch.id");
+
+// Identity of this launch, the same in every block and different for every launch (also for every
+// replay of a captured graph): never zero, so a zero-filled workspace never matches.
+__device__ __forceinline__ uint32_t small_m_launch_tag()
+{
+    const uint64_t id = fbq_few_tokens_dispatch_id();
+    const uint64_t q = (uint64_t)__builtin_amdgcn_queue_ptr();
+    const uint32_t tag = (uint32_t)id + (uint32_t)(q >> 6) * 0x9E3779B1u;
+    return tag ? tag : 0x80000000u;
+}
+
+// ------------------------------------------------------------------ down-projection, inside the launch
+
+constexpr int kCacheSc1 = 16 | (1 << 31);   // buffer-load policy: device scope (sc1), and volatile so that a poll is never hoisted or merged
+
+// Down-projection for up to 16 tokens: block b = (K slice, column tile of 16); the block's eight
+// waves take an eighth of the slice each.  partial[slice][token][j] = sum over the slice of
+// x[token][k] At[j][k], stored with the launch tag in the other half of its 8-byte word; token rows
+// past M repeat the last token.  The slices only exist to put more compute units to work on this
+// short, latency-bound step; the consumers add them up.
+template <typename Params>
+__device__ void down_proj_block(const Params &p, int b, uint32_t tag, float4_t (*red)[64])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = lane & 15, q = lane >> 4;
+    const int col_tiles = (p.r + 15) / 16;
+    const int slice = b / col_tiles, j0 = (b - slice * col_tiles) * 16;
+    const int kw = p.kslice / kMainWaves;               // a multiple of 32
+    const int kbeg = slice * p.kslice + wave * kw;
+    const int kend = min(p.K, kbeg + kw);
+    // As in the consumers: lane l fetches the piece l % 4 of row l / 4 (a load quad reads 64 contiguous bytes
+    // of one row), and lane (c, q) then takes the words of lane 4 c + q.
+    const int ld_row = lane >> 2, ld_piece = lane & 3, from_lane = (4 * c + q) * 4;
+    const uint16_t *xr = p.x + (size_t)min(ld_row, p.M - 1) * p.K + 8 * ld_piece;
+    const uint16_t *ar = p.At + (size_t)min(j0 + ld_row, p.r - 1) * p.K + 8 * ld_piece;
+    auto to_matrix_order = [&](uint4 v) __attribute__((always_inline)) {
+        const uint4_t w = {(uint32_t)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.x), (uint32_t)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.y),
+                           (uint32_t)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.z), (uint32_t)__builtin_amdgcn_ds_bpermute(from_lane, (int)v.w)};
+        return __builtin_bit_cast(half8_t, w);
+    };
+    float4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    // Four steps' pieces are asked for at once (left to the compiler, which does not unroll a loop with exchanges between lanes in
+    // it, every step was a round trip to memory).  Steps past the end re-read the last one, unused.
+    constexpr int kAtOnce = 4;
+    for (int k = kbeg; k < kend; k += 32 * kAtOnce) {
+        uint4 xv[kAtOnce], av[kAtOnce];
+#pragma unroll
+        for (int i = 0; i < kAtOnce; ++i) {
+            const int at = min(k + 32 * i, kend - 32);
+            xv[i] = *reinterpret_cast<const uint4 *>(xr + at);
+            av[i] = *reinterpret_cast<const uint4 *>(ar + at);
+        }
+#pragma unroll
+        for (int i = 0; i < kAtOnce; ++i)
+            if (k + 32 * i < kend) acc = mfma(to_matrix_order(xv[i]), to_matrix_order(av[i]), acc);   // (wave-uniform)
+    }
+    red[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0) {
+        float4_t sum = red[0][lane];
+#pragma unroll
+        for (int w = 1; w < kMainWaves; ++w) sum += red[w][lane];
+        const int j = j0 + c;                           // lane (c, q) holds column j and tokens 4 q + v
+        if (j < p.r) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float partial = sum[v];        // a scalar first: bit_cast of a vector component reads the wrong element
+                const uint64_t word = (uint64_t)__builtin_bit_cast(uint32_t, partial) | ((uint64_t)tag << 32);
+                __hip_atomic_store(p.tpart + ((size_t)slice * kTokens + 4 * q + v) * p.r + j, word, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+}
+
+// Second step of the down-projection: block b adds up the K slices of columns 16 b .. 16 b + 15 for all
+// 16 token rows (one thread per sum) as soon as their words carry this launch's tag, and passes t on
+// in the same form.  Consumers then read one word per value, whatever the number of slices.
+template <typename Params>
+__device__ void sum_slices_block(const Params &p, int b, uint32_t tag)
+{
+    const int tid = threadIdx.x;
+    if (tid >= 256) return;                             // whole waves
+    const int token = tid >> 4, j = 16 * b + (tid & 15);
+    const bool mine = j < p.r;
+    const __amdgpu_buffer_rsrc_t pb = buffer_of(p.tpart, (long)p.slices * kTokens * p.r * 8);
+    float t = 0.0f;
+    bool ready = false;
+    for (int spin = 0; spin < p.spin_limit && !ready; ++spin) {
+        bool ok = true;
+        t = 0.0f;
+        // all slices are asked for at once (one device-scope round trip per poll, not one per slice);
+        // slices the layer does not have aim past the buffer: zero, no access
+        uint2_t w[kSumSlices];
+#pragma unroll
+        for (int sl = 0; sl < kSumSlices; ++sl)
+            w[sl] = __builtin_amdgcn_raw_buffer_load_b64(pb, mine && sl < p.slices ? ((sl * kTokens + token) * p.r + j) * 8 : 0x7FFFFFF0, 0, kCacheSc1);
+#pragma unroll
+        for (int sl = 0; sl < kSumSlices; ++sl) {
+            const uint32_t v = w[sl].x;
+            t += __builtin_bit_cast(float, v);               // (zero for the slices that are not there)
+            ok = ok && (!mine || sl >= p.slices || w[sl].y == tag);
+        }
+        ready = __all(ok);
+        if (!ready) __builtin_amdgcn_s_sleep(4);
+    }
+    if (!mine) return;
+    if (!ready) {                                       // the slices never showed up: the whole sum, here
+        const uint16_t *xr = p.x + (size_t)min(token, p.M - 1) * p.K, *ar = p.At + (size_t)j * p.K;
+        t = 0.0f;
+        for (int k = 0; k < p.K; ++k) t = fmaf((float)__builtin_bit_cast(half_t, xr[k]), (float)__builtin_bit_cast(half_t, ar[k]), t);
+    }
+    const uint64_t word = (uint64_t)__builtin_bit_cast(uint32_t, t) | ((uint64_t)tag << 32);
+    __hip_atomic_store(p.tsum + (size_t)token * p.r + j, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+inline int cu_count()
+{
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+            n = 256;
+        return n;
+    }();
+    return cus;
+}
+
+}  // namespace fbq
+
+#endif

@@ -51,11 +51,21 @@ struct LinearArgs {
     uint16_t *mix_out;          // ... null, or [M][N] that the two decode launchers write y averaged with mix_with to (see launch_mix)
 };
 
+// 3 to 16 tokens: which of the two kernels serves a layer of N rows (for sets of 16 tokens side by side: rows times sets).  Of
+// the layer alone, so that a layer of a grouped call gets exactly what a call of its own gives it.  The streaming kernel
+// keeps a wave's activations for all tiles of its block and has the next tiles' codes under way while it works on one; it wins where a
+// CU has several tiles.  The other one is a single burst of requests, and takes what is small.  us, burst / stream, 16 tokens or as
+// stated: 28672 x 8192 INT4 r = 128 49.6 / 30.8; two of 11008 x 4096 INT3 r = 64 at 8 tokens 19.9 / 15.3, one alone
+// 11.1 / 9.5; 14336 x 4096 r = 128 at 8 17.3 / 13.7; 50257 x 1024 r = 16 at 8 32.9 / 21; on the burst's side of the line 8192 x 4096 r = 64
+// 9.9 / 10.4, 4096 x 4096 6.6 / 7.2, 4096 x 11008 INT3 at 8 15.9 / 16.7, {4096, 1024, 1024} x 4096 at 8 9.3 / 10.9.
+inline bool few_stream(long rows, int K) { return rows >= 10240 && rows * K >= 40000000L; }
+
 // Launchers (validated arguments only).  Each returns the hipError_t of its launches.
 hipError_t launch_gemv_decode(const LinearArgs *layers, int n_layers, hipStream_t stream);
 bool decode_group_compatible(const LinearArgs &a, const LinearArgs &b);
 hipError_t launch_gemv_small_m(const LinearArgs *layers, int n_layers, hipStream_t stream);
 bool small_m_group_compatible(const LinearArgs &a, const LinearArgs &b);
+hipError_t launch_few_stream(const LinearArgs *layers, int n_layers, hipStream_t stream);   // (by way of launch_gemv_small_m)
 hipError_t launch_prepass_prefill(const LinearArgs &a, hipStream_t stream);
 hipError_t launch_gemm_prefill(const LinearArgs &a, hipStream_t stream);
 hipError_t launch_unpack(const fbq_desc &d, const uint32_t *qw, uint8_t *codes, hipStream_t stream);

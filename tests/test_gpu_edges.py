@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import fbq_synth
-from helpers import assert_matches_oracle, framed_in_nan, make_oracle_layer
+from helpers import assert_matches_oracle, framed_in_nan, framed_layer, gpu_y, make_oracle_layer
 from oracle import fbq_oracle as orc
 from prefill_cases import CUT_CASES
 
@@ -292,3 +292,83 @@ def test_silu_mul_equals_two_element_wise_kernels(count):
     want = torch.nn.functional.silu(gate) * up
     torch.cuda.synchronize()
     assert float(((out.double() - want.double()).abs() - 2.0 ** -9 * want.double().abs()).max()) <= 2.0 ** -24
+
+
+# ------------------------------------------------------------------ streaming kernel for 3 to 16 tokens: 10240 rows and 40 million codes on
+
+def framed_random_layer(N, K, r, bits, seed):
+    """A layer of random codes inside NaN frames, and W_F = s (q - z) + B A of it in 64 bits."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    from paper_2501_16385_amd.random_layers import random_layer
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    dev = framed_layer(random_layer(fbq.Desc(N, K, r, bits), g, gain=1.0))
+    q = fbq.unpack_codes(dev).view(N, K // 128, 128).double()
+    s, z = (t.view(torch.float16).double()[:, :, None] for t in (dev.scales, dev.zeros))
+    W = ((q - z) * s).view(N, K)
+    if r:
+        W.addmm_(dev.Bt.view(torch.float16).double(), dev.At.view(torch.float16).double())
+    return dev, W, g
+
+
+STREAM_CASES = [
+    # N, K, r, M: group counts below, at and above one pass (32), two units (64) and several passes; odd numbers of scales; tiles of
+    # one row; one to more than eight tiles a block; token counts on both sides of 8; ranks on both sides of 32 and 128
+    (10241, 3968, 8, 3),
+    (40001, 1024, 16, 16),
+    (10243, 4224, 40, 9),
+    (10240, 8192, 200, 8),
+    (10245, 8320, 72, 5),
+    (10305, 32768, 256, 16),
+    (140001, 512, 0, 4),
+    (140001, 384, 24, 7),
+    (70003, 1408, 136, 16),
+    (16384, 4096, 64, 8),
+    # sets of 16 tokens side by side, one set not full, one or two tokens left over
+    (4096, 4096, 64, 64),
+    (4099, 4224, 0, 51),
+    (5120, 4096, 128, 49),
+    (3585, 11008, 96, 34),
+]
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("N,K,r,M", STREAM_CASES)
+def test_stream_edges(bits, N, K, r, M):
+    import torch
+    dev, W, g = framed_random_layer(N, K, r, bits, 51 + N + M)
+    x = torch.randn(M, K, device="cuda", generator=g).half()
+    want = (x.double() @ W.T).cpu().numpy()
+    del W
+    x_np = x.cpu().view(torch.int16).numpy().view(np.float16)
+    y = gpu_y(dev, x_np)
+    assert_matches_oracle(y, want, f"INT{bits} {N}x{K} r={r} M={M}")
+    assert np.array_equal(y, gpu_y(dev, x_np))
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("N,K,r,M", [(33001, 1280, 72, 6), (10241, 4096, 8, 16)])
+def test_stream_group_average_and_late_hand_over(bits, N, K, r, M):
+    """Grouped, averaged and single calls agree bit for bit; and with consumers that never wait for the down-projection (they compute t
+    themselves, in another order) the result is still the oracle's."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    (a, Wa, g), (b, _, _) = (framed_random_layer(N, K, r, bits, 61 + i) for i in range(2))
+    x = torch.randn(M, K, device="cuda", generator=g).half()
+    single = [fbq.linear(l, x) for l in (a, b)]
+    with_ = framed_in_nan(torch.randn(M, N, device="cuda", generator=g).half())
+    ys, out = [torch.empty_like(y) for y in single], framed_in_nan(torch.empty(M, N, dtype=torch.float16, device="cuda"))
+    wss = [torch.zeros(fbq.workspace_bytes(l.desc, M), dtype=torch.uint8, device="cuda") for l in (a, b)]
+    arr = fbq.make_group([a, b], [x, x], ys, wss)
+    assert fbq.load().fbq_linear_group_mix(arr, fbq.make_mix([None, with_], [None, out]), 2, M, torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0], single[0]) and torch.equal(ys[1], single[1])
+    assert torch.equal(out, torch.lerp(with_, single[1], 0.5))
+    before = fbq.load().fbq_test_set_spin_limit(-1)
+    try:
+        alone = fbq.linear(a, x)
+        torch.cuda.synchronize()
+    finally:
+        assert fbq.load().fbq_test_set_spin_limit(before) == -1
+    assert_matches_oracle(alone.cpu().numpy(), (x.double() @ Wa.T).cpu().numpy(), f"INT{bits} {N}x{K} r={r} M={M}, t computed by its consumers")
