@@ -634,9 +634,10 @@ __global__ __launch_bounds__(256) void fbq_arrange_x_kernel(const ArrangeParams 
 // for fewer tokens so that the pass has about one block per compute unit (256 assumed: the workspace is sized
 // without a device), never narrower than 256 activations.  Slices are whole quantization groups: the kernel walks
 // them in chunks of 128.
+constexpr int kMaxDownSlices = 32;
 static int down_slice_len(int M, int K)
 {
-    const int want = std::min(32, std::max(8, ceil_div(256, ceil_div(M, 32))));
+    const int want = std::min(kMaxDownSlices, std::max(8, ceil_div(256, ceil_div(M, 32))));
     return std::max(256, ceil_div(ceil_div(K, want), kGroup) * kGroup);
 }
 static int down_slices(int M, int K) { return ceil_div(K, down_slice_len(M, K)); }
@@ -670,8 +671,17 @@ __global__ __launch_bounds__(256) void fbq_down_proj_prefill_kernel(const Arrang
         return;
     }
     const int M = a.M, K = a.K;
-    const int m0 = blockIdx.x * 32;
-    const int k_lo = blockIdx.y * kslice, k_hi = min(K, k_lo + kslice);
+    // Blocks go to the XCDs round-robin by linear id.  Eight slices at a time get an XCD each, with all of their token tiles one
+    // after the other, so that a slice of A^T comes into one L2 and not into each that has one of its token tiles (256 tokens, 28672 x 128:
+    // FBQ_MEASURED).
+    int tile = blockIdx.x, slice = blockIdx.y;
+    if (slice < (slices & ~(kXcds - 1))) {
+        const int id = slice * gridDim.x + tile, i = id / kXcds;
+        slice = id % kXcds + kXcds * (i / (int)gridDim.x);
+        tile = i % (int)gridDim.x;
+    }
+    const int m0 = tile * 32;
+    const int k_lo = slice * kslice, k_hi = min(K, k_lo + kslice);
     const int chunks = (k_hi - k_lo) / kStepK;          // K and the slices are whole groups of 128
 
     const __amdgpu_buffer_rsrc_t xbuf = buffer_of(a.x + (size_t)m0 * K, (long)min(32, M - m0) * K * 2);   // (tokens past M, columns past r: zeros)
@@ -745,29 +755,27 @@ __global__ __launch_bounds__(256) void fbq_down_proj_prefill_kernel(const Arrang
 #pragma unroll
         for (int v = 0; v < 16; ++v) sum[(wave * 32 + 8 * (v / 4) + 4 * h + (v % 4)) * ld + rt * 32 + col] = acc[rt][v];
     __syncthreads();
-    float *out = partial + (size_t)blockIdx.y * M * r;
+    float *out = partial + (size_t)slice * M * r;
     for (int idx = tid; idx < 32 * ld; idx += 256) {
         const int i = idx / ld, j = idx % ld;
         if (m0 + i < M && j < r) out[(size_t)(m0 + i) * r + j] = ((sum[i * ld + j] + sum[(32 + i) * ld + j]) + sum[(64 + i) * ld + j]) + sum[(96 + i) * ld + j];
     }
 }
 
-// Stage 2: t = sum of the slices in slice order, written as t_hi = fp16(t), t_lo = fp16(t - t_hi).
+// Stage 2: t = sum of the slices in slice order, written as t_hi = fp16(t), t_lo = fp16(t - t_hi).  One thread per value, and all of
+// its slices (COUNT at most) asked for at once: eight at a time, 32 slices were four round trips to memory one after the other.
+template <int COUNT>
 __global__ __launch_bounds__(256) void fbq_down_proj_finish_kernel(const float *__restrict__ partial, uint16_t *__restrict__ thl,
                                                                    int M, int r, int slices)
 {
     const size_t total = (size_t)M * r;
     for (size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (size_t)gridDim.x * 256) {
-        // eight slices per round trip to memory, added in slice order
-        float t = 0.0f;
-        for (int s0 = 0; s0 < slices; s0 += 8) {
-            float v[8];
+        float v[COUNT], t = 0.0f;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) v[k] = partial[(size_t)min(s0 + k, slices - 1) * total + idx];
+        for (int k = 0; k < COUNT; ++k) v[k] = partial[(size_t)min(k, slices - 1) * total + idx];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) t += s0 + k < slices ? v[k] : 0.0f;
-        }
-        const size_t m = idx / r, j = idx - m * r;
+        for (int k = 0; k < COUNT; ++k) t += k < slices ? v[k] : 0.0f;
+        const size_t m = total <= 0xFFFFFFFFu ? (uint32_t)idx / (uint32_t)r : idx / r, j = idx - m * r;   // (a 64-bit division costs more than the sum)
         const half_t hi = (half_t)t;
         const half_t lo = (half_t)(t - (float)hi);
         thl[m * (2 * r) + j] = __builtin_bit_cast(uint16_t, hi);
@@ -837,7 +845,10 @@ hipError_t launch_prepass_prefill(const LinearArgs &a, hipStream_t stream)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int blocks = std::min(1024, ceil_div(a.M * a.r, 256));
-    hipLaunchKernelGGL(fbq_down_proj_finish_kernel, dim3(blocks), dim3(256), 0, stream, s.partial, s.thl, a.M, a.r, slices);
+    static_assert(kMaxDownSlices <= 32, "the kernel below adds up at most 32 slices");
+    if (slices <= 8) hipLaunchKernelGGL(fbq_down_proj_finish_kernel<8>, dim3(blocks), dim3(256), 0, stream, s.partial, s.thl, a.M, a.r, slices);
+    else if (slices <= 16) hipLaunchKernelGGL(fbq_down_proj_finish_kernel<16>, dim3(blocks), dim3(256), 0, stream, s.partial, s.thl, a.M, a.r, slices);
+    else hipLaunchKernelGGL(fbq_down_proj_finish_kernel<32>, dim3(blocks), dim3(256), 0, stream, s.partial, s.thl, a.M, a.r, slices);
     return hipGetLastError();
 }
 
