@@ -634,10 +634,9 @@ __global__ __launch_bounds__(256) void fbq_arrange_x_kernel(const ArrangeParams 
 // for fewer tokens so that the pass has about one block per compute unit (256 assumed: the workspace is sized
 // without a device), never narrower than 256 activations.  Slices are whole quantization groups: the kernel walks
 // them in chunks of 128.
-constexpr int kMaxDownSlices = 32;
 static int down_slice_len(int M, int K)
 {
-    const int want = std::min(kMaxDownSlices, std::max(8, ceil_div(256, ceil_div(M, 32))));
+    const int want = std::min(32, std::max(8, ceil_div(256, ceil_div(M, 32))));
     return std::max(256, ceil_div(ceil_div(K, want), kGroup) * kGroup);
 }
 static int down_slices(int M, int K) { return ceil_div(K, down_slice_len(M, K)); }
@@ -672,8 +671,8 @@ __global__ __launch_bounds__(256) void fbq_down_proj_prefill_kernel(const Arrang
     }
     const int M = a.M, K = a.K;
     // Blocks go to the XCDs round-robin by linear id.  Eight slices at a time get an XCD each, with all of their token tiles one
-    // after the other, so that a slice of A^T comes into one L2 and not into each that has one of its token tiles (256 tokens, 28672 x 128:
-    // FBQ_MEASURED).
+    // after the other, so that a slice of A^T comes into one L2 and not into each that has one of its token tiles (256 tokens, 28672 x 128,
+    // INT3: the pass 24.6 us before, 16.8 with it; 2048 tokens, 8192 x 128: 24.6 either way).
     int tile = blockIdx.x, slice = blockIdx.y;
     if (slice < (slices & ~(kXcds - 1))) {
         const int id = slice * gridDim.x + tile, i = id / kXcds;
@@ -762,20 +761,22 @@ __global__ __launch_bounds__(256) void fbq_down_proj_prefill_kernel(const Arrang
     }
 }
 
-// Stage 2: t = sum of the slices in slice order, written as t_hi = fp16(t), t_lo = fp16(t - t_hi).  One thread per value, and all of
-// its slices (COUNT at most) asked for at once: eight at a time, 32 slices were four round trips to memory one after the other.
-template <int COUNT>
+// Stage 2: t = sum of the slices in slice order, written as t_hi = fp16(t), t_lo = fp16(t - t_hi).
 __global__ __launch_bounds__(256) void fbq_down_proj_finish_kernel(const float *__restrict__ partial, uint16_t *__restrict__ thl,
                                                                    int M, int r, int slices)
 {
     const size_t total = (size_t)M * r;
     for (size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (size_t)gridDim.x * 256) {
-        float v[COUNT], t = 0.0f;
+        // eight slices per round trip to memory, added in slice order
+        float t = 0.0f;
+        for (int s0 = 0; s0 < slices; s0 += 8) {
+            float v[8];
 #pragma unroll
-        for (int k = 0; k < COUNT; ++k) v[k] = partial[(size_t)min(k, slices - 1) * total + idx];
+            for (int k = 0; k < 8; ++k) v[k] = partial[(size_t)min(s0 + k, slices - 1) * total + idx];
 #pragma unroll
-        for (int k = 0; k < COUNT; ++k) t += k < slices ? v[k] : 0.0f;
-        const size_t m = total <= 0xFFFFFFFFu ? (uint32_t)idx / (uint32_t)r : idx / r, j = idx - m * r;   // (a 64-bit division costs more than the sum)
+            for (int k = 0; k < 8; ++k) t += s0 + k < slices ? v[k] : 0.0f;
+        }
+        const size_t m = idx / r, j = idx - m * r;
         const half_t hi = (half_t)t;
         const half_t lo = (half_t)(t - (float)hi);
         thl[m * (2 * r) + j] = __builtin_bit_cast(uint16_t, hi);
@@ -845,10 +846,7 @@ hipError_t launch_prepass_prefill(const LinearArgs &a, hipStream_t stream)
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int blocks = std::min(1024, ceil_div(a.M * a.r, 256));
-    static_assert(kMaxDownSlices <= 32, "the kernel below adds up at most 32 slices");
-    if (slices <= 8) hipLaunchKernelGGL(fbq_down_proj_finish_kernel<8>, dim3(blocks), dim3(256), 0, stream, s.partial, s.thl, a.M, a.r, slices);
-    else if (slices <= 16) hipLaunchKernelGGL(fbq_down_proj_finish_kernel<16>, dim3(blocks), dim3(256), 0, stream, s.partial, s.thl, a.M, a.r, slices);
-    else hipLaunchKernelGGL(fbq_down_proj_finish_kernel<32>, dim3(blocks), dim3(256), 0, stream, s.partial, s.thl, a.M, a.r, slices);
+    hipLaunchKernelGGL(fbq_down_proj_finish_kernel, dim3(blocks), dim3(256), 0, stream, s.partial, s.thl, a.M, a.r, slices);
     return hipGetLastError();
 }
 
