@@ -112,8 +112,9 @@ fbq_status fbq_pack(const fbq_desc *d, const uint8_t *codes, const uint16_t *sca
  * the same launch, one column of A per block as a small job in front of the block's first tile).  3 <= M <= 16 streams the packed words once for all
  * tokens against a 16-token matrix-core tile, also in ONE launch whose first blocks do the
  * down-projection; 17 <= M <= 64 is the same launch with the sets of 16 tokens side by side (the packed words are read
- * once per 16 tokens and the codes multiplied exactly; one or two tokens left over go through the GEMV; a layer so large that
- * reading it two to four times costs far more takes the path of M > 64 instead).  M > 64 runs the fp16 MFMA GEMM after a pass that
+ * once per 16 tokens and the codes multiplied exactly; one or two tokens left over go through the GEMV
+ * or, in larger layers, are a set too; a layer so large that reading it two to four times costs far more takes the path
+ * of M > 64 instead).  M > 64 runs the fp16 MFMA GEMM after a pass that
  * re-orders x and a separate down-projection; a layer with too few output tiles to fill the GPU has
  * its K range split over up to 8 blocks per tile, summed in fp32 by a last small launch.
  *   x         device [M, K] fp16             qweight, scales, zeros, At, Bt: device, layout above

@@ -51,14 +51,21 @@ extern "C" size_t fbq_packed_bytes(const fbq_desc *d)
 // to which a call has the smaller error: who had it keeps it.  What that costs by now, sets / GEMM, us: nothing for
 // 4096 x 4096 (9.5 / 25 at 32 tokens, 19 / 28 at 64) and 4096 -> 11008 up to 48 tokens (26 / 30; 34 / 32 at 64); 13824 -> 5120 at 48
 // tokens INT4 47 / 41, INT3 41 / 42; 8192 -> 8192 at 48 40 / 39 and 45 / 38; 28672 -> 8192 at 32 76 / 65 and 68 / 64; 5120 -> 13824
-// at 32 42 / 36.  On the GEMM's side of the line it is the faster one throughout: 8192 -> 28672 at 17 tokens 79 / 63, at 64 155 / 68.
+// at 32 42 / 36.
+//
+// Beyond that line the sets are faster too where they add up to a launch of the streaming kernel and K is 3072 to 8192 (longer rows:
+// a wave's activations come again and again; shorter ones: too little work per row): two sets at any N, four up to 70 million codes.
+// Sets / GEMM, us.  Two, at 32 tokens: 8192 -> 28672, r = 128, 49 / 65; 3072 -> 40000 33 / 41; 4096 -> 131072 99 / 111; but
+// 2048 -> 60000 41 / 36, 1024 -> 40000 30 / 24.  Four, at 64: 4096 -> 17088 31 / 37, 3072 -> 22784 34 / 39, 8192 -> 8544, r = 128, 36 / 41; but
+// 6144 -> 20000 48 / 41, 8192 -> 28672 88 / 71.  Three (48 tokens) are a draw or worse: 5120 -> 13824 INT3 42 / 40, 8192 -> 28672 82 / 69.
 static bool takes_sets(int M, int N, int K)
 {
     const int sets = (M + kDecodeMaxM - 1) / kDecodeMaxM;
     const double k_passes = 4096.0 * ((K + 4095) / 4096);
     const double cost_sets = 2.0 + sets * (2.2 + 0.165e-6 * N * k_passes);
     const double cost_gemm = 30.0 + 0.135e-6 * N * (double)K + 1.5 * K / 1024.0;
-    return cost_sets <= cost_gemm;
+    if (cost_sets <= cost_gemm) return true;
+    return K >= 3072 && K <= 8192 && few_stream((long)sets * N, K) && (sets == 2 || (sets == 4 && (long)N * K <= 70000000L));
 }
 
 // In front of what the prefill path keeps in a workspace: room for the hand-over words of the decode paths, which the
@@ -75,7 +82,7 @@ extern "C" size_t fbq_workspace_bytes(const fbq_desc *d, int M)
     if (fbq_check_desc(d) != FBQ_OK || M < 1) return 0;
     if (M <= kPerTokenMaxM) return d->r == 0 ? 0 : decode_workspace_bytes(M, d->K, d->r);
     // up to 64 tokens go through the few-token kernel 16 at a time, all in one launch, every 16 tokens with hand-over
-    // words of their own (one or two left over go through the GEMV afterwards, whose words fit the first set);
+    // words of their own (one or two left over, where they go through the GEMV afterwards, have words that fit the first set);
     // nothing to hand over without a sub-branch
     if (M <= kDecodeMaxM) return small_m_workspace_bytes(d->K, d->r);
     if (M <= kChunkedMaxM && takes_sets(M, d->N, d->K))
@@ -208,6 +215,10 @@ hipError_t launch_one(const LinearArgs &a, hipStream_t s)
         static_assert(kChunkedMaxM <= kMaxSmallGroup * kDecodeMaxM, "the sets of 16 tokens must fit one grouped launch");
         LinearArgs set[kMaxSmallGroup], rest = a;
         const size_t ws_each = small_m_workspace_bytes(a.K, a.r);
+        // One or two tokens left over are a set like the others where the streaming kernel takes the sets: a pass of their own would
+        // read the words again.  As a set / with the GEMV, us: 28672 -> 8192 at 17 tokens 58 / 72, at 18 57 / 118 (INT3); 4096 -> 11008 at 18
+        // 15 / 21; 4096 -> 4096 at 49 13.8 / 15.7.  One beside two sets is left to the GEMV: 8192 -> 8192 at 33 31.7 / 30.2, 5120 -> 5120 21.0 / 20.2.
+        const bool all_in_sets = a.M != 2 * kDecodeMaxM + 1 && few_stream((long)ceil_div(a.M, kDecodeMaxM) * a.N, a.K);
         int n = 0;
         rest.M = 0;
         for (int m0 = 0; m0 < a.M; m0 += kDecodeMaxM) {
@@ -215,7 +226,7 @@ hipError_t launch_one(const LinearArgs &a, hipStream_t s)
             c.M = std::min(kDecodeMaxM, a.M - m0);
             c.x = a.x + (size_t)m0 * a.K;
             c.y = a.y + (size_t)m0 * a.N;
-            if (c.M <= kPerTokenMaxM) { rest = c; continue; }   // one or two tokens left over: the GEMV is cheaper
+            if (c.M <= kPerTokenMaxM && !all_in_sets) { rest = c; continue; }
             c.workspace = a.workspace ? (char *)a.workspace + (size_t)n * ws_each : nullptr;
             set[n++] = c;
         }

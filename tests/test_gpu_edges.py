@@ -347,6 +347,42 @@ def test_stream_edges(bits, N, K, r, M):
     assert np.array_equal(y, gpu_y(dev, x_np))
 
 
+SETS_OR_GEMM_CASES = [
+    # N, K, r, M, whether the sets of 16 take it.  The shortest and the longest rows that two and four sets take beyond the GEMM's
+    # old line, and one group of 128 past either
+    (40001, 3072, 40, 17, True), (40001, 2944, 40, 17, False),
+    (20001, 8192, 0, 32, True), (20001, 8320, 0, 32, False),
+    (8543, 8192, 72, 64, True), (8545, 8320, 72, 64, False),
+    # either side of 70 million codes at four sets; three sets; a rank above 128
+    (17089, 4096, 136, 50, True), (17091, 4096, 136, 50, False),
+    (28673, 8192, 16, 18, True), (28673, 8192, 16, 33, False),
+    # one or two tokens left over as a set, and beside two sets
+    (5121, 5120, 24, 33, True), (5121, 5120, 24, 34, True), (4097, 14336, 96, 49, True),
+]
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("N,K,r,M,sets", SETS_OR_GEMM_CASES)
+def test_sets_or_gemm_edges(bits, N, K, r, M, sets):
+    """Each within the bound of the path that takes it (the sets multiply the codes exactly, the GEMM rounds every weight to fp16: the
+    two bounds beside ELEMENT_SLACK), also with a workspace that calls of other token counts have used."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    dev, W, g = framed_random_layer(N, K, r, bits, 71 + N + M)
+    assert (fbq.workspace_bytes(dev.desc, M) == -(-M // 16) * fbq.workspace_bytes(dev.desc, 16)) == sets
+    x = torch.randn(M, K, device="cuda", generator=g).half()
+    want = (x.double() @ W.T).cpu().numpy()
+    del W
+    x_np = x.cpu().view(torch.int16).numpy().view(np.float16)
+    y = gpu_y(dev, x_np)
+    assert_matches_oracle(y, want, f"INT{bits} {N}x{K} r={r} M={M}", "few" if sets else "prefill")
+    x65 = torch.randn(65, K, device="cuda", generator=g).half()
+    ws = torch.zeros(max(fbq.workspace_bytes(dev.desc, m) for m in (65, M, 16, 2)), dtype=torch.uint8, device="cuda")
+    for other in (x65, x65[:16], x65[:2], x):
+        shared = fbq.linear(dev, other, workspace=ws)
+    assert np.array_equal(shared.cpu().view(torch.int16).numpy(), y.view(np.int16))
+
+
 @pytest.mark.parametrize("bits", [4, 3])
 @pytest.mark.parametrize("N,K,r,M", [(33001, 1280, 72, 6), (10241, 4096, 8, 16)])
 def test_stream_group_average_and_late_hand_over(bits, N, K, r, M):
