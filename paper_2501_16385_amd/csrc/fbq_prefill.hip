@@ -672,9 +672,11 @@ __global__ __launch_bounds__(256) void fbq_down_proj_prefill_kernel(const Arrang
     const int M = a.M, K = a.K;
     // Blocks go to the XCDs round-robin by linear id.  Eight slices at a time get an XCD each, with all of their token tiles one
     // after the other, so that a slice of A^T comes into one L2 and not into each that has one of its token tiles (256 tokens, 28672 x 128,
-    // INT3: the pass 24.6 us before, 16.8 with it; 2048 tokens, 8192 x 128: 24.6 either way).
+    // INT3: the pass 24.6 us before, 16.8 with it).  It pays where A^T is large and eight tiles or more read it (the call before / with it, us:
+    // 256 tokens of 20480 x 256 92 / 87.5, of 13952 x 128 63.7 / 63.0, but of 4096 x 128 36.3 / 37.1; 160 tokens of 8192 x 256 41.6 / 43.2), and
+    // where all blocks fit the GPU at once: 1092 tokens, 280 blocks, of 13952 x 128 151 / 156.
     int tile = blockIdx.x, slice = blockIdx.y;
-    if (slice < (slices & ~(kXcds - 1))) {
+    if (gridDim.x >= 8 && (int)gridDim.x * slices <= 256 && r * K >= 1500000 && slice < (slices & ~(kXcds - 1))) {
         const int id = slice * gridDim.x + tile, i = id / kXcds;
         slice = id % kXcds + kXcds * (i / (int)gridDim.x);
         tile = i % (int)gridDim.x;
