@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "fbq_few_tokens.h"
+#include "fbq_stream_plan.h"
 
 namespace fbq {
 
@@ -481,47 +482,18 @@ constexpr int kLateBytes = 115000;
 hipError_t launch_few_stream(const LinearArgs *layers, int n_layers, hipStream_t stream)
 {
     const LinearArgs &first = layers[0];
-    long total_rows = 0;
-    int most = 0;
+    int rows_of[kMaxSmallGroup], preparing[kMaxSmallGroup], most = 0;
     for (int i = 0; i < n_layers; ++i) {
-        total_rows += layers[i].N;
+        rows_of[i] = layers[i].N;
+        preparing[i] = preparing_blocks(layers[i]);
         most = std::max(most, layers[i].M);
     }
-    const int G = first.K / kGroup, cus = cu_count();
+    const int G = first.K / kGroup;
     const int chunks = G > kPassGroups && G <= 2 * kPassGroups ? 2 : 1;
     const int passes = ceil_div(G, chunks * kPassGroups), share = ceil_div(G, kMainWaves * passes);
-    // Blocks run one per CU, in dispatch order: every layer's down-projection first, then rows.  Those that find no CU free start when
-    // the down-projection's are done; they own as many rows less as a CU streams in that time - or there are none, where that is all
-    // (two layers of 11008 x 4096 at 8 tokens, by the bytes allowed for: 40000 17.4 us, 70000 15.3, 100000 14.8, 130000 15.6).
-    int preparing = 0;
-    for (int i = 0; i < n_layers; ++i) preparing += preparing_blocks(layers[i]);
+    // (two layers of 11008 x 4096 at 8 tokens, by the bytes allowed for: 40000 17.4 us, 70000 15.3, 100000 14.8, 130000 15.6)
     const int behind = std::max(1, kLateBytes / ((int)row_words(first.K, first.bits) * 4 + 4 * G));
-    auto owners = [&](const LinearArgs &a, int rows) { return ceil_div(a.N, rows); };
-    int rows = (int)((total_rows + (long)preparing * behind + cus - 1) / cus);
-    bool late = preparing > 0 && rows > behind;
-    int late_rows = rows - behind;
-    if (!late) {
-        const int free_cus = std::max(cus - preparing, cus / 2);
-        for (rows = std::max(16, (int)((total_rows + free_cus - 1) / free_cus));; ++rows) {
-            int blocks = 0;
-            for (int i = 0; i < n_layers; ++i) blocks += owners(layers[i], rows);
-            if (blocks <= std::max(free_cus, n_layers)) break;
-        }
-        if (rows > 16 && rows <= 32) rows = 32;
-        late_rows = rows;
-    }
-    // (where the activations are loaded anew for every round of four tiles: no round for a few rows)
-    const int whole = late ? 64 * ceil_div(late_rows, 64) : 0;
-    if (late && passes > 1 && rows > whole && preparing < cus) {
-        const int more = (int)((total_rows - (long)(cus - preparing) * whole + preparing - 1) / preparing);
-        if (more <= whole) { rows = whole; late_rows = std::max(more, 1); }
-    }
-    int in_order = cus;                                  // blocks of a grid row that start at once
-    for (; late && in_order > 1; --in_order) {
-        int started = 0;
-        for (int i = 0; i < n_layers; ++i) started += std::min(in_order, preparing_blocks(layers[i]) + owners(layers[i], rows));
-        if (started <= cus) break;
-    }
+    const StreamPlan plan = plan_stream(rows_of, preparing, n_layers, behind, passes, cu_count());
     StreamGroup g;
     int widest = 0;
     for (int i = 0; i < n_layers; ++i) {
@@ -538,13 +510,12 @@ hipError_t launch_few_stream(const LinearArgs *layers, int n_layers, hipStream_t
         p.slices = ceil_div(a.K, p.kslice);
         p.down_blocks = a.r > 0 ? ceil_div(a.r, 16) * p.slices : 0;
         p.sum_blocks = a.r > 0 ? ceil_div(a.r, 16) : 0;
-        p.rows = rows;
-        p.late_rows = late_rows;
-        p.early = late ? std::max(0, std::min(owners(a, rows), in_order - preparing_blocks(a))) : owners(a, rows);
-        const int left = std::max(0, a.N - p.early * rows);
+        p.rows = plan.rows;
+        p.late_rows = plan.late_rows;
+        p.early = plan.early[i];
         p.passes = passes; p.share = share;
         p.spin_limit = spin_limit();
-        widest = std::max(widest, p.down_blocks + p.sum_blocks + p.early + ceil_div(left, p.late_rows));
+        widest = std::max(widest, p.down_blocks + p.sum_blocks + p.early + plan.late[i]);
     }
     for (int i = n_layers; i < kMaxSmallGroup; ++i) g.layer[i] = g.layer[0];   // never indexed: grid.x stops at n_layers
     const dim3 grid(n_layers, widest);
