@@ -73,6 +73,9 @@ struct StreamParams {
 };
 struct StreamGroup {
     StreamParams layer[kMaxSmallGroup];
+    // Blocks of a grid one block wide and high are in line (see fbq_stream_plan.h): segments 0..3 are the layers' preparing blocks, 4..7
+    // those with their rows; where each starts.
+    int segment[2 * kMaxSmallGroup];
 };
 
 // The four matrix operands of a lane's 32 codes: every field stays where it is, masked out, i.e. it is the subnormal fp16
@@ -115,19 +118,28 @@ __global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu
     constexpr int kPiece = BITS == 4 ? 16 : 12;         // bytes of 32 codes
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kLdsBytes];
 
-    const auto p = g.layer[blockIdx.x];
+    int layer = blockIdx.x, index = blockIdx.y;         // the block's place in its layer, preparing blocks first
+    if (blockIdx.z > 0) {                               // in line (the first block of a line is the first of a grid, too)
+        const int id = blockIdx.z;
+        int s = 0;
+#pragma unroll
+        for (int i = 1; i < 2 * kMaxSmallGroup; ++i) s = id >= g.segment[i] ? i : s;
+        layer = s & (kMaxSmallGroup - 1);
+        index = id - g.segment[s] + (s < kMaxSmallGroup ? 0 : g.segment[layer + 1] - g.segment[layer]);
+    }
+    const auto p = g.layer[layer];
     // (all of them before the first branch: left alone, the compiler fetches only what the branch needs first)
     asm volatile("" :: "s"(p.qw), "s"(p.scales), "s"(p.zeros), "s"(p.x), "s"(p.y), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.row_words), "s"(p.G), "s"(p.early), "s"(p.rows), "s"(p.late_rows), "s"(p.down_blocks), "s"(p.sum_blocks));
     asm volatile("" :: "s"(p.Bt), "s"(p.At), "s"(p.tpart), "s"(p.tsum), "s"(p.r), "s"(p.passes), "s"(p.share), "s"(p.spin_limit));
     const uint32_t tag = small_m_launch_tag();
     // The first blocks of a grid row do the layer's down-projection.  They come first in dispatch order, so whoever waits for their
     // words waits for blocks that are already running.
-    if ((int)blockIdx.y < p.down_blocks + p.sum_blocks) {
-        if ((int)blockIdx.y < p.down_blocks) down_proj_block(p, blockIdx.y, tag, reinterpret_cast<float4_t (*)[64]>(lds));
-        else sum_slices_block(p, blockIdx.y - p.down_blocks, tag);
+    if (index < p.down_blocks + p.sum_blocks) {
+        if (index < p.down_blocks) down_proj_block(p, index, tag, reinterpret_cast<float4_t (*)[64]>(lds));
+        else sum_slices_block(p, index - p.down_blocks, tag);
         return;
     }
-    const int block = blockIdx.y - p.down_blocks - p.sum_blocks;
+    const int block = index - p.down_blocks - p.sum_blocks;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, q = lane >> 4;
@@ -136,7 +148,7 @@ __global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu
     const int row0 = min(block < p.early ? block * p.rows : p.early * p.rows + (block - p.early) * p.late_rows, p.N);
     const int row_end = min(p.N, row0 + (block < p.early ? p.rows : p.late_rows));
     const int tiles = (row_end - row0 + 15) >> 4;
-    if (tiles == 0) return;                             // a layer with fewer blocks than the widest
+    if (tiles == 0) return;                             // (a column of the grid with a block less than the others)
     const int passes = MULTI ? p.passes : 1;
     const int row_bytes = p.row_words * 4;
     constexpr int kNowhere = 0x40000000;                // beyond every buffer
@@ -518,7 +530,16 @@ hipError_t launch_few_stream(const LinearArgs *layers, int n_layers, hipStream_t
         widest = std::max(widest, p.down_blocks + p.sum_blocks + p.early + plan.late[i]);
     }
     for (int i = n_layers; i < kMaxSmallGroup; ++i) g.layer[i] = g.layer[0];   // never indexed: grid.x stops at n_layers
-    const dim3 grid(n_layers, widest);
+    dim3 grid(n_layers, widest);
+    if (stream_in_line(rows_of, preparing, n_layers)) {
+        int start = 0;
+        for (int s = 0; s < 2 * kMaxSmallGroup; ++s) {
+            const int i = s & (kMaxSmallGroup - 1);
+            g.segment[s] = start;
+            if (i < n_layers) start += s < kMaxSmallGroup ? preparing[i] : plan.early[i] + plan.late[i];
+        }
+        grid = dim3(1, 1, start);
+    }
     return first.bits == 4 ? launch_bits<4>(g, chunks, most <= 8, grid, stream) : launch_bits<3>(g, chunks, most <= 8, grid, stream);
 }
 

@@ -6,13 +6,29 @@
 
 namespace fbq {
 
-// Blocks run one per CU, in dispatch order: every layer's preparing blocks first (its down-projection), then rows; a grid row is a
-// layer, and the layers' blocks of equal index start one after the other.  The first `early` blocks of a layer's rows find a CU at once and own
-// `rows` of them; those that start when preparing blocks are done own `late_rows`, as many less as a CU streams in that time.
+// Blocks run one per CU, in dispatch order: every layer's preparing blocks first (its down-projection), then rows.  The first `early`
+// blocks of a layer's rows find a CU at once and own `rows` of them; those that start when preparing blocks are done own `late_rows`, as many
+// less as a CU streams in that time.
+//
+// Layers that are alike are the columns of a grid: their blocks of equal index start one after the other.  Of layers that are not, the
+// narrower ones would leave empty blocks in it, and as blocks go to the XCDs round-robin, a layer's blocks to only four of them (two
+// layers) or two (four): an XCD with more blocks than CUs takes twice as long.  So these are in line: all preparing blocks, then the rows' blocks, layer
+// after layer, and nothing in between.  That is not done for all, because a block in line learns its layer, and with it the address
+// of its parameters, from the kernel's arguments: a second round trip to them.  us, in a grid / in line: {28672, 14336} x 13824, INT3, 16 tokens
+// 149 / 84.6; {12000, 11008, 16000, 10240} x 4096, INT4, 4 tokens 40.1 / 25.8; but two of 11008 x 4096, INT3, 8 tokens 16.1 / 16.3, three sets of
+// 4096 x 4096 11.2 / 12.0.
 struct StreamPlan {
     int rows, late_rows;
     int early[kMaxSmallGroup], late[kMaxSmallGroup];   // blocks with rows, by layer
 };
+
+// Whether the layers of a launch are dealt out in line.
+inline bool stream_in_line(const int *N, const int *preparing, int n)
+{
+    for (int i = 1; i < n; ++i)
+        if (N[i] != N[0] || preparing[i] != preparing[0]) return true;
+    return false;
+}
 
 // n layers of N[i] rows with preparing[i] preparing blocks; behind: rows that a CU streams while these run; passes over K.
 inline StreamPlan plan_stream(const int *N, const int *preparing, int n, int behind, int passes, int cus)
@@ -21,8 +37,20 @@ inline StreamPlan plan_stream(const int *N, const int *preparing, int n, int beh
     long total = 0;
     int prep = 0;
     for (int i = 0; i < n; ++i) { total += N[i]; prep += preparing[i]; }
+    const bool in_line = stream_in_line(N, preparing, n);
     // Row blocks of all layers with the plan's rows and late_rows: early, and late.
     auto deal = [&]() {
+        int blocks = 0;
+        if (in_line) {
+            int at_once = std::max(0, cus - prep);
+            for (int i = 0; i < n; ++i) {
+                p.early[i] = std::min(at_once, ceil_div(N[i], p.rows));
+                at_once -= p.early[i];
+                p.late[i] = ceil_div(std::max(0, N[i] - p.early[i] * p.rows), p.late_rows);
+                blocks += p.early[i] + p.late[i];
+            }
+            return blocks;
+        }
         int owners[kMaxSmallGroup];
         for (int i = 0; i < n; ++i) owners[i] = ceil_div(N[i], p.rows);
         int each = cus / n, spare = 0;                      // blocks of every grid row that find a CU at once (as long as it has more); CUs left over
@@ -36,7 +64,6 @@ inline StreamPlan plan_stream(const int *N, const int *preparing, int n, int beh
             if (open == 0 || spare < open) break;
             each += spare / open;
         }
-        int blocks = 0;
         for (int i = 0; i < n; ++i) {
             p.early[i] = std::max(0, std::min(owners[i], each - preparing[i]));
             if (spare > 0 && preparing[i] + owners[i] > each) {   // the next ones in order

@@ -408,3 +408,34 @@ def test_stream_group_average_and_late_hand_over(bits, N, K, r, M):
     finally:
         assert fbq.load().fbq_test_set_spin_limit(before) == -1
     assert_matches_oracle(alone.cpu().numpy(), (x.double() @ Wa.T).cpu().numpy(), f"INT{bits} {N}x{K} r={r} M={M}, t computed by its consumers")
+
+
+UNEQUAL_GROUPS = [
+    # K, {N, r} of each layer: two to four layers in line, one to more than eight tiles a block, ranks on both sides of 32 and 128, none
+    (4096, [(10240, 8), (14337, 256), (20001, 40)]),
+    (1280, [(50001, 0), (33251, 0)]),
+    (4224, [(10241, 64), (10240, 64), (12289, 8), (16385, 200)]),
+    (8320, [(10240, 24), (13001, 136)]),
+    (4096, [(10240, 64), (10240, 72), (10240, 64)]),
+]
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("M", [5, 16])
+@pytest.mark.parametrize("K,layers", UNEQUAL_GROUPS)
+def test_stream_group_of_unequal_layers(K, layers, M, bits):
+    """Every layer of a grouped call gets exactly what a call of its own gives it, whatever it shares the launch with."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    from paper_2501_16385_amd.random_layers import random_layer
+    g = torch.Generator(device="cuda")
+    g.manual_seed(81 + K + M)
+    devs = [framed_layer(random_layer(fbq.Desc(N, K, r, bits), g, gain=1.0)) for N, r in layers]
+    x = framed_in_nan(torch.randn(M, K, device="cuda", generator=g).half())
+    single = [fbq.linear(l, x) for l in devs]
+    for order in (slice(None), slice(None, None, -1)):
+        ys = [framed_in_nan(torch.empty_like(y)) for y in single[order]]
+        fbq.linear_group(devs[order], [x] * len(devs), ys=ys)
+        torch.cuda.synchronize()
+        for (N, r), y, want in zip(layers[order], ys, single[order]):
+            assert torch.equal(y, want), (N, r)
