@@ -488,23 +488,20 @@ static int slice_length(int K, int r)
 }
 static int preparing_blocks(const LinearArgs &a) { return a.r > 0 ? ceil_div(a.r, 16) * (ceil_div(a.K, slice_length(a.K, a.r)) + 1) : 0; }
 
-// What a CU streams in while the blocks of a down-projection run: at 23 KB per us and CU, 5 us.
-constexpr int kLateBytes = 115000;
-
 hipError_t launch_few_stream(const LinearArgs *layers, int n_layers, hipStream_t stream)
 {
     const LinearArgs &first = layers[0];
-    int rows_of[kMaxSmallGroup], preparing[kMaxSmallGroup], most = 0;
+    int rows_of[kMaxSmallGroup], preparing[kMaxSmallGroup], most = 0, slice = 1024;
     for (int i = 0; i < n_layers; ++i) {
         rows_of[i] = layers[i].N;
         preparing[i] = preparing_blocks(layers[i]);
+        if (layers[i].r > 0) slice = std::max(slice, slice_length(layers[i].K, layers[i].r));
         most = std::max(most, layers[i].M);
     }
     const int G = first.K / kGroup;
     const int chunks = G > kPassGroups && G <= 2 * kPassGroups ? 2 : 1;
     const int passes = ceil_div(G, chunks * kPassGroups), share = ceil_div(G, kMainWaves * passes);
-    // (two layers of 11008 x 4096 at 8 tokens, by the bytes allowed for: 40000 17.4 us, 70000 15.3, 100000 14.8, 130000 15.6)
-    const int behind = std::max(1, kLateBytes / ((int)row_words(first.K, first.bits) * 4 + 4 * G));
+    const int behind = stream_rows_behind(slice, (int)row_words(first.K, first.bits) * 4 + 4 * G);
     const StreamPlan plan = plan_stream(rows_of, preparing, n_layers, behind, passes, cu_count());
     StreamGroup g;
     int widest = 0;

@@ -22,6 +22,14 @@ struct StreamPlan {
     int early[kMaxSmallGroup], late[kMaxSmallGroup];   // blocks with rows, by layer
 };
 
+// Rows that a CU streams in while the blocks of a down-projection run (row_bytes: codes, scales and zeros of a row): at 23 KB per us, 5 us.
+// Two layers of 11008 x 4096 at 8 tokens, by the bytes allowed for: 40000 17.4 us, 70000 15.3, 100000 14.8, 130000 15.6.
+inline int stream_rows_behind(int /*slice*/, int row_bytes)
+{
+    constexpr int kBytes = 115000;
+    return std::max(1, kBytes / row_bytes);
+}
+
 // Whether the layers of a launch are dealt out in line.
 inline bool stream_in_line(const int *N, const int *preparing, int n)
 {
@@ -40,36 +48,10 @@ inline StreamPlan plan_stream(const int *N, const int *preparing, int n, int beh
     const bool in_line = stream_in_line(N, preparing, n);
     // Row blocks of all layers with the plan's rows and late_rows: early, and late.
     auto deal = [&]() {
-        int blocks = 0;
-        if (in_line) {
-            int at_once = std::max(0, cus - prep);
-            for (int i = 0; i < n; ++i) {
-                p.early[i] = std::min(at_once, ceil_div(N[i], p.rows));
-                at_once -= p.early[i];
-                p.late[i] = ceil_div(std::max(0, N[i] - p.early[i] * p.rows), p.late_rows);
-                blocks += p.early[i] + p.late[i];
-            }
-            return blocks;
-        }
-        int owners[kMaxSmallGroup];
-        for (int i = 0; i < n; ++i) owners[i] = ceil_div(N[i], p.rows);
-        int each = cus / n, spare = 0;                      // blocks of every grid row that find a CU at once (as long as it has more); CUs left over
-        for (;;) {
-            int open = 0;
-            spare = cus;
-            for (int i = 0; i < n; ++i) {
-                spare -= std::min(each, preparing[i] + owners[i]);
-                open += preparing[i] + owners[i] > each;
-            }
-            if (open == 0 || spare < open) break;
-            each += spare / open;
-        }
+        int at_once = std::max(0, cus - prep), blocks = 0;
         for (int i = 0; i < n; ++i) {
-            p.early[i] = std::max(0, std::min(owners[i], each - preparing[i]));
-            if (spare > 0 && preparing[i] + owners[i] > each) {   // the next ones in order
-                --spare;
-                if (each >= preparing[i]) ++p.early[i];
-            }
+            p.early[i] = std::min(in_line ? at_once : std::max(0, cus / n - preparing[i]), ceil_div(N[i], p.rows));
+            at_once -= p.early[i];
             p.late[i] = ceil_div(std::max(0, N[i] - p.early[i] * p.rows), p.late_rows);
             blocks += p.early[i] + p.late[i];
         }

@@ -1,6 +1,6 @@
-// Deals rows of streamed layers out to blocks (plan_stream, csrc/fbq_stream_plan.h): one line on stdout for each line "cus passes behind N
-// preparing [N preparing ..]" on stdin, "rows late_rows early late [early late ..]"; after the plan a walk over the blocks as the kernel indexes
-// them, which ends with an error where a row is owned by no block or by two.
+// Deals rows of streamed layers out to blocks (plan_stream, csrc/fbq_stream_plan.h): one line on stdout for each line "cus passes slice
+// row_bytes N preparing [N preparing ..]" on stdin, "behind in_line rows late_rows early late [early late ..]"; after the plan a walk over the
+// blocks as the kernel indexes them, which ends with an error where a row is owned by no block or by two.
 #include <cstdio>
 #include <cstdlib>
 #include <iostream>
@@ -16,11 +16,12 @@ int main()
     std::string line;
     while (std::getline(std::cin, line)) {
         std::istringstream in(line);
-        int cus, passes, behind, N[kMaxSmallGroup], preparing[kMaxSmallGroup], n = 0;
-        in >> cus >> passes >> behind;
+        int cus, passes, slice, row_bytes, N[kMaxSmallGroup], preparing[kMaxSmallGroup], n = 0;
+        in >> cus >> passes >> slice >> row_bytes;
         while (n < kMaxSmallGroup && in >> N[n] >> preparing[n]) ++n;
+        const int behind = stream_rows_behind(slice, row_bytes);
         const StreamPlan p = plan_stream(N, preparing, n, behind, passes, cus);
-        printf("%d %d", p.rows, p.late_rows);
+        printf("%d %d %d %d", behind, stream_in_line(N, preparing, n), p.rows, p.late_rows);
         for (int i = 0; i < n; ++i) {
             int next = 0;
             for (int block = 0; block < p.early[i] + p.late[i]; ++block) {

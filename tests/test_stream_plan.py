@@ -20,24 +20,42 @@ def plans(tmp_path_factory):
                     "-I", os.path.join(ROOT, "paper_2501_16385_amd", "csrc"), os.path.join(ROOT, "tests", "host", "plan_driver.cpp"), "-o", exe], check=True)
 
     def run(calls):
-        given = "".join(" ".join(map(str, (cus, passes, behind, *(v for layer in layers for v in layer)))) + "\n" for cus, passes, behind, layers in calls)
+        given = "".join(" ".join(map(str, (CUS, passes, slice_, row_bytes, *(v for layer in layers for v in layer)))) + "\n" for passes, slice_, row_bytes, layers in calls)
         res = subprocess.run([exe], input=given, text=True, capture_output=True, timeout=120)
         assert res.returncode == 0, res.stderr
         return [[int(v) for v in line.split()] for line in res.stdout.split("\n") if line]
     return run
 
 
-# cus, passes, behind, {rows, preparing blocks} of each layer: three sets of 48 tokens through 28672 -> 5120, r = 64, INT4 and 4096 -> 4593 INT3;
-# 13824 -> 5120, r = 128, INT3; two grouped 4096 -> 11008; layers of unequal rows and ranks; preparing blocks on every CU; one layer; no sub-branch
+CUS, XCDS = 256, 8
+
+# passes over K, activations of a down-projection's slice, bytes of a row, {rows, preparing blocks} of each layer: three sets of 48 tokens through
+# 28672 -> 5120, r = 64, INT4, 4096 -> 4593, r = 64, INT3 and 13824 -> 5120, r = 128, INT3; two grouped 4096 -> 11008; layers of unequal rows and
+# ranks; preparing blocks on every CU; one layer; no sub-branch
 CALLS = [
-    (256, 7, 7, [(5120, 68)] * 3), (256, 1, 69, [(4593, 20)] * 3), (256, 4, 20, [(5120, 72)] * 3), (256, 1, 69, [(11008, 20)] * 2),
-    (256, 1, 52, [(14336, 80), (10240, 5), (28672, 20), (10241, 0)]), (256, 1, 40, [(4096, 80)] * 4), (256, 1, 26, [(28672, 72)]), (256, 2, 18, [(10245, 0)]),
+    (7, 1792, 15232, [(5120, 68)] * 3), (1, 1024, 1664, [(4593, 20)] * 3), (4, 1792, 5616, [(5120, 72)] * 3), (1, 1024, 1664, [(11008, 20)] * 2),
+    (1, 1024, 2176, [(14336, 80), (10240, 5), (28672, 20), (10241, 0)]), (1, 1024, 2176, [(4096, 80)] * 4), (1, 1024, 4352, [(28672, 72)]),
+    (2, 1024, 8704, [(10245, 0)]), (4, 1024, 5616, [(28672, 0), (14336, 0)]),
 ]
 
 
+def check(layers, plan):
+    """No more blocks with rows than CUs, on the whole and - blocks go to the XCDs round-robin, in dispatch order - on any XCD."""
+    _, in_line, rows, late_rows, *blocks = plan
+    blocks = [e + l for e, l in zip(blocks[::2], blocks[1::2])]
+    assert sum(blocks) <= CUS and 0 < late_rows <= rows, (layers, plan)
+    if in_line:
+        first = sum(p for _, p in layers)
+        ids = range(first, first + sum(blocks))
+    else:
+        assert len(set(layers)) == 1
+        ids = [(p + b) * len(layers) + i for i, ((_, p), n) in enumerate(zip(layers, blocks)) for b in range(n)]
+    assert max(sum(i % XCDS == x for i in ids) for x in range(XCDS)) <= CUS // XCDS, (layers, plan)
+
+
 def test_no_more_blocks_than_compute_units(plans):
-    for (cus, _, _, layers), (rows, late_rows, *blocks) in zip(CALLS, plans(CALLS)):
-        assert sum(blocks) <= cus and 0 < late_rows <= rows, (layers, rows, late_rows, blocks)
+    for (*_, layers), plan in zip(CALLS, plans(CALLS)):
+        check(layers, plan)
 
 
 def test_random_launches(plans):
@@ -47,11 +65,12 @@ def test_random_launches(plans):
         n = rng.randint(1, 4)
         rows = [round(10240 * 28 ** rng.random()) for _ in range(n)] if rng.random() < 0.5 else [round(10240 / n * 28 ** rng.random())] * n
         preparing = [rng.choice([0, 2, 5, 20, 40, 72, 80]) for _ in range(n)] if rng.random() < 0.3 else [rng.choice([0, 2, 5, 20, 40, 72, 80])] * n
-        calls.append((256, rng.randint(1, 8), round(2 * 400 ** rng.random()), list(zip(rows, preparing))))
-    for (cus, _, behind, layers), (rows, late_rows, *blocks) in zip(calls, plans(calls)):
-        assert sum(blocks) <= cus and 0 < late_rows <= rows, (behind, layers, rows, late_rows, blocks)
+        calls.append((rng.randint(1, 8), 1024 * rng.choice([1, 1, 2, 4, 8]), round(150 * 100 ** rng.random()), list(zip(rows, preparing))))
+    for (*_, layers), plan in zip(calls, plans(calls)):
+        check(layers, plan)
         # and they are dealt out evenly: nobody owns more than 1.3 times the even share, with those that wait owning `behind` rows less,
         # and a round of four tiles
-        total, prep = sum(n for n, _ in layers), sum(p for _, p in layers)
-        even = max((total + prep * behind) / cus, total / max(cus - prep, cus / 2))
-        assert rows <= 1.3 * even + 64, (behind, layers, rows, even)
+        total, prep, behind, rows = sum(n for n, _ in layers), sum(p for _, p in layers), plan[0], plan[2]
+        even = max((total + prep * behind) / CUS, total / max(CUS - prep, CUS / 2))
+        assert rows <= 1.3 * even + 64, (layers, plan, even)
+
