@@ -74,3 +74,9 @@ def test_random_launches(plans):
         even = max((total + prep * behind) / CUS, total / max(CUS - prep, CUS / 2))
         assert rows <= 1.3 * even + 64, (layers, plan, even)
 
+
+def test_blocks_behind_long_slices_own_fewer_rows(plans):
+    """A down-projection over slices of 8192 activations (K = 32768, r = 200) takes more than twice as long as one over 1024."""
+    layer = [(10240, 65)]
+    short, long = plans([(8, 1024, 17408, layer), (8, 8192, 17408, layer)])
+    assert long[0] >= 3 * short[0] and long[2] - long[3] > short[2] - short[3]
