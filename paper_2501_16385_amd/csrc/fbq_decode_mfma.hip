@@ -38,9 +38,8 @@
 // s (D' - XS - z X) to its accumulator: the same factorisation as in the one-token kernel.
 //
 // A block's eight waves split K.  The up-projection enters the same accumulators as r more values of
-// k (t split into two fp16 halves: t_hi + t_lo carries 22 bits of the fp32 sum), in units of
-// (tile, 32 taps) dealt out to the waves; then the waves' partial tiles meet in LDS and y is stored
-// once.  Layers that read the same activations (q/k/v, gate/up) share the launch.
+// k (t split into two fp16 halves: t_hi + t_lo carries 22 bits of the fp32 sum), 32 taps a wave for all tiles of
+// the block; then the waves' partial tiles meet in LDS and y is stored once.  Layers that read the same activations (q/k/v, gate/up) share the launch.
 #include <type_traits>
 
 #include "fbq_few_tokens.h"
@@ -222,24 +221,28 @@ __global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const Smal
         odd[ti] = (n * p.G) & 1;                        // of the row the lane ends up with; the wave's first group is a multiple of four
     }
 
-    // Up-projection: r more values of k, in units of (tile, 32 taps) dealt out to the waves.  Lane (c, q)
-    // needs t[token c][j .. j + 7] and Bt[row c of the tile][j .. j + 7], j = 32 js + 8 q; taps past r read
-    // beyond the buffers, i.e. zeros.  The Bt part of the wave's first unit (cold, from HBM) is requested
+    // Up-projection: r more values of k, 32 taps a wave.  Lane (c, q) needs t[token c][j .. j + 7] and Bt[row c of every tile][j .. j + 7],
+    // j = 32 wave + 8 q; taps past r read beyond the buffers, i.e. zeros.  The Bt part of the first tile or two (cold, from HBM) is requested
     // here with everything else; t (a few KB that every block reads) is fetched when it is needed.
+    // The wave follows from the taps alone: dealt out by (tile, taps), what is added to which partial sum, and with it a result's last
+    // bit, depended on how many tiles a block owned, i.e. on what the layer shared the launch with.  And a wave polls for t once and not
+    // for every tile, and the first waves, which are done first, do it: us, INT3, r = 64, 16 tokens of 4096 x 4096 8.6 dealt out by (tile, taps) of the
+    // block, 9.2 by the tile's place in the layer, 8.4 like this; 8192 x 4096, r = 200, 8 tokens 12.7 / 10.2; 4096 x 11008, INT4, 8 tokens 14.9 / 15.0.
     const int tap_steps = BRANCH ? (p.r + 31) / 32 : 0;
-    const int units = T * tap_steps;
     const __amdgpu_buffer_rsrc_t tbuf = buffer_of(p.tsum, BRANCH ? (long)kTokens * p.r * 8 : 0);
     const __amdgpu_buffer_rsrc_t bbuf = buffer_of(p.Bt, BRANCH ? (long)p.N * p.r * 2 : 0);
     constexpr int kNowhere = 0x7FFFFFF0;                // beyond every buffer
-    half8_t ubf;
-    auto request_taps = [&](int u) __attribute__((always_inline)) {
-        const int ti = u / max(tap_steps, 1), js = u - ti * tap_steps;
-        const int j = js * 32 + q * 8;
-        const bool on = u < units && j < p.r;          // r is a multiple of 8: all eight taps or none
+    constexpr int kEarlyTaps = T <= 2 ? T : (BITS == 4 && T == 3 ? 0 : 1);   // (no register left for it there)
+    half8_t ubf[kEarlyTaps > 0 ? kEarlyTaps : 1];
+    auto taps_of = [&](int ti) __attribute__((always_inline)) {
+        const int j = wave * 32 + q * 8;
         const int n = min((tile0 + ti) * 16 + c, p.N - 1);
-        ubf = __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(bbuf, on ? (n * p.r + j) * 2 : kNowhere, 0, 0));
+        return __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(bbuf, j < p.r ? (n * p.r + j) * 2 : kNowhere, 0, 0));   // r is a multiple of 8: all eight taps or none
     };
-    if (BRANCH) request_taps(wave);
+    if (BRANCH) {
+#pragma unroll
+        for (int ti = 0; ti < kEarlyTaps; ++ti) ubf[ti] = taps_of(ti);
+    }
 
     uint32_t k6400 = 0x64006400u;
     asm volatile("" : "+v"(k6400));                     // keep the constant in a VGPR for v_and_or_b32
@@ -357,50 +360,50 @@ __global__ __launch_bounds__(64 * kMainWaves) void fbq_small_m_kernel(const Smal
         }
     }
 
-    if (BRANCH) {
-        for (int u = wave; u < units; u += kMainWaves) {   // wave-uniform; the first unit's Bt operand is already here
-            const int ti = u / tap_steps, js = u - ti * tap_steps;
-            const int j = js * 32 + q * 8;
-            // t[token c][j .. j + 7]: eight words {t, launch tag} (four 16-byte device-scope loads), written long ago
-            // as a rule.  Should the tags not turn up, the lane computes its eight values itself.
-            float t[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};   // (taps past r stay zero also when nothing is ever polled)
-            bool ready = false;
-            const int off = j < p.r ? (c * p.r + j) * 8 : kNowhere;
-            for (int spin = 0; spin < p.spin_limit && !ready; ++spin) {
-                bool ok = true;
+    if (BRANCH && wave < tap_steps) {                   // wave-uniform
+        half8_t late[T];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint4_t w = __builtin_amdgcn_raw_buffer_load_b128(tbuf, off + 16 * i, 0, kCacheSc1);
-                    const uint32_t v0 = w.x, v1 = w.z;
-                    t[2 * i] = __builtin_bit_cast(float, v0);
-                    t[2 * i + 1] = __builtin_bit_cast(float, v1);
-                    ok = ok && (j >= p.r || (w.y == tag && w.w == tag));
-                }
-                ready = __all(ok);
-                if (!ready) __builtin_amdgcn_s_sleep(4);
-            }
-            if (!ready && j < p.r) {
-                const uint16_t *xr = p.x + (size_t)min(c, p.M - 1) * p.K;
+        for (int ti = kEarlyTaps; ti < T; ++ti) late[ti] = taps_of(ti);
+        const int j = wave * 32 + q * 8;
+        // t[token c][j .. j + 7]: eight words {t, launch tag} (four 16-byte device-scope loads), written long ago
+        // as a rule.  Should the tags not turn up, the lane computes its eight values itself.
+        float t[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};   // (taps past r stay zero also when nothing is ever polled)
+        bool ready = false;
+        const int off = j < p.r ? (c * p.r + j) * 8 : kNowhere;
+        for (int spin = 0; spin < p.spin_limit && !ready; ++spin) {
+            bool ok = true;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const uint16_t *ar = p.At + (size_t)(j + e) * p.K;
-                    float a = 0.0f;
-                    for (int k = 0; k < p.K; ++k) a = fmaf((float)__builtin_bit_cast(half_t, xr[k]), (float)__builtin_bit_cast(half_t, ar[k]), a);
-                    t[e] = a;
-                }
+            for (int i = 0; i < 4; ++i) {
+                const uint4_t w = __builtin_amdgcn_raw_buffer_load_b128(tbuf, off + 16 * i, 0, kCacheSc1);
+                const uint32_t v0 = w.x, v1 = w.z;
+                t[2 * i] = __builtin_bit_cast(float, v0);
+                t[2 * i + 1] = __builtin_bit_cast(float, v1);
+                ok = ok && (j >= p.r || (w.y == tag && w.w == tag));
             }
-            half8_t thi, tlo;                           // t_hi + t_lo carries 22 bits of the fp32 sum
+            ready = __all(ok);
+            if (!ready) __builtin_amdgcn_s_sleep(4);
+        }
+        if (!ready && j < p.r) {
+            const uint16_t *xr = p.x + (size_t)min(c, p.M - 1) * p.K;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                thi[e] = (half_t)t[e];
-                tlo[e] = (half_t)(t[e] - (float)thi[e]);
+                const uint16_t *ar = p.At + (size_t)(j + e) * p.K;
+                float a = 0.0f;
+                for (int k = 0; k < p.K; ++k) a = fmaf((float)__builtin_bit_cast(half_t, xr[k]), (float)__builtin_bit_cast(half_t, ar[k]), a);
+                t[e] = a;
             }
-            float4_t d = mfma(thi, ubf, zero4);
-            d = mfma(tlo, ubf, d);
+        }
+        half8_t thi, tlo;                               // t_hi + t_lo carries 22 bits of the fp32 sum
 #pragma unroll
-            for (int k = 0; k < T; ++k)
-                if (k == ti) acc[k] += d;
-            if (u + kMainWaves < units) request_taps(u + kMainWaves);
+        for (int e = 0; e < 8; ++e) {
+            thi[e] = (half_t)t[e];
+            tlo[e] = (half_t)(t[e] - (float)thi[e]);
+        }
+#pragma unroll
+        for (int ti = 0; ti < T; ++ti) {
+            const half8_t b = ti < kEarlyTaps ? ubf[ti < kEarlyTaps ? ti : 0] : late[ti];
+            float4_t d = mfma(thi, b, zero4);
+            acc[ti] += mfma(tlo, b, d);
         }
     }
 

@@ -301,6 +301,25 @@ def test_group_of_wide_layers_four_tiles_per_block(bits):
         assert_matches_oracle(y.cpu().numpy(), oracle_y(L, x_np), "grouped call", tol=Y_TOL)
 
 
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("K,layers", [(4096, [(4096, 64)] * 3), (4096, [(4096, 128), (1024, 128), (1000, 40)]), (2048, [(2048, 128)] * 4),
+                                      (8192, [(8192, 128), (1024, 72)]), (11008, [(4096, 64), (4099, 256)])])
+def test_group_gives_each_layer_its_own_bits(bits, K, layers):
+    """Blocks own another number of tiles in a group than in a call of its own, and the waves split a tile's taps: the order in which a
+    result's fp32 parts are added must not depend on that.  (A few results in a hundred thousand differ in their last bit if it does.)"""
+    import torch
+    import paper_2501_16385_amd as fbq
+    from paper_2501_16385_amd.random_layers import random_layer
+    g = torch.Generator(device="cuda")
+    g.manual_seed(33)
+    devs = [random_layer(fbq.Desc(N, K, r, bits), g, gain=0.5) for N, r in layers]
+    for M in (4, 16):
+        x = torch.randn(M, K, device="cuda", generator=g).half()
+        ys = fbq.linear_group(devs, [x] * len(devs))
+        for dev, y in zip(devs, ys):
+            assert torch.equal(y, fbq.linear(dev, x)), (dev.desc, M)
+
+
 def test_group_rejects_a_bad_layer_before_launching_any():
     import torch
     import paper_2501_16385_amd as fbq
