@@ -293,7 +293,6 @@ __global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu
     uint4_t tw[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) tw[k] = uint4_t{0, 0, 0, 0};
-    bool asked = false;
     auto ask_t = [&]() __attribute__((always_inline)) {
         const int l = afresh(lane), j = 32 * wave + 8 * (l >> 4);
         const int off = (l & 15) < 4 * XL && j < p.r ? ((l & 15) * p.r + j) * 8 : kNowhere;
@@ -341,10 +340,6 @@ __global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu
                     u_slot = u_slot + 1 == kRing ? 0 : u_slot + 1;
                     --ahead;
                     issue_next();
-                    if (C == 1 && ti == nt - 1 && pass == passes - 1 && first_tile + kRoundTiles >= tiles && wave < tap_steps && p.spin_limit > 0) {
-                        ask_t();                        // while the last tile is worked on
-                        asked = true;
-                    }
                     const uint32_t s01 = __builtin_amdgcn_alignbit(s4.y, s4.x, 16 * odd) & smask[ch][0], s23 = __builtin_amdgcn_alignbit(s4.z, s4.y, 16 * odd) & smask[ch][1];
                     // the zero points of all four groups are one more product: sums of activations [token][group] times -s z [group][row]
                     acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[ch], q < valid[ch] ? -(float)sq * (float)zq : 0.0f, acc, 0, 0, 0);
@@ -379,7 +374,9 @@ __global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu
                 for (int k = 0; k < kHeld; ++k) late[k] = taps(my_row, k);
             }
             if (wave < tap_steps) {
-                if (!asked && p.spin_limit > 0) ask_t();
+                // (Not while the last tile is worked on: an answer that comes too early costs a second round trip, and more blocks
+                // wait for words that are not there yet.  11008 x 4096, r = 64, 16 tokens: INT4 11.4 us with the early request, 11.1 without, INT3 10.5 / 10.0.)
+                if (p.spin_limit > 0) ask_t();
                 const int l = afresh(lane), c = l & 15, j = 32 * wave + 8 * (l >> 4);
                 const bool mine_too = c < 4 * XL && j < p.r;
                 bool ready = false;
@@ -410,7 +407,6 @@ __global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu
                 *reinterpret_cast<half8_t *>(lds + kTapAt + wave * 2048 + l * 16) = hi;
                 *reinterpret_cast<half8_t *>(lds + kTapAt + wave * 2048 + 1024 + l * 16) = lo;
             }
-            asked = false;
         }
         block_barrier();
         const int mt = wave - (first_tile - eight);
