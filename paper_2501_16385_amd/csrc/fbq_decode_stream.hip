@@ -30,13 +30,13 @@
 // out in sweeps over the layer instead of runs (35.8 against 33.3).  Instances must not spill: scratch memory alone costs a launch 2 us.
 #include <type_traits>
 
-#include "fbq_few_tokens.h"
+#include "fbq_few_burst.h"
 #include "fbq_stream_plan.h"
 
 namespace fbq {
 
 constexpr int kUnitGroups = 4;       // quantization groups of a unit: 16 rows x 4 groups, what one ring slot holds
-constexpr int kPassGroups = kMainWaves * kUnitGroups;
+static_assert(kPassGroups == kMainWaves * kUnitGroups, "both kernels take as many groups a pass");
 constexpr int kRing = 3;             // ring slots per wave
 constexpr int kRoundTiles = 4;       // row tiles between two meetings of the waves
 
@@ -71,12 +71,35 @@ struct StreamParams {
     int passes, share;     // passes over K, and the groups a wave takes in each
     int spin_limit;        // polls for t before a wave computes it itself; negative: at once (test hook)
 };
+template <bool LINE>
 struct StreamGroup {
     StreamParams layer[kMaxSmallGroup];
-    // Blocks of a grid one block wide and high are in line (see fbq_stream_plan.h): segments 0..3 are the layers' preparing blocks, 4..7
-    // those with their rows; where each starts.
+};
+// Blocks in line (see fbq_stream_plan.h): segments 0..3 are the layers' preparing blocks, 4..7 those with their rows; where each starts.
+// Layers that are too small for this kernel can come along: `early` is kBurst, and blocks of the other kernel are among their preparing ones.
+template <>
+struct StreamGroup<true> {
+    StreamParams layer[kMaxSmallGroup];
     int segment[2 * kMaxSmallGroup];
 };
+constexpr int kBurst = -1;
+constexpr int burst_tiles(int G) { return G <= kPassGroups ? 3 : 2; }   // tiles of rows of such a block (two or three up to K = 4096: {11008, 4096} x 4096, INT3, no sub-branch 12.6 / 11.8 us)
+
+// Whether small layers share the launch of streamed ones.  Not where rows are so short that a block of theirs is all fixed cost, so long that their
+// blocks' passes outlast the stream, or, with two passes and more, where they alone fill the GPU.  us, each kind in a launch of its own / together, 8 tokens
+// without a sub-branch and 16 with r = 64: {11008, 4096} x 4096, INT4, 15.6 / 12.6 and 18.9 / 15.4; {10240, 1024, 1024} x 4096, INT3, 14.4 / 10.4 and 17.9 / 13.6;
+// {32768, 1024, 1024} x 2048, INT4, 19.0 / 16.1 and 25.1 / 19.7; {12288, 1024, 1024} x 12288, INT4, 34.8 / 27.9 and 39.9 / 38.5.  On the other
+// side: {110000, 4000} x 384, INT3, 37.9 / 42.9 and 44.8 / 51.0; {40000, 2048, 2048, 2048} x 1024, INT3, 22.4 / 23.9 and 26.7 / 29.4;
+// {16384, 1024, 1024} x 16384, INT3, 47.5 / 50.7 and 56.0 / 69.6; {13000, 1000} x 14336, INT3, 43.7 / 29.6 and 48.2 / 49.5; {10240, 8192} x
+// 8192, INT4, 28.4 / 26.4 and, r = 128, 33.1 / 34.9.
+bool burst_joins_stream(const LinearArgs *layers, int n_layers, const bool *burst)
+{
+    int bursts = 0;
+    for (int i = 0; i < n_layers; ++i) bursts += burst[i] ? ceil_div(layers[i].N, 16 * burst_tiles(layers[i].K / kGroup)) : 0;
+    const int K = layers[0].K;
+    return K >= 2048 && (K <= 4096 || (K <= (layers[0].r > 0 ? 12288 : 14336) && bursts < cu_count()));
+}
+static_assert(kMainWaves * (3 * 1024 + kTokens * 17 * 16) <= kLdsBytes, "the other kernel's buffers must fit into this one's");
 
 // The four matrix operands of a lane's 32 codes: every field stays where it is, masked out, i.e. it is the subnormal fp16
 // number code x gain x 2^-24, which the matrix cores multiply exactly (measured).  Pair order (also the order of the
@@ -112,15 +135,16 @@ __device__ __forceinline__ void code_operands(const uint4_t w, half8_t (&b)[4])
 // ------------------------------------------------------------------ fused kernel
 
 // BITS: 3 or 4.  C: units of weights a wave takes per tile and pass (4 C groups).  MULTI: several passes over K.  XL: loads of four token rows a group of activations takes.
-template <int BITS, int C, int XL, bool MULTI>
-__global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void fbq_few_stream_kernel(const StreamGroup g)
+// LINE: layers dealt out in line; instances of their own, as finding out the layer costs every block 0.05 to 0.1 us.
+template <int BITS, int C, int XL, bool MULTI, bool LINE>
+__global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void fbq_few_stream_kernel(const StreamGroup<LINE> g)
 {
     constexpr int kPiece = BITS == 4 ? 16 : 12;         // bytes of 32 codes
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kLdsBytes];
 
     int layer = blockIdx.x, index = blockIdx.y;         // the block's place in its layer, preparing blocks first
-    if (blockIdx.z > 0) {                               // in line (the first block of a line is the first of a grid, too)
-        const int id = blockIdx.z;
+    if constexpr (LINE) {
+        const int id = blockIdx.x;
         int s = 0;
 #pragma unroll
         for (int i = 1; i < 2 * kMaxSmallGroup; ++i) s = id >= g.segment[i] ? i : s;
@@ -140,6 +164,14 @@ __global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu
         return;
     }
     const int block = index - p.down_blocks - p.sum_blocks;
+    if constexpr (LINE) {
+        if (p.early == kBurst) {
+            constexpr int kBurstTiles = burst_tiles(C == 1 && !MULTI ? kPassGroups : 2 * kPassGroups);
+            few_burst_block<BITS, kBurstTiles, true, true, true>(p, block * kBurstTiles, tag, reinterpret_cast<float4_t (*)[kBurstTiles][64]>(lds),
+                                                                 reinterpret_cast<uint4_t (*)[kTokens * 17]>(lds + kMainWaves * kBurstTiles * 1024));
+            return;
+        }
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, q = lane >> 4;
@@ -456,19 +488,24 @@ __global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu
     }
 }
 
-template <int BITS, int C, bool MULTI>
-static void launch_instance(const StreamGroup &g, bool half, dim3 grid, hipStream_t stream)
+template <int BITS, int C, bool MULTI, bool LINE>
+static void launch_instance(const StreamGroup<LINE> &g, bool half, dim3 grid, hipStream_t stream)
 {
-    if (half) hipLaunchKernelGGL((fbq_few_stream_kernel<BITS, C, 2, MULTI>), grid, dim3(64 * kMainWaves), 0, stream, g);
-    else hipLaunchKernelGGL((fbq_few_stream_kernel<BITS, C, 4, MULTI>), grid, dim3(64 * kMainWaves), 0, stream, g);
+    if (half) hipLaunchKernelGGL((fbq_few_stream_kernel<BITS, C, 2, MULTI, LINE>), grid, dim3(64 * kMainWaves), 0, stream, g);
+    else hipLaunchKernelGGL((fbq_few_stream_kernel<BITS, C, 4, MULTI, LINE>), grid, dim3(64 * kMainWaves), 0, stream, g);
 }
-template <int BITS>
-static hipError_t launch_bits(const StreamGroup &g, int chunks, bool half, dim3 grid, hipStream_t stream)
+template <bool LINE>
+static hipError_t launch_group(const StreamGroup<LINE> &g, int bits, int chunks, bool multi, bool half, dim3 grid, hipStream_t stream)
 {
-    const bool multi = g.layer[0].passes > 1;
-    if (chunks > 1) launch_instance<BITS, 2, false>(g, half, grid, stream);
-    else if (multi) launch_instance<BITS, 1, true>(g, half, grid, stream);
-    else launch_instance<BITS, 1, false>(g, half, grid, stream);
+    if (bits == 4) {
+        if (chunks > 1) launch_instance<4, 2, false>(g, half, grid, stream);
+        else if (multi) launch_instance<4, 1, true>(g, half, grid, stream);
+        else launch_instance<4, 1, false>(g, half, grid, stream);
+    } else {
+        if (chunks > 1) launch_instance<3, 2, false>(g, half, grid, stream);
+        else if (multi) launch_instance<3, 1, true>(g, half, grid, stream);
+        else launch_instance<3, 1, false>(g, half, grid, stream);
+    }
     return hipGetLastError();
 }
 
@@ -482,27 +519,39 @@ static int slice_length(int K, int r)
     while (ceil_div(r, 16) * ceil_div(K, len) > kMaxDownBlocks) len += kStep;
     return len;
 }
-static int preparing_blocks(const LinearArgs &a) { return a.r > 0 ? ceil_div(a.r, 16) * (ceil_div(a.K, slice_length(a.K, a.r)) + 1) : 0; }
+static int down_blocks(const LinearArgs &a, int slice) { return a.r > 0 ? ceil_div(a.r, 16) * (ceil_div(a.K, slice) + 1) : 0; }
 
-hipError_t launch_few_stream(const LinearArgs *layers, int n_layers, hipStream_t stream)
+hipError_t launch_few_stream(const LinearArgs *layers, int n_layers, const bool *burst, hipStream_t stream)
 {
     const LinearArgs &first = layers[0];
-    int rows_of[kMaxSmallGroup], preparing[kMaxSmallGroup], most = 0, slice = 1024;
-    for (int i = 0; i < n_layers; ++i) {
-        rows_of[i] = layers[i].N;
-        preparing[i] = preparing_blocks(layers[i]);
-        if (layers[i].r > 0) slice = std::max(slice, slice_length(layers[i].K, layers[i].r));
-        most = std::max(most, layers[i].M);
-    }
     const int G = first.K / kGroup;
     const int chunks = G > kPassGroups && G <= 2 * kPassGroups ? 2 : 1;
     const int passes = ceil_div(G, chunks * kPassGroups), share = ceil_div(G, kMainWaves * passes);
-    const int behind = stream_rows_behind(slice, (int)row_words(first.K, first.bits) * 4 + 4 * G);
+    int order[kMaxSmallGroup], rows_of[kMaxSmallGroup], preparing[kMaxSmallGroup], slice[kMaxSmallGroup], most = 0, n = 0;
+    long busy = 0;                                       // what CUs would stream in while they run preparing blocks, in bytes
+    int prep = 0;
+    for (int kind = 1; kind >= 0; --kind) {              // small layers first: their blocks are short
+        for (int i = 0; i < n_layers; ++i) {
+            if (burst[i] != (bool)kind) continue;
+            const LinearArgs &a = layers[i];
+            slice[n] = kind ? burst_slice_length(a.K) : slice_length(a.K, a.r);
+            const int down = down_blocks(a, slice[n]), bursts = kind ? ceil_div(a.N, 16 * burst_tiles(G)) : 0;
+            rows_of[n] = kind ? 0 : a.N;
+            preparing[n] = down + bursts;
+            busy += (long)down * stream_down_bytes(slice[n]) + (long)bursts * stream_burst_bytes(a.K);
+            prep += preparing[n];
+            most = std::max(most, a.M);
+            order[n++] = i;
+        }
+    }
+    const int row_bytes = (int)row_words(first.K, first.bits) * 4 + 4 * G;
+    const int behind = prep ? std::max(1, (int)(busy / prep / row_bytes)) : 0;
+    const bool line = stream_in_line(rows_of, preparing, n_layers);
     const StreamPlan plan = plan_stream(rows_of, preparing, n_layers, behind, passes, cu_count());
-    StreamGroup g;
+    StreamGroup<true> g;
     int widest = 0;
     for (int i = 0; i < n_layers; ++i) {
-        const LinearArgs &a = layers[i];
+        const LinearArgs &a = layers[order[i]];
         StreamParams &p = g.layer[i];
         p.qw = a.qw; p.scales = a.scales; p.zeros = a.zeros; p.At = a.At; p.Bt = a.Bt; p.x = a.x; p.y = a.y;
         p.tpart = (uint64_t *)a.workspace;               // each layer's own partial sums of t ...
@@ -511,29 +560,31 @@ hipError_t launch_few_stream(const LinearArgs *layers, int n_layers, hipStream_t
         p.M = a.M; p.N = a.N; p.K = a.K; p.r = a.r;
         p.row_words = (int)row_words(a.K, a.bits);
         p.G = G;
-        p.kslice = slice_length(a.K, a.r);
+        p.kslice = slice[i];
         p.slices = ceil_div(a.K, p.kslice);
         p.down_blocks = a.r > 0 ? ceil_div(a.r, 16) * p.slices : 0;
         p.sum_blocks = a.r > 0 ? ceil_div(a.r, 16) : 0;
         p.rows = plan.rows;
         p.late_rows = plan.late_rows;
-        p.early = plan.early[i];
+        p.early = burst[order[i]] ? kBurst : plan.early[i];
         p.passes = passes; p.share = share;
         p.spin_limit = spin_limit();
-        widest = std::max(widest, p.down_blocks + p.sum_blocks + p.early + plan.late[i]);
+        widest = std::max(widest, preparing[i] + plan.early[i] + plan.late[i]);
     }
-    for (int i = n_layers; i < kMaxSmallGroup; ++i) g.layer[i] = g.layer[0];   // never indexed: grid.x stops at n_layers
-    dim3 grid(n_layers, widest);
-    if (stream_in_line(rows_of, preparing, n_layers)) {
+    for (int i = n_layers; i < kMaxSmallGroup; ++i) g.layer[i] = g.layer[0];   // never indexed: the grid stops before
+    const bool half = most <= 8;
+    if (line) {
         int start = 0;
         for (int s = 0; s < 2 * kMaxSmallGroup; ++s) {
             const int i = s & (kMaxSmallGroup - 1);
             g.segment[s] = start;
             if (i < n_layers) start += s < kMaxSmallGroup ? preparing[i] : plan.early[i] + plan.late[i];
         }
-        grid = dim3(1, 1, start);
+        return launch_group(g, first.bits, chunks, passes > 1, half, dim3(start), stream);
     }
-    return first.bits == 4 ? launch_bits<4>(g, chunks, most <= 8, grid, stream) : launch_bits<3>(g, chunks, most <= 8, grid, stream);
+    StreamGroup<false> alike;
+    std::copy(g.layer, g.layer + kMaxSmallGroup, alike.layer);
+    return launch_group(alike, first.bits, chunks, passes > 1, half, dim3(n_layers, widest), stream);
 }
 
 }  // namespace fbq

@@ -65,7 +65,8 @@ hipError_t launch_gemv_decode(const LinearArgs *layers, int n_layers, hipStream_
 bool decode_group_compatible(const LinearArgs &a, const LinearArgs &b);
 hipError_t launch_gemv_small_m(const LinearArgs *layers, int n_layers, hipStream_t stream);
 bool small_m_group_compatible(const LinearArgs &a, const LinearArgs &b);
-hipError_t launch_few_stream(const LinearArgs *layers, int n_layers, hipStream_t stream);   // (by way of launch_gemv_small_m)
+bool burst_joins_stream(const LinearArgs *layers, int n_layers, const bool *burst);
+hipError_t launch_few_stream(const LinearArgs *layers, int n_layers, const bool *burst, hipStream_t stream);   // (by way of launch_gemv_small_m, which says which layers are too small)
 hipError_t launch_prepass_prefill(const LinearArgs &a, hipStream_t stream);
 hipError_t launch_gemm_prefill(const LinearArgs &a, hipStream_t stream);
 hipError_t launch_unpack(const fbq_desc &d, const uint32_t *qw, uint8_t *codes, hipStream_t stream);

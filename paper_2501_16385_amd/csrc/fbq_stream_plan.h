@@ -22,16 +22,14 @@ struct StreamPlan {
     int early[kMaxSmallGroup], late[kMaxSmallGroup];   // blocks with rows, by layer
 };
 
-// Rows that a CU streams in while the blocks of a down-projection run (slice: activations of each, row_bytes: codes, scales and zeros of a
-// row), at 23 KB per us: 5 us, and as a wave has an eighth of the slice and asks for 128 activations at once, 1.7 more for every further 1024 of
+// What a CU would stream in, in bytes at 23 KB per us, while it runs a block of a down-projection over `slice` activations: 5 us, and as a wave
+// has an eighth of the slice and asks for 128 activations at once, 1.7 more for every further 1024 of
 // a slice.  Two layers of 11008 x 4096 at 8 tokens, by the bytes allowed for: 40000 17.4 us, 70000 15.3, 100000 14.8, 130000 15.6;
 // 10240 x 32768, r = 200, slices of 8192: INT4, 8 tokens 60.2 us without the longer slices' time and 54.1 with it, INT3, 16 tokens 65.5 / 58.4
 // (slices of 4096, i.e. twice the blocks, 53.7 and 58.2, but two sets of 28672 -> 8192, r = 128, 80.5 instead of 60.7).
-inline int stream_rows_behind(int slice, int row_bytes)
-{
-    constexpr int kBytes = 115000, kBytesPerStep = 40000;
-    return std::max(1, (kBytes + (slice - 1024) / 1024 * kBytesPerStep) / row_bytes);
-}
+inline int stream_down_bytes(int slice) { return 115000 + (slice - 1024) / 1024 * 40000; }
+// ... and a block of the other kernel, three tiles of rows up to K = 4096, two beyond.
+inline int stream_burst_bytes(int K) { return K <= 4096 ? 60000 + 35 * K : 35000 + ceil_div(K, 4096) * 120000; }
 
 // Whether the layers of a launch are dealt out in line.
 inline bool stream_in_line(const int *N, const int *preparing, int n)

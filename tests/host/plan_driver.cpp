@@ -19,7 +19,7 @@ int main()
         int cus, passes, slice, row_bytes, N[kMaxSmallGroup], preparing[kMaxSmallGroup], n = 0;
         in >> cus >> passes >> slice >> row_bytes;
         while (n < kMaxSmallGroup && in >> N[n] >> preparing[n]) ++n;
-        const int behind = stream_rows_behind(slice, row_bytes);
+        const int behind = std::max(1, stream_down_bytes(slice) / row_bytes);
         const StreamPlan p = plan_stream(N, preparing, n, behind, passes, cus);
         printf("%d %d %d %d", behind, stream_in_line(N, preparing, n), p.rows, p.late_rows);
         for (int i = 0; i < n; ++i) {

@@ -417,6 +417,13 @@ UNEQUAL_GROUPS = [
     (4224, [(10241, 64), (10240, 64), (12289, 8), (16385, 200)]),
     (8320, [(10240, 24), (13001, 136)]),
     (4096, [(10240, 64), (10240, 72), (10240, 64)]),
+    # layers too small for the streaming kernel along with it: below one block's rows, odd numbers of scales, more blocks than CUs, alone after it
+    (4096, [(10240, 64), (1024, 64), (1000, 16)]),
+    (4096, [(8200, 128), (11008, 8)]),
+    (1280, [(33001, 0), (700, 0), (8001, 0)]),
+    (4224, [(999, 40), (10241, 200), (7, 8)]),
+    (8320, [(13001, 136), (4099, 8)]),
+    (12288, [(10240, 64), (1024, 64), (1024, 64)]),
 ]
 
 
@@ -433,9 +440,17 @@ def test_stream_group_of_unequal_layers(K, layers, M, bits):
     devs = [framed_layer(random_layer(fbq.Desc(N, K, r, bits), g, gain=1.0)) for N, r in layers]
     x = framed_in_nan(torch.randn(M, K, device="cuda", generator=g).half())
     single = [fbq.linear(l, x) for l in devs]
+    with_ = [framed_in_nan(torch.randn(M, N, device="cuda", generator=g).half()) for N, _ in layers]
     for order in (slice(None), slice(None, None, -1)):
-        ys = [framed_in_nan(torch.empty_like(y)) for y in single[order]]
-        fbq.linear_group(devs[order], [x] * len(devs), ys=ys)
+        ys, outs = ([framed_in_nan(torch.empty_like(y)) for y in single[order]] for _ in range(2))
+        wss = [torch.zeros(fbq.workspace_bytes(l.desc, M), dtype=torch.uint8, device="cuda") if l.desc.r else None for l in devs[order]]
+        fbq.linear_group(devs[order], [x] * len(devs), ys=ys, workspaces=wss)
         torch.cuda.synchronize()
         for (N, r), y, want in zip(layers[order], ys, single[order]):
             assert torch.equal(y, want), (N, r)
+            y.fill_(0)
+        arr, mix = fbq.make_group(devs[order], [x] * len(devs), ys, wss), fbq.make_mix(with_[order], outs)
+        assert fbq.load().fbq_linear_group_mix(arr, mix, len(devs), M, torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        for (N, r), y, want, w, out in zip(layers[order], ys, single[order], with_[order], outs):
+            assert torch.equal(y, want) and torch.equal(out, torch.lerp(w, want, 0.5)), (N, r)

@@ -1,4 +1,4 @@
-"""What a call leaves behind when one of its launches fails, on the CPU: the process's kernel launches go to a recorder
+"""What a call launches, and what it leaves behind when one of its launches fails, on the CPU: the process's kernel launches go to a recorder
 (tests/host/launch_recorder.cpp) that lets the n-th one fail, and nothing runs."""
 import os
 import shutil
@@ -70,3 +70,45 @@ def test_train_step_moves_both_masters_in_its_last_launch(recorder):
         assert "cast_masters" in launches[0][0] and launches[0][1:] == [True, True]
         assert launches[-1][1:] == [True, True], launches
         assert all(l[1:] == [False, False] for l in launches[1:-1]), launches
+
+
+GROUP_CHILD = r"""
+import ctypes, json, sys
+sys.path[:0] = [sys.argv[1]]
+import paper_2501_16385_amd as fbq
+lib = fbq.load()
+launched = []
+
+@ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_char_p, ctypes.POINTER(ctypes.c_void_p))
+def on_launch(name, args):
+    launched.append(name.decode())
+    return 0
+
+ctypes.CDLL(None).recorder_set_callback(on_launch)
+out = []
+for K, r, M, rows in json.loads(sys.argv[2]):
+    calls = [fbq.Desc(N, K, r, 4) for N in rows]
+    p = lambda i, j: 0x100000000 * (10 * i + j + 2)
+    arr = (fbq.fbq._CLayerCall * len(calls))(*(fbq.fbq._CLayerCall(d.c(), 0x100000000, p(i, 0), p(i, 1), p(i, 2), p(i, 3), p(i, 4), p(i, 5), p(i, 6), 1 << 30)
+                                               for i, d in enumerate(calls)))
+    launched.clear()
+    assert lib.fbq_linear_group(arr, len(calls), M, None) == 0
+    out.append(list(launched))
+print("RESULT " + json.dumps(out))
+"""
+
+
+def test_grouped_layers_share_a_launch(recorder):
+    """3 to 16 tokens: one launch for layers of one K on the same activations, also for a few small ones beside a large one (two launches cost 2 to 4 us
+    more); two where that is slower; never one for the large ones on their own account."""
+    import json
+    one = [(4096, 64, 16, [11008, 4096]), (4096, 0, 8, [1024, 10240, 1000]), (12288, 64, 4, [12288, 1024, 1024]), (4096, 64, 16, [4096, 4096, 4096]),
+           (4096, 64, 5, [11008, 11008]), (8192, 8, 3, [10240, 20000, 30000, 10241]), (14336, 0, 8, [13000, 1000])]
+    two = [(1024, 64, 16, [40000, 1024]), (16384, 64, 16, [16384, 1024]), (8192, 64, 16, [10240, 8192]), (14336, 64, 8, [13000, 1000])]
+    env = dict(os.environ, LD_PRELOAD=" ".join([recorder] + os.environ.get("LD_PRELOAD", "").split()))
+    res = subprocess.run([sys.executable, "-c", GROUP_CHILD, ROOT, json.dumps(one + two)], env=env, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
+    launches = json.loads(res.stdout.split("RESULT ")[1])
+    for call, names in zip(one + two, launches):
+        assert len(names) == (1 if call in one else 2), (call, names)
+        assert any("few_stream" in n for n in names) == any(N >= 10240 for N in call[3]), (call, names)

@@ -36,6 +36,8 @@ CALLS = [
     (7, 1792, 15232, [(5120, 68)] * 3), (1, 1024, 1664, [(4593, 20)] * 3), (4, 1792, 5616, [(5120, 72)] * 3), (1, 1024, 1664, [(11008, 20)] * 2),
     (1, 1024, 2176, [(14336, 80), (10240, 5), (28672, 20), (10241, 0)]), (1, 1024, 2176, [(4096, 80)] * 4), (1, 1024, 4352, [(28672, 72)]),
     (2, 1024, 8704, [(10245, 0)]), (4, 1024, 5616, [(28672, 0), (14336, 0)]),
+    # small layers along with a large one: they own no rows here, and have more preparing blocks, with 10240 and 8000 rows more than there are CUs
+    (1, 1024, 2176, [(0, 106), (11008, 20)]), (1, 1024, 2176, [(0, 190), (0, 190), (10240, 24)]), (1, 1024, 1664, [(0, 22), (0, 22), (10240, 0)]),
 ]
 
 
