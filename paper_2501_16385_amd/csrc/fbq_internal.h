@@ -192,6 +192,31 @@ inline PrefillCut prefill_cut(int M, int N, int K, int r)
     return best;
 }
 
+// K slices of the prefill down-projection, one block per slice and 32-token tile: eight for a thousand tokens, more
+// for fewer tokens so that the pass has about one block per compute unit (256 assumed: the workspace is sized
+// without a device), never narrower than 256 activations.  Slices are whole quantization groups: the kernel walks
+// them in chunks of 128.
+inline int down_slice_len(int M, int K)
+{
+    const int want = std::min(32, std::max(8, ceil_div(256, ceil_div(M, 32))));
+    return std::max(256, ceil_div(ceil_div(K, want), kGroup) * kGroup);
+}
+inline int down_slices(int M, int K) { return ceil_div(K, down_slice_len(M, K)); }
+
+// How many of the slices, in eights, are dealt out to the XCDs whole, so that a slice of A^T comes into one L2 and not into each that has
+// one of its token tiles (256 tokens of 28672 x 128, INT3: the pass reads 30 MB instead of 81 and takes 17.4 us instead of 19.6).  It pays
+// where A^T is large and eight tiles or more read it and where all blocks fit the GPU at once; the fused kernel finds the re-ordered x in other
+// L2s then, which costs the more of the call the narrower and shorter the layer is.  The call, us, before /
+// with it: 256 tokens of 20480 -> 1024, r = 256, 66.2 / 61.6, of 28672 -> 5120, r = 128, 115.3 / 112.5, of 13824 -> 1024, r = 128, 42.5 / 41.9, of
+// 28672 -> 512, r = 64, 54.4 / 53.3; on the other side of a line 256 tokens of 8192 -> 1024, r = 200, 44.6 / 46.7, of 6144 -> 512, r = 256, 3 % slower, of
+// 16384 -> 512, r = 96, 4 %, of 4096 -> 3456, r = 128, 36.3 / 37.1; 160 of 8192 -> 1024, r = 256, 41.6 / 43.2; 1092, 280 blocks, of 13952 -> 3456, r = 128, 151 / 156.
+inline int down_slices_by_xcd(int M, int N, int K, int r)
+{
+    const int tiles = ceil_div(M, 32), slices = down_slices(M, K);
+    const bool pays = r * K >= 1500000 && ((long)K * std::min(N, 2304) >= 14000000 || r * K >= 2600000);
+    return pays && tiles >= 8 && tiles * slices <= 256 ? slices & ~7 : 0;
+}
+
 size_t decode_workspace_bytes(int M, int K, int r);
 size_t small_m_workspace_bytes(int K, int r);
 size_t prefill_workspace_bytes(int M, int N, int K, int r);

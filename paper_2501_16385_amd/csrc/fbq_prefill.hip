@@ -630,17 +630,6 @@ __global__ __launch_bounds__(256) void fbq_arrange_x_kernel(const ArrangeParams 
 
 // ------------------------------------------------------------------ down-projection (prefill)
 
-// K slices of the prefill down-projection, one block per slice and 32-token tile: eight for a thousand tokens, more
-// for fewer tokens so that the pass has about one block per compute unit (256 assumed: the workspace is sized
-// without a device), never narrower than 256 activations.  Slices are whole quantization groups: the kernel walks
-// them in chunks of 128.
-static int down_slice_len(int M, int K)
-{
-    const int want = std::min(32, std::max(8, ceil_div(256, ceil_div(M, 32))));
-    return std::max(256, ceil_div(ceil_div(K, want), kGroup) * kGroup);
-}
-static int down_slices(int M, int K) { return ceil_div(K, down_slice_len(M, K)); }
-
 // Stage 1: partial[s][m][j] = sum over K slice s of x[m][k] * At[j][k], for one 32-row tile of tokens and all r
 // columns.  RT = 32-column tiles (r <= 32 * RT).  The block also writes the arranged copy of the activations it
 // reads (its 32 rows, its K slice): one pass over x serves both, and the re-ordering needs no launch of its own.
@@ -655,7 +644,7 @@ static int down_slices(int M, int K) { return ceil_div(K, down_slice_len(M, K));
 constexpr int kDownStages = 4;
 template <int BITS, int RT>
 __global__ __launch_bounds__(256) void fbq_down_proj_prefill_kernel(const ArrangeParams a, const uint16_t *__restrict__ At, float *__restrict__ partial,
-                                                                    int r, int kslice, int slices)
+                                                                    int r, int kslice, int slices, int by_xcd)
 {
     constexpr int kRows = 32 + 32 * RT;                 // rows of a chunk in LDS: the tokens, then the columns of A
     constexpr int kChunkBytes = kRows * 128, kCopies = kRows / 8 / 4;   // copies per wave and chunk
@@ -670,13 +659,10 @@ __global__ __launch_bounds__(256) void fbq_down_proj_prefill_kernel(const Arrang
         return;
     }
     const int M = a.M, K = a.K;
-    // Blocks go to the XCDs round-robin by linear id.  Eight slices at a time get an XCD each, with all of their token tiles one
-    // after the other, so that a slice of A^T comes into one L2 and not into each that has one of its token tiles (256 tokens, 28672 x 128,
-    // INT3: the pass 24.6 us before, 16.8 with it).  It pays where A^T is large and eight tiles or more read it (the call before / with it, us:
-    // 256 tokens of 20480 x 256 92 / 87.5, of 13952 x 128 63.7 / 63.0, but of 4096 x 128 36.3 / 37.1; 160 tokens of 8192 x 256 41.6 / 43.2), and
-    // where all blocks fit the GPU at once: 1092 tokens, 280 blocks, of 13952 x 128 151 / 156.
+    // The first `by_xcd` slices (a multiple of eight): blocks go to the XCDs round-robin by linear id, and eight slices at a time get an
+    // XCD each, with all of their token tiles one after the other.
     int tile = blockIdx.x, slice = blockIdx.y;
-    if (gridDim.x >= 8 && (int)gridDim.x * slices <= 256 && r * K >= 1500000 && slice < (slices & ~(kXcds - 1))) {
+    if (slice < by_xcd) {
         const int id = slice * gridDim.x + tile, i = id / kXcds;
         slice = id % kXcds + kXcds * (i / (int)gridDim.x);
         tile = i % (int)gridDim.x;
@@ -835,10 +821,11 @@ hipError_t launch_prepass_prefill(const LinearArgs &a, hipStream_t stream)
     }
     const int kslice = down_slice_len(a.M, a.K);
     const int slices = down_slices(a.M, a.K);
+    const int by_xcd = down_slices_by_xcd(a.M, a.N, a.K, a.r);
     const int row_tiles = ceil_div(a.M, 32);
     const dim3 grid(row_tiles, slices + ceil_div(ap.sz_tiles, row_tiles));
     const int rt = ceil_div(a.r, 32);
-#define FBQ_DOWN(B, R) hipLaunchKernelGGL((fbq_down_proj_prefill_kernel<B, R>), grid, dim3(256), 0, stream, ap, a.At, s.partial, a.r, kslice, slices)
+#define FBQ_DOWN(B, R) hipLaunchKernelGGL((fbq_down_proj_prefill_kernel<B, R>), grid, dim3(256), 0, stream, ap, a.At, s.partial, a.r, kslice, slices, by_xcd)
     if (a.bits == 4) {
         if (rt <= 1) FBQ_DOWN(4, 1); else if (rt <= 2) FBQ_DOWN(4, 2); else if (rt <= 4) FBQ_DOWN(4, 4); else FBQ_DOWN(4, 8);
     } else {

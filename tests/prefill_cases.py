@@ -32,3 +32,15 @@ CUT_CASES = [
     (33355, 2176, 72, 581, "256+128"),
     (32821, 1664, 128, 683, "256+192"),
 ]
+
+# The order of the down-projection's blocks: N, K, r, M, and the token tiles, K slices and slices dealt out to the XCDs whole.  A ragged last tile,
+# more tiles than XCDs and a number of slices that is no multiple of eight wherever slices are; either side of the lines of narrow layers
+ORDER_CASES = [
+    (300, 20480, 200, 290, (10, 23, 16)),
+    (301, 16384, 200, 333, (11, 22, 16)),
+    (2049, 13824, 128, 333, (11, 22, 16)),
+    (2050, 8320, 200, 289, (10, 22, 16)),
+    (300, 28672, 128, 230, (8, 32, 32)),
+    (1600, 8320, 200, 289, (10, 22, 0)),
+    (300, 13824, 128, 290, (10, 22, 0)),
+]

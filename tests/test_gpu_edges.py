@@ -7,7 +7,7 @@ import pytest
 import fbq_synth
 from helpers import assert_matches_oracle, framed_in_nan, framed_layer, gpu_y, make_oracle_layer
 from oracle import fbq_oracle as orc
-from prefill_cases import CUT_CASES
+from prefill_cases import CUT_CASES, ORDER_CASES
 
 pytestmark = pytest.mark.gpu
 
@@ -145,7 +145,7 @@ def test_prefill_tile_edges(bits, N, K, r, M):
 
 
 @pytest.mark.parametrize("bits", [4, 3])
-@pytest.mark.parametrize("N,K,r,M,cut", CUT_CASES)
+@pytest.mark.parametrize("N,K,r,M,cut", CUT_CASES + ORDER_CASES)
 def test_prefill_every_kind_of_cut(bits, N, K, r, M, cut):
     """The bars of the test above (assert_matches_oracle's), against W_F in 64 bits from the layer's own codes on the device: these
     layers are too large for the oracle on the host."""

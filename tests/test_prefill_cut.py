@@ -7,7 +7,7 @@ import subprocess
 
 import pytest
 
-from prefill_cases import CUT_CASES
+from prefill_cases import CUT_CASES, ORDER_CASES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
@@ -49,3 +49,16 @@ def test_every_kind_of_cut_has_a_case(cuts):
 def test_many_short_blocks_share_the_compute_units(driver, M, N, K, r):
     """Several blocks per CU and few steps each: one block per CU took 10 to 30 % longer here."""
     assert run_driver(driver, f"{M} {N} {K} {r}\n")[0][0].endswith(" single")
+
+
+def test_the_down_projections_are_ordered_as_they_say(driver):
+    given = "".join(f"{M} {N} {K} {r}\n" for N, K, r, M, _ in ORDER_CASES)
+    out = subprocess.run([driver, "order"], input=given, text=True, capture_output=True, check=True, timeout=120).stdout.split("\n")
+    assert [tuple(map(int, line.split())) for line in out if line] == [order for *_, order in ORDER_CASES]
+
+
+@pytest.mark.parametrize("M,N,K,r", [(256, 1024, 8192, 200), (225, 512, 6144, 256), (289, 1024, 6144, 256), (160, 1024, 8192, 256), (1092, 3456, 13952, 128)])
+def test_no_order_by_xcd_where_it_is_slower(driver, M, N, K, r):
+    """2 to 6 % of the call's time."""
+    out = subprocess.run([driver, "order"], input=f"{M} {N} {K} {r}\n", text=True, capture_output=True, check=True, timeout=120).stdout
+    assert out.split()[2] == "0"
