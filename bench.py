@@ -21,7 +21,8 @@ batch of exactly --steps steps, and mean and minimum are printed beside it.
 set in INT3 at 1, 4, 8 and 16 tokens; the two MLP shapes at 1024 tokens; the large-layer sweep at
 1, 16 and 256 tokens in both bit widths), each with its branch-free twin, and
 `measured_read_peak_GBps` what a kernel that only reads gets out of the memory system at the launch
-sizes of the decode path.  Prints ONE JSON line.
+sizes of the decode path.  Prints ONE JSON line on stdout: the headline with its timing and roofline, and of everything else its
+time and the branch's overhead; the complete record, four times as long, goes to stderr as one JSON line.
 """
 from __future__ import annotations
 
@@ -327,6 +328,18 @@ def layer_entry(perf, N, K, r, bits, M, iters, rotate=1.0e9):
     return e
 
 
+DETAILS = ("schedules", "launches_of_the_staged_schedule", "unfused_comparator", "measured_read_peak_GBps", "other_kernel_families", "cpu_baseline")
+
+
+def headline(out):
+    """What the one line on stdout holds (a few thousand characters: whoever keeps only the end of the output still has all of it): the record
+    without its details, and [workload, us, branch overhead in %] for each of its `configs`."""
+    line = {k: v for k, v in out.items() if k not in DETAILS and k != "configs"}
+    if "configs" in out:
+        line["configs"] = [[c["workload"], c.get("us_median", c.get("us_per_step_median")), c.get("branch_overhead_pct")] for c in out["configs"]]
+    return line
+
+
 def main():
     args = parse_args()
     if args.gpus != 1:
@@ -515,7 +528,8 @@ def main():
         out["other_kernel_families"] = fam
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(specs, CONFIG, M, args.cpu_seconds)
-    print(json.dumps(out))
+    print(json.dumps(out), file=sys.stderr, flush=True)
+    print(json.dumps(headline(out)))
 
 
 if __name__ == "__main__":
