@@ -454,3 +454,90 @@ def test_stream_group_of_unequal_layers(K, layers, M, bits):
         torch.cuda.synchronize()
         for (N, r), y, want, w, out in zip(layers[order], ys, single[order], with_[order], outs):
             assert torch.equal(y, want) and torch.equal(out, torch.lerp(w, want, 0.5)), (N, r)
+
+
+LATE_GROUPS = [
+    # K, M, {N, r}: two units a tile, several passes, in line with a small layer; one tile a block and more than the eight of two rounds
+    (4224, 6, [(33001, 40)]),
+    (4224, 16, [(10243, 200)]),
+    (8320, 16, [(33001, 72)]),
+    (16384, 3, [(10241, 8)]),
+    (4096, 16, [(10240, 64), (1000, 16)]),
+    (8192, 7, [(1001, 136), (10241, 24), (12289, 72)]),
+]
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("K,M,layers", LATE_GROUPS)
+def test_stream_consumers_that_never_wait(K, M, layers, bits):
+    """Blocks that find no down-projection compute t themselves, in another order: the result, and its average, are the oracle's all the same."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    from paper_2501_16385_amd.random_layers import random_layer
+    g = torch.Generator(device="cuda")
+    g.manual_seed(91 + K + M)
+    devs = [framed_layer(random_layer(fbq.Desc(N, K, r, bits), g, gain=1.0)) for N, r in layers]
+    x = framed_in_nan(torch.randn(M, K, device="cuda", generator=g).half())
+    ys, outs = ([framed_in_nan(torch.empty(M, N, dtype=torch.float16, device="cuda")) for N, _ in layers] for _ in range(2))
+    with_ = [framed_in_nan(torch.randn(M, N, device="cuda", generator=g).half()) for N, _ in layers]
+    wss = [torch.zeros(fbq.workspace_bytes(l.desc, M), dtype=torch.uint8, device="cuda") for l in devs]
+    before = fbq.load().fbq_test_set_spin_limit(-1)
+    try:
+        arr, mix = fbq.make_group(devs, [x] * len(devs), ys, wss), fbq.make_mix(with_, outs)
+        assert fbq.load().fbq_linear_group_mix(arr, mix, len(devs), M, torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+    finally:
+        assert fbq.load().fbq_test_set_spin_limit(before) == -1
+    f64 = lambda t: t.view(torch.float16).double()
+    for dev, y, w, out in zip(devs, ys, with_, outs):
+        N = dev.desc.N
+        want = x.double() @ ((fbq.unpack_codes(dev).view(N, K // 128, 128).double() - f64(dev.zeros)[:, :, None]) * f64(dev.scales)[:, :, None]).view(N, K).T
+        want += (x.double() @ f64(dev.At).T) @ f64(dev.Bt).T
+        assert_matches_oracle(y.cpu().numpy(), want.cpu().numpy(), f"INT{bits} {N}x{K} M={M}, t computed by its consumers")
+        assert torch.equal(out, torch.lerp(w, y, 0.5))
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("K,M,layers", [(4096, 9, [(10240, 64)]), (8192, 16, [(10245, 200)]), (8320, 5, [(10240, 72)]),
+                                    XX
+def test_stream_replayed_graph_follows_new_activations(K, M, layers, bits):
+    """Replays of a captured launch hand over the t of their own activations, with eager calls on the same workspace in between."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    from paper_2501_16385_amd.random_layers import random_layer
+    g = torch.Generator(device="cuda")
+    g.manual_seed(101 + K + M)
+    devs = [random_layer(fbq.Desc(N, K, r, bits), g, gain=1.0) for N, r in layers]
+    x = torch.randn(M, K, device="cuda", generator=g).half()
+    ys = [torch.empty(M, N, dtype=torch.float16, device="cuda") for N, _ in layers]
+    wss = [torch.zeros(fbq.workspace_bytes(l.desc, M), dtype=torch.uint8, device="cuda") for l in devs]
+    fbq.linear_group(devs, [x] * len(devs), ys=ys, workspaces=wss)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        fbq.linear_group(devs, [x] * len(devs), ys=ys, workspaces=wss)
+    for rep in range(4):
+        x.copy_(torch.randn(M, K, device="cuda", generator=g).half())
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [y.clone() for y in ys]
+        fresh = fbq.linear_group(devs, [x] * len(devs))
+        fbq.linear_group(devs, [x.flip(0)] * len(devs), ys=ys, workspaces=wss)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, fresh)), rep
+        assert not torch.equal(got[0], ys[0])
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("N,K,r,M", [(10241, 4224, 40, 9), (10240, 8320, 72, 3), (33001, 1280, 8, 16)])
+def test_stream_behind_the_other_entry_points(N, K, r, M, bits):
+    """The library's own scratch gives the bits of fbq_linear; the unfused comparator differs by the fp16 rounding of t."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    dev, W, g = framed_random_layer(N, K, r, bits, 111 + N + M)
+    x = framed_in_nan(torch.randn(M, K, device="cuda", generator=g).half())
+    y = fbq.linear(dev, x)
+    assert torch.equal(fbq.linear_static(dev, x), y)
+    want = x.double() @ W.T
+    miss = (fbq.linear_unfused(dev, x).double() - want).norm() / want.norm()
+    assert float(miss) <= 1.5e-3, float(miss)

@@ -50,6 +50,16 @@ def test_two_blocks_of_the_gemv_fit_a_compute_unit(kernels):
         assert k[".group_segment_fixed_size"] <= 80 * 1024, n
 
 
+def test_streaming_instances_have_their_registers_and_a_cu_each(kernels):
+    """One block of eight waves per CU: two waves per SIMD, 256 registers each, no scratch memory (that alone costs a launch 2 us; scalar registers do spill
+    into vector ones), and more than half of the LDS, so that no second block starts beside it on rows that were meant for another CU."""
+    stream = {n: k for n, k in kernels.items() if "fbq_few_stream_kernel<" in n}
+    assert len(stream) == 24                                        # 2 bit widths x 3 shapes of K x 2 token classes x (in a grid, in line)
+    for n, k in stream.items():
+        assert k[".vgpr_count"] <= 256 and k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, n
+        assert 80 * 1024 < k[".group_segment_fixed_size"] <= 160 * 1024, n
+
+
 def test_inline_assembly_declares_the_scalar_register_it_overwrites():
     """M0 belongs to the compiler: a statement that moves an LDS address into it without saying so would silently change
     whatever value the compiler keeps there."""
