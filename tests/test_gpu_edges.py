@@ -499,7 +499,7 @@ def test_stream_consumers_that_never_wait(K, M, layers, bits):
 
 @pytest.mark.parametrize("bits", [4, 3])
 @pytest.mark.parametrize("K,M,layers", [(4096, 9, [(10240, 64)]), (8192, 16, [(10245, 200)]), (8320, 5, [(10240, 72)]),
-                                    XX
+                                        (4096, 16, [(10240, 64), (1000, 16)]), (4096, 40, [(5121, 24)])])
 def test_stream_replayed_graph_follows_new_activations(K, M, layers, bits):
     """Replays of a captured launch hand over the t of their own activations, with eager calls on the same workspace in between."""
     import torch
