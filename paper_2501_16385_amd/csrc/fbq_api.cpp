@@ -43,21 +43,21 @@ extern "C" size_t fbq_packed_bytes(const fbq_desc *d)
     return (size_t)d->N * row_words(d->K, d->bits) * sizeof(uint32_t);
 }
 
-// 17..64 tokens: whether the few-token kernel, the sets of 16 tokens side by side in one launch, takes the call, or the prefill
-// GEMM.  The sets stream the packed words once per set, in passes of 4096 along K, and multiply the codes exactly (relative error
-// of y 2.2e-4); the GEMM reads the words once and rounds the weights to fp16 (2.9e-4).  The line is the cost of both, in us, that
-// was fitted to ten shapes when the GEMM was slower than it is: sets 2 + sets x (2.2 + 0.165 MC), GEMM 30 + 0.135 MC + 1.5 K / 1024
-// (MC = millions of codes, K counted in whole passes for the sets).  As an estimate of the GEMM it is obsolete; it stays as the line up
-// to which a call has the smaller error: who had it keeps it.  What that costs by now, sets / GEMM, us: nothing for
-// 4096 x 4096 (9.5 / 25 at 32 tokens, 19 / 28 at 64) and 4096 -> 11008 up to 48 tokens (26 / 30; 34 / 32 at 64); 13824 -> 5120 at 48
-// tokens INT4 47 / 41, INT3 41 / 42; 8192 -> 8192 at 48 40 / 39 and 45 / 38; 28672 -> 8192 at 32 76 / 65 and 68 / 64; 5120 -> 13824
-// at 32 42 / 36.
+// 17..64 tokens: whether the few-token kernels, the sets of 16 tokens side by side in one launch, take the call, or the prefill
+// GEMM.  The sets stream the packed words once per set and multiply the codes exactly (relative error of y 2.2e-4); the GEMM reads the words
+// once and rounds the weights to fp16 (2.9e-4).  The first line is the cost of both, in us, that was fitted to ten shapes when there was neither
+// the streaming kernel nor the GEMM of today: sets 2 + sets x (2.2 + 0.165 MC), in passes of 4096 along K, GEMM 30 + 0.135 MC + 1.5 K / 1024 (MC = millions
+// of codes, K counted in whole passes for the sets).  As an estimate it is obsolete; it stays as the line up to which a call has the smaller error: who had it
+// keeps it.  What that costs by now, sets / GEMM, us: nothing for 4096 x 4096 (8.8 / 28 at 32 tokens, 13.7 / 30 at 64), 4096 -> 11008 (20 / 31 at 48,
+// 24 / 32 at 64), 8192 -> 8192 at 48 (27 / 37), 13824 -> 5120 at 48 (37.5 / 42.0, INT3 36.0 / 43.7) and 28672 -> 8192 at 32 (61 / 69); 28672 -> 5120 at 48 62.6 / 60.6.
 //
 // Beyond that line the sets are faster too where they add up to a launch of the streaming kernel and K is 3072 to 8192 (longer rows:
 // a wave's activations come again and again; shorter ones: too little work per row): two sets at any N, four up to 70 million codes.
-// Sets / GEMM, us.  Two, at 32 tokens: 8192 -> 28672, r = 128, 49 / 65; 3072 -> 40000 33 / 41; 4096 -> 131072 99 / 111; but
-// 2048 -> 60000 41 / 36, 1024 -> 40000 30 / 24.  Four, at 64: 4096 -> 17088 31 / 37, 3072 -> 22784 34 / 39, 8192 -> 8544, r = 128, 36 / 41; but
-// 6144 -> 20000 48 / 41, 8192 -> 28672 88 / 71.  Three (48 tokens) are a draw or worse: 5120 -> 13824 INT3 42 / 40, 8192 -> 28672 82 / 69.
+// Sets / GEMM, us, r = 64 or as stated.  Two, at 32 tokens: 8192 -> 28672, r = 128, 49.0 / 65.5; 3072 -> 40000 32.7 / 40.7; 4096 -> 131072 99 / 116; but
+// 2048 -> 60000 40.2 / 35.7, 1024 -> 40000 29.6 / 23.9, 8320 -> 20001, r = 0, 55.4 / 42.7.  Four, at 64: 4096 -> 17088 31.5 / 37.5, 3072 -> 22784 33.7 / 38.6,
+// 8192 -> 8544, r = 128, 36.5 / 42.0; but 6144 -> 20000 49.3 / 47.2, 8192 -> 28672 87.9 / 70.9.  Three were left to the GEMM while their launches had more
+// blocks than CUs; at 48 tokens they would now win over the same K: 3072 -> 22784 28.5 / 37.8, 5120 -> 11008, r = 128, 27.6 / 36.8, 5120 -> 13824, r = 128, 32.6 / 38.1,
+// 6144 -> 20000 40.2 / 45.2, 8192 -> 28672 68.0 / 68.4 (INT3 61.1 / 69.0).
 static bool takes_sets(int M, int N, int K)
 {
     const int sets = (M + kDecodeMaxM - 1) / kDecodeMaxM;
@@ -216,8 +216,9 @@ hipError_t launch_one(const LinearArgs &a, hipStream_t s)
         LinearArgs set[kMaxSmallGroup], rest = a;
         const size_t ws_each = small_m_workspace_bytes(a.K, a.r);
         // One or two tokens left over are a set like the others where the streaming kernel takes the sets: a pass of their own would
-        // read the words again.  As a set / with the GEMV, us: 28672 -> 8192 at 17 tokens 58 / 72, at 18 57 / 118 (INT3); 4096 -> 11008 at 18
-        // 15 / 21; 4096 -> 4096 at 49 13.8 / 15.7.  One beside two sets is left to the GEMV: 8192 -> 8192 at 33 31.7 / 30.2, 5120 -> 5120 21.0 / 20.2.
+        // read the words again.  As a set / with the GEMV, us: 28672 -> 8192 at 17 tokens 58 / 73, at 18 57 / 119 (INT3); 4096 -> 11008 at 18
+        // 15 / 21; 4096 -> 4096 at 49 13.8 / 15.7.  One beside two sets is left to the GEMV; three sets in one launch have since become faster
+        // (8192 -> 8192 at 33 30.3 with the GEMV, at 48 27.4; 5120 -> 5120 20.4 at 33, 17.9 at 34).
         const bool all_in_sets = a.M != 2 * kDecodeMaxM + 1 && few_stream((long)ceil_div(a.M, kDecodeMaxM) * a.N, a.K);
         int n = 0;
         rest.M = 0;

@@ -20,14 +20,15 @@
 // rows' blocks that start in their place own fewer rows.  (As a job on the rows' own blocks, which have the activations
 // anyway, t came 2 us later: 14336 x 4096, r = 64, 8 tokens 13.5 us with blocks of their own and 14.8 without.)
 //
-// What bounds it: memory, at about 6 TB/s over a long stream, and in front of it 2.7 us for the activations: launch, first round
+// What bounds it: memory, at about 5.4 TB/s over a long stream, and in front of it 2.7 us for the activations: launch, first round
 // trip, change of order (K up to 8192: once; beyond, once a pass and four tiles, 1.5 us each with little under way).  us, the other kernel
-// and this one: 28672 x 8192, INT4, r = 128, 16 tokens 49.6 / 30.8 (r = 0: 44.3 / 28.5, of which launch 2, activations 3.4);
-// 13824 x 5120, r = 64, 8 tokens 21 / 15.6; two layers of 11008 x 4096, INT3, r = 64, 8 tokens 19.9 / 15.3; 5120 x 13824, INT3, r = 128, 48 tokens
-// as three sets 41 / 34.6.  Tried: four waves with twice the registers (one wave per SIMD issues too slowly: 16 us where this takes 14);
+// and this one: 28672 x 8192, INT4, r = 128, 16 tokens 46.5 / 31.1 (r = 0: 43.8 / 28.6, of which launch 2, activations 3.4);
+// 13824 x 5120, r = 64, 8 tokens 20.3 / 15.8; two layers of 11008 x 4096, INT3, r = 64, 8 tokens 18.7 / 15.5; 5120 x 13824, INT3, r = 128, 48 tokens
+// as three sets 38.8 / 36.1.  Tried: four waves with twice the registers (one wave per SIMD issues too slowly: 16 us where this takes 14);
 // activations by way of the ring as well (a branch more per unit and twice the code: 15.1 against 13.9); the next
 // pass's activations asked for while one is worked on (the wait for them is one for the ring behind them: 38.8 against 33.1); rows dealt
-// out in sweeps over the layer instead of runs (35.8 against 33.3).  Instances must not spill: scratch memory alone costs a launch 2 us.
+// out in sweeps over the layer instead of runs (35.8 against 33.3).  Instances must not spill vector registers: scratch memory alone costs a launch
+// 2 us (50 to 97 scalar ones spill into vector lanes).
 #include <type_traits>
 
 #include "fbq_few_burst.h"
@@ -199,7 +200,8 @@ __global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu
 
     // A unit's copies.  Copy j of the codes moves rows 4 j .. 4 j + 3, 16 lanes and up to 256 contiguous bytes a row; row n's piece i
     // (32 codes) lies at position i ^ n of it, so that the 16 rows of a matrix operand touch every bank once.  Scales and zeros: the
-    // aligned dwords that hold the four groups' halves, four lanes a row.  Groups past the wave's share aim nowhere.
+    // aligned dwords that hold the four groups' halves, four lanes a row.  Groups past the wave's share aim nowhere; those of the share that lie
+    // past the end of K are whatever follows, and meet activations of zero.
     int qoff[4], qoff_last[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {

@@ -55,9 +55,11 @@ struct LinearArgs {
 // the layer alone, so that a layer of a grouped call gets exactly what a call of its own gives it.  The streaming kernel
 // keeps a wave's activations for all tiles of its block and has the next tiles' codes under way while it works on one; it wins where a
 // CU has several tiles.  The other one is a single burst of requests, and takes what is small.  us, burst / stream, 16 tokens or as
-// stated: 28672 x 8192 INT4 r = 128 49.6 / 30.8; two of 11008 x 4096 INT3 r = 64 at 8 tokens 19.9 / 15.3, one alone
-// 11.1 / 9.5; 14336 x 4096 r = 128 at 8 17.3 / 13.7; 50257 x 1024 r = 16 at 8 32.9 / 21; on the burst's side of the line 8192 x 4096 r = 64
-// 9.9 / 10.4, 4096 x 4096 6.6 / 7.2, 4096 x 11008 INT3 at 8 15.9 / 16.7, {4096, 1024, 1024} x 4096 at 8 9.3 / 10.9.
+// stated, r = 64 or as stated: 28672 x 8192 INT4 r = 128 46.5 / 31.1; two of 11008 x 4096 INT3 at 8 tokens 18.7 / 15.5, INT4 18.6 / 16.6; one alone
+// INT3 11.0 / 10.0, but INT4 10.0 / 11.1 and 10240 x 4096 INT4 9.9 / 10.7, which the pairs decide; 14336 x 4096 r = 128 at 8 15.4 / 14.0; 50257 x 1024 r = 16 at
+// 8 31.6 / 19.5.  On the burst's side of the line 8192 x 4096 INT4 9.3 / 10.3, 4096 x 4096 7.8 / 9.2, 4096 x 11008 INT3 at 8 15.7 / 16.1, INT4 16.0 / 17.7,
+// {4096, 1024, 1024} x 4096 at 8 8.6 / 9.4; the line is on the safe side where it leaves the burst 8192 x 5120 (15.8 / 13.7), 8192 x 8192 (16.7 / 14.9, INT3 19.1 / 14.7)
+// and 12288 x 2048 (11.8 / 9.9).
 inline bool few_stream(long rows, int K) { return rows >= 10240 && rows * K >= 40000000L; }
 
 // Launchers (validated arguments only).  Each returns the hipError_t of its launches.
