@@ -98,8 +98,9 @@ def gpu_y(dev_layer, x: np.ndarray) -> np.ndarray:
 # rounds y once to fp16 (half an ulp: 2^-11 |y|; 2^-10 |y| leaves room for a value next to a binade edge).  On top of
 # that, relative to the rms of the outputs compared, by kernel family (chosen by the token count, as the dispatch does):
 #   gemv    (1-2 tokens)   fp32 accumulation of exact products only: about 1e-6 sqrt(K)
-#   few     (3-64 tokens)  the matrix cores sum q.x' on top of the offset 1024 sum(x') per group, about 40 times the
-#                          signal, in fp32, and the offset is subtracted afterwards: about 5e-5 rms(y) per output
+#   few     (3-64 tokens)  in smaller layers the matrix cores sum q.x' on top of the offset 1024 sum(x') per group, about 40 times
+#                          the signal, in fp32, and the offset is subtracted afterwards: about 5e-5 rms(y) per output (larger ones have
+#                          no offset and stay below)
 #   prefill (> 64 tokens)  every de-quantized weight is rounded to fp16 (2^-11 relative, independent): about 3e-4 rms(y)
 # The slack is about ten standard deviations of that noise; a dropped or doubled term of the sum is 1e-2 rms(y) or more.
 ELEMENT_SLACK = {"gemv": 2e-4, "few": 1e-3, "prefill": 3e-3}
