@@ -183,8 +183,8 @@ typedef struct {
  * launch, up to 8 layers per launch, in the order they appear.  For 3 <= M <= 16, layers with the
  * same bits and K that read the SAME x (the same pointer) and all have a sub-branch (or all have
  * none) share one launch, up to 4 layers (two launches where layers of 10240 rows and 40 million codes or more, which have
- * a kernel of their own, come with smaller ones and K is below 2048 or above 12288).  Anything else, and every layer when M > 16, is
- * launched on its own.
+ * a kernel of their own, come with smaller ones and K is below 2048 or above 12288, or above 4096 with smaller ones that fill
+ * the GPU by themselves).  Anything else, and every layer when M > 16, is launched on its own.
  *   calls host array of n layers (read during the call only); M tokens, the same for all layers
  * Errors: those of fbq_linear for any layer, and FBQ_ERR_WORKSPACE if the workspaces of two layers
  * overlap, reported before ANY launch.

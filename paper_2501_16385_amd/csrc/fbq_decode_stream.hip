@@ -66,7 +66,7 @@ struct StreamParams {
     int M, N, K, r;
     int row_words, G;
     int slices, kslice;    // down-projection: number of K slices and their length (a multiple of 256)
-    int down_blocks;       // blocks at the start of this layer's grid row that do its down-projection, slice by slice ...
+    int down_blocks;       // the layer's first blocks, which do its down-projection, slice by slice ...
     int sum_blocks;        // ... and the blocks after them that add the slices up (16 columns each)
     int early, rows, late_rows;   // the first blocks behind those, `early` of them, own `rows` output rows each, the others fewer
     int passes, share;     // passes over K, and the groups a wave takes in each
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(64 * kMainWaves) __attribute__((amdgpu_waves_per_eu
     asm volatile("" :: "s"(p.qw), "s"(p.scales), "s"(p.zeros), "s"(p.x), "s"(p.y), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.row_words), "s"(p.G), "s"(p.early), "s"(p.rows), "s"(p.late_rows), "s"(p.down_blocks), "s"(p.sum_blocks));
     asm volatile("" :: "s"(p.Bt), "s"(p.At), "s"(p.tpart), "s"(p.tsum), "s"(p.r), "s"(p.passes), "s"(p.share), "s"(p.spin_limit));
     const uint32_t tag = small_m_launch_tag();
-    // The first blocks of a grid row do the layer's down-projection.  They come first in dispatch order, so whoever waits for their
+    // A layer's first blocks do its down-projection.  They come first in dispatch order, so whoever waits for their
     // words waits for blocks that are already running.
     if (index < p.down_blocks + p.sum_blocks) {
         if (index < p.down_blocks) down_proj_block(p, index, tag, reinterpret_cast<float4_t (*)[64]>(lds));

@@ -464,6 +464,7 @@ LATE_GROUPS = [
     (16384, 3, [(10241, 8)]),
     (4096, 16, [(10240, 64), (1000, 16)]),
     (8192, 7, [(1001, 136), (10241, 24), (12289, 72)]),
+    (12288, 5, [(10240, 64), (1024, 40)]),
 ]
 
 
