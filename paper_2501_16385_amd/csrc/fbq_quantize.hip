@@ -1,0 +1,383 @@
+// The feedback quantizer Q(W - B A) (Sec. 4.1): the step before the path, and a sixth of a reconstruction iteration.
+//
+// Codes, scales and zeros are defined in 64 bits.  The kernel gets them from 32-bit sums with a bound on their error: Sigma = B A
+// on the fp16 matrix instruction, extremes and codes in fp32.  Where the bound leaves open which fp16 number a scale or a zero
+// rounds to, or which whole number a code rounds to, that row of the group is done again in fp64; so the result is that of
+// fp64 throughout, and with weights as they come one row in 200 pays for it (r = 64; 1 in 70 at r = 200).
+//
+// Layout.  One block takes one group of 128 input features and one or two tiles of rows, 16 rows a wave.  Its tile of At is transposed
+// into LDS as fp16, [feature][tap]; the features are the rows of the matrix product and the rows of W its columns, features dealt to the
+// eight row tiles so that a lane (c = lane % 16, q = lane / 16) ends up with 32 consecutive features 32 q .. 32 q + 31 of row c: whole
+// packed words (four of INT4, one unit of three of INT3), one scale and one zero, 64 bytes of W and of Delta_F, and extremes that
+// are found in the lane but for two steps between lanes.
+//
+// What it takes, us, against the same in fp64 throughout (fp64 matrix instruction, a thirtieth of the fp16 rate): 11008 x 4096 INT3, r = 64,
+// 124 -> 50; without a sub-branch 38 -> 30; INT4, r = 200, 335 -> 96; 4096 x 4096, r = 128, 79 -> 32.  Of the 50, 23 are the bytes at the rate of
+// a large copy, about 15 getting At into LDS and out of it (without a sub-branch 30), 4 the rows in fp64.
+//
+// With DELTA the kernel also writes what the reconstruction step needs from the same registers: Delta_F = (W - Sigma) - s (q - z), times
+// `gain`, as fp16 in both orientations (D16 [N][K]; Dt16 [K][ldt] with columns N..ldt-1 zero, ldt a multiple of 64), the transposed copy
+// through LDS as whole row pieces.  In fp32 it is off by a few 2^-24 of the group's largest |R|, the rounding to fp16 by 2^-12 of itself.
+#include <hip/hip_fp16.h>
+
+#include "fbq_internal.h"
+
+namespace fbq {
+
+typedef _Float16 half_t;
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ double half_bits_to_double(uint16_t h) { return (double)__builtin_bit_cast(half_t, h); }
+
+// double -> fp16 bits, rounded once, to nearest even: by way of an fp32 number rounded to odd.  A NaN becomes an infinity of its sign.
+__device__ __forceinline__ uint16_t double_to_half_bits(double d)
+{
+    const float f = (float)d;
+    uint32_t u = __builtin_bit_cast(uint32_t, f);
+    if (__builtin_fabs((double)f) > __builtin_fabs(d)) u -= 1;
+    if ((double)f != d) u |= 1;
+    const uint16_t h = __builtin_bit_cast(uint16_t, (_Float16)__builtin_bit_cast(float, u));
+    return d != d ? (uint16_t)(((__builtin_bit_cast(uint64_t, d) >> 48) & 0x8000u) | 0x7c00u) : h;
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t bounded_buffer(const void *p, long bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ half8_t load_half8(__amdgpu_buffer_rsrc_t b, int off)
+{
+    return __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0));
+}
+
+// Scale (low half) and zero (high half) of a group from its extremes.
+__device__ __forceinline__ uint32_t search_scale(double lo, double hi, int qmax)
+{
+#pragma clang fp contract(off)
+    double s = (hi - lo) / (double)qmax;
+    if (!(s > 0.0)) s = 1.0;
+    uint16_t s16 = double_to_half_bits(s);
+    if (s16 < 0x0400u) s16 = 0x0400u;
+    // (extremes that are infinite or NaN never meet the condition below, whatever the scale: straight to the last one)
+    if (!(__builtin_fabs(lo) < __builtin_inf() && __builtin_fabs(hi) < __builtin_inf()) && s16 < 0x7bffu) s16 = 0x7bffu;
+    uint16_t z16;
+    for (;;) {
+        const double sd = half_bits_to_double(s16), up = -lo / sd;
+        z16 = double_to_half_bits(up);
+        const double zd = half_bits_to_double(z16);
+        if ((zd - up >= -0.5 && hi / sd + zd <= (double)qmax + 0.5) || s16 >= 0x7bffu) break;
+        s16 += 1;
+    }
+    return (uint32_t)s16 | ((uint32_t)z16 << 16);
+}
+
+// The packed words of 32 consecutive codes, from the codes as floats.  Fields are added up in fp32, where they are whole numbers below 2^16.
+template <int BITS>
+__device__ __forceinline__ void pack_codes(const float *x, uint32_t *words)
+{
+    if constexpr (BITS == 4) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            uint32_t h[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float *f = x + 8 * w + 4 * i;
+                h[i] = (uint32_t)__builtin_fmaf(__builtin_fmaf(__builtin_fmaf(f[3], 16.0f, f[2]), 16.0f, f[1]), 16.0f, f[0]);
+            }
+            words[w] = h[0] | (h[1] << 16);
+        }
+    } else {
+        const uint32_t c30 = (uint32_t)x[30], c31 = (uint32_t)x[31];
+#pragma unroll
+        for (int w = 0; w < 3; ++w) {
+            uint32_t h[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float *f = x + 10 * w + 5 * i;
+                h[i] = (uint32_t)__builtin_fmaf(__builtin_fmaf(__builtin_fmaf(__builtin_fmaf(f[4], 8.0f, f[3]), 8.0f, f[2]), 8.0f, f[1]), 8.0f, f[0]);
+            }
+            words[w] = h[0] | (h[1] << 16) | ((c30 >> w) & 1u) << 15 | ((c31 >> w) & 1u) << 31;
+        }
+    }
+}
+
+// Extremes over the four lanes that hold one row (lanes 16 apart).
+__device__ __forceinline__ void row_extremes(float &lo, float &hi)
+{
+    auto swap16 = [](float v) { return __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), false, false); };
+    auto swap32 = [](float v) { return __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), false, false); };
+    auto f = [](uint32_t u) { return __builtin_bit_cast(float, u); };
+    auto a = swap16(lo), b = swap16(hi);
+    lo = fminf(f(a[0]), f(a[1]));
+    hi = fmaxf(f(b[0]), f(b[1]));
+    a = swap32(lo);
+    b = swap32(hi);
+    lo = fminf(f(a[0]), f(a[1]));
+    hi = fmaxf(f(b[0]), f(b[1]));
+}
+
+constexpr int kQuantTapStep = 32;      // taps one matrix instruction takes
+
+// Taps in LDS: 16-byte pieces of eight taps, [feature][piece], a piece's place XORed with a key so that the sixteen features that
+// one matrix operand reads (bits 0, 1, 5, 6 of the feature differ) lie in sixteen different places of 256 bytes.
+__device__ __forceinline__ int tap_key(int f) { return ((f >> 1) & 1) | ((f >> 4) & 6); }
+
+// STEPS: the most steps of 32 taps.  WAVES: a block's.
+template <int BITS, bool DELTA, int STEPS, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 4) void fbq_quantize_kernel(const uint16_t *__restrict__ W, const uint16_t *__restrict__ At,
+                                                                  const uint16_t *__restrict__ Bt, uint32_t *__restrict__ qw,
+                                                                  uint16_t *__restrict__ scales, uint16_t *__restrict__ zeros, int N,
+                                                                  int K, int r, int row_words, uint16_t *__restrict__ D16,
+                                                                  uint16_t *__restrict__ Dt16, int ldt, float gain, int tiles)
+{
+#pragma clang fp contract(off)
+    constexpr int kRows = 16 * WAVES, kPieces = 4 * STEPS;
+    __shared__ half8_t taps[kGroup][kPieces];
+    __shared__ uint32_t longest;                                                // largest squared norm of a feature's taps
+    // Delta_F by column: [feature][row], features 2 kRows + 16 bytes apart and 32 more for every 32 of them (the lanes of a quarter wave write 32 of these bytes)
+    constexpr int kTurnStride = kRows + 8;
+    __shared__ uint16_t turn[DELTA ? kGroup * kTurnStride + 64 : 8];
+    auto turn_at = [](int f) { return f * kTurnStride + (f >> 5) * 16; };
+    __shared__ struct { float code[kGroup]; alignas(16) _Float16 delta[DELTA ? kGroup : 8]; } exact[WAVES];
+    constexpr int qmax = (1 << BITS) - 1;
+    constexpr int kNowhere = 0x7FFFFFF0;                                        // beyond every buffer: taps past r are zeros in both operands
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, q = lane >> 4;
+    const int G = K / kGroup, g = blockIdx.x;
+    const int steps = (r + kQuantTapStep - 1) / kQuantTapStep;
+
+    if (threadIdx.x == 0) longest = 0;
+    if (r > 0) {
+        // eight features of eight taps a thread, turned in registers
+        const __amdgpu_buffer_rsrc_t abuf = bounded_buffer(At, (long)r * K * 2);
+        for (int u = threadIdx.x; u < 64 * steps; u += 64 * WAVES) {
+            const int fb = u & 15, p = u >> 4;
+            half8_t a[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) a[j] = load_half8(abuf, 8 * p + j < r ? ((8 * p + j) * K + g * kGroup + 8 * fb) * 2 : kNowhere);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int f = 8 * fb + i;
+                taps[f][p ^ tap_key(f)] = half8_t{a[0][i], a[1][i], a[2][i], a[3][i], a[4][i], a[5][i], a[6][i], a[7][i]};
+            }
+        }
+        __syncthreads();
+        // WAVES / 2 threads a feature, side by side
+        constexpr int kSide = WAVES / 2;
+        const int f = threadIdx.x / kSide;
+        float even = 0.0f, odd = 0.0f;
+        for (int p = threadIdx.x % kSide; p < 4 * steps; p += kSide) {
+            const half8_t a = taps[f][p ^ tap_key(f)];
+#pragma unroll
+            for (int j = 0; j < 8; j += 2) {
+                even = __builtin_fmaf((float)a[j], (float)a[j], even);
+                odd = __builtin_fmaf((float)a[j + 1], (float)a[j + 1], odd);
+            }
+        }
+        even += odd;
+#pragma unroll
+        for (int away = 1; away < kSide; away *= 2) even += __shfl_xor(even, away, 64);
+        uint32_t most = __builtin_bit_cast(uint32_t, even);                    // (not negative; a NaN is larger than all numbers this way)
+#pragma unroll
+        for (int away = kSide; away < 64; away *= 2) most = max(most, (uint32_t)__shfl_xor((int)most, away, 64));
+        if (lane == 0 && most) atomicMax(&longest, most);
+    }
+    __syncthreads();
+    // (the instruction aligns a subnormal operand as one of 2^-14)
+    const float a_norm2 = longest ? __builtin_bit_cast(float, longest) + (float)r * 0x1p-28f : 0.0f;
+
+    for (int tile = 0; tile < tiles; ++tile) {
+        const int nb = (blockIdx.y * tiles + tile) * kRows, n0 = nb + 16 * wave;   // the block's first row, the wave's
+        if (nb >= N) break;
+        const int rows = min(16, N - n0);                                       // may be <= 0: such a wave computes zeros and stores nothing
+        // The wave's rows of W and Bt through descriptors that end with row N - 1: rows past it read as zeros.
+        const __amdgpu_buffer_rsrc_t wbuf = bounded_buffer(W + (size_t)min(n0, N - 1) * K, rows > 0 ? (long)rows * K * 2 : 0);
+        const __amdgpu_buffer_rsrc_t bbuf = bounded_buffer(Bt + (size_t)min(n0, N - 1) * r, rows > 0 ? (long)rows * r * 2 : 0);
+        half8_t w[4], b[2];
+        auto branch_rows = [&](int j) __attribute__((always_inline)) { return load_half8(bbuf, j < r ? (c * r + j) * 2 : kNowhere); };
+        b[0] = branch_rows(8 * q);                                              // (r is a multiple of 8: all of a lane's taps or none)
+        b[1] = branch_rows(kQuantTapStep + 8 * q);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = load_half8(wbuf, (c * K + g * kGroup + 32 * q + 8 * i) * 2);
+
+        // ---- 32 bits, with a bound
+        uint32_t words[BITS], sz;
+        half8_t d8[4];
+        bool sure;
+        {
+            float R[32];                                                         // Sigma first
+#pragma unroll
+            for (int i = 0; i < 32; ++i) R[i] = 0.0f;
+            float b_norm2 = 0.0f;
+#pragma unroll 1
+            for (int s = 0; s < steps; ++s) {
+                const half8_t b8 = b[0];
+                b[0] = b[1];
+                b[1] = branch_rows(kQuantTapStep * (s + 2) + 8 * q);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) b_norm2 = __builtin_fmaf((float)b8[j], (float)b8[j], b_norm2);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const int f = 32 * (c >> 2) + 4 * t + (c & 3);
+                    const float4_t sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(taps[f][(4 * s + q) ^ tap_key(f)], b8, float4_t{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) R[4 * t + v] += sum[v];
+                }
+            }
+            b_norm2 += __shfl_xor(b_norm2, 16, 64);
+            b_norm2 += __shfl_xor(b_norm2, 32, 64);
+#pragma unroll
+            for (int i = 0; i < 32; ++i) R[i] = (float)w[i >> 3][i & 7] - R[i];
+            if (b_norm2 != 0.0f) b_norm2 += (float)(8 * steps) * 0x1p-28f;
+            float lo = R[0], hi = R[0];
+#pragma unroll
+            for (int i = 1; i < 32; ++i) { lo = fminf(lo, R[i]); hi = fmaxf(hi, R[i]); }
+            row_extremes(lo, hi);
+            // How far R can be off.  The instruction adds eight products at a time to what it has, cutting each operand off 2^-24 below the
+            // largest and rounding the sum once (measured, bit by bit): 10 x 2^-24 of what the operands may be at most, which is |a| |b| of the
+            // step's 32 taps, four times a step; then come the steps' sums, rounded in fp32, and the subtraction.  Two more and the last factor
+            // are for the roundings of this bound itself.  A branch that is zero leaves R = W exactly.
+            const float most = fmaxf(fabsf(lo), fabsf(hi));
+            const float off_sum = (float)(42 + steps) * 0x1.04p-24f * sqrtf(a_norm2 * b_norm2);
+            const float off = off_sum == 0.0f ? 0.0f : off_sum + 0x1.04p-24f * (most + off_sum);
+            // the search from the widest and from the narrowest extremes that the bound allows (even and odd quarter waves): it is monotone
+            // in them while a zero's last place is below one, so where both agree the true ones do
+            const double e = q & 1 ? -(double)off : (double)off;
+            sz = search_scale((double)lo - e, (double)hi + e, qmax);
+            sure = (uint32_t)__shfl_xor((int)sz, 16, 64) == sz && (off == 0.0f || hi - lo > 8.0f * off);
+            const float s = (float)__builtin_bit_cast(half_t, (uint16_t)sz), z = (float)__builtin_bit_cast(half_t, (uint16_t)(sz >> 16));
+            // (far from zero the differences inside a group are lost in R's own rounding, which Delta_F would show)
+            sure = sure && fabsf(z) <= (DELTA && off != 0.0f ? 32.0f : 1024.0f);
+            const float inv = 1.0f / s;
+            // t below is off by R's error, the reciprocal's, and one rounding
+            const float lim = 0.5f - (off * inv + 0x1.1p-24f * (most * inv + (float)(qmax + 1)) + 0x1.1p-24f * most * inv);
+            float x[32];
+            bool clear = true;
+#pragma unroll
+            for (int i = 0; i < 32; ++i) {
+                const float t = __builtin_fmaf(R[i], inv, z);
+                x[i] = rintf(t);                                                 // ties to even
+                clear = clear && fabsf(t - x[i]) <= lim;
+                x[i] = fminf(fmaxf(x[i], 0.0f), (float)qmax);
+                if (DELTA) d8[i >> 3][i & 7] = (_Float16)(gain * __builtin_fmaf(-s, x[i] - z, R[i]));   // Delta_F (Sec. 4.2)
+            }
+            sure = (sure && clear) || lo != lo;                                  // (no number in the whole group: nothing more exact to be had)
+            pack_codes<BITS>(x, words);
+        }
+        // ---- rows that 32 bits leave open, in 64: two features a lane.  The products of two fp16 values have 22 significant bits, so the
+        // order of the taps matters only where a sum needs more than 53 bits.
+        const unsigned long long unsure = __ballot(!sure);
+        for (uint32_t open = (uint32_t)(unsure | unsure >> 16 | unsure >> 32 | unsure >> 48) & 0xFFFFu; open; open &= open - 1) {
+            const int n = __builtin_ctz(open);
+            uint16_t wi[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) wi[i] = __builtin_amdgcn_raw_buffer_load_b16(wbuf, (n * K + g * kGroup + lane + 64 * i) * 2, 0, 0);
+            // the row's taps, four a lane
+            const auto b4 = __builtin_amdgcn_raw_buffer_load_b64(bbuf, 4 * lane < r ? (n * r + 4 * lane) * 2 : kNowhere, 0, 0);
+            double R[2] = {0.0, 0.0};
+            half8_t next[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) next[i] = taps[lane + 64 * i][tap_key(lane + 64 * i)];
+#pragma unroll 1
+            for (int p = 0; 8 * p < r; ++p) {
+                half8_t a[2];
+                const int after = min(p + 1, 4 * steps - 1);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    a[i] = next[i];
+                    next[i] = taps[lane + 64 * i][after ^ tap_key(lane + 64 * i)];
+                }
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const uint32_t two = __builtin_amdgcn_readlane(b4[(j >> 1) & 1], 2 * p + (j >> 2));
+                    const float bj = (float)__builtin_bit_cast(half_t, (uint16_t)(two >> (16 * (j & 1))));
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) R[i] += (double)__builtin_fmaf((float)a[i][j], bj, 0.0f);   // (a product of two fp16 is an fp32 number)
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) R[i] = half_bits_to_double(wi[i]) - R[i];
+            double lo = fmin(R[0], R[1]), hi = fmax(R[0], R[1]);
+#pragma unroll
+            for (int away = 1; away < 64; away *= 2) {
+                lo = fmin(lo, __shfl_xor(lo, away, 64));
+                hi = fmax(hi, __shfl_xor(hi, away, 64));
+            }
+            const uint32_t found = search_scale(lo, hi, qmax);
+            const double sd = half_bits_to_double((uint16_t)found), zd = half_bits_to_double((uint16_t)(found >> 16));
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const double code = fmin(fmax(rint(R[i] / sd + zd), 0.0), (double)qmax);
+                exact[wave].code[lane + 64 * i] = (float)code;
+                if (DELTA) exact[wave].delta[lane + 64 * i] = (_Float16)(float)((double)gain * (R[i] - sd * (code - zd)));
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (c == n) {
+                sz = found;
+                float x[32];
+#pragma unroll
+                for (int i = 0; i < 32; ++i) x[i] = exact[wave].code[32 * q + i];
+                pack_codes<BITS>(x, words);
+                if (DELTA) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) d8[i] = *reinterpret_cast<const half8_t *>(&exact[wave].delta[32 * q + 8 * i]);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+
+        if (c < rows) {
+            const size_t n = (size_t)(n0 + c);
+            if (q == 0) scales[n * G + g] = (uint16_t)sz;
+            if (q == 1) zeros[n * G + g] = (uint16_t)(sz >> 16);
+            uint32_t *to = qw + n * row_words + g * (4 * BITS) + BITS * q;
+            if constexpr (BITS == 4) *reinterpret_cast<uint4 *>(to) = uint4{words[0], words[1], words[2], words[3]};
+            else { to[0] = words[0]; to[1] = words[1]; to[2] = words[2]; }
+            if (DELTA) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) *reinterpret_cast<half8_t *>(D16 + n * K + g * kGroup + 32 * q + 8 * i) = d8[i];
+            }
+        }
+        if (DELTA) {
+#pragma unroll
+            for (int i = 0; i < 32; ++i) turn[turn_at(32 * q + i) + 16 * wave + c] = c < rows ? __builtin_bit_cast(uint16_t, (_Float16)d8[i >> 3][i & 7]) : (uint16_t)0;
+            __syncthreads();
+            int tid = threadIdx.x;                                              // (not known to be the same in every tile: addresses kept over the loop spill)
+            asm volatile("" : "+v"(tid));
+            // whole rows of Dt16, kRows / 8 lanes each (ldt is a multiple of 64: a piece lies before it or behind)
+#pragma unroll
+            for (int it = 0; it < kGroup * kRows / 8 / (64 * WAVES); ++it) {
+                const int piece = it * 64 * WAVES + tid, f = piece / (kRows / 8), part = piece % (kRows / 8);
+                if (nb + 8 * part < ldt)
+                    *reinterpret_cast<uint4 *>(Dt16 + (size_t)(g * kGroup + f) * ldt + nb + 8 * part) = *reinterpret_cast<const uint4 *>(&turn[turn_at(f) + 8 * part]);
+            }
+            if (tile + 1 < tiles) __syncthreads();                              // everybody has read before the next tile's rows come
+        }
+    }
+}
+
+hipError_t launch_quantize(const fbq_desc &d, const uint16_t *W, const uint16_t *At, const uint16_t *Bt, uint32_t *qw,
+                           uint16_t *scales, uint16_t *zeros, hipStream_t stream, uint16_t *D16, uint16_t *Dt16, int ldt, float gain)
+{
+    const int words = (int)row_words(d.K, d.bits), G = d.K / kGroup;
+    // Waves a block: four, so that four blocks share a CU, but eight where the taps (64 KB above rank 128) or the taps and Delta_F's turned copy
+    // leave room for two blocks at most (11008 x 4096 INT4, r = 200: 125 us with four, 96 with eight), unless those are too few to go round.
+    // Tiles a block: two, which halves the work of getting At into LDS (r = 64, INT3, 11008 x 4096: 55 us with one tile, 50 with two, 49 with three),
+    // where the GPU is full with them; one without a sub-branch (30, 32, 33 us: blocks that start in the order of the rows read memory best).
+    const bool wide = (d.r > 128 || (D16 && d.r > 64)) && G * ceil_div(d.N, 128) >= 256;
+    const int rows = wide ? 128 : 64, blocks = G * ceil_div(d.N, rows);
+    const int tiles = d.r > 0 && blocks >= (wide ? 1024 : 2048) ? 2 : 1;
+    const dim3 grid(G, ceil_div(d.N, rows * tiles));
+#define FBQ_QUANT(B, D, S, V) hipLaunchKernelGGL((fbq_quantize_kernel<B, D, S, V>), grid, dim3(64 * V), 0, stream, W, At, Bt, qw, scales, zeros, d.N, d.K, d.r, words, D16, Dt16, ldt, gain, tiles)
+#define FBQ_QUANT_R(B, D) do { if (wide) { if (D && d.r <= 128) FBQ_QUANT(B, D, 4, 8); else FBQ_QUANT(B, D, 8, 8); } \
+                               else if (d.r <= 64) FBQ_QUANT(B, D, 2, 4); else if (d.r <= 128) FBQ_QUANT(B, D, 4, 4); else FBQ_QUANT(B, D, 8, 4); } while (0)
+    if (d.bits == 4) { if (D16) FBQ_QUANT_R(4, true); else FBQ_QUANT_R(4, false); }
+    else { if (D16) FBQ_QUANT_R(3, true); else FBQ_QUANT_R(3, false); }
+#undef FBQ_QUANT_R
+#undef FBQ_QUANT
+    return hipGetLastError();
+}
+
+}  // namespace fbq

@@ -33,6 +33,45 @@ def test_quantizer_tile_edges(bits, N, K, r):
     assert np.array_equal(dev.qweight.cpu().numpy().view(np.uint32), L.words)
 
 
+@pytest.mark.parametrize("bits,N,K,r,kind", [
+    (4, 33, 256, 0, "ties"), (3, 33, 256, 8, "ties"), (4, 64, 128, 64, "large branch"), (3, 50, 128, 256, "large branch"), (4, 40, 256, 40, "offset"),
+    (3, 40, 256, 16, "subnormal"), (4, 40, 256, 136, "subnormal"), (3, 40, 384, 24, "few values"), (4, 20, 256, 8, "zero branch"),
+    (3, 513, 32768, 8, "plain"), (4, 129, 32768, 136, "plain"), (3, 641, 32768, 200, "plain")])
+def test_quantizer_where_32_bits_leave_rows_open(bits, N, K, r, kind):
+    """Rows whose scale, zero or codes lie on, or within fp32's reach of, a rounding boundary go through fp64; the last three sizes have two
+    row tiles a block and blocks of eight waves.  Every word as in 64 bits: sums of dyadic numbers, or of values of one size, need fewer than 53 bits."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    rng = np.random.Generator(np.random.Philox(61 + r + bits))
+    W = rng.standard_normal((N, K)) * 0.02
+    A, B = rng.standard_normal((K, max(r, 1))) * 0.01, rng.standard_normal((max(r, 1), N)) * 0.01
+    if kind == "ties":                                  # scale 1 (or 1/2), zero 0: half the values lie half-way between two codes
+        W = rng.integers(0, 2 * (2 ** bits - 1) + 1, (N, K)) / 2.0
+        W[:, ::128], W[:, 1::128] = 0.0, 2 ** bits - 1.0
+        W[::2] /= 2
+        A, B = np.where(np.arange(K)[:, None] % 128 < 2, 0.0, np.round(A * 400) / 16), np.round(B * 400) / 16
+    elif kind == "large branch":
+        A, B = A * 1000, B * 1000
+    elif kind == "offset":
+        W += rng.choice([0.5, 3.0, 40.0, -500.0], (N, 1))
+    elif kind == "subnormal":
+        W, A, B = W * 1e-4, A * np.where(rng.random((K, r)) < 0.5, 1e-4, 1.0), B * np.where(rng.random((r, N)) < 0.5, 1e-4, 1.0)
+    elif kind == "few values":
+        W = rng.choice([-0.25, 0.25, 0.125, 0.0], (N, K))
+    elif kind == "zero branch":
+        B *= 0
+    W, A, B = (a.astype(np.float16) for a in (W, A, B))
+    dev = fbq.quantize_feedback(fbq.Desc(N, K, r, bits), t16(W), t16(A.T) if r else None, t16(B.T) if r else None)
+    codes = fbq.unpack_codes(dev).cpu().numpy()
+    rows = np.arange(N) if N * K <= 1 << 20 else np.unique(np.r_[0:17, 63:66, 127:130, N - 2:N, rng.integers(0, N, 12)] % N)
+    Bs = np.ascontiguousarray(B[:, rows])
+    want, s, z = orc.quantize(np.ascontiguousarray(W[rows]), A if r else None, Bs if r else None, bits, 128)
+    assert np.array_equal(dev.scales.cpu().numpy().view(np.uint16)[rows], s.view(np.uint16))
+    got_z = dev.zeros.cpu().numpy().view(np.float16)[rows]
+    assert np.array_equal(got_z, z)
+    assert np.array_equal(codes[rows], want)
+
+
 def quantize_group_by_the_book(R, qmax):
     """Scale, zero and codes of one group as include/fbq.h defines them, the scale stepped through every fp16 number: extremes that
     ignore NaN, comparisons that a NaN fails, clamping that turns a NaN into code 0."""

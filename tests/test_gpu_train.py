@@ -175,3 +175,27 @@ def test_reconstruction_loop_lowers_the_loss_and_keeps_the_bound():
     WF = fbq.reconstruct(layer).cpu().numpy().astype(np.float64)
     s = np.repeat(layer.scales.cpu().numpy().view(np.float16).astype(np.float64), 128, axis=1)
     assert np.all(np.abs(W.astype(np.float64) - WF) <= 0.5 * s * (1 + 1e-4) + 1e-7)
+
+
+@pytest.mark.parametrize("bits,N,K,r", [(3, 4100, 4096, 8), (4, 2100, 2048, 72), (4, 1030, 4096, 136), (3, 4100, 4096, 72), (4, 70, 256, 200), (3, 129, 128, 128)])
+def test_delta_in_both_orientations_at_the_quantizers_block_shapes(bits, N, K, r):
+    """Blocks of four and eight waves, of one and two row tiles, rows past the last: the gradients, which see Delta_F in both orientations,
+    against 64 bits from the step's own layer.  Three roundings to fp16 of 2^-11 each, as above: 2e-3."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + r)
+    rand = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    W, X, At, Bt = (rand(N, K) * 0.02).half(), rand(256, K).half(), rand(r, K) * 0.01, rand(N, r) * 0.01
+    d = fbq.Desc(N, K, r, bits)
+    H16 = fbq.gram(d, X, 1.0 / 256)
+    st = fbq.train_state(d, At.clone(), Bt.clone())
+    fbq.train_step(st, W, H16, 1.0 / 256, 0.0, want_loss=False)
+    plain = fbq.quantize_feedback(d, W, At.half().view(torch.int16), Bt.half().view(torch.int16))
+    for a, b in ((st.layer.qweight, plain.qweight), (st.layer.scales, plain.scales), (st.layer.zeros, plain.zeros)):
+        assert torch.equal(a, b)
+    A, B, H = At.half().double(), Bt.half().double(), H16.double() * 256
+    s, z = (t.view(torch.float16).double()[:, :, None] for t in (plain.scales, plain.zeros))
+    delta = W.double() - B @ A - (s * (fbq.unpack_codes(plain).view(N, K // 128, 128) - z)).view(N, K)
+    P = delta @ H
+    want_A, want_B = -2 * (B.T.contiguous() @ P), -2 * (P @ A.T.contiguous())
+    for got, want in ((st.grad_At, want_A), (st.grad_Bt, want_B)):
+        assert float((got.double() - want).norm() / want.norm()) < 2e-3
