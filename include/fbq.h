@@ -84,6 +84,10 @@ size_t fbq_packed_bytes(const fbq_desc *d);
  * re-ordered for the matrix cores (M rows of K fp16), scales and zeros by group (K/g rows of N words, N rounded up
  * to 256), t as two fp16 halves and its partial sums, and, where the launch splits K over blocks, fp32 partial
  * outputs (up to 8 x M x N); not 0 even when r == 0.  0 for an invalid descriptor or M < 1.
+ * 3 <= M <= 64 where K is split over blocks (see fbq_linear): also room for the fp32 partial sums, K segments x token
+ * rows x N, not 0 even when r == 0.  A workspace without that room, as large as the hand-over words (or, where the sets of 16
+ * would not serve the call, the path of M > 64) ask for - NULL where that is 0 - is accepted too; the call then goes unsplit, with the same error bound
+ * or that path's and other last bits.
  * The size is NOT monotonic in M (fewer tokens can mean more K slices or a K split with partial outputs): a workspace
  * meant for several token counts takes the largest of their sizes. */
 size_t fbq_workspace_bytes(const fbq_desc *d, int M);
@@ -114,7 +118,8 @@ fbq_status fbq_pack(const fbq_desc *d, const uint8_t *codes, const uint16_t *sca
  * down-projection; 17 <= M <= 64 is the same launch with the sets of 16 tokens side by side (the packed words are read
  * once per 16 tokens and the codes multiplied exactly; one or two tokens left over go through the GEMV
  * or, in larger layers, are a set too; a layer so large that reading it two to four times costs far more takes the path
- * of M > 64 instead).  M > 64 runs the fp16 MFMA GEMM after a pass that
+ * of M > 64 instead).  With long rows (up to 16 tokens from 14336 activations on in layers of 2048 to 10239 rows, with more above 8192
+ * and in those large layers) K is split over blocks that take all tokens of the call at once, and a second launch adds up.  M > 64 runs the fp16 MFMA GEMM after a pass that
  * re-orders x and a separate down-projection; a layer with too few output tiles to fill the GPU has
  * its K range split over up to 8 blocks per tile, summed in fp32 by a last small launch.
  *   x         device [M, K] fp16             qweight, scales, zeros, At, Bt: device, layout above
@@ -135,7 +140,7 @@ fbq_status fbq_linear(const fbq_desc *d, int M, const void *x, const void *qweig
 /*
  * fbq_linear_static - fbq_linear for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc) and therefore cannot supply a
- * workspace: the same kernels, with the hand-over scratch taken from a device array inside the
+ * workspace: the same kernels (those that need no partial sums in a workspace), with the hand-over scratch taken from a device array inside the
  * library (544 KiB per GPU the library runs on, held until the process ends).  The call itself
  * allocates nothing and frees nothing.
  *   Arguments as for fbq_linear, without workspace and workspace_bytes.  M <= 16 only: larger token

@@ -6,6 +6,7 @@
 #include <atomic>
 
 #include "fbq_internal.h"
+#include "fbq_split_plan.h"
 
 using namespace fbq;
 
@@ -68,16 +69,30 @@ static bool takes_sets(int M, int N, int K)
     return K >= 3072 && K <= 8192 && few_stream((long)sets * N, K) && (sets == 2 || (sets == 4 && (long)N * K <= 70000000L));
 }
 
-// In front of what the prefill path keeps in a workspace: room for the hand-over words of the decode paths, which the
-// prefill path never touches.  A workspace that serves calls of every token count then only ever holds words with a
-// launch's tag, or the zeros it started with, where the decode kernels look for tags - never activations or partial
-// sums that happen to look like one.
-static size_t handover_reserve(int K, int r)
+namespace fbq {
+size_t handover_reserve(int K, int r)
 {
     return r > 0 ? (size_t)kMaxSmallGroup * small_m_workspace_bytes(K, r) : 0;
 }
+}  // namespace fbq
 
-extern "C" size_t fbq_workspace_bytes(const fbq_desc *d, int M)
+// Whether a call of 3 to 64 tokens has its K split over blocks (fbq_few_split.hip) instead of going where it would go otherwise.  us, otherwise / split.
+// Up to 16 tokens: from 14336 activations on and between 2048 and 10240 rows: 28672 -> 2048 INT4, r = 64, 16 tokens 20.8 / 14.6, -> 4096 25.3 / 20.2, -> 8192
+// 42.8 / 34.3; 14336 -> 4096 INT3, 8 tokens 16.3 / 15.2, -> 8192, 16 tokens 21.2 / 21.4; on the other side 11008 -> 4096 INT3, 8 tokens 13.5 / 14.1, 8320 -> 4096, r =
+// 200, 14.4 / 17.6.  (Wider layers stream; narrower ones share launches with them.)
+// 17 to 64: instead of sets of 16 with more than 8192 activations and 25 million codes: 13824 -> 5120 INT4, r = 128, 17 tokens 28.1 / 22.1, 64 40.0 / 26.0; 11008 ->
+// 4096 INT3 at 32 18.3 / 17.8, at 48 23.9 / 19.5; 14336 -> 2000 at 32 14.9 / 14.6; but 8320 -> 1000 at 32 10.7 / 13.4.  Instead of the GEMM from 2048
+// activations on: 4096 -> 28672 INT3 at 48 33.9 / 26.3, 20480 -> 9000 at 64 52.3 / 46.8, 6144 -> 20000 at 64 53.2 / 40.5, 2048 -> 28000 at 64 26.7 / 25.7; but
+// 1024 -> 28672 at 48 20.9 / 21.7, at 64 21.2 / 25.7.
+static bool takes_split(int M, int N, int K)
+{
+    if (M <= kPerTokenMaxM || M > kChunkedMaxM) return false;
+    if (M <= kDecodeMaxM) return K >= 14336 && N >= 2048 && N < 10240;
+    return takes_sets(M, N, K) ? K > 8192 && (long)N * K >= 25000000L : K >= 2048;
+}
+
+// What a call cannot do without.
+static size_t least_workspace(const fbq_desc *d, int M)
 {
     if (fbq_check_desc(d) != FBQ_OK || M < 1) return 0;
     if (M <= kPerTokenMaxM) return d->r == 0 ? 0 : decode_workspace_bytes(M, d->K, d->r);
@@ -88,6 +103,23 @@ extern "C" size_t fbq_workspace_bytes(const fbq_desc *d, int M)
     if (M <= kChunkedMaxM && takes_sets(M, d->N, d->K))
         return (size_t)((M + kDecodeMaxM - 1) / kDecodeMaxM) * small_m_workspace_bytes(d->K, d->r);
     return handover_reserve(d->K, d->r) + prefill_workspace_bytes(M, d->N, d->K, d->r);      // holds the re-ordered activations even when r == 0
+}
+
+// Room for 16 tokens' partial sums where K is split, whatever the number of sets, and behind it the hand-over words.
+static size_t split_set_bytes(const fbq_desc *d)
+{
+    size_t most = 0;
+    for (int sets = 1; sets <= kMaxSmallGroup; ++sets) most = std::max(most, few_split_bytes(sets, d->N, d->K, d->r, d->bits) / sets);
+    return most + handover_reserve(d->K, d->r);
+}
+
+extern "C" size_t fbq_workspace_bytes(const fbq_desc *d, int M)
+{
+    const size_t least = least_workspace(d, M);
+    if (fbq_check_desc(d) != FBQ_OK || M < 1 || !takes_split(M, d->N, d->K)) return least;
+    const int sets = (M + kDecodeMaxM - 1) / kDecodeMaxM;
+    if (M <= kDecodeMaxM || takes_sets(M, d->N, d->K)) return least + sets * split_set_bytes(d);   // (as for the sets: so many times that of 16 tokens, where these take it too)
+    return std::max(least, handover_reserve(d->K, d->r) + few_split_bytes(sets, d->N, d->K, d->r, d->bits));
 }
 
 // ------------------------------------------------------------------ host-side packing
@@ -174,12 +206,14 @@ fbq_status check_layer(const fbq_desc *d, int M, const void *x, const void *qwei
     if (M < 1) return FBQ_ERR_SHAPE;
     if (!x || !qweight || !scales || !zeros || !y) return FBQ_ERR_NULL;
     if (d->r > 0 && (!At || !Bt)) return FBQ_ERR_NULL;
-    const size_t need = fbq_workspace_bytes(d, M);
+    const size_t need = least_workspace(d, M);
     if (need > 0 && !workspace) return FBQ_ERR_NULL;
     if (misaligned(x) || misaligned(qweight) || misaligned(scales) || misaligned(zeros) || misaligned(y)) return FBQ_ERR_ALIGN;
     if (d->r > 0 && (misaligned(At) || misaligned(Bt))) return FBQ_ERR_ALIGN;
     if (need > 0 && misaligned(workspace)) return FBQ_ERR_ALIGN;
     if (workspace_bytes < need) return FBQ_ERR_WORKSPACE;
+    // (a workspace of the size that was enough before K was split is still accepted, and served without the split)
+    a->split = takes_split(M, d->N, d->K) && workspace && !misaligned(workspace) && workspace_bytes >= fbq_workspace_bytes(d, M);
     a->qw = (const uint32_t *)qweight;
     a->scales = (const uint16_t *)scales;
     a->zeros = (const uint16_t *)zeros;
@@ -188,7 +222,7 @@ fbq_status check_layer(const fbq_desc *d, int M, const void *x, const void *qwei
     a->x = (const uint16_t *)x;
     a->y = (uint16_t *)y;
     a->workspace = workspace;
-    a->workspace_need = need;
+    a->workspace_need = a->split ? fbq_workspace_bytes(d, M) : need;
     a->M = M; a->N = d->N; a->K = d->K; a->r = d->r; a->bits = d->bits;
     a->mix_with = nullptr; a->mix_out = nullptr;
     return FBQ_OK;
@@ -210,6 +244,7 @@ static hipError_t launch_prefill(const LinearArgs &call, hipStream_t s)
 hipError_t launch_one(const LinearArgs &a, hipStream_t s)
 {
     if (a.M <= kPerTokenMaxM) return launch_gemv_decode(&a, 1, s);
+    if (a.split) return launch_few_split(&a, 1, s);
     if (a.M <= kDecodeMaxM) return launch_gemv_small_m(&a, 1, s);
     if (a.M <= kChunkedMaxM && takes_sets(a.M, a.N, a.K)) {
         static_assert(kChunkedMaxM <= kMaxSmallGroup * kDecodeMaxM, "the sets of 16 tokens must fit one grouped launch");
@@ -253,6 +288,7 @@ extern "C" fbq_status fbq_linear_unfused(const fbq_desc *d, int M, const void *x
     hipStream_t s = (hipStream_t)stream;
     LinearArgs main_path = a;                           // the quantized layer without its sub-branch ...
     main_path.r = 0; main_path.At = nullptr; main_path.Bt = nullptr;
+    main_path.split = false;                            // (in one launch)
     hipError_t e = launch_one(main_path, s);
     if (e == hipSuccess && d->r > 0) e = launch_unfused_branch(a, (uint16_t *)workspace, s);   // ... and the sub-branch on top
     return hip_status(e);
@@ -342,12 +378,12 @@ static fbq_status linear_group(const fbq_layer_call *calls, const fbq_mix *mix, 
         LinearArgs batch[kMaxGroup];
         int nb = 0;
         for (int j = i; j < n && nb < cap; ++j) {
-            if (!done[j] && (few ? small_m_group_compatible(args[i], args[j]) : decode_group_compatible(args[i], args[j]))) {
+            if (!done[j] && (few ? args[j].split == args[i].split && small_m_group_compatible(args[i], args[j]) : decode_group_compatible(args[i], args[j]))) {
                 batch[nb++] = args[j];
                 done[j] = true;
             }
         }
-        e = few ? launch_gemv_small_m(batch, nb, s) : launch_gemv_decode(batch, nb, s);
+        e = !few ? launch_gemv_decode(batch, nb, s) : batch[0].split ? launch_few_split(batch, nb, s) : launch_gemv_small_m(batch, nb, s);
     }
     return hip_status(e);
 }

@@ -72,6 +72,37 @@ __device__ __forceinline__ void arrange_operands(const uint4_t (&raw)[4], half8_
     for (int t = 0; t < 4; ++t) ops[t] = pack8(pr[4 * t], pr[4 * t + 1], pr[4 * t + 2], pr[4 * t + 3]);
 }
 
+// The four matrix operands of a lane's 32 codes: every field stays where it is, masked out, i.e. it is the subnormal fp16
+// number code x gain x 2^-24, which the matrix cores multiply exactly (measured).  Pair order (also the order of the
+// arranged activations): INT4 word j -> codes (8j+f, 8j+f+4), f = 0..3;  INT3 word j -> codes (10j+f, 10j+f+5), f = 0..4,
+// and codes (30, 31) last.
+template <int BITS>
+__device__ __forceinline__ void code_operands(const uint4_t w, half8_t (&b)[4])
+{
+    const uint32_t wd[4] = {w.x, w.y, w.z, w.w};
+    if constexpr (BITS == 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t lo = wd[j], hi = wd[j] >> 8;
+            b[j] = pack8(h2_of(lo & 0x000F000Fu), h2_of(lo & 0x00F000F0u), h2_of(hi & 0x000F000Fu), h2_of(hi & 0x00F000F0u));
+        }
+    } else {
+        half2_t d[16];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const uint32_t lo = wd[j], hi = wd[j] >> 9;
+            d[5 * j + 0] = h2_of(lo & 0x00070007u);
+            d[5 * j + 1] = h2_of(lo & 0x00380038u);
+            d[5 * j + 2] = h2_of(lo & 0x01C001C0u);
+            d[5 * j + 3] = h2_of(hi & 0x00070007u);
+            d[5 * j + 4] = h2_of(hi & 0x00380038u);
+        }
+        d[15] = h2_of(((wd[0] >> 15) & 0x00010001u) | (((wd[1] >> 14) & 0x00020002u) | ((wd[2] >> 13) & 0x00040004u)));
+#pragma unroll
+        for (int t = 0; t < 4; ++t) b[t] = pack8(d[4 * t], d[4 * t + 1], d[4 * t + 2], d[4 * t + 3]);
+    }
+}
+
 // The gains of the eight weight fields that operand t holds: against this column the scaled
 // activations sum to X = sum x.
 template <int BITS>

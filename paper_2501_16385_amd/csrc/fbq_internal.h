@@ -48,7 +48,8 @@ struct LinearArgs {
     size_t workspace_need;   // fbq_workspace_bytes of the call (above 64 tokens a search, so looked up once)
     int M, N, K, r, bits;
     const uint16_t *mix_with;   // [M][N] and ...
-    uint16_t *mix_out;          // ... null, or [M][N] that the two decode launchers write y averaged with mix_with to (see launch_mix)
+    uint16_t *mix_out;          // ... null, or [M][N] that the decode launchers write y averaged with mix_with to (see launch_mix)
+    bool split;                 // 3 to 64 tokens: K is split over blocks (see takes_split), and the workspace has room for it
 };
 
 // 3 to 16 tokens: which of the two kernels serves a layer of N rows (for sets of 16 tokens side by side: rows times sets).  Of
@@ -69,6 +70,7 @@ hipError_t launch_gemv_small_m(const LinearArgs *layers, int n_layers, hipStream
 bool small_m_group_compatible(const LinearArgs &a, const LinearArgs &b);
 bool burst_joins_stream(const LinearArgs *layers, int n_layers, const bool *burst);
 hipError_t launch_few_stream(const LinearArgs *layers, int n_layers, const bool *burst, hipStream_t stream);   // (by way of launch_gemv_small_m, which says which layers are too small)
+hipError_t launch_few_split(const LinearArgs *layers, int n_layers, hipStream_t stream);
 hipError_t launch_prepass_prefill(const LinearArgs &a, hipStream_t stream);
 hipError_t launch_gemm_prefill(const LinearArgs &a, hipStream_t stream);
 hipError_t launch_unpack(const fbq_desc &d, const uint32_t *qw, uint8_t *codes, hipStream_t stream);
@@ -218,6 +220,12 @@ inline int down_slices_by_xcd(int M, int N, int K, int r)
     const bool pays = r * K >= 1500000 && ((long)K * std::min(N, 2304) >= 14000000 || r * K >= 2600000);
     return pays && tiles >= 8 && tiles * slices <= 256 ? slices & ~7 : 0;
 }
+
+// In front of what the prefill path and the K split keep in a workspace: room for the hand-over words of the decode paths, which those
+// never touch.  A workspace that serves calls of every token count then only ever holds words with a
+// launch's tag, or the zeros it started with, where the decode kernels look for tags - never activations or partial
+// sums that happen to look like one.
+size_t handover_reserve(int K, int r);
 
 size_t decode_workspace_bytes(int M, int K, int r);
 size_t small_m_workspace_bytes(int K, int r);

@@ -46,8 +46,6 @@ extern "C" fbq_status fbq_linear_static(const fbq_desc *d, int M, const void *x,
     if (ds != FBQ_OK) return ds;
     if (M < 1) return FBQ_ERR_SHAPE;
     if (M > kDecodeMaxM) return FBQ_ERR_UNSUPPORTED;     // larger token counts need scratch that grows with M, N and K
-    const size_t need = fbq_workspace_bytes(d, M);
-    if (need > kStaticScratchBytes) return FBQ_ERR_WORKSPACE;
     // every argument is checked before the GPU is asked for anything (the workspace passed here is a stand-in)
     LinearArgs a;
     fbq_status st = check_layer(d, M, x, qweight, scales, zeros, At, Bt, y, (void *)(uintptr_t)256, kStaticScratchBytes, &a);
@@ -56,5 +54,6 @@ extern "C" fbq_status fbq_linear_static(const fbq_desc *d, int M, const void *x,
     st = scratch_on_current_device(&ws);
     if (st != FBQ_OK) return st;
     a.workspace = ws;
+    a.split = false;                                     // (no room for partial sums)
     return hip_status(launch_one(a, (hipStream_t)stream));
 }

@@ -6,6 +6,7 @@
 namespace fbq {
 hipError_t launch_gemv_decode(const LinearArgs *, int, hipStream_t) { return hipErrorNotSupported; }
 bool decode_group_compatible(const LinearArgs &, const LinearArgs &) { return false; }
+hipError_t launch_few_split(const LinearArgs *, int, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_gemv_small_m(const LinearArgs *, int, hipStream_t) { return hipErrorNotSupported; }
 bool small_m_group_compatible(const LinearArgs &, const LinearArgs &) { return false; }
 hipError_t launch_prepass_prefill(const LinearArgs &, hipStream_t) { return hipErrorNotSupported; }

@@ -581,3 +581,72 @@ def test_stream_behind_the_other_entry_points(N, K, r, M, bits):
     want = x.double() @ W.T
     miss = (fbq.linear_unfused(dev, x).double() - want).norm() / want.norm()
     assert float(miss) <= 1.5e-3, float(miss)
+
+
+SPLIT_CASES = [
+    # N, K, r, M: one to four sets, a token more or less than whole ones; last segments of one group; odd numbers of scales; a row more than whole
+    # tiles and units; no sub-branch, ranks on both sides of 16, 32 and 128; the shortest and the longest rows
+    (2048, 14336, 8, 3), (2049, 14464, 0, 8), (4099, 28672, 200, 16), (10239, 16384, 40, 9),
+    (3001, 8448, 72, 17), (2100, 14336, 0, 32), (5121, 13824, 136, 33), (3001, 8448, 8, 48), (4097, 14336, 256, 64),
+    (28673, 2048, 16, 50), (28001, 2176, 40, 49), (30001, 2176, 0, 20), (1025, 32768, 24, 63),
+]
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("N,K,r,M", SPLIT_CASES)
+def test_split_edges(bits, N, K, r, M):
+    """Against 64 bits, with the bound of exactly multiplied codes, on a workspace whose every byte was part of a NaN; the same bits again; and,
+    without the room that the split needs, within the bound of the path that serves such a workspace."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    dev, W, g = framed_random_layer(N, K, r, bits, 111 + N + M)
+    x = framed_in_nan(torch.randn(M, K, device="cuda", generator=g).half())
+    want = (x.double() @ W.T).cpu().numpy()
+    del W
+    need = fbq.workspace_bytes(dev.desc, M)
+    ws = framed_in_nan(torch.full((need,), 0x7D, dtype=torch.uint8, device="cuda"))
+    ys = [framed_in_nan(torch.empty(M, N, dtype=torch.float16, device="cuda")) for _ in range(2)]
+    for y in ys:
+        fbq.linear(dev, x, y, ws)
+    assert_matches_oracle(ys[0].cpu().numpy(), want, f"INT{bits} {N}x{K} r={r} M={M}", "few")
+    assert torch.equal(ys[0], ys[1])
+    words = 17 * 16 * r * 8                              # hand-over words of 16 tokens
+    small = torch.zeros(-(-M // 16) * words, dtype=torch.uint8, device="cuda") if r else None
+    try:
+        fbq.linear_group([dev], [x], ys=[ys[1]], workspaces=[small])
+    except fbq.FbqError:
+        assert M > 16                                    # (where the GEMM would serve it, which needs more)
+    else:
+        assert_matches_oracle(ys[1].cpu().numpy(), want, f"INT{bits} {N}x{K} r={r} M={M}, smaller workspace", "few")
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("M", [5, 16])
+def test_split_group_average_and_replayed_graph(bits, M):
+    """Layers of a grouped call get the bits of their own calls, averages included, also in replays on new activations with eager calls in between."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    from paper_2501_16385_amd.random_layers import random_layer
+    g = torch.Generator(device="cuda")
+    g.manual_seed(121 + M)
+    K, shapes = 14336, [(2049, 8), (4100, 72), (1000, 16), (2304, 0)]
+    devs = [framed_layer(random_layer(fbq.Desc(N, K, r, bits), g, gain=1.0)) for N, r in shapes]
+    x = torch.randn(M, K, device="cuda", generator=g).half()
+    with_ = [torch.randn(M, N, device="cuda", generator=g).half() for N, _ in shapes]
+    ys, outs = ([framed_in_nan(torch.empty(M, N, dtype=torch.float16, device="cuda")) for N, _ in shapes] for _ in range(2))
+    need = [fbq.workspace_bytes(d.desc, M) for d in devs]
+    wss = [torch.zeros(n, dtype=torch.uint8, device="cuda") if n else None for n in need]
+    arr, mix = fbq.make_group(devs, [x] * 4, ys, wss), fbq.make_mix(with_, outs)
+    call = lambda: fbq.load().fbq_linear_group_mix(arr, mix, 4, M, torch.cuda.current_stream().cuda_stream)
+    assert call() == 0
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        assert call() == 0
+    for _ in range(3):
+        x.copy_(torch.randn(M, K, device="cuda", generator=g).half())
+        single = [fbq.linear(d, x) for d in devs]
+        graph.replay()
+        torch.cuda.synchronize()
+        for y, want, w, out in zip(ys, single, with_, outs):
+            assert torch.equal(y, want) and torch.equal(out, torch.lerp(w, want, 0.5))
