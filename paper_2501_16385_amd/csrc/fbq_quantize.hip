@@ -17,7 +17,7 @@
 //
 // With DELTA the kernel also writes what the reconstruction step needs from the same registers: Delta_F = (W - Sigma) - s (q - z), times
 // `gain`, as fp16 in both orientations (D16 [N][K]; Dt16 [K][ldt] with columns N..ldt-1 zero, ldt a multiple of 64), the transposed copy
-// through LDS as whole row pieces.  In fp32 it is off by a few 2^-24 of the group's largest |R|, the rounding to fp16 by 2^-12 of itself.
+// through LDS as whole row pieces.  It is the fp16 number that fp64 gives: where the bound leaves two open, that element is done again.
 #include <hip/hip_fp16.h>
 
 #include "fbq_internal.h"
@@ -25,6 +25,7 @@
 namespace fbq {
 
 typedef _Float16 half_t;
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
@@ -116,15 +117,24 @@ __device__ __forceinline__ void row_extremes(float &lo, float &hi)
     hi = fmaxf(f(b[0]), f(b[1]));
 }
 
+// The power of two that takes numbers whose largest is `peak` (an fp32 number's bits) to 2^10 and above, below 2^11; 1 where that would be a step down.
+__device__ __forceinline__ float fixed_point_factor(uint32_t peak)
+{
+    const int exponent = (int)(peak >> 23) - 127;
+    return peak == 0 || exponent > 10 ? 1.0f : __builtin_bit_cast(float, (uint32_t)(127 + 10 - exponent) << 23);
+}
+
 constexpr int kQuantTapStep = 32;      // taps one matrix instruction takes
+constexpr int kOpenList = 256;         // elements of Delta_F that a wave lists at a time
 
 // Taps in LDS: 16-byte pieces of eight taps, [feature][piece], a piece's place XORed with a key so that the sixteen features that
 // one matrix operand reads (bits 0, 1, 5, 6 of the feature differ) lie in sixteen different places of 256 bytes.
 __device__ __forceinline__ int tap_key(int f) { return ((f >> 1) & 1) | ((f >> 4) & 6); }
 
 // STEPS: the most steps of 32 taps.  WAVES: a block's.
+// With DELTA 128 registers spill 22 (4096 x 4096, r = 64, a step with loss 176.6 us; 173.0 with three waves a SIMD instead of four).
 template <int BITS, bool DELTA, int STEPS, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, 4) void fbq_quantize_kernel(const uint16_t *__restrict__ W, const uint16_t *__restrict__ At,
+__global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void fbq_quantize_kernel(const uint16_t *__restrict__ W, const uint16_t *__restrict__ At,
                                                                   const uint16_t *__restrict__ Bt, uint32_t *__restrict__ qw,
                                                                   uint16_t *__restrict__ scales, uint16_t *__restrict__ zeros, int N,
                                                                   int K, int r, int row_words, uint16_t *__restrict__ D16,
@@ -133,20 +143,20 @@ __global__ __launch_bounds__(64 * WAVES, 4) void fbq_quantize_kernel(const uint1
 #pragma clang fp contract(off)
     constexpr int kRows = 16 * WAVES, kPieces = 4 * STEPS;
     __shared__ half8_t taps[kGroup][kPieces];
-    __shared__ uint32_t longest;                                                // largest squared norm of a feature's taps
+    __shared__ uint32_t longest, highest;                                       // largest squared norm of a feature's taps; DELTA: largest tap
     // Delta_F by column: [feature][row], features 2 kRows + 16 bytes apart and 32 more for every 32 of them (the lanes of a quarter wave write 32 of these bytes)
     constexpr int kTurnStride = kRows + 8;
     __shared__ uint16_t turn[DELTA ? kGroup * kTurnStride + 64 : 8];
     auto turn_at = [](int f) { return f * kTurnStride + (f >> 5) * 16; };
-    __shared__ struct { float code[kGroup]; alignas(16) _Float16 delta[DELTA ? kGroup : 8]; } exact[WAVES];
+    __shared__ struct { float code[kGroup]; alignas(16) _Float16 delta[DELTA ? kGroup : 8]; uint16_t list[DELTA ? kOpenList : 8]; } exact[WAVES];
     constexpr int qmax = (1 << BITS) - 1;
     constexpr int kNowhere = 0x7FFFFFF0;                                        // beyond every buffer: taps past r are zeros in both operands
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int c = lane & 15, q = lane >> 4;
     const int G = K / kGroup, g = blockIdx.x;
     const int steps = (r + kQuantTapStep - 1) / kQuantTapStep;
 
-    if (threadIdx.x == 0) longest = 0;
+    if (threadIdx.x == 0) longest = highest = 0;
+    float a_factor = 1.0f;                                                      // DELTA: the taps in LDS are At's times this power of two
     if (r > 0) {
         // eight features of eight taps a thread, turned in registers
         const __amdgpu_buffer_rsrc_t abuf = bounded_buffer(At, (long)r * K * 2);
@@ -166,12 +176,17 @@ __global__ __launch_bounds__(64 * WAVES, 4) void fbq_quantize_kernel(const uint1
         constexpr int kSide = WAVES / 2;
         const int f = threadIdx.x / kSide;
         float even = 0.0f, odd = 0.0f;
+        uint32_t peak = 0;
         for (int p = threadIdx.x % kSide; p < 4 * steps; p += kSide) {
             const half8_t a = taps[f][p ^ tap_key(f)];
 #pragma unroll
             for (int j = 0; j < 8; j += 2) {
                 even = __builtin_fmaf((float)a[j], (float)a[j], even);
                 odd = __builtin_fmaf((float)a[j + 1], (float)a[j + 1], odd);
+            }
+            if (DELTA) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) peak = max(peak, __builtin_bit_cast(uint32_t, fabsf((float)a[j])));   // (a NaN is the largest)
             }
         }
         even += odd;
@@ -181,14 +196,30 @@ __global__ __launch_bounds__(64 * WAVES, 4) void fbq_quantize_kernel(const uint1
 #pragma unroll
         for (int away = kSide; away < 64; away *= 2) most = max(most, (uint32_t)__shfl_xor((int)most, away, 64));
         if (lane == 0 && most) atomicMax(&longest, most);
+        if (DELTA) {
+#pragma unroll
+            for (int away = 1; away < 64; away *= 2) peak = max(peak, (uint32_t)__shfl_xor((int)peak, away, 64));
+            if (lane == 0 && peak) atomicMax(&highest, peak);
+            __syncthreads();
+            a_factor = fixed_point_factor(highest);
+            for (int p = threadIdx.x % kSide; p < 4 * steps; p += kSide) {
+                half8_t &a = taps[f][p ^ tap_key(f)];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) a[j] = (half_t)((float)a[j] * a_factor);
+            }
+        }
     }
     __syncthreads();
     // (the instruction aligns a subnormal operand as one of 2^-14)
+    const double a_back = 1.0 / (double)a_factor;
     const float a_norm2 = longest ? __builtin_bit_cast(float, longest) + (float)r * 0x1p-28f : 0.0f;
 
     for (int tile = 0; tile < tiles; ++tile) {
         const int nb = (blockIdx.y * tiles + tile) * kRows, n0 = nb + 16 * wave;   // the block's first row, the wave's
         if (nb >= N) break;
+        int lane_now = lane;                                                    // (not known to be the same in every tile: addresses kept over the loop spill)
+        if (DELTA) asm volatile("" : "+v"(lane_now));
+        const int c = lane_now & 15, q = lane_now >> 4;
         const int rows = min(16, N - n0);                                       // may be <= 0: such a wave computes zeros and stores nothing
         // The wave's rows of W and Bt through descriptors that end with row N - 1: rows past it read as zeros.
         const __amdgpu_buffer_rsrc_t wbuf = bounded_buffer(W + (size_t)min(n0, N - 1) * K, rows > 0 ? (long)rows * K * 2 : 0);
@@ -203,42 +234,102 @@ __global__ __launch_bounds__(64 * WAVES, 4) void fbq_quantize_kernel(const uint1
         // ---- 32 bits, with a bound
         uint32_t words[BITS], sz;
         half8_t d8[4];
+        uint32_t open_delta = 0;                                                // DELTA: features whose fp16 number 32 bits leave open
         bool sure;
         {
-            float R[32];                                                         // Sigma first
+            float Sigma[32];
 #pragma unroll
-            for (int i = 0; i < 32; ++i) R[i] = 0.0f;
-            float b_norm2 = 0.0f;
+            for (int i = 0; i < 32; ++i) Sigma[i] = 0.0f;
+            float b_norm2 = 0.0f, off_sum, off_rest = 0.0f;                      // off_rest: of off_sum, what is not in proportion to Sigma
+            bool coarse = false;
+            if constexpr (!DELTA) {
 #pragma unroll 1
-            for (int s = 0; s < steps; ++s) {
-                const half8_t b8 = b[0];
-                b[0] = b[1];
-                b[1] = branch_rows(kQuantTapStep * (s + 2) + 8 * q);
+                for (int s = 0; s < steps; ++s) {
+                    const half8_t b8 = b[0];
+                    b[0] = b[1];
+                    b[1] = branch_rows(kQuantTapStep * (s + 2) + 8 * q);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) b_norm2 = __builtin_fmaf((float)b8[j], (float)b8[j], b_norm2);
+                    for (int j = 0; j < 8; ++j) b_norm2 = __builtin_fmaf((float)b8[j], (float)b8[j], b_norm2);
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int f = 32 * (c >> 2) + 4 * t + (c & 3);
-                    const float4_t sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(taps[f][(4 * s + q) ^ tap_key(f)], b8, float4_t{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+                    for (int t = 0; t < 8; ++t) {
+                        const int f = 32 * (c >> 2) + 4 * t + (c & 3);
+                        const float4_t sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(taps[f][(4 * s + q) ^ tap_key(f)], b8, float4_t{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) R[4 * t + v] += sum[v];
+                        for (int v = 0; v < 4; ++v) Sigma[4 * t + v] += sum[v];
+                    }
                 }
-            }
-            b_norm2 += __shfl_xor(b_norm2, 16, 64);
-            b_norm2 += __shfl_xor(b_norm2, 32, 64);
+                b_norm2 += __shfl_xor(b_norm2, 16, 64);
+                b_norm2 += __shfl_xor(b_norm2, 32, 64);
+                if (b_norm2 != 0.0f) b_norm2 += (float)(8 * steps) * 0x1p-28f;
+                // How far Sigma can be off.  The instruction adds eight products at a time to what it has, cutting each operand off 2^-24 below the
+                // largest and rounding the sum once (measured, bit by bit): 10 x 2^-24 of what the operands may be at most, which is |a| |b| of the
+                // step's 32 taps, four times a step; then come the steps' sums, rounded in fp32.  Two more and the last factor
+                // are for the roundings of this bound itself.
+                off_sum = (float)(42 + steps) * 0x1.04p-24f * sqrtf(a_norm2 * b_norm2);
+            } else {
+                // Delta_F is small beside what adds up to it, so Sigma is had more exactly: taps and rows of B, at 2^10 and above, are each a multiple of
+                // `unit` (at most 2^9 or 2^8 units) and a rest of half a unit.  Products of the multiples are whole numbers of unit^2 whose sums stay within
+                // 2^24 (|a| |b| <= r 2^18 or r 2^16): exact.  The rests' products are a hundredth of the whole, and so is their error.
+                float peak = 0.0f;
+#pragma unroll 1
+                for (int s = 0; s < steps; ++s) {
+                    const half8_t b8 = s == 0 ? b[0] : (s == 1 ? b[1] : branch_rows(kQuantTapStep * s + 8 * q));
 #pragma unroll
-            for (int i = 0; i < 32; ++i) R[i] = (float)w[i >> 3][i & 7] - R[i];
-            if (b_norm2 != 0.0f) b_norm2 += (float)(8 * steps) * 0x1p-28f;
+                    for (int j = 0; j < 8; ++j) {
+                        b_norm2 = __builtin_fmaf((float)b8[j], (float)b8[j], b_norm2);
+                        peak = fmaxf(peak, fabsf((float)b8[j]));
+                    }
+                }
+                b_norm2 += __shfl_xor(b_norm2, 16, 64);
+                b_norm2 += __shfl_xor(b_norm2, 32, 64);
+                peak = fmaxf(peak, __shfl_xor(peak, 16, 64));
+                peak = fmaxf(peak, __shfl_xor(peak, 32, 64));
+                const float b_factor = fixed_point_factor(__builtin_bit_cast(uint32_t, peak));
+                coarse = peak >= 2048.0f || highest >= 0x45000000u;              // (2048: numbers that are not stepped down; their rows go to 64 bits)
+                const half_t grid = STEPS <= 2 ? (half_t)6144.0f : (half_t)12288.0f;   // 1.5 x 2^10 units
+                const half8_t grid8 = {grid, grid, grid, grid, grid, grid, grid, grid};
+                float rest[32];
+#pragma unroll
+                for (int i = 0; i < 32; ++i) rest[i] = 0.0f;
+#pragma unroll 1
+                for (int s = 0; s < steps; ++s) {
+                    half8_t b8 = s == 0 ? b[0] : (s == 1 ? b[1] : branch_rows(kQuantTapStep * s + 8 * q));
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) b8[j] = (half_t)((float)b8[j] * b_factor);
+                    const half8_t b_whole = (b8 + grid8) - grid8, b_rest = b8 - b_whole;
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        const int f = 32 * (c >> 2) + 4 * t + (c & 3);
+                        const half8_t a8 = taps[f][(4 * s + q) ^ tap_key(f)], a_whole = (a8 + grid8) - grid8, a_rest = a8 - a_whole;
+                        const float4_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f}, had = {Sigma[4 * t], Sigma[4 * t + 1], Sigma[4 * t + 2], Sigma[4 * t + 3]};
+                        const float4_t whole = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_whole, b_whole, had, 0, 0, 0);
+                        const float4_t one = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_whole, b_rest, zero4, 0, 0, 0);
+                        const float4_t two = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_rest, b8, zero4, 0, 0, 0);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            Sigma[4 * t + v] = whole[v];
+                            rest[4 * t + v] += one[v] + two[v];
+                        }
+                        __builtin_amdgcn_sched_barrier(0);                       // (operands of all eight at once spill)
+                    }
+                }
+                const float back = 1.0f / (a_factor * b_factor);
+#pragma unroll
+                for (int i = 0; i < 32; ++i) Sigma[i] = (Sigma[i] + rest[i]) * back;
+                // The bound of the instruction (above) for the products with a rest, the additions of the rests, and the last one, rounded in fp32
+                const float a_norm = sqrtf(a_norm2) * a_factor, b_norm = sqrtf(b_norm2) * b_factor, half_units = sqrtf((float)r) * (STEPS <= 2 ? 2.0f : 4.0f);
+                off_rest = peak == 0.0f || longest == 0 ? 0.0f : 0x1.04p-24f * back * (float)(44 + 2 * steps) * half_units * (a_norm + half_units + b_norm);
+                off_sum = off_rest == 0.0f ? 0.0f : off_rest + 0x1.04p-24f * back * a_norm * b_norm;
+            }
+            float R[32];
+#pragma unroll
+            for (int i = 0; i < 32; ++i) R[i] = (float)w[i >> 3][i & 7] - Sigma[i];
             float lo = R[0], hi = R[0];
 #pragma unroll
             for (int i = 1; i < 32; ++i) { lo = fminf(lo, R[i]); hi = fmaxf(hi, R[i]); }
             row_extremes(lo, hi);
-            // How far R can be off.  The instruction adds eight products at a time to what it has, cutting each operand off 2^-24 below the
-            // largest and rounding the sum once (measured, bit by bit): 10 x 2^-24 of what the operands may be at most, which is |a| |b| of the
-            // step's 32 taps, four times a step; then come the steps' sums, rounded in fp32, and the subtraction.  Two more and the last factor
-            // are for the roundings of this bound itself.  A branch that is zero leaves R = W exactly.
+            // How far R can be off: as Sigma, and by the subtraction.  A branch that is zero leaves R = W exactly.
             const float most = fmaxf(fabsf(lo), fabsf(hi));
-            const float off_sum = (float)(42 + steps) * 0x1.04p-24f * sqrtf(a_norm2 * b_norm2);
             const float off = off_sum == 0.0f ? 0.0f : off_sum + 0x1.04p-24f * (most + off_sum);
             // the search from the widest and from the narrowest extremes that the bound allows (even and odd quarter waves): it is monotone
             // in them while a zero's last place is below one, so where both agree the true ones do
@@ -246,20 +337,37 @@ __global__ __launch_bounds__(64 * WAVES, 4) void fbq_quantize_kernel(const uint1
             sz = search_scale((double)lo - e, (double)hi + e, qmax);
             sure = (uint32_t)__shfl_xor((int)sz, 16, 64) == sz && (off == 0.0f || hi - lo > 8.0f * off);
             const float s = (float)__builtin_bit_cast(half_t, (uint16_t)sz), z = (float)__builtin_bit_cast(half_t, (uint16_t)(sz >> 16));
-            // (far from zero the differences inside a group are lost in R's own rounding, which Delta_F would show)
-            sure = sure && fabsf(z) <= (DELTA && off != 0.0f ? 32.0f : 1024.0f);
+            // (far from zero the differences inside a group are lost in R's own rounding)
+            sure = sure && fabsf(z) <= 1024.0f;
+            if (DELTA) sure = sure && !coarse && (z == 0.0f || fabsf(z) >= 0x1p-9f);   // a code less z is an fp32 number
             const float inv = 1.0f / s;
             // t below is off by R's error, the reciprocal's, and one rounding
             const float lim = 0.5f - (off * inv + 0x1.1p-24f * (most * inv + (float)(qmax + 1)) + 0x1.1p-24f * most * inv);
             float x[32];
             bool clear = true;
+            // Delta_F below is W - s (q - z), one rounding, less Sigma, another one; two more for the bounds themselves
+            const float off_delta = gain * 1.1f * (DELTA ? off_rest : 0.0f), off_sigma = off_sum == 0.0f ? 0.0f : gain * 0x1.1p-23f;
+            float below[2], above[2];
 #pragma unroll
             for (int i = 0; i < 32; ++i) {
                 const float t = __builtin_fmaf(R[i], inv, z);
                 x[i] = rintf(t);                                                 // ties to even
                 clear = clear && fabsf(t - x[i]) <= lim;
                 x[i] = fminf(fmaxf(x[i], 0.0f), (float)qmax);
-                if (DELTA) d8[i >> 3][i & 7] = (_Float16)(gain * __builtin_fmaf(-s, x[i] - z, R[i]));   // Delta_F (Sec. 4.2)
+                if (DELTA) {                                                     // Delta_F (Sec. 4.2)
+                    const float d = gain * (__builtin_fmaf(-s, x[i] - z, (float)w[i >> 3][i & 7]) - Sigma[i]);
+                    const float e = __builtin_fmaf(off_sigma, fabsf(Sigma[i]), __builtin_fmaf(0x1p-22f, fabsf(d), off_delta));
+                    below[i & 1] = d - e;
+                    above[i & 1] = d + e;
+                    if (i & 1) {
+                        const half2_t l = {(half_t)below[0], (half_t)below[1]}, h = {(half_t)above[0], (half_t)above[1]};
+                        d8[i >> 3][(i & 7) - 1] = l.x;
+                        d8[i >> 3][i & 7] = l.y;
+                        const uint32_t apart = __builtin_bit_cast(uint32_t, l) ^ __builtin_bit_cast(uint32_t, h);
+                        open_delta |= (apart & 0xFFFFu ? 1u << (i - 1) : 0u) | (apart >> 16 ? 1u << i : 0u);
+                        asm volatile("" : "+v"(open_delta));                     // (one after the other: as a tree the partial masks spill)
+                    }
+                }
             }
             sure = (sure && clear) || lo != lo;                                  // (no number in the whole group: nothing more exact to be had)
             pack_codes<BITS>(x, words);
@@ -267,7 +375,8 @@ __global__ __launch_bounds__(64 * WAVES, 4) void fbq_quantize_kernel(const uint1
         // ---- rows that 32 bits leave open, in 64: two features a lane.  The products of two fp16 values have 22 significant bits, so the
         // order of the taps matters only where a sum needs more than 53 bits.
         const unsigned long long unsure = __ballot(!sure);
-        for (uint32_t open = (uint32_t)(unsure | unsure >> 16 | unsure >> 32 | unsure >> 48) & 0xFFFFu; open; open &= open - 1) {
+        const uint32_t open_rows = (uint32_t)(unsure | unsure >> 16 | unsure >> 32 | unsure >> 48) & 0xFFFFu;
+        for (uint32_t open = open_rows; open; open &= open - 1) {
             const int n = __builtin_ctz(open);
             uint16_t wi[2];
 #pragma unroll
@@ -296,7 +405,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void fbq_quantize_kernel(const uint1
                 }
             }
 #pragma unroll
-            for (int i = 0; i < 2; ++i) R[i] = half_bits_to_double(wi[i]) - R[i];
+            for (int i = 0; i < 2; ++i) R[i] = half_bits_to_double(wi[i]) - (DELTA ? R[i] * a_back : R[i]);
             double lo = fmin(R[0], R[1]), hi = fmax(R[0], R[1]);
 #pragma unroll
             for (int away = 1; away < 64; away *= 2) {
@@ -343,6 +452,54 @@ __global__ __launch_bounds__(64 * WAVES, 4) void fbq_quantize_kernel(const uint1
         if (DELTA) {
 #pragma unroll
             for (int i = 0; i < 32; ++i) turn[turn_at(32 * q + i) + 16 * wave + c] = c < rows ? __builtin_bit_cast(uint16_t, (_Float16)d8[i >> 3][i & 7]) : (uint16_t)0;
+            // ---- elements that 32 bits leave open (r = 64: two in a thousand): the wave lists them and takes 64 at a time,
+            // a lane each, or up to eight lanes that share the taps of one.  What they find goes over what was stored above (the
+            // wavefront-scope fences order the two).
+            auto in_order = []() __attribute__((always_inline)) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            };
+            uint32_t pending = c < rows && !(open_rows >> c & 1) ? open_delta : 0u;
+            int rank = __builtin_popcount(pending), total;                      // of the lane's first element in the list
+            {
+                int upto = rank;
+#pragma unroll
+                for (int away = 1; away < 64; away *= 2) {
+                    const int below_me = __shfl_up(upto, away, 64);
+                    upto += lane >= away ? below_me : 0;
+                }
+                total = __builtin_amdgcn_readlane(upto, 63);
+                rank = upto - rank;
+            }
+            uint16_t *const list = exact[wave].list;
+            for (int from = 0; from < total; from += kOpenList) {
+                in_order();
+                for (; pending && rank < from + kOpenList; pending &= pending - 1) list[rank++ - from] = (uint16_t)(c << 7 | (32 * q + __builtin_ctz(pending)));
+                in_order();
+                const int listed = min(kOpenList, total - from);
+#pragma unroll 1
+                for (int at = 0; at < listed; at += 64) {
+                    const int left = min(64, listed - at), shift = left > 32 ? 0 : (left > 16 ? 1 : (left > 8 ? 2 : 3));
+                    const int mine = lane >> shift, element = list[at + min(mine, left - 1)];
+                    const int n = element >> 7, f = element & 127;
+                    const half_t wi = __builtin_bit_cast(half_t, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(wbuf, (n * K + g * kGroup + f) * 2, 0, 0));
+                    const uint32_t of_row = (uint32_t)__shfl((int)sz, n, 64);
+                    double sum = 0.0;
+                    for (int p = lane & ((1 << shift) - 1); 8 * p < r; p += 1 << shift) {
+                        const half8_t b8 = load_half8(bbuf, (n * r + 8 * p) * 2), a = taps[f][p ^ tap_key(f)];
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) sum += (double)__builtin_fmaf((float)a[j], (float)b8[j], 0.0f);
+                    }
+                    for (int away = 1; away < 1 << shift; away *= 2) sum += __shfl_xor(sum, away, 64);
+                    const double sd = half_bits_to_double((uint16_t)of_row), zd = half_bits_to_double((uint16_t)(of_row >> 16)), R = (double)wi - sum * a_back;
+                    const _Float16 d = (_Float16)(float)((double)gain * (R - sd * (fmin(fmax(rint(R / sd + zd), 0.0), (double)qmax) - zd)));
+                    if ((lane & ((1 << shift) - 1)) == 0 && mine < left) {
+                        D16[(size_t)(n0 + n) * K + g * kGroup + f] = __builtin_bit_cast(uint16_t, d);
+                        turn[turn_at(f) + 16 * wave + n] = __builtin_bit_cast(uint16_t, d);
+                    }
+                }
+            }
             __syncthreads();
             int tid = threadIdx.x;                                              // (not known to be the same in every tile: addresses kept over the loop spill)
             asm volatile("" : "+v"(tid));

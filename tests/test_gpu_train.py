@@ -199,3 +199,31 @@ def test_delta_in_both_orientations_at_the_quantizers_block_shapes(bits, N, K, r
     want_A, want_B = -2 * (B.T.contiguous() @ P), -2 * (P @ A.T.contiguous())
     for got, want in ((st.grad_At, want_A), (st.grad_Bt, want_B)):
         assert float((got.double() - want).norm() / want.norm()) < 2e-3
+
+
+@pytest.mark.parametrize("bits,N,r,near", [(4, 4, 256, False), (3, 4, 72, True), (4, 3, 8, True), (3, 5, 136, False), (4, 4, 64, True)])
+def test_delta_is_the_fp16_number_of_64_bits(bits, N, r, near):
+    """With an H of one diagonal entry the loss is the sum over the rows of one feature's Delta_F squared, and so shows fp16(256 Delta_F).  The next
+    fp16 number in one of the rows moves the sum by 2^-10 of that row's square; the sum of N fp32 products is within N 2^-23 of itself, and
+    H's 2^-10 is exact.  Also with weights near the branch's product, where Delta_F is small beside what the 32-bit sums add up."""
+    K, gain, scale = 128, 256.0, 2.0**-10
+    g = torch.Generator(device="cuda")
+    g.manual_seed(10 * r + N)
+    rand = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    At, Bt = rand(r, K) * 0.1, rand(N, r) * 0.1
+    A, B = At.half().double(), Bt.half().double()
+    W = ((B @ A).float() + 0.02 * rand(N, K)).half() if near else (rand(N, K) * 0.1).half()
+    d = fbq.Desc(N, K, r, bits)
+    st = fbq.train_state(d, At.clone(), Bt.clone())
+    losses = []
+    for k in range(K):
+        H16 = torch.zeros(K, K, dtype=torch.float16, device="cuda")
+        H16[k, k] = 1.0
+        fbq.train_step(st, W, H16, scale, 0.0, want_loss=True)
+        losses.append(st.loss.clone())
+    losses = torch.cat(losses).double() * scale
+    s, z = (t.view(torch.float16).double() for t in (st.layer.scales, st.layer.zeros))
+    delta = (W.double() - B @ A) - s * (fbq.unpack_codes(st.layer).double() - z)
+    want = ((delta * gain).float().half().double() / gain).square().sum(0)
+    miss = (losses - want).abs() / want
+    assert float(miss.max()) <= N * 2.0**-23, (float(miss.max()), int((miss > N * 2.0**-23).sum()))
