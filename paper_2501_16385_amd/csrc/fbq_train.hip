@@ -21,11 +21,11 @@
 // quantity that needs a contraction over N and K x K, and as tr(Delta_F H Delta_F^T) = sum (Delta_F^T Delta_F) o H that is a
 // symmetric one, half the work of Delta_F H.
 //
-// Two matrix-core kernels (v_mfma_f32_32x32x16_f16, fp16 in, fp32 accumulate, operands contiguous along the contraction):
-// fbq_gemm_nt_kernel for the products with r rows or columns, fbq_syrk_kernel for A A^T.  Both pass their operands through LDS
-// by buffer_load ... lds, several steps of 64 ahead; rows (128 bytes a step, whole cache lines) are stored with their 16-byte
-// pieces XOR-swizzled so that reads have no bank conflict; rows past the end of an operand are fetched through a bounds-checked
-// buffer descriptor and arrive as zeros.  fp16 operands carry Delta_F times 256 and H times the caller's h_scale, so
+// Two matrix-core kernels (v_mfma_f32_32x32x16_f16, fp16 in, fp32 accumulate): fbq_gemm_nt_kernel for the products with r rows or
+// columns, operands contiguous along the contraction, and fbq_syrk_kernel for A^T A, whose operand lies as it is and is turned by the
+// reads from LDS (ds_read_b64_tr_b16).  Both pass their operands through LDS by buffer_load ... lds, several steps of 64 ahead; rows (whole
+// cache lines) are stored with their 16-byte pieces XOR-swizzled so that reads have no bank conflict; rows past the end of an
+// operand are fetched through a bounds-checked buffer descriptor and arrive as zeros.  fp16 operands carry Delta_F times 256 and H times the caller's h_scale, so
 // that neither leaves the normal range; the factors come out again in the epilogues.
 #include <hip/hip_fp16.h>
 
@@ -44,6 +44,28 @@ typedef float float16_t __attribute__((ext_vector_type(16)));
 constexpr int kStepK = 64;           // k per step: one 128-byte row segment per operand row
 constexpr float kDeltaGain = 256.0f; // Delta_F is stored as fp16(256 Delta_F)
 constexpr int kXcds = 8;
+
+// An operand whose rows run along the contraction, [k][column], in LDS: rows of PIECES 16-byte pieces, piece p of row k at p ^ turned_key.
+// Lane 16 b + i of a transposed read asks for 8 bytes of row i / 4 and gets column i of its sixteen lanes' 4 x 16 block: two reads are the eight k of
+// a matrix operand's lane.  The key puts the four rows of a block, 32 bytes each for 16 lanes and 64 for 32, on different banks,
+// whether the LDS serves 128 or 256 bytes per clock.
+__device__ __forceinline__ constexpr int turned_key(int k, int pieces) { return pieces == 16 ? (4 * (k & 3)) ^ (k & 2) : 2 * (k & 3); }
+// Of this lane's 8 bytes of the operand's first eight rows (lanes 32 and up: the second eight), columns 8 first_piece and up
+template <int PIECES>
+__device__ __forceinline__ int turned_offset(int lane, int first_piece)
+{
+    const int k = (lane & 15) >> 2, piece = first_piece + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+    return (8 * (lane >> 5) + k) * (PIECES * 16) + ((piece ^ turned_key(k, PIECES)) << 4) + 8 * (lane & 1);
+}
+template <int PIECES>
+__device__ __forceinline__ half8_t read_turned(const unsigned char *at)
+{
+    typedef __fp16 four_t __attribute__((vector_size(8)));
+    typedef __attribute__((address_space(3))) four_t lds_four_t;
+    const half4_t lo = __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_four_t *)(__attribute__((address_space(3))) const void *)at));
+    const half4_t hi = __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_four_t *)(__attribute__((address_space(3))) const void *)(at + 4 * PIECES * 16)));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
 
 struct GemmArgs {
     const uint16_t *A;   // [Mr][lda] fp16
@@ -302,38 +324,11 @@ static GemmArgs gemm_args(const uint16_t *A, int Mr, int lda, const uint16_t *B,
     return g;
 }
 
-// dst [C][ldd] = transpose of src [R][C] (fp16), columns R..ldd-1 of dst zero; C a multiple of 8, ldd of 64.  Tile 64 x 64:
-// whole 128-byte row pieces in and out, 16 bytes per lane (2048 x 4096: two bytes per lane took 13 us, this takes 7).
-__global__ __launch_bounds__(256) void fbq_transpose_f16_kernel(const uint16_t *__restrict__ src, uint16_t *__restrict__ dst,
-                                                                int R, int C, int ldd)
-{
-    __shared__ uint32_t t[64][33];                      // rows 132 bytes apart: the eight row groups of a column fall on different banks
-    const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int piece = i * 256 + threadIdx.x, r = piece >> 3, c = (piece & 7) * 8;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (r0 + r < R && c0 + c < C) v = *reinterpret_cast<const uint4 *>(src + (size_t)(r0 + r) * C + c0 + c);
-        t[r][c / 2] = v.x; t[r][c / 2 + 1] = v.y; t[r][c / 2 + 2] = v.z; t[r][c / 2 + 3] = v.w;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int piece = i * 256 + threadIdx.x, c = piece >> 3, r = (piece & 7) * 8;
-        if (c0 + c >= C) continue;
-        uint32_t w[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            w[e] = __builtin_amdgcn_perm(t[r + 2 * e + 1][c / 2], t[r + 2 * e][c / 2], (c & 1) ? 0x07060302u : 0x05040100u);
-        *reinterpret_cast<uint4 *>(dst + (size_t)(c0 + c) * ldd + r0 + r) = make_uint4(w[0], w[1], w[2], w[3]);
-    }
-}
-
 // ------------------------------------------------------------------ symmetric products
 
-// G = A A^T of one operand A [R][Kd]: the lower triangle of tiles of 192 x 192 is computed, half the work of the square.
-//   DOT false: C = fp16(beta G), both triangles (H = X^T X with A = X^T)
-//   DOT true:  dot[unit] = the tile's share of sum G o H (the loss with A = Delta_F^T: tr(Delta H Delta^T) = sum
+// G = A^T A of one operand A [Kd][R]: the lower triangle of tiles of 192 x 192 is computed, half the work of the square.
+//   DOT false: C = fp16(beta G), both triangles (H = X^T X with A = X)
+//   DOT true:  dot[unit] = the tile's share of sum G o H (the loss with A = Delta_F: tr(Delta H Delta^T) = sum
 //              (Delta^T Delta) o H; a tile below the diagonal stands for its mirror image as well and meets H + H^T)
 // Four waves of 96 x 96 (3 x 3 of v_mfma_f32_32x32x16_f16), one per SIMD; k advances in steps of 64, three steps in LDS
 // (48 KiB each), copied there without passing registers and waited for by count as in the prefill kernel.  The copies of
@@ -343,15 +338,17 @@ __global__ __launch_bounds__(256) void fbq_transpose_f16_kernel(const uint16_t *
 // G), through fp32 partial tiles and a summing launch otherwise.
 // Bound: matrix cores; 4096 x 4096 in us, the whole square in 128-row tiles staged through registers / this: H over 2048 tokens
 // 103 / 41, the loss over 4096 rows 196 / 71 (both 34 and 69 GFLOP of the triangle: 0.84 and 0.97 PFLOP/s).
-// Other sizes leave the last round emptier and keep the gain; H with the transpose, the square / this: 3072 features, 4096 tokens
+// H used to be taken from a transposed copy of X, 7 us more at this size (46.4 / 40.6 for all of H, 128 features over some tokens 18.0 / 15.6); the
+// turned reads are twice as many instructions for the same bytes and cost nothing beside the matrix instructions.
+// Other sizes leave the last round emptier and keep the gain; H with that transpose, the square / this: 3072 features, 4096 tokens
 // 152 / 66 (136 tiles); 5120, 2048 185 / 81 (378); 8192, 512 168 / 80 (946); 11008, 4096 1362 / 493 (1711).
 constexpr int kSyTile = 192, kSyWave = 96, kSyStages = 3;
 constexpr int kSySide = kSyTile * 128, kSyStep = 2 * kSySide;       // LDS bytes of one operand's rows and of a step
 constexpr int kSyBand = 6;                                          // tiles are numbered in bands of six tile rows
 
 struct SyrkArgs {
-    const uint16_t *A;
-    int R, ld, Kd;                       // Kd a multiple of 64, ld elements
+    const uint16_t *A;                   // [Kd][R], R a multiple of 8
+    int R, Kd;
     int side, tiles, splits;             // tiles per side, tiles of the lower triangle, blocks that share a tile's contraction
     uint16_t *C; int ldc; float beta;
     float *part;                         // splits > 1 and not DOT: [splits][tiles][192][192]
@@ -400,18 +397,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int wm = wave >> 1, wn = wave & 1;
     const int col = lane & 31, h = lane >> 5;
 
-    // waves 0 and 1 copy the rows of the tile's row side, 96 each, waves 2 and 3 those of its column side: eight rows per copy
+    // Waves 0 and 1 copy the tile's row side, 64 rows of A by 192 columns a step, 32 rows each, waves 2 and 3 its column side.  A copy moves 64
+    // pieces of 24 a row, as they lie in LDS: three copies are eight rows.  A descriptor ends with the step's last row (rows past A's: zeros);
+    // columns past A's aim nowhere.
     const int side0 = wm ? n0 : m0;
-    const __amdgpu_buffer_rsrc_t buf = buffer_of(g.A + (size_t)side0 * g.ld, (long)min(kSyTile, g.R - side0) * g.ld * 2);
-    const int lrow = lane >> 3;
-    const int loff[2] = {lrow * g.ld * 2 + ((lane & 7) ^ piece_key(lrow)) * 16, lrow * g.ld * 2 + ((lane & 7) ^ piece_key(8 + lrow)) * 16};
+    int loff[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        const int row = (b * 64 + lane) / 24, column = (((b * 64 + lane) % 24) ^ turned_key(row, 24)) * 8;
+        loff[b] = side0 + column < g.R ? (row * g.R + column) * 2 : 0x40000000;
+    }
     const uint32_t lds0 = lds_offset(lds);
-    const int all_steps = g.Kd / 64, per_split = (all_steps + g.splits - 1) / g.splits;
+    const int all_steps = (g.Kd + 63) / 64, per_split = (all_steps + g.splits - 1) / g.splits;
     const int first = split * per_split, steps = max(0, min(all_steps, first + per_split) - first);
     constexpr int kCopies = kSyWave / 8;                // per wave and step
-    auto issue = [&](int st, int stage, int j) __attribute__((always_inline)) {   // (past the end: the last step again, never used)
-        const int row = wn * kSyWave + 8 * j;
-        copy16_to_lds(buf, loff[j & 1], row * g.ld * 2 + min(first + st, all_steps - 1) * 128, lds0 + stage * kSyStep + wm * kSySide + row * 128);
+    auto rows_of = [&](int st) __attribute__((always_inline)) {               // (past the end: the last step again, never used)
+        const int k0 = __builtin_amdgcn_readfirstlane(min(first + st, all_steps - 1) * 64);
+        return buffer_of(g.A + (size_t)k0 * g.R + side0, __builtin_amdgcn_readfirstlane((min(64, g.Kd - k0) * g.R - side0) * 2));
+    };
+    auto issue = [&](const __amdgpu_buffer_rsrc_t &buf, int stage, int j) __attribute__((always_inline)) {
+        copy16_to_lds(buf, loff[j % 3], (wn * 32 + j / 3 * 8) * g.R * 2, lds0 + stage * kSyStep + wm * kSySide + (wn * kCopies + j) * 1024);
     };
     auto wait_and_meet = [&](auto N) __attribute__((always_inline)) {
         constexpr int n = decltype(N)::value;
@@ -426,24 +431,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-    // fragment of K step i: pieces 2 i + h of its rows
-    const int key = (h ^ piece_key(col & 15)) << 4;
-    const int a_lane = (wm * kSyWave + col) * 128 + key, b_lane = kSySide + (wn * kSyWave + col) * 128 + key;
-    auto frag = [&](int stage, int lane_off, int i, int t) __attribute__((always_inline)) {
-        return *reinterpret_cast<const half8_t *>(lds + stage * kSyStep + (lane_off ^ (i << 5)) + t * (32 * 128));
+    // fragment of K step i: rows 16 i + 8 h and up of A, 32 columns
+    int a_lane[3], b_lane[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        a_lane[t] = turned_offset<24>(lane, wm * (kSyWave / 8) + 4 * t);
+        b_lane[t] = kSySide + turned_offset<24>(lane, wn * (kSyWave / 8) + 4 * t);
+    }
+    auto frag = [&](int stage, const int (&lane_off)[3], int i, int t) __attribute__((always_inline)) {
+        return read_turned<24>(lds + stage * kSyStep + lane_off[t] + i * (16 * 24 * 16));
     };
     half8_t af[2][3], bf[2][3];
     auto do_step = [&](int st, int s0, int s1, int s2) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int cur = i & 1, nxt = cur ^ 1;
+            const __amdgpu_buffer_rsrc_t buf = rows_of(i == 3 ? st + 3 : st + 2);
             __builtin_amdgcn_sched_barrier(0);
             // the next step has landed, and everybody has read all of this one: its stage may be filled again
             if (i == 3) wait_and_meet(std::integral_constant<int, kCopies>{});
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
-                if (i == 3) issue(st + 3, s0, t);
-                else issue(st + 2, s2, 3 + 3 * i + t);
+                if (i == 3) issue(buf, s0, t);
+                else issue(buf, s2, 3 + 3 * i + t);
                 af[nxt][t] = i < 3 ? frag(s0, a_lane, i + 1, t) : frag(s1, a_lane, 0, t);
                 bf[nxt][t] = i < 3 ? frag(s0, b_lane, i + 1, t) : frag(s1, b_lane, 0, t);
 #pragma unroll
@@ -455,9 +465,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int j = 0; j < kCopies; ++j) issue(s, s, j);
+        for (int j = 0; j < kCopies; ++j) issue(rows_of(s), s, j);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) issue(2, 2, j);
+    for (int j = 0; j < 3; ++j) issue(rows_of(2), 2, j);
     wait_and_meet(std::integral_constant<int, kCopies + 3>{});
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
@@ -619,7 +629,7 @@ __global__ __launch_bounds__(256) void fbq_syrk_sum_kernel(const SyrkArgs g)
 struct SyrkShape { int side, tiles, splits; };
 static SyrkShape syrk_shape(int R, int Kd, bool dot)
 {
-    const int side = ceil_div(R, kSyTile), tiles = side * (side + 1) / 2, steps = Kd / 64;
+    const int side = ceil_div(R, kSyTile), tiles = side * (side + 1) / 2, steps = ceil_div(Kd, 64);
     SyrkShape best{side, tiles, 1};
     double best_cost = 1e300;
     for (int s = 1; s <= 64 && s <= steps && (s == 1 || tiles * s <= 768); ++s) {
@@ -705,13 +715,16 @@ size_t train_workspace_bytes(int N, int K, int r, int T)
 
 hipError_t launch_gram(int K, int T, const uint16_t *X, float h_scale, uint16_t *H16, void *workspace, hipStream_t stream)
 {
-    const int Tp = pad64(T);
-    uint16_t *Xt = (uint16_t *)workspace;                       // [K][Tp], tokens past T zero
-    float *scratch = (float *)((unsigned char *)workspace + pad256((size_t)K * Tp * 2));
-    hipLaunchKernelGGL(fbq_transpose_f16_kernel, dim3(ceil_div(K, 64), Tp / 64), dim3(256), 0, stream, X, Xt, T, K, Tp);
+    // (a result over the activations themselves: from a copy of them)
+    const size_t x_bytes = (size_t)T * K * 2;
+    if ((uintptr_t)X < (uintptr_t)H16 + (size_t)K * K * 2 && (uintptr_t)H16 < (uintptr_t)X + x_bytes) {
+        const hipError_t e = hipMemcpyAsync(workspace, X, x_bytes, hipMemcpyDeviceToDevice, stream);
+        if (e != hipSuccess) return e;
+        X = (const uint16_t *)workspace;
+    }
     SyrkArgs g{};
-    g.A = Xt; g.R = K; g.ld = Tp; g.Kd = Tp;
-    g.C = H16; g.ldc = K; g.beta = h_scale; g.part = scratch;
+    g.A = X; g.R = K; g.Kd = T;
+    g.C = H16; g.ldc = K; g.beta = h_scale; g.part = (float *)((unsigned char *)workspace + pad256((size_t)K * pad64(T) * 2));
     return launch_syrk<false>(g, stream);
 }
 
@@ -752,7 +765,7 @@ hipError_t launch_train_step(const TrainArgs &a, hipStream_t stream)
     LastArgs last{};
     if (a.loss) {
         SyrkArgs g{};
-        g.A = Dt16; g.R = K; g.ld = Np; g.Kd = Np;
+        g.A = D16; g.R = K; g.Kd = N;
         g.H = a.H16; g.dot = dot;
         if ((e = launch_syrk<true>(g, stream)) != hipSuccess) return e;
         last.loss = {dot, (int)syrk_units(syrk_shape(K, Np, true)), 1.0f / (kDeltaGain * kDeltaGain * a.h_scale), a.loss};

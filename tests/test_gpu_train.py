@@ -8,6 +8,8 @@ fp16 (2^-11 relative each, independent) and are accumulated in fp32: every gradi
 thousands of such products, so the relative L2 error of a gradient is a few 1e-4; the bar is 2e-3 for
 the gradients and the updated masters' movement, 1e-3 for the loss.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -227,3 +229,20 @@ def test_delta_is_the_fp16_number_of_64_bits(bits, N, r, near):
     want = ((delta * gain).float().half().double() / gain).square().sum(0)
     miss = (losses - want).abs() / want
     assert float(miss.max()) <= N * 2.0**-23, (float(miss.max()), int((miss > N * 2.0**-23).sum()))
+
+
+@pytest.mark.parametrize("K,T", [(128, 1), (256, 63), (1408, 65), (384, 1000), (4224, 129)])
+def test_gram_of_turned_reads_is_exact_on_whole_numbers(K, T):
+    """Small whole numbers: every sum is exact, so H is, whatever the order.  Tiles past the last feature, steps past the last token, contractions split
+    over blocks; and H written over the activations themselves."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K + T)
+    X = torch.randint(-3, 4, (T, K), device="cuda", generator=g).half()
+    want = (X.double().T.contiguous() @ X.double() / 16).half()
+    d = fbq.Desc(128, K, 8, 4)
+    assert torch.equal(fbq.gram(d, X, 1.0 / 16), want)
+    both = torch.full((max(T, K) * K,), float("nan"), dtype=torch.float16, device="cuda")
+    both[: T * K] = X.flatten()
+    ws = torch.empty(fbq.train_workspace_bytes(d, T), dtype=torch.uint8, device="cuda")
+    rc = fbq.load().fbq_gram(ctypes.byref(d.c()), T, both.data_ptr(), 1.0 / 16, both.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert rc == 0 and torch.equal(both[: K * K].view(K, K), want)
