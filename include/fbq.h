@@ -278,7 +278,7 @@ fbq_status fbq_measure_read_stream(const void *buf, size_t bytes, fbq_stream str
  * is formed once per layer and every iteration works from it.
  *
  * fbq_train_workspace_bytes - device scratch for fbq_gram (T tokens) and fbq_train_step: a copy
- *   of X (used where H16_out lies over X) and partial sums, or fp16 copies of the branch, Delta_F in both orientations, the r-row products
+ *   of X (used where H16_out lies over X) and partial sums, or fp16 copies of the branch, Delta_F, the r-row products
  *   and the partial sums of contractions whose K range is split over blocks (about 4 N K bytes).
  *   0 for an invalid descriptor, r < 1 or T < 1.
  *

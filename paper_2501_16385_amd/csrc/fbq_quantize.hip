@@ -16,8 +16,12 @@
 // a large copy, about 15 getting At into LDS and out of it (without a sub-branch 30), 4 the rows in fp64.
 //
 // With DELTA the kernel also writes what the reconstruction step needs from the same registers: Delta_F = (W - Sigma) - s (q - z), times
-// `gain`, as fp16 in both orientations (D16 [N][K]; Dt16 [K][ldt] with columns N..ldt-1 zero, ldt a multiple of 64), the transposed copy
-// through LDS as whole row pieces.  It is the fp16 number that fp64 gives: where the bound leaves two open, that element is done again.
+// `gain`, as fp16 (D16 [N][K]).  It is the fp16 number that fp64 gives: where the bound leaves two open, that element is done again.  Sigma is
+// had more exactly for that (below); with the bound of the fp16 products as they are, eight elements in a hundred were open and a step took 233 us,
+// now four in a thousand at the start and some two in a hundred after thousands of steps.
+// A step with loss, us, fp64 throughout (Delta_F written in both orientations) / now: 4096 x 4096 INT4, r = 64, 182 / 173, without loss 108 / 99.5;
+// 4096 x 11008, r = 64, without loss 298 / 243; 11008 x 4096, r = 200, 719 / 638; 1000 x 1024, r = 64, 48.8 / 50.0 (one tile a wave: the chain of
+// a wave's instructions bounds it).  What bounds the kernel (47 of the 173): vector instructions, about 2300 a tile of 16 rows.
 #include <hip/hip_fp16.h>
 
 #include "fbq_internal.h"
@@ -117,37 +121,38 @@ __device__ __forceinline__ void row_extremes(float &lo, float &hi)
     hi = fmaxf(f(b[0]), f(b[1]));
 }
 
-// The power of two that takes numbers whose largest is `peak` (an fp32 number's bits) to 2^10 and above, below 2^11; 1 where that would be a step down.
-__device__ __forceinline__ float fixed_point_factor(uint32_t peak)
+// The power of two that takes numbers whose largest is `peak` to 2^10 and above, below 2^11; 1 where that would be a step down.
+__device__ __forceinline__ float fixed_point_factor(float peak)
 {
-    const int exponent = (int)(peak >> 23) - 127;
-    return peak == 0 || exponent > 10 ? 1.0f : __builtin_bit_cast(float, (uint32_t)(127 + 10 - exponent) << 23);
+    const int exponent = (int)(__builtin_bit_cast(uint32_t, peak) >> 23) - 127;
+    return peak == 0.0f || exponent > 10 ? 1.0f : __builtin_bit_cast(float, (uint32_t)(127 + 10 - exponent) << 23);
 }
 
 constexpr int kQuantTapStep = 32;      // taps one matrix instruction takes
-constexpr int kOpenList = 256;         // elements of Delta_F that a wave lists at a time
+constexpr float kLongest = 16300.0f;   // of 128 taps or a row of as many, at 2^10 and above: what the exact sums (below) have room for; evenly spread ones are 13400 long
+constexpr int kOpenList = 128;         // pairs of elements of Delta_F that a wave lists at a time
 
 // Taps in LDS: 16-byte pieces of eight taps, [feature][piece], a piece's place XORed with a key so that the sixteen features that
 // one matrix operand reads (bits 0, 1, 5, 6 of the feature differ) lie in sixteen different places of 256 bytes.
 __device__ __forceinline__ int tap_key(int f) { return ((f >> 1) & 1) | ((f >> 4) & 6); }
 
 // STEPS: the most steps of 32 taps.  WAVES: a block's.
-// With DELTA 128 registers spill 22 (4096 x 4096, r = 64, a step with loss 176.6 us; 173.0 with three waves a SIMD instead of four).
+// DELTA: three waves a SIMD (with four, 128 registers spilled 22: a step with loss 2 % longer).
 template <int BITS, bool DELTA, int STEPS, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void fbq_quantize_kernel(const uint16_t *__restrict__ W, const uint16_t *__restrict__ At,
+__global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 3) : 4) void fbq_quantize_kernel(const uint16_t *__restrict__ W, const uint16_t *__restrict__ At,
                                                                   const uint16_t *__restrict__ Bt, uint32_t *__restrict__ qw,
                                                                   uint16_t *__restrict__ scales, uint16_t *__restrict__ zeros, int N,
                                                                   int K, int r, int row_words, uint16_t *__restrict__ D16,
-                                                                  uint16_t *__restrict__ Dt16, int ldt, float gain, int tiles)
+                                                                  float gain, int tiles)
 {
 #pragma clang fp contract(off)
     constexpr int kRows = 16 * WAVES, kPieces = 4 * STEPS;
-    __shared__ half8_t taps[kGroup][kPieces];
-    __shared__ uint32_t longest, highest;                                       // largest squared norm of a feature's taps; DELTA: largest tap
-    // Delta_F by column: [feature][row], features 2 kRows + 16 bytes apart and 32 more for every 32 of them (the lanes of a quarter wave write 32 of these bytes)
-    constexpr int kTurnStride = kRows + 8;
-    __shared__ uint16_t turn[DELTA ? kGroup * kTurnStride + 64 : 8];
-    auto turn_at = [](int f) { return f * kTurnStride + (f >> 5) * 16; };
+    // DELTA, up to 64 taps: taps[] holds their multiples of a unit and rests[] the rest (below); otherwise each wave splits what it reads
+    constexpr bool kSplitTaps = DELTA && STEPS <= 2;
+    __shared__ half8_t taps[kGroup][kPieces], rests[kSplitTaps ? kGroup : 1][kSplitTaps ? kPieces : 1];
+    __shared__ uint32_t longest, too_high;                                      // largest squared norm of a feature's taps; DELTA: whether a tap is 2048 or more
+    // DELTA, by feature: what takes its taps back to At's, and its bound (below)
+    __shared__ __attribute__((aligned(16))) float tap_back[DELTA ? kGroup : 4], tap_norm[DELTA ? kGroup : 4];
     __shared__ struct { float code[kGroup]; alignas(16) _Float16 delta[DELTA ? kGroup : 8]; uint16_t list[DELTA ? kOpenList : 8]; } exact[WAVES];
     constexpr int qmax = (1 << BITS) - 1;
     constexpr int kNowhere = 0x7FFFFFF0;                                        // beyond every buffer: taps past r are zeros in both operands
@@ -155,8 +160,13 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
     const int G = K / kGroup, g = blockIdx.x;
     const int steps = (r + kQuantTapStep - 1) / kQuantTapStep;
 
-    if (threadIdx.x == 0) longest = highest = 0;
-    float a_factor = 1.0f;                                                      // DELTA: the taps in LDS are At's times this power of two
+    if (threadIdx.x == 0) longest = too_high = 0;
+    const half_t grid = STEPS <= 4 ? (half_t)6144.0f : (half_t)12288.0f;        // 1.5 x 2^10 units: added and taken away, it leaves whole units
+    const half8_t grid8 = {grid, grid, grid, grid, grid, grid, grid, grid};
+    auto tap8 = [&](int f, int p) __attribute__((always_inline)) {
+        if constexpr (kSplitTaps) return taps[f][p ^ tap_key(f)] + rests[f][p ^ tap_key(f)];   // (exact)
+        else return taps[f][p ^ tap_key(f)];
+    };
     if (r > 0) {
         // eight features of eight taps a thread, turned in registers
         const __amdgpu_buffer_rsrc_t abuf = bounded_buffer(At, (long)r * K * 2);
@@ -175,8 +185,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
         // WAVES / 2 threads a feature, side by side
         constexpr int kSide = WAVES / 2;
         const int f = threadIdx.x / kSide;
-        float even = 0.0f, odd = 0.0f;
-        uint32_t peak = 0;
+        float even = 0.0f, odd = 0.0f, peak = 0.0f;
         for (int p = threadIdx.x % kSide; p < 4 * steps; p += kSide) {
             const half8_t a = taps[f][p ^ tap_key(f)];
 #pragma unroll
@@ -186,32 +195,40 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
             }
             if (DELTA) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) peak = max(peak, __builtin_bit_cast(uint32_t, fabsf((float)a[j])));   // (a NaN is the largest)
+                for (int j = 0; j < 8; ++j) peak = fmaxf(peak, fabsf((float)a[j]));
             }
         }
         even += odd;
 #pragma unroll
-        for (int away = 1; away < kSide; away *= 2) even += __shfl_xor(even, away, 64);
+        for (int away = 1; away < kSide; away *= 2) {
+            even += __shfl_xor(even, away, 64);
+            if (DELTA) peak = fmaxf(peak, __shfl_xor(peak, away, 64));
+        }
+        if (DELTA) {                                                            // (each thread has the pieces that it read)
+            const float factor = fixed_point_factor(peak);
+            for (int p = threadIdx.x % kSide; p < 4 * steps; p += kSide) {
+                half8_t a = taps[f][p ^ tap_key(f)];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) a[j] = (half_t)((float)a[j] * factor);
+                const half8_t whole = kSplitTaps ? (a + grid8) - grid8 : a;
+                taps[f][p ^ tap_key(f)] = whole;
+                if constexpr (kSplitTaps) rests[f][p ^ tap_key(f)] = a - whole;
+            }
+            const float back = peak == 0.0f ? 0.0f : 1.0f / factor;
+            even = peak == 0.0f ? even : fmaxf(sqrtf(even), 2048.0f * back);    // (at least the largest tap)
+            if (threadIdx.x % kSide == 0) {
+                tap_back[f] = back;
+                tap_norm[f] = even;
+                if (peak >= 2048.0f || (STEPS == 4 && even > kLongest * back)) too_high = 1;
+            }
+        }
         uint32_t most = __builtin_bit_cast(uint32_t, even);                    // (not negative; a NaN is larger than all numbers this way)
 #pragma unroll
         for (int away = kSide; away < 64; away *= 2) most = max(most, (uint32_t)__shfl_xor((int)most, away, 64));
         if (lane == 0 && most) atomicMax(&longest, most);
-        if (DELTA) {
-#pragma unroll
-            for (int away = 1; away < 64; away *= 2) peak = max(peak, (uint32_t)__shfl_xor((int)peak, away, 64));
-            if (lane == 0 && peak) atomicMax(&highest, peak);
-            __syncthreads();
-            a_factor = fixed_point_factor(highest);
-            for (int p = threadIdx.x % kSide; p < 4 * steps; p += kSide) {
-                half8_t &a = taps[f][p ^ tap_key(f)];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) a[j] = (half_t)((float)a[j] * a_factor);
-            }
-        }
     }
     __syncthreads();
     // (the instruction aligns a subnormal operand as one of 2^-14)
-    const double a_back = 1.0 / (double)a_factor;
     const float a_norm2 = longest ? __builtin_bit_cast(float, longest) + (float)r * 0x1p-28f : 0.0f;
 
     for (int tile = 0; tile < tiles; ++tile) {
@@ -234,13 +251,13 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
         // ---- 32 bits, with a bound
         uint32_t words[BITS], sz;
         half8_t d8[4];
-        uint32_t open_delta = 0;                                                // DELTA: features whose fp16 number 32 bits leave open
+        uint32_t open_delta = 0;                                                // DELTA: pairs of features with an fp16 number that 32 bits leave open, the first pair in bit 15
         bool sure;
         {
-            float Sigma[32];
+            float Sigma[32];                                                     // DELTA: times gain, a power of two
 #pragma unroll
             for (int i = 0; i < 32; ++i) Sigma[i] = 0.0f;
-            float b_norm2 = 0.0f, off_sum, off_rest = 0.0f;                      // off_rest: of off_sum, what is not in proportion to Sigma
+            float b_norm2 = 0.0f, off_sum, off_rest = 0.0f;                      // off_rest: DELTA, without a rounding of Sigma, for a feature of tap_norm 1
             bool coarse = false;
             if constexpr (!DELTA) {
 #pragma unroll 1
@@ -268,8 +285,8 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
                 off_sum = (float)(42 + steps) * 0x1.04p-24f * sqrtf(a_norm2 * b_norm2);
             } else {
                 // Delta_F is small beside what adds up to it, so Sigma is had more exactly: taps and rows of B, at 2^10 and above, are each a multiple of
-                // `unit` (at most 2^9 or 2^8 units) and a rest of half a unit.  Products of the multiples are whole numbers of unit^2 whose sums stay within
-                // 2^24 (|a| |b| <= r 2^18 or r 2^16): exact.  The rests' products are a hundredth of the whole, and so is their error.
+                // `unit` (at most 2^9 units, 2^8 above rank 128) and a rest of half a unit.  Products of the multiples are whole numbers of unit^2 whose sums stay within
+                // 2^24 (|a| |b| <= r 2^18 or r 2^16, and between rank 64 and 128 it is checked): exact.  The rests' products are a hundredth of the whole, and so is their error.
                 float peak = 0.0f;
 #pragma unroll 1
                 for (int s = 0; s < steps; ++s) {
@@ -284,10 +301,8 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
                 b_norm2 += __shfl_xor(b_norm2, 32, 64);
                 peak = fmaxf(peak, __shfl_xor(peak, 16, 64));
                 peak = fmaxf(peak, __shfl_xor(peak, 32, 64));
-                const float b_factor = fixed_point_factor(__builtin_bit_cast(uint32_t, peak));
-                coarse = peak >= 2048.0f || highest >= 0x45000000u;              // (2048: numbers that are not stepped down; their rows go to 64 bits)
-                const half_t grid = STEPS <= 2 ? (half_t)6144.0f : (half_t)12288.0f;   // 1.5 x 2^10 units
-                const half8_t grid8 = {grid, grid, grid, grid, grid, grid, grid, grid};
+                const float b_factor = fixed_point_factor(peak);
+                coarse = peak >= 2048.0f || too_high || (STEPS == 4 && b_norm2 * b_factor * b_factor > kLongest * kLongest);   // (to 64 bits)
                 float rest[32];
 #pragma unroll
                 for (int i = 0; i < 32; ++i) rest[i] = 0.0f;
@@ -300,30 +315,40 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
 #pragma unroll
                     for (int t = 0; t < 8; ++t) {
                         const int f = 32 * (c >> 2) + 4 * t + (c & 3);
-                        const half8_t a8 = taps[f][(4 * s + q) ^ tap_key(f)], a_whole = (a8 + grid8) - grid8, a_rest = a8 - a_whole;
-                        const float4_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f}, had = {Sigma[4 * t], Sigma[4 * t + 1], Sigma[4 * t + 2], Sigma[4 * t + 3]};
+                        half8_t a_whole = taps[f][(4 * s + q) ^ tap_key(f)], a_rest;
+                        if constexpr (kSplitTaps) a_rest = rests[f][(4 * s + q) ^ tap_key(f)];
+                        else {
+                            const half8_t a8 = a_whole;
+                            a_whole = (a8 + grid8) - grid8;
+                            a_rest = a8 - a_whole;
+                        }
+                        const float4_t had = {Sigma[4 * t], Sigma[4 * t + 1], Sigma[4 * t + 2], Sigma[4 * t + 3]};
                         const float4_t whole = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_whole, b_whole, had, 0, 0, 0);
-                        const float4_t one = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_whole, b_rest, zero4, 0, 0, 0);
-                        const float4_t two = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_rest, b8, zero4, 0, 0, 0);
+                        const float4_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+                        const float4_t one = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_whole, b_rest, zero4, 0, 0, 0), two = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_rest, b8, zero4, 0, 0, 0);
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             Sigma[4 * t + v] = whole[v];
                             rest[4 * t + v] += one[v] + two[v];
                         }
-                        __builtin_amdgcn_sched_barrier(0);                       // (operands of all eight at once spill)
                     }
                 }
-                const float back = 1.0f / (a_factor * b_factor);
+                const float b_back = 1.0f / b_factor, up = gain * b_back;
 #pragma unroll
-                for (int i = 0; i < 32; ++i) Sigma[i] = (Sigma[i] + rest[i]) * back;
-                // The bound of the instruction (above) for the products with a rest, the additions of the rests, and the last one, rounded in fp32
-                const float a_norm = sqrtf(a_norm2) * a_factor, b_norm = sqrtf(b_norm2) * b_factor, half_units = sqrtf((float)r) * (STEPS <= 2 ? 2.0f : 4.0f);
-                off_rest = peak == 0.0f || longest == 0 ? 0.0f : 0x1.04p-24f * back * (float)(44 + 2 * steps) * half_units * (a_norm + half_units + b_norm);
-                off_sum = off_rest == 0.0f ? 0.0f : off_rest + 0x1.04p-24f * back * a_norm * b_norm;
+                for (int t = 0; t < 8; ++t) {
+                    const float4_t back = *reinterpret_cast<const float4_t *>(&tap_back[32 * q + 4 * t]);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) Sigma[4 * t + v] = (Sigma[4 * t + v] + rest[4 * t + v]) * (back[v] * up);
+                }
+                // The bound of the instruction (above) for the products with a rest, the additions of the rests, and the last one, rounded in fp32.
+                // Rests are `half` long at most, where a feature's taps, at 2^10 and above, are tap_norm / tap_back long and tap_norm / tap_back is 2^11 at least.
+                const float half = sqrtf((float)r) * (STEPS <= 4 ? 2.0f : 4.0f), b_norm = sqrtf(b_norm2);
+                off_rest = peak == 0.0f ? 0.0f : 0x1.06p-24f * (float)(44 + 2 * steps) * half * (b_back + (half * b_back + b_norm) * 0x1p-11f);
+                off_sum = (off_rest + 0x1.06p-24f * b_norm) * (longest ? __builtin_bit_cast(float, longest) : 0.0f);
             }
             float R[32];
 #pragma unroll
-            for (int i = 0; i < 32; ++i) R[i] = (float)w[i >> 3][i & 7] - Sigma[i];
+            for (int i = 0; i < 32; ++i) R[i] = DELTA ? __builtin_fmaf(Sigma[i], -1.0f / gain, (float)w[i >> 3][i & 7]) : (float)w[i >> 3][i & 7] - Sigma[i];
             float lo = R[0], hi = R[0];
 #pragma unroll
             for (int i = 1; i < 32; ++i) { lo = fminf(lo, R[i]); hi = fmaxf(hi, R[i]); }
@@ -346,25 +371,25 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
             float x[32];
             bool clear = true;
             // Delta_F below is W - s (q - z), one rounding, less Sigma, another one; two more for the bounds themselves
-            const float off_delta = gain * 1.1f * (DELTA ? off_rest : 0.0f), off_sigma = off_sum == 0.0f ? 0.0f : gain * 0x1.1p-23f;
+            const float off_delta = gain * 1.1f * off_rest;
+            float4_t norm4;
             float below[2], above[2];
 #pragma unroll
             for (int i = 0; i < 32; ++i) {
+                if (DELTA && !(i & 3)) norm4 = *reinterpret_cast<const float4_t *>(&tap_norm[32 * q + i]);
                 const float t = __builtin_fmaf(R[i], inv, z);
                 x[i] = rintf(t);                                                 // ties to even
                 clear = clear && fabsf(t - x[i]) <= lim;
                 x[i] = fminf(fmaxf(x[i], 0.0f), (float)qmax);
                 if (DELTA) {                                                     // Delta_F (Sec. 4.2)
-                    const float d = gain * (__builtin_fmaf(-s, x[i] - z, (float)w[i >> 3][i & 7]) - Sigma[i]);
-                    const float e = __builtin_fmaf(off_sigma, fabsf(Sigma[i]), __builtin_fmaf(0x1p-22f, fabsf(d), off_delta));
+                    const float d = __builtin_fmaf(gain, __builtin_fmaf(-s, x[i] - z, (float)w[i >> 3][i & 7]), -Sigma[i]), e = __builtin_fmaf(0x1p-22f, fabsf(d), __builtin_fmaf(0x1.1p-23f, fabsf(Sigma[i]), off_delta * norm4[i & 3]));
                     below[i & 1] = d - e;
                     above[i & 1] = d + e;
                     if (i & 1) {
                         const half2_t l = {(half_t)below[0], (half_t)below[1]}, h = {(half_t)above[0], (half_t)above[1]};
                         d8[i >> 3][(i & 7) - 1] = l.x;
                         d8[i >> 3][i & 7] = l.y;
-                        const uint32_t apart = __builtin_bit_cast(uint32_t, l) ^ __builtin_bit_cast(uint32_t, h);
-                        open_delta |= (apart & 0xFFFFu ? 1u << (i - 1) : 0u) | (apart >> 16 ? 1u << i : 0u);
+                        open_delta += open_delta + (__builtin_bit_cast(uint32_t, l) != __builtin_bit_cast(uint32_t, h) ? 1u : 0u);
                         asm volatile("" : "+v"(open_delta));                     // (one after the other: as a tree the partial masks spill)
                     }
                 }
@@ -386,7 +411,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
             double R[2] = {0.0, 0.0};
             half8_t next[2];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) next[i] = taps[lane + 64 * i][tap_key(lane + 64 * i)];
+            for (int i = 0; i < 2; ++i) next[i] = tap8(lane + 64 * i, 0);
 #pragma unroll 1
             for (int p = 0; 8 * p < r; ++p) {
                 half8_t a[2];
@@ -394,7 +419,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     a[i] = next[i];
-                    next[i] = taps[lane + 64 * i][after ^ tap_key(lane + 64 * i)];
+                    next[i] = tap8(lane + 64 * i, after);
                 }
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
@@ -405,7 +430,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
                 }
             }
 #pragma unroll
-            for (int i = 0; i < 2; ++i) R[i] = half_bits_to_double(wi[i]) - (DELTA ? R[i] * a_back : R[i]);
+            for (int i = 0; i < 2; ++i) R[i] = half_bits_to_double(wi[i]) - (DELTA ? R[i] * (double)tap_back[lane + 64 * i] : R[i]);
             double lo = fmin(R[0], R[1]), hi = fmax(R[0], R[1]);
 #pragma unroll
             for (int away = 1; away < 64; away *= 2) {
@@ -450,9 +475,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
             }
         }
         if (DELTA) {
-#pragma unroll
-            for (int i = 0; i < 32; ++i) turn[turn_at(32 * q + i) + 16 * wave + c] = c < rows ? __builtin_bit_cast(uint16_t, (_Float16)d8[i >> 3][i & 7]) : (uint16_t)0;
-            // ---- elements that 32 bits leave open (r = 64: two in a thousand): the wave lists them and takes 64 at a time,
+            // ---- elements that 32 bits leave open (r = 64: four in a thousand, more as the branch grows): the wave lists them, in pairs, and takes 64 at a time,
             // a lane each, or up to eight lanes that share the taps of one.  What they find goes over what was stored above (the
             // wavefront-scope fences order the two).
             auto in_order = []() __attribute__((always_inline)) {
@@ -475,60 +498,55 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 ? 2 : 3) : 4) void 
             uint16_t *const list = exact[wave].list;
             for (int from = 0; from < total; from += kOpenList) {
                 in_order();
-                for (; pending && rank < from + kOpenList; pending &= pending - 1) list[rank++ - from] = (uint16_t)(c << 7 | (32 * q + __builtin_ctz(pending)));
+                for (; pending && rank < from + kOpenList; pending &= pending - 1) list[rank++ - from] = (uint16_t)(c << 7 | (32 * q + 30 - 2 * __builtin_ctz(pending)));
                 in_order();
-                const int listed = min(kOpenList, total - from);
+                const int listed = 2 * min(kOpenList, total - from);
 #pragma unroll 1
                 for (int at = 0; at < listed; at += 64) {
                     const int left = min(64, listed - at), shift = left > 32 ? 0 : (left > 16 ? 1 : (left > 8 ? 2 : 3));
-                    const int mine = lane >> shift, element = list[at + min(mine, left - 1)];
+                    const int mine = lane >> shift, entry = at + min(mine, left - 1), element = list[entry >> 1] + (entry & 1);
                     const int n = element >> 7, f = element & 127;
                     const half_t wi = __builtin_bit_cast(half_t, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(wbuf, (n * K + g * kGroup + f) * 2, 0, 0));
                     const uint32_t of_row = (uint32_t)__shfl((int)sz, n, 64);
                     double sum = 0.0;
-                    for (int p = lane & ((1 << shift) - 1); 8 * p < r; p += 1 << shift) {
-                        const half8_t b8 = load_half8(bbuf, (n * r + 8 * p) * 2), a = taps[f][p ^ tap_key(f)];
+                    for (int p = lane & ((1 << shift) - 1); 8 * p < r; p += 4 << shift) {   // four pieces asked for at once
+                        half8_t a8[4], b8[4];
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) sum += (double)__builtin_fmaf((float)a[j], (float)b8[j], 0.0f);
+                        for (int k = 0; k < 4; ++k) {
+                            const int piece = p + (k << shift);
+                            b8[k] = load_half8(bbuf, 8 * piece < r ? (n * r + 8 * piece) * 2 : kNowhere);
+                            a8[k] = tap8(f, min(piece, 4 * steps - 1));
+                        }
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) sum += (double)__builtin_fmaf((float)a8[k][j], (float)b8[k][j], 0.0f);
                     }
                     for (int away = 1; away < 1 << shift; away *= 2) sum += __shfl_xor(sum, away, 64);
-                    const double sd = half_bits_to_double((uint16_t)of_row), zd = half_bits_to_double((uint16_t)(of_row >> 16)), R = (double)wi - sum * a_back;
+                    const double sd = half_bits_to_double((uint16_t)of_row), zd = half_bits_to_double((uint16_t)(of_row >> 16)), R = (double)wi - sum * (double)tap_back[f];
                     const _Float16 d = (_Float16)(float)((double)gain * (R - sd * (fmin(fmax(rint(R / sd + zd), 0.0), (double)qmax) - zd)));
-                    if ((lane & ((1 << shift) - 1)) == 0 && mine < left) {
-                        D16[(size_t)(n0 + n) * K + g * kGroup + f] = __builtin_bit_cast(uint16_t, d);
-                        turn[turn_at(f) + 16 * wave + n] = __builtin_bit_cast(uint16_t, d);
-                    }
+                    if ((lane & ((1 << shift) - 1)) == 0 && mine < left) D16[(size_t)(n0 + n) * K + g * kGroup + f] = __builtin_bit_cast(uint16_t, d);
                 }
             }
-            __syncthreads();
-            int tid = threadIdx.x;                                              // (not known to be the same in every tile: addresses kept over the loop spill)
-            asm volatile("" : "+v"(tid));
-            // whole rows of Dt16, kRows / 8 lanes each (ldt is a multiple of 64: a piece lies before it or behind)
-#pragma unroll
-            for (int it = 0; it < kGroup * kRows / 8 / (64 * WAVES); ++it) {
-                const int piece = it * 64 * WAVES + tid, f = piece / (kRows / 8), part = piece % (kRows / 8);
-                if (nb + 8 * part < ldt)
-                    *reinterpret_cast<uint4 *>(Dt16 + (size_t)(g * kGroup + f) * ldt + nb + 8 * part) = *reinterpret_cast<const uint4 *>(&turn[turn_at(f) + 8 * part]);
-            }
-            if (tile + 1 < tiles) __syncthreads();                              // everybody has read before the next tile's rows come
+            in_order();                                                         // (the list and the row of codes are written again)
         }
     }
 }
 
 hipError_t launch_quantize(const fbq_desc &d, const uint16_t *W, const uint16_t *At, const uint16_t *Bt, uint32_t *qw,
-                           uint16_t *scales, uint16_t *zeros, hipStream_t stream, uint16_t *D16, uint16_t *Dt16, int ldt, float gain)
+                           uint16_t *scales, uint16_t *zeros, hipStream_t stream, uint16_t *D16, float gain)
 {
     const int words = (int)row_words(d.K, d.bits), G = d.K / kGroup;
-    // Waves a block: four, so that four blocks share a CU, but eight where the taps (64 KB above rank 128) or the taps and Delta_F's turned copy
-    // leave room for two blocks at most (11008 x 4096 INT4, r = 200: 125 us with four, 96 with eight), unless those are too few to go round.
+    // Waves a block: four, so that four blocks share a CU, but eight where the taps (64 KB above rank 128) leave
+    // room for two blocks at most (11008 x 4096 INT4, r = 200: 125 us with four, 96 with eight), unless those are too few to go round.
     // Tiles a block: two, which halves the work of getting At into LDS (r = 64, INT3, 11008 x 4096: 55 us with one tile, 50 with two, 49 with three),
     // where the GPU is full with them; one without a sub-branch (30, 32, 33 us: blocks that start in the order of the rows read memory best).
-    const bool wide = (d.r > 128 || (D16 && d.r > 64)) && G * ceil_div(d.N, 128) >= 256;
+    const bool wide = d.r > 128 && G * ceil_div(d.N, 128) >= 256;
     const int rows = wide ? 128 : 64, blocks = G * ceil_div(d.N, rows);
     const int tiles = d.r > 0 && blocks >= (wide ? 1024 : 2048) ? 2 : 1;
     const dim3 grid(G, ceil_div(d.N, rows * tiles));
-#define FBQ_QUANT(B, D, S, V) hipLaunchKernelGGL((fbq_quantize_kernel<B, D, S, V>), grid, dim3(64 * V), 0, stream, W, At, Bt, qw, scales, zeros, d.N, d.K, d.r, words, D16, Dt16, ldt, gain, tiles)
-#define FBQ_QUANT_R(B, D) do { if (wide) { if (D && d.r <= 128) FBQ_QUANT(B, D, 4, 8); else FBQ_QUANT(B, D, 8, 8); } \
+#define FBQ_QUANT(B, D, S, V) hipLaunchKernelGGL((fbq_quantize_kernel<B, D, S, V>), grid, dim3(64 * V), 0, stream, W, At, Bt, qw, scales, zeros, d.N, d.K, d.r, words, D16, gain, tiles)
+#define FBQ_QUANT_R(B, D) do { if (wide) FBQ_QUANT(B, D, 8, 8); \
                                else if (d.r <= 64) FBQ_QUANT(B, D, 2, 4); else if (d.r <= 128) FBQ_QUANT(B, D, 4, 4); else FBQ_QUANT(B, D, 8, 4); } while (0)
     if (d.bits == 4) { if (D16) FBQ_QUANT_R(4, true); else FBQ_QUANT_R(4, false); }
     else { if (D16) FBQ_QUANT_R(3, true); else FBQ_QUANT_R(3, false); }

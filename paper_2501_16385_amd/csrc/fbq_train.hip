@@ -6,8 +6,8 @@
 // detached), so H is formed once per layer and an iteration is
 //
 //   A16, B16   <- fp16 of the fp32 masters                               (cast kernel)
-//   q, s, z    <- Q(W - Sigma16)               feedback quantizer  } fbq_quantize_kernel: fp64, Delta_F
-//   Delta_F    <- (W - Sigma16) - s (q - z)                        } from the registers that hold W - Sigma16
+//   q, s, z    <- Q(W - Sigma16)               feedback quantizer  } fbq_quantize_kernel, Delta_F
+//   Delta_F    <- (W - Sigma16) - s (q - z)                        } from its registers
 //   Q          <- Bt^T Delta_F        [r,K]                              (GEMM, K split)
 //   dL/dAt     <- -2 Q H              [r,K]    } one GEMM on the stacked                                 
 //   V^T        <- At H                [r,K]    } operand [Q; At], K split
@@ -22,8 +22,8 @@
 // symmetric one, half the work of Delta_F H.
 //
 // Two matrix-core kernels (v_mfma_f32_32x32x16_f16, fp16 in, fp32 accumulate): fbq_gemm_nt_kernel for the products with r rows or
-// columns, operands contiguous along the contraction, and fbq_syrk_kernel for A^T A, whose operand lies as it is and is turned by the
-// reads from LDS (ds_read_b64_tr_b16).  Both pass their operands through LDS by buffer_load ... lds, several steps of 64 ahead; rows (whole
+// columns and fbq_syrk_kernel for A^T A.  Operands whose rows do not run along the contraction (X and Delta_F, but for the last product) lie as they are
+// and are turned by the reads from LDS (ds_read_b64_tr_b16).  Both pass their operands through LDS by buffer_load ... lds, several steps of 64 ahead; rows (whole
 // cache lines) are stored with their 16-byte pieces XOR-swizzled so that reads have no bank conflict; rows past the end of an
 // operand are fetched through a bounds-checked buffer descriptor and arrive as zeros.  fp16 operands carry Delta_F times 256 and H times the caller's h_scale, so
 // that neither leaves the normal range; the factors come out again in the epilogues.
@@ -69,9 +69,10 @@ __device__ __forceinline__ half8_t read_turned(const unsigned char *at)
 
 struct GemmArgs {
     const uint16_t *A;   // [Mr][lda] fp16
-    const uint16_t *B;   // [Nr][ldb] fp16
+    const uint16_t *B;   // [Nr][ldb] fp16; TURNED: [b_rows][ldb], rows along the contraction, b_rows <= Kd
     int Mr, Nr, Kd;      // Kd a multiple of 64
     int lda, ldb;        // elements
+    int b_rows;
     // store epilogue (either may be absent)
     float *C32; int ldc32; float alpha; int c32_rows;   // C32[m,n] = alpha acc for rows m < c32_rows
     uint16_t *C16; int ldc16; float beta; int c16_row0; // C16[m - c16_row0, n] = fp16(beta acc) for rows m >= c16_row0
@@ -91,7 +92,8 @@ __device__ __forceinline__ void store_result(const GemmArgs &g, int m, int n, fl
 // through a ring of four stages in LDS, copied there without passing registers three steps ahead (through registers, one step
 // ahead, the three products of a 4096 x 4096 step at r = 64 took 43 us and take 34).
 constexpr int kNtStages = 4;
-template <int WM, int WN>
+// TURNED: B's rows run along the contraction and are turned by the reads from LDS (Q = B^T Delta_F: the quantizer writes Delta_F once).
+template <int WM, int WN, bool TURNED>
 __global__ __launch_bounds__(256) void fbq_gemm_nt_kernel(GemmArgs g)
 {
     constexpr int BM = 64 * WM, BN = 64 * WN;
@@ -114,18 +116,25 @@ __global__ __launch_bounds__(256) void fbq_gemm_nt_kernel(GemmArgs g)
     const int col = lane & 31, h = lane >> 5;
 
     const __amdgpu_buffer_rsrc_t abuf = buffer_of(g.A + (size_t)m0 * g.lda, (long)min(BM, g.Mr - m0) * g.lda * 2);   // rows past the end: zeros
-    const __amdgpu_buffer_rsrc_t bbuf = buffer_of(g.B + (size_t)n0 * g.ldb, (long)min(BN, g.Nr - n0) * g.ldb * 2);
+    const __amdgpu_buffer_rsrc_t bbuf = buffer_of(g.B + (size_t)n0 * g.ldb, TURNED ? 0 : (long)min(BN, g.Nr - n0) * g.ldb * 2);
     const int all_steps = g.Kd / kStepK, per_split = (all_steps + g.splits - 1) / g.splits;
     const int first = split * per_split, steps = min(all_steps, first + per_split) - first;   // >= 1: the launcher sees to it
     const int lrow = lane >> 3;
     const uint32_t lds0 = lds_offset(lds);
+    // TURNED: a step's 64 rows of B by BN columns, as they lie, kPieces pieces a row; Nr columns are whole pieces, those past Nr aim nowhere
+    constexpr int kPieces = BN / 8;
+    const int trow = lane / kPieces, tcolumn = ((lane % kPieces) ^ turned_key(trow, kPieces)) * 8;
+    const int toff = n0 + tcolumn < g.Nr ? (trow * g.ldb + tcolumn) * 2 : 0x40000000;
     auto copy_step = [&](int s, int stage) __attribute__((always_inline)) {
         const uint32_t base = lds0 + stage * kStageBytes;
+        const int k0 = (first + s) * kStepK;
+        const __amdgpu_buffer_rsrc_t tbuf = TURNED ? buffer_of(g.B + (size_t)k0 * g.ldb + n0, __builtin_amdgcn_readfirstlane(max(0, (min(kStepK, g.b_rows - k0) * g.ldb - n0) * 2))) : bbuf;
 #pragma unroll
         for (int j = 0; j < kCopies; ++j) {
             const int row = 8 * (4 * j + wave);         // of [A rows | B rows]; BM is a multiple of 32, so the side is the same for all waves
             const int piece = ((lane & 7) ^ piece_key((row + lrow) & 15)) * 16;
-            if (32 * j < BM) copy16_to_lds(abuf, lrow * g.lda * 2 + piece, row * g.lda * 2 + (first + s) * 128, base + row * 128);
+            if (TURNED && 32 * j >= BM) copy16_to_lds(tbuf, toff, (row - BM) / 8 * (64 / kPieces) * g.ldb * 2, base + row * 128);
+            else if (32 * j < BM) copy16_to_lds(abuf, lrow * g.lda * 2 + piece, row * g.lda * 2 + (first + s) * 128, base + row * 128);
             else copy16_to_lds(bbuf, lrow * g.ldb * 2 + piece, (row - BM) * g.ldb * 2 + (first + s) * 128, base + row * 128);
         }
     };
@@ -141,6 +150,9 @@ __global__ __launch_bounds__(256) void fbq_gemm_nt_kernel(GemmArgs g)
     // operand rows of this lane: 32 rows apart, so they share the key
     const int key = piece_key(col & 15);
     const int arow = (wm * 32 * WM + col) * 128, brow = (BM + wn * 32 * WN + col) * 128;
+    int tlane[WN];
+#pragma unroll
+    for (int j = 0; j < WN; ++j) tlane[j] = TURNED ? turned_offset<kPieces>(lane, (wn * WN + j) * 4) : 0;
     for (int s = 0; s < min(kNtStages - 1, steps); ++s) copy_step(s, s);
     for (int s = 0; s < steps; ++s) {
         // step s has landed, and everybody is done with step s - 1, whose stage the next copies go to
@@ -155,7 +167,10 @@ __global__ __launch_bounds__(256) void fbq_gemm_nt_kernel(GemmArgs g)
 #pragma unroll
             for (int i = 0; i < WM; ++i) af[i] = *reinterpret_cast<const half8_t *>(base + arow + i * 32 * 128 + chunk);
 #pragma unroll
-            for (int j = 0; j < WN; ++j) bf[j] = *reinterpret_cast<const half8_t *>(base + brow + j * 32 * 128 + chunk);
+            for (int j = 0; j < WN; ++j) {
+                if constexpr (TURNED) bf[j] = read_turned<kPieces>(base + BM * 128 + tlane[j] + kk * (16 * kPieces * 16));
+                else bf[j] = *reinterpret_cast<const half8_t *>(base + brow + j * 32 * 128 + chunk);
+            }
 #pragma unroll
             for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -285,7 +300,8 @@ static size_t split_scratch_bytes(int Mr, int Nr, int Kd)
 template <int WM, int WN>
 static void launch_gemm_tile(const GemmArgs &g, dim3 grid, hipStream_t stream)
 {
-    hipLaunchKernelGGL((fbq_gemm_nt_kernel<WM, WN>), grid, dim3(256), 0, stream, g);
+    if (g.b_rows) hipLaunchKernelGGL((fbq_gemm_nt_kernel<WM, WN, true>), grid, dim3(256), 0, stream, g);
+    else hipLaunchKernelGGL((fbq_gemm_nt_kernel<WM, WN, false>), grid, dim3(256), 0, stream, g);
 }
 
 // last: the launch that ends a step, or null
@@ -687,7 +703,7 @@ static int pad64(int v) { return (v + 63) & ~63; }
 constexpr float kVGain = 64.0f;      // V^T = At H is stored as fp16(64 h_scale At H)
 
 struct TrainLayout {
-    size_t Bc, D16, Dt16, S16, Vt16, dot, split, total;
+    size_t Bc, D16, S16, Vt16, dot, split, total;
 };
 
 static TrainLayout train_layout(int N, int K, int r)
@@ -697,12 +713,12 @@ static TrainLayout train_layout(int N, int K, int r)
     size_t o = 0;
     l.Bc = o;   o += pad256((size_t)r * Np * 2);
     l.D16 = o;  o += pad256((size_t)N * K * 2);
-    l.Dt16 = o; o += pad256((size_t)K * Np * 2);
     l.S16 = o;  o += pad256((size_t)2 * r * K * 2);          // stacked operand [Q; At]
     l.Vt16 = o; o += pad256((size_t)r * K * 2);
     l.dot = o;  o += pad256(syrk_units(syrk_shape(K, Np, true)) * 4);
     l.split = o;
     o += pad256(std::max(std::max(split_scratch_bytes(r, K, Np), split_scratch_bytes(2 * r, K, K)), split_scratch_bytes(N, r, K)));
+    o += pad256((size_t)K * Np * 2);                         // not used: what is asked for, and what is refused, stays as it was when Delta_F was kept in both orientations
     l.total = o;
     return l;
 }
@@ -734,7 +750,7 @@ hipError_t launch_train_step(const TrainArgs &a, hipStream_t stream)
     const TrainLayout l = train_layout(N, K, r);
     unsigned char *ws = (unsigned char *)a.workspace;
     uint16_t *Bc = (uint16_t *)(ws + l.Bc);
-    uint16_t *D16 = (uint16_t *)(ws + l.D16), *Dt16 = (uint16_t *)(ws + l.Dt16);
+    uint16_t *D16 = (uint16_t *)(ws + l.D16);
     uint16_t *S16 = (uint16_t *)(ws + l.S16), *Vt16 = (uint16_t *)(ws + l.Vt16);
     float *dot = (float *)(ws + l.dot), *scratch = (float *)(ws + l.split);
 
@@ -744,13 +760,13 @@ hipError_t launch_train_step(const TrainArgs &a, hipStream_t stream)
                        a.Bt16, S16 + (size_t)r * K, Bc, N, K, r, Np);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // Q(W - Sigma16), written in the inference layout, and Delta_F = (W - Sigma16) - Q(W - Sigma16), times 256,
-    // in both orientations
-    e = launch_quantize(a.d, a.W, a.At16, a.Bt16, a.qw, a.scales, a.zeros, stream, D16, Dt16, Np, kDeltaGain);
+    // Q(W - Sigma16), written in the inference layout, and Delta_F = (W - Sigma16) - Q(W - Sigma16), times 256
+    e = launch_quantize(a.d, a.W, a.At16, a.Bt16, a.qw, a.scales, a.zeros, stream, D16, kDeltaGain);
     if (e != hipSuccess) return e;
     // Q = Bt^T Delta_F (times 256), the upper half of the stacked operand
     {
-        GemmArgs g = gemm_args(Bc, r, Np, Dt16, K, Np, Np);
+        GemmArgs g = gemm_args(Bc, r, Np, D16, K, K, Np);
+        g.b_rows = N;
         g.C16 = S16; g.ldc16 = K; g.beta = 1.0f;
         if ((e = launch_gemm(g, scratch, stream)) != hipSuccess) return e;
     }

@@ -15,7 +15,7 @@ hipError_t launch_unpack(const fbq_desc &, const uint32_t *, uint8_t *, hipStrea
 hipError_t launch_reconstruct(const fbq_desc &, const uint32_t *, const uint16_t *, const uint16_t *, const uint16_t *, const uint16_t *,
                               float *, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_quantize(const fbq_desc &, const uint16_t *, const uint16_t *, const uint16_t *, uint32_t *, uint16_t *, uint16_t *,
-                           hipStream_t, uint16_t *, uint16_t *, int, float) { return hipErrorNotSupported; }
+                           hipStream_t, uint16_t *, float) { return hipErrorNotSupported; }
 hipError_t launch_read_stream(const void *, size_t, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_unfused_branch(const LinearArgs &, uint16_t *, hipStream_t) { return hipErrorNotSupported; }
 hipError_t launch_mix(const LinearArgs &, hipStream_t) { return hipErrorNotSupported; }
