@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfbq.so")
+CALL = os.path.join(HERE, "_fbq_call.so")     # the binding's call of fbq_linear: host code, a CPython module
 SOURCES = ["fbq_api.cpp", "fbq_decode.hip", "fbq_decode_mfma.hip", "fbq_decode_stream.hip", "fbq_few_split.hip", "fbq_prefill.hip", "fbq_quantize.hip", "fbq_util.hip", "fbq_train.hip",
            "fbq_static.hip", "fbq_mix.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
@@ -38,6 +40,8 @@ def build(verbose: bool = False, extra_flags=()) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(jobs))) as pool:
         list(pool.map(lambda c: _run(c, verbose), jobs))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, verbose)
+    _run([os.environ.get("CC", "gcc"), "-O2", "-std=c11", "-Wall", "-Wextra", "-fPIC", "-shared", "-I", INCLUDE, "-I", sysconfig.get_paths()["include"],
+          os.path.join(CSRC, "fbq_call.c"), "-o", CALL], verbose)
     return LIB
 
 

@@ -16,6 +16,8 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libfbq.so")
 _lib: Optional[ctypes.CDLL] = None
+_call_linear = None             # _fbq_call.linear and what it calls, once the library is loaded
+_linear_address = 0
 
 EXPORTED_SYMBOLS = ["fbq_status_string", "fbq_check_desc", "fbq_packed_bytes", "fbq_workspace_bytes", "fbq_pack",
                     "fbq_linear", "fbq_linear_static", "fbq_linear_unfused", "fbq_linear_group", "fbq_linear_group_mix", "fbq_silu_mul", "fbq_reconstruct", "fbq_unpack_codes", "fbq_quantize_feedback",
@@ -71,6 +73,7 @@ def load() -> ctypes.CDLL:
         # when this library came first the process ended up with two runtimes and every launch on a torch stream
         # failed with a launch error.
         import torch  # noqa: F401
+        from . import _fbq_call                # (built with the library)
         lib = ctypes.CDLL(_LIB_PATH)
         vp, sz, i32 = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int
         dp = ctypes.POINTER(_CDesc)
@@ -113,6 +116,8 @@ def load() -> ctypes.CDLL:
         lib.fbq_gram.argtypes = [dp, i32, vp, f32, vp, vp, sz, vp]
         lib.fbq_train_step.restype = i32
         lib.fbq_train_step.argtypes = [dp, vp, vp, f32, vp, vp, f32] + [vp] * 9 + [sz, vp]
+        global _call_linear, _linear_address
+        _call_linear, _linear_address = _fbq_call.linear, ctypes.cast(lib.fbq_linear, vp).value
         _lib = lib
     return _lib
 
@@ -235,6 +240,13 @@ def linear(layer: DeviceLayer, x, y=None, workspace=None, stream=None):
         need = 0 if workspace is not None else workspace_bytes(d, M)   # (a workspace that is given is checked by the library)
         if need:
             workspace = torch.zeros(need, dtype=torch.uint8, device=x.device)
+    if _lib is None:
+        load()
+    # one token through 4096 x 4096, us a call: 6.1 by way of ctypes' argument objects, 5.0 this way
+    rc = _call_linear(_linear_address, layer, x, y, workspace, _stream(stream))
+    if rc is not None:
+        _check(rc, "fbq_linear")
+        return y
     wbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     rc = load().fbq_linear(ctypes.byref(d.c()), M, _dev_ptr(x), _dev_ptr(layer.qweight), _dev_ptr(layer.scales),
                            _dev_ptr(layer.zeros), _dev_ptr(layer.At), _dev_ptr(layer.Bt), _dev_ptr(y), _dev_ptr(workspace),

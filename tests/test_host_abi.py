@@ -224,3 +224,40 @@ def test_loading_the_library_first_still_leaves_one_hip_runtime():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     res = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stdout + res.stderr
+
+
+def test_native_call_of_linear_hands_over_what_ctypes_would():
+    """The compiled call against what fbq_linear is given, with stand-ins for tensors; whatever is not as expected is left to the Python code."""
+    from types import SimpleNamespace as NS
+    from paper_2501_16385_amd import _fbq_call
+    seen = []
+    vp = ctypes.c_void_p
+
+    @ctypes.CFUNCTYPE(ctypes.c_int, ctypes.POINTER(type(fbq.Desc(1, 1, 0, 4).c())), ctypes.c_int, *[vp] * 8, ctypes.c_size_t, vp)
+    def callee(d, M, *rest):
+        seen.append(((d[0].N, d[0].K, d[0].r, d[0].bits, d[0].group), M) + rest)
+        return 4
+
+    address = ctypes.cast(callee, vp).value
+    tensor = lambda p, cuda=True, contiguous=True, shape=(3, 128): NS(is_cuda=cuda, is_contiguous=lambda: contiguous, data_ptr=lambda: p, shape=shape,
+                                                                     numel=lambda: 1 << 33, element_size=lambda: 2)
+    layer = lambda d=fbq.Desc(8, 128, 16, 3), **more: NS(**{"desc": d, **{n: tensor(0x7F0000000000 + i) for i, n in enumerate(("qweight", "scales", "zeros", "At", "Bt"))}, **more})
+    call = lambda l, x=tensor(64), y=tensor(80), ws=tensor(96), stream=1 << 40: _fbq_call.linear(address, l, x, y, ws, stream)
+    base = 0x7F0000000000
+    assert call(layer()) == 4
+    assert seen.pop() == ((8, 128, 16, 3, 128), 3, 64, base, base + 1, base + 2, base + 3, base + 4, 80, 96, 1 << 34, 1 << 40)
+    assert call(layer(fbq.Desc(8, 128, 0, 4), At=None, Bt=None), ws=None, stream=0) == 4
+    assert seen.pop() == ((8, 128, 0, 4, 128), 3, 64, base, base + 1, base + 2, None, None, 80, None, 0, None)
+    for odd in (call(layer(), x=tensor(64, cuda=False)), call(layer(scales=tensor(1, contiguous=False))), call(layer(), y=tensor(2, cuda=False)),
+                call(layer(), ws=tensor(2, contiguous=False)), call(layer(At=object())), call(layer(fbq.Desc(-8, 128, 0, 4))), call(layer(fbq.Desc(8.0, 128, 0, 4))),
+                call(layer(), x=tensor(64, shape=())), call(layer(), x=tensor(64, shape=(2.5,))), call(layer(), stream=None), call(NS())):
+        assert odd is None and not seen
+    with pytest.raises(TypeError):
+        _fbq_call.linear(address)
+
+
+def test_linear_refuses_host_tensors_as_before():
+    import torch
+    layer = fbq.DeviceLayer(fbq.Desc(128, 128, 0, 4), torch.zeros(128, 16, dtype=torch.int32), *[torch.zeros(128, 1, dtype=torch.int16)] * 2, None, None)
+    with pytest.raises(ValueError, match="device tensor"):
+        fbq.linear(layer, torch.zeros(1, 128).half(), torch.zeros(1, 128).half(), torch.zeros(64, dtype=torch.uint8), stream=type("S", (), {"cuda_stream": 0}))
