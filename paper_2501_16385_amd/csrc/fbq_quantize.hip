@@ -210,9 +210,10 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
                 half8_t a = taps[f][p ^ tap_key(f)];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) a[j] = (half_t)((float)a[j] * factor);
-                const half8_t whole = kSplitTaps ? (a + grid8) - grid8 : a;
+                // (from 2048 on nothing is split: on such a grid the largest fp16 numbers are infinite, and an infinity less itself is none)
+                const half8_t whole = kSplitTaps && peak < 2048.0f ? (a + grid8) - grid8 : a;
                 taps[f][p ^ tap_key(f)] = whole;
-                if constexpr (kSplitTaps) rests[f][p ^ tap_key(f)] = a - whole;
+                if constexpr (kSplitTaps) rests[f][p ^ tap_key(f)] = peak < 2048.0f ? a - whole : half8_t{};
             }
             const float back = peak == 0.0f ? 0.0f : 1.0f / factor;
             even = peak == 0.0f ? even : fmaxf(sqrtf(even), 2048.0f * back);    // (at least the largest tap)
@@ -394,12 +395,12 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
                     }
                 }
             }
-            sure = (sure && clear) || lo != lo;                                  // (no number in the whole group: nothing more exact to be had)
+            sure = sure && clear;                                                // (never where nothing is a number: the split of large numbers can make it so)
             pack_codes<BITS>(x, words);
         }
         // ---- rows that 32 bits leave open, in 64: two features a lane.  The products of two fp16 values have 22 significant bits, so the
         // order of the taps matters only where a sum needs more than 53 bits.
-        const unsigned long long unsure = __ballot(!sure);
+        const unsigned long long unsure = __ballot(!sure && c < rows);
         const uint32_t open_rows = (uint32_t)(unsure | unsure >> 16 | unsure >> 32 | unsure >> 48) & 0xFFFFu;
         for (uint32_t open = open_rows; open; open &= open - 1) {
             const int n = __builtin_ctz(open);

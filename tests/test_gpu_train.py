@@ -246,3 +246,35 @@ def test_gram_of_turned_reads_is_exact_on_whole_numbers(K, T):
     ws = torch.empty(fbq.train_workspace_bytes(d, T), dtype=torch.uint8, device="cuda")
     rc = fbq.load().fbq_gram(ctypes.byref(d.c()), T, both.data_ptr(), 1.0 / 16, both.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
     assert rc == 0 and torch.equal(both[: K * K].view(K, K), want)
+
+
+@pytest.mark.parametrize("bits,r", [(4, 64), (3, 24), (4, 128), (3, 200)])
+@pytest.mark.parametrize("where", ["taps", "rows of B", "both"])
+def test_step_with_a_branch_near_the_end_of_fp16(bits, r, where):
+    """Numbers that the split of the 32-bit sums has no room for (from 59360 on, and infinities) go to 64 bits as they are: codes, scales and zeros are those of
+    the quantizer by itself, and Delta_F is finite where the branch is (fp16 roundings of the gradient of B as above: 2e-3)."""
+    N, K, scale = 48, 384, 2.0**-10
+    g = torch.Generator(device="cuda")
+    g.manual_seed(r)
+    rand = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    W, At, Bt = (rand(N, K) * 0.02).half(), rand(r, K) * 3e-4, rand(N, r) * 0.01    # (256 Delta_F stays an fp16 number)
+    if where != "rows of B":
+        At[2, 7], At[1, 140] = 60000.0, -65504.0
+        At[3, 260], At[4, 261], At[5, 262] = float("inf"), float("nan"), 2048.0    # (the third group's taps)
+    if where != "taps":
+        Bt[3, 5], Bt[4, 0], Bt[7, 2], Bt[40] = 60000.0, -65504.0, 3000.0, 59500.0
+        Bt[9, 1], Bt[10, 4] = float("inf"), float("nan")
+    d = fbq.Desc(N, K, r, bits)
+    H16 = torch.eye(K, device="cuda").half() * scale
+    st = fbq.train_state(d, At.clone(), Bt.clone())
+    fbq.train_step(st, W, H16, scale, 0.0, want_loss=False)
+    plain = fbq.quantize_feedback(d, W, At.half().view(torch.int16), Bt.half().view(torch.int16))
+    for a, b in ((st.layer.qweight, plain.qweight), (st.layer.scales, plain.scales), (st.layer.zeros, plain.zeros)):
+        assert torch.equal(a, b)
+    if where == "rows of B":
+        A, B = At.half().double(), Bt.half().double()
+        s, z = (t.view(torch.float16).double()[:, :, None] for t in (plain.scales, plain.zeros))
+        delta = W.double() - B @ A - (s * (fbq.unpack_codes(plain).view(N, K // 128, 128) - z)).view(N, K)
+        rows = [n for n in range(N) if n not in (9, 10)]
+        want = -2 * (delta @ A.T.contiguous())[rows]
+        assert float((st.grad_Bt.double()[rows] - want).norm() / want.norm()) < 2e-3
