@@ -12,16 +12,18 @@
 // are found in the lane but for two steps between lanes.
 //
 // What it takes, us, against the same in fp64 throughout (fp64 matrix instruction, a thirtieth of the fp16 rate): 11008 x 4096 INT3, r = 64,
-// 124 -> 50; without a sub-branch 38 -> 30; INT4, r = 200, 335 -> 96; 4096 x 4096, r = 128, 79 -> 32.  Of the 50, 23 are the bytes at the rate of
-// a large copy, about 15 getting At into LDS and out of it (without a sub-branch 30), 4 the rows in fp64.
+// 124 -> 50; without a sub-branch 38 -> 27; INT4, r = 200, 335 -> 94; 4096 x 4096, r = 128, 79 -> 33.  Of the 50, 23 are the bytes at the rate of
+// a large copy, about 15 getting At into LDS and out of it (without a sub-branch 27), 4 the rows in fp64.
+// Weights that leave nearly every row open (groups far from zero beside their spread, |z| above 1024; values on half steps) take the attempt and the fp64 product of all rows:
+// fp64 throughout / row by row / all sixteen of a wave at once, as now: 11008 x 4096 INT3, r = 64, 124 / 449 / 147, without a sub-branch 37 / 160 / 49; INT4, r = 200, 364 / 1255 / 441.
 //
 // With DELTA the kernel also writes what the reconstruction step needs from the same registers: Delta_F = (W - Sigma) - s (q - z), times
 // `gain`, as fp16 (D16 [N][K]).  It is the fp16 number that fp64 gives: where the bound leaves two open, that element is done again.  Sigma is
 // had more exactly for that (below); with the bound of the fp16 products as they are, eight elements in a hundred were open and a step took 233 us,
 // now four in a thousand at the start and some two in a hundred after thousands of steps.
-// A step with loss, us, fp64 throughout (Delta_F written in both orientations) / now: 4096 x 4096 INT4, r = 64, 182 / 173, without loss 108 / 99.5;
-// 4096 x 11008, r = 64, without loss 298 / 243; 11008 x 4096, r = 200, 719 / 638; 1000 x 1024, r = 64, 48.8 / 50.0 (one tile a wave: the chain of
-// a wave's instructions bounds it).  What bounds the kernel (47 of the 173): vector instructions, about 2300 a tile of 16 rows.
+// A step with loss, us, fp64 throughout (Delta_F written in both orientations) / now: 4096 x 4096 INT4, r = 64, 182 / 173, without loss 104 / 92;
+// 4096 x 11008, r = 64, without loss 298 / 243; 11008 x 4096, r = 200, 719 / 638; taps all of one size, 4096 x 4096, r = 128, without loss 149 / 161 (row by row 413).  What bounds
+// the kernel (47 of the 173): vector instructions, about 2300 a tile of 16 rows.
 #include <hip/hip_fp16.h>
 
 #include "fbq_internal.h"
@@ -32,6 +34,7 @@ typedef _Float16 half_t;
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef double double4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double half_bits_to_double(uint16_t h) { return (double)__builtin_bit_cast(half_t, h); }
 
@@ -130,6 +133,7 @@ __device__ __forceinline__ float fixed_point_factor(float peak)
 
 constexpr int kQuantTapStep = 32;      // taps one matrix instruction takes
 constexpr float kLongest = 16300.0f;   // of 128 taps or a row of as many, at 2^10 and above: what the exact sums (below) have room for; evenly spread ones are 13400 long
+constexpr int kFewOpen = 3;            // open rows of a wave's sixteen that go to 64 bits one by one
 constexpr int kOpenList = 128;         // pairs of elements of Delta_F that a wave lists at a time
 
 // Taps in LDS: 16-byte pieces of eight taps, [feature][piece], a piece's place XORed with a key so that the sixteen features that
@@ -150,7 +154,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
     // DELTA, up to 64 taps: taps[] holds their multiples of a unit and rests[] the rest (below); otherwise each wave splits what it reads
     constexpr bool kSplitTaps = DELTA && STEPS <= 2;
     __shared__ half8_t taps[kGroup][kPieces], rests[kSplitTaps ? kGroup : 1][kSplitTaps ? kPieces : 1];
-    __shared__ uint32_t longest, too_high;                                      // largest squared norm of a feature's taps; DELTA: whether a tap is 2048 or more
+    __shared__ uint32_t longest, straight;                                      // largest squared norm of a feature's taps; whether rows go to 64 bits without an attempt in 32
     // DELTA, by feature: what takes its taps back to At's, and its bound (below)
     __shared__ __attribute__((aligned(16))) float tap_back[DELTA ? kGroup : 4], tap_norm[DELTA ? kGroup : 4];
     __shared__ struct { float code[kGroup]; alignas(16) _Float16 delta[DELTA ? kGroup : 8]; uint16_t list[DELTA ? kOpenList : 8]; } exact[WAVES];
@@ -160,7 +164,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
     const int G = K / kGroup, g = blockIdx.x;
     const int steps = (r + kQuantTapStep - 1) / kQuantTapStep;
 
-    if (threadIdx.x == 0) longest = too_high = 0;
+    if (threadIdx.x == 0) longest = straight = 0;
     const half_t grid = STEPS <= 4 ? (half_t)6144.0f : (half_t)12288.0f;        // 1.5 x 2^10 units: added and taken away, it leaves whole units
     const half8_t grid8 = {grid, grid, grid, grid, grid, grid, grid, grid};
     auto tap8 = [&](int f, int p) __attribute__((always_inline)) {
@@ -220,7 +224,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
             if (threadIdx.x % kSide == 0) {
                 tap_back[f] = back;
                 tap_norm[f] = even;
-                if (peak >= 2048.0f || (STEPS == 4 && even > kLongest * back)) too_high = 1;
+                if (peak >= 2048.0f || (STEPS == 4 && even > kLongest * back)) straight = 1;
             }
         }
         uint32_t most = __builtin_bit_cast(uint32_t, even);                    // (not negative; a NaN is larger than all numbers this way)
@@ -236,25 +240,25 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
         const int nb = (blockIdx.y * tiles + tile) * kRows, n0 = nb + 16 * wave;   // the block's first row, the wave's
         if (nb >= N) break;
         int lane_now = lane;                                                    // (not known to be the same in every tile: addresses kept over the loop spill)
-        if (DELTA) asm volatile("" : "+v"(lane_now));
+        asm volatile("" : "+v"(lane_now));
         const int c = lane_now & 15, q = lane_now >> 4;
         const int rows = min(16, N - n0);                                       // may be <= 0: such a wave computes zeros and stores nothing
         // The wave's rows of W and Bt through descriptors that end with row N - 1: rows past it read as zeros.
         const __amdgpu_buffer_rsrc_t wbuf = bounded_buffer(W + (size_t)min(n0, N - 1) * K, rows > 0 ? (long)rows * K * 2 : 0);
         const __amdgpu_buffer_rsrc_t bbuf = bounded_buffer(Bt + (size_t)min(n0, N - 1) * r, rows > 0 ? (long)rows * r * 2 : 0);
-        half8_t w[4], b[2];
-        auto branch_rows = [&](int j) __attribute__((always_inline)) { return load_half8(bbuf, j < r ? (c * r + j) * 2 : kNowhere); };
-        b[0] = branch_rows(8 * q);                                              // (r is a multiple of 8: all of a lane's taps or none)
-        b[1] = branch_rows(kQuantTapStep + 8 * q);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = load_half8(wbuf, (c * K + g * kGroup + 32 * q + 8 * i) * 2);
+        auto branch_rows = [&](int j) __attribute__((always_inline)) { return load_half8(bbuf, j < r ? (c * r + j) * 2 : kNowhere); };   // (r is a multiple of 8: all of a lane's taps or none)
+        auto weights = [&](int i) __attribute__((always_inline)) { return load_half8(wbuf, (c * K + g * kGroup + 32 * q + 8 * i) * 2); };
 
         // ---- 32 bits, with a bound
-        uint32_t words[BITS], sz;
+        uint32_t words[BITS], sz = 0, open_rows = (1u << max(0, min(16, rows))) - 1;
         half8_t d8[4];
         uint32_t open_delta = 0;                                                // DELTA: pairs of features with an fp16 number that 32 bits leave open, the first pair in bit 15
-        bool sure;
-        {
+        if (!__builtin_amdgcn_readfirstlane(__hip_atomic_load(&straight, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) {   // wave-uniform
+            half8_t w[4], b[2];
+            b[0] = branch_rows(8 * q);
+            b[1] = branch_rows(kQuantTapStep + 8 * q);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = weights(i);
             float Sigma[32];                                                     // DELTA: times gain, a power of two
 #pragma unroll
             for (int i = 0; i < 32; ++i) Sigma[i] = 0.0f;
@@ -303,7 +307,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
                 peak = fmaxf(peak, __shfl_xor(peak, 16, 64));
                 peak = fmaxf(peak, __shfl_xor(peak, 32, 64));
                 const float b_factor = fixed_point_factor(peak);
-                coarse = peak >= 2048.0f || too_high || (STEPS == 4 && b_norm2 * b_factor * b_factor > kLongest * kLongest);   // (to 64 bits)
+                coarse = peak >= 2048.0f || (STEPS == 4 && b_norm2 * b_factor * b_factor > kLongest * kLongest);   // (to 64 bits)
                 float rest[32];
 #pragma unroll
                 for (int i = 0; i < 32; ++i) rest[i] = 0.0f;
@@ -361,7 +365,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
             // in them while a zero's last place is below one, so where both agree the true ones do
             const double e = q & 1 ? -(double)off : (double)off;
             sz = search_scale((double)lo - e, (double)hi + e, qmax);
-            sure = (uint32_t)__shfl_xor((int)sz, 16, 64) == sz && (off == 0.0f || hi - lo > 8.0f * off);
+            bool sure = (uint32_t)__shfl_xor((int)sz, 16, 64) == sz && (off == 0.0f || hi - lo > 8.0f * off);
             const float s = (float)__builtin_bit_cast(half_t, (uint16_t)sz), z = (float)__builtin_bit_cast(half_t, (uint16_t)(sz >> 16));
             // (far from zero the differences inside a group are lost in R's own rounding)
             sure = sure && fabsf(z) <= 1024.0f;
@@ -370,7 +374,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
             // t below is off by R's error, the reciprocal's, and one rounding
             const float lim = 0.5f - (off * inv + 0x1.1p-24f * (most * inv + (float)(qmax + 1)) + 0x1.1p-24f * most * inv);
             float x[32];
-            bool clear = true;
+            float furthest = 0.0f;                                               // of t from the code it rounds to; NaN where one is
             // Delta_F below is W - s (q - z), one rounding, less Sigma, another one; two more for the bounds themselves
             const float off_delta = gain * 1.1f * off_rest;
             float4_t norm4;
@@ -380,7 +384,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
                 if (DELTA && !(i & 3)) norm4 = *reinterpret_cast<const float4_t *>(&tap_norm[32 * q + i]);
                 const float t = __builtin_fmaf(R[i], inv, z);
                 x[i] = rintf(t);                                                 // ties to even
-                clear = clear && fabsf(t - x[i]) <= lim;
+                furthest = __builtin_elementwise_maximum(furthest, fabsf(t - x[i]));
                 x[i] = fminf(fmaxf(x[i], 0.0f), (float)qmax);
                 if (DELTA) {                                                     // Delta_F (Sec. 4.2)
                     const float d = __builtin_fmaf(gain, __builtin_fmaf(-s, x[i] - z, (float)w[i >> 3][i & 7]), -Sigma[i]), e = __builtin_fmaf(0x1p-22f, fabsf(d), __builtin_fmaf(0x1.1p-23f, fabsf(Sigma[i]), off_delta * norm4[i & 3]));
@@ -395,14 +399,87 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
                     }
                 }
             }
-            sure = sure && clear;                                                // (never where nothing is a number: the split of large numbers can make it so)
+            sure = sure && furthest <= lim;                                                // (never where nothing is a number: the split of large numbers can make it so)
             pack_codes<BITS>(x, words);
+            const unsigned long long unsure = __ballot(!sure);
+            open_rows &= (uint32_t)(unsure | unsure >> 16 | unsure >> 32 | unsure >> 48);
         }
-        // ---- rows that 32 bits leave open, in 64: two features a lane.  The products of two fp16 values have 22 significant bits, so the
+        // ---- rows that 32 bits leave open, in 64.  The products of two fp16 values have 22 significant bits, so the
         // order of the taps matters only where a sum needs more than 53 bits.
-        const unsigned long long unsure = __ballot(!sure && c < rows);
-        const uint32_t open_rows = (uint32_t)(unsure | unsure >> 16 | unsure >> 32 | unsure >> 48) & 0xFFFFu;
-        for (uint32_t open = open_rows; open; open &= open - 1) {
+        // Many of them: all sixteen at once on the fp64 matrix instruction.  Lane (c, q) supplies tap q of four of feature 32 (c % 4) + 4 t + c / 4 and of row c, and ends up
+        // with the features 32 q + 4 t .. + 3 of row c, as above.  (An open row takes a quarter of the time of all sixteen.)
+        const bool many = __builtin_popcount(open_rows) > kFewOpen;
+        if (many) {
+            int lane_here = lane;                                                // (as above)
+            asm volatile("" : "+v"(lane_here));
+            const int c = lane_here & 15, q = lane_here >> 4;
+            auto branch_rows = [&](int j) __attribute__((always_inline)) { return load_half8(bbuf, j < r ? (c * r + j) * 2 : kNowhere); };
+            auto weights = [&](int i) __attribute__((always_inline)) { return load_half8(wbuf, (c * K + g * kGroup + 32 * q + 8 * i) * 2); };
+            half8_t w[4];
+            auto all_weights = [&]() __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[i] = weights(i);
+            };
+            if (DELTA) all_weights();                                            // (no registers for them this early in the other instances)
+            double4_t R[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) R[t] = double4_t{0.0, 0.0, 0.0, 0.0};
+            half8_t next = branch_rows(8 * q);
+#pragma unroll 1
+            for (int s = 0; s < steps; ++s) {
+                const half8_t b8 = next;
+                next = branch_rows(kQuantTapStep * (s + 1) + 8 * q);
+                double bd[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) bd[j] = (double)(float)b8[j];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    __builtin_amdgcn_sched_barrier(0);                           // (all eight operands at once spill)
+                    const half8_t a8 = tap8(32 * (c & 3) + 4 * t + (c >> 2), 4 * s + q);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) R[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(float)a8[j], bd[j], R[t], 0, 0, 0);
+                }
+            }
+            if (!DELTA) all_weights();
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) R[t][v] = (double)(float)w[t >> 1][4 * (t & 1) + v] - (DELTA ? R[t][v] * (double)tap_back[32 * q + 4 * t + v] : R[t][v]);
+            }
+            double lo = R[0][0], hi = R[0][0];
+#pragma unroll
+            for (int i = 1; i < 32; ++i) { lo = fmin(lo, R[i >> 2][i & 3]); hi = fmax(hi, R[i >> 2][i & 3]); }
+#pragma unroll
+            for (int away = 16; away < 64; away *= 2) {
+                lo = fmin(lo, __shfl_xor(lo, away, 64));
+                hi = fmax(hi, __shfl_xor(hi, away, 64));
+            }
+            const uint32_t found = search_scale(lo, hi, qmax);
+            const double sd = half_bits_to_double((uint16_t)found), zd = half_bits_to_double((uint16_t)(found >> 16)), inv = 1.0 / sd;
+            // R / s costs eleven fp64 instructions, R * inv and one correction three, and the result is the same number: with
+            // u = R * inv the residual e = R - u s is exact, u + e * inv is off the quotient by about 2^-105 of it before its one
+            // rounding, and a quotient of a 53-bit number by an 11-bit one is never that close to the middle between two fp64
+            // numbers (it is at least 2^-12 of a last place away from it, and the middle itself would need 54 bits of R).  With an
+            // infinite scale (weights that are infinite) inv is 0, and so, with no s in the residual, is the quotient of every number.
+            const double s_back = (found & 0x7FFFu) == 0x7c00u ? 0.0 : sd;
+            float x[32];
+#pragma unroll
+            for (int i = 0; i < 32; ++i) {
+                if (!(i & 3)) __builtin_amdgcn_sched_barrier(0);
+                const double Ri = R[i >> 2][i & 3];
+                const double u = Ri * inv, code = fmin(fmax(rint(__builtin_fma(__builtin_fma(-u, s_back, Ri), inv, u) + zd), 0.0), (double)qmax);   // ties to even
+                x[i] = (float)code;
+                if (DELTA) d8[i >> 3][i & 7] = (half_t)(float)((double)gain * (Ri - sd * (code - zd)));   // Delta_F (Sec. 4.2)
+            }
+            pack_codes<BITS>(x, words);
+            sz = found;
+            // (rows of one layer are alike; a wave that sees it late finds the same)
+            if (lane == 0 && __builtin_popcount(open_rows) > 8) __hip_atomic_store(&straight, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            open_rows = 0xFFFFu;                                                 // (the others come out as they were)
+        }
+        // A few: one by one, two features a lane.
+        for (uint32_t open = many ? 0u : open_rows; open; open &= open - 1) {
             const int n = __builtin_ctz(open);
             uint16_t wi[2];
 #pragma unroll

@@ -278,3 +278,50 @@ def test_step_with_a_branch_near_the_end_of_fp16(bits, r, where):
         rows = [n for n in range(N) if n not in (9, 10)]
         want = -2 * (delta @ A.T.contiguous())[rows]
         assert float((st.grad_Bt.double()[rows] - want).norm() / want.norm()) < 2e-3
+
+
+def stored_delta(st):
+    """fp16(256 Delta_F) of a state's last step, as the quantizer left it in the workspace: behind B^T with rows padded to 64."""
+    N, K, r = st.desc.N, st.desc.K, st.desc.r
+    at = (r * (-(-N // 64) * 64) * 2 + 255) // 256 * 256
+    return st.workspace[at:at + N * K * 2].view(torch.float16).view(N, K)
+
+
+@pytest.mark.parametrize("bits,N,K,r,kind", [
+    # blocks that all start at once, which go to 64 bits as they are: whole tiles and not, ranks of each class
+    (4, 100, 512, 64, "near"), (3, 63, 128, 200, "plain"), (4, 33, 256, 72, "offset"), (3, 4096, 512, 8, "plain"),
+    # one block more: one tile a block; two tiles a block; blocks of eight waves and two tiles
+    (4, 4097, 512, 64, "plain"), (3, 4097, 512, 40, "offset"), (4, 4100, 512, 128, "one size"), (3, 4100, 512, 72, "near"), (4, 4097, 512, 200, "ties"),
+    (3, 4100, 4096, 64, "ties"), (4, 4100, 4096, 24, "near"), (4, 4100, 4096, 200, "plain"), (3, 4100, 4096, 136, "near"), (3, 4100, 4096, 136, "offset")])
+def test_every_element_of_delta_is_that_of_64_bits(bits, N, K, r, kind):
+    """Rows that 32 bits decide, that they leave open one by one, and that are open nearly all: far from zero, on half steps, with taps all of one size (r = 128: their
+    whole parts have no room), and weights near the branch's product (more than 128 pairs of elements open in a wave's tile).  Every word of the layer is that of the quantizer by itself,
+    and every stored element the fp16 number of 64 bits, by way of fp32 as the kernel rounds it."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(17 * r + N)
+    rand = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    At, Bt, W = rand(r, K) * 0.01, rand(N, r) * 0.01, rand(N, K) * 0.02
+    if kind == "offset":
+        W = 4 + torch.randint(0, 4, (N, K), device="cuda", generator=g) * 2.0**-8
+    elif kind == "one size":
+        At = torch.sign(At) * 0.0149
+    elif kind == "ties":
+        W = torch.randint(0, 2 * (2**bits - 1) + 1, (N, K), device="cuda", generator=g) / 2.0
+        W[:, ::128], W[:, 1::128] = 0.0, 2.0**bits - 1
+        Bt = Bt * 0
+    elif kind == "near":
+        At, Bt = At * 30, Bt * 30
+        W = Bt.half().float() @ At.half().float() + 0.02 * W
+    W = W.half()
+    d = fbq.Desc(N, K, r, bits)
+    st = fbq.train_state(d, At.clone(), Bt.clone())
+    H16 = torch.zeros(K, K, dtype=torch.float16, device="cuda")
+    fbq.train_step(st, W, H16, 1.0, 0.0, want_loss=False)
+    plain = fbq.quantize_feedback(d, W, At.half().view(torch.int16), Bt.half().view(torch.int16))
+    for a, b in ((st.layer.qweight, plain.qweight), (st.layer.scales, plain.scales), (st.layer.zeros, plain.zeros)):
+        assert torch.equal(a, b)
+    s, z = (t.view(torch.float16).double()[:, :, None] for t in (plain.scales, plain.zeros))
+    R = W.double() - Bt.half().double() @ At.half().double()
+    want = (256.0 * (R.view(N, K // 128, 128) - s * (fbq.unpack_codes(plain).view(N, K // 128, 128) - z))).view(N, K).float().half()
+    off = stored_delta(st) != want
+    assert not bool(off.any()), (int(off.sum()), off.nonzero()[:5].tolist())
