@@ -24,6 +24,10 @@
 // A step with loss, us, fp64 throughout (Delta_F written in both orientations) / now: 4096 x 4096 INT4, r = 64, 182 / 173, without loss 104 / 92;
 // 4096 x 11008, r = 64, without loss 298 / 243; 11008 x 4096, r = 200, 719 / 638; taps all of one size, 4096 x 4096, r = 128, without loss 149 / 161 (row by row 413).  What bounds
 // the kernel (47 of the 173): vector instructions, about 2300 a tile of 16 rows.
+// With a block a CU or less, a wave's chain of instructions bounds a step, and the rows and elements done again are its end.  Such grids go to fp64 as they are (IN64: no norms, no split of
+// the taps, nothing done again), and the first tile's W and B are asked for with the taps.  The kernel / a step with loss, us, fp64 throughout / in 32 bits / now: 1000 x 1024, r = 64, 13.9 / 14.5 / 12.9 and
+// 50.8 / 52.4 / 50.0; 2000 x 1024, r = 64, 15.0 / 15.8 / 14.5 and 54.1 / 56.4 / 54.0; 1024 x 1024, r = 200, 24.6 / 32.7 / 25.3 and 75.4 / 82.5 / 77.5.  With more blocks than CUs 32 bits win: 1500 x
+// 1536, r = 128 (288 blocks), the kernel 25.5 against 29.6; 2048 x 2048, r = 64, 21.0 against 25.4.
 #include <hip/hip_fp16.h>
 
 #include "fbq_internal.h"
@@ -140,9 +144,9 @@ constexpr int kOpenList = 128;         // pairs of elements of Delta_F that a wa
 // one matrix operand reads (bits 0, 1, 5, 6 of the feature differ) lie in sixteen different places of 256 bytes.
 __device__ __forceinline__ int tap_key(int f) { return ((f >> 1) & 1) | ((f >> 4) & 6); }
 
-// STEPS: the most steps of 32 taps.  WAVES: a block's.
+// STEPS: the most steps of 32 taps.  WAVES: a block's.  IN64 (with DELTA only): no attempt in 32 bits.
 // DELTA: three waves a SIMD (with four, 128 registers spilled 22: a step with loss 2 % longer).
-template <int BITS, bool DELTA, int STEPS, int WAVES>
+template <int BITS, bool DELTA, int STEPS, int WAVES, bool IN64>
 __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 3) : 4) void fbq_quantize_kernel(const uint16_t *__restrict__ W, const uint16_t *__restrict__ At,
                                                                   const uint16_t *__restrict__ Bt, uint32_t *__restrict__ qw,
                                                                   uint16_t *__restrict__ scales, uint16_t *__restrict__ zeros, int N,
@@ -152,7 +156,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
 #pragma clang fp contract(off)
     constexpr int kRows = 16 * WAVES, kPieces = 4 * STEPS;
     // DELTA, up to 64 taps: taps[] holds their multiples of a unit and rests[] the rest (below); otherwise each wave splits what it reads
-    constexpr bool kSplitTaps = DELTA && STEPS <= 2;
+    constexpr bool kSplitTaps = DELTA && !IN64 && STEPS <= 2;
     __shared__ half8_t taps[kGroup][kPieces], rests[kSplitTaps ? kGroup : 1][kSplitTaps ? kPieces : 1];
     __shared__ uint32_t longest, straight;                                      // largest squared norm of a feature's taps; whether rows go to 64 bits without an attempt in 32
     // DELTA, by feature: what takes its taps back to At's, and its bound (below)
@@ -165,6 +169,14 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
     const int steps = (r + kQuantTapStep - 1) / kQuantTapStep;
 
     if (threadIdx.x == 0) longest = straight = 0;
+    // few blocks: what the first tile reads is asked for together with the taps
+    half8_t early[5];
+    if constexpr (IN64) {
+        const int n = min((int)blockIdx.y * tiles * kRows + 16 * wave + (lane & 15), N - 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) early[i] = *reinterpret_cast<const half8_t *>(W + (size_t)n * K + g * kGroup + 32 * (lane >> 4) + 8 * i);
+        early[4] = *reinterpret_cast<const half8_t *>(Bt + (size_t)n * r + min(8 * (lane >> 4), r - 8));
+    }
     const half_t grid = STEPS <= 4 ? (half_t)6144.0f : (half_t)12288.0f;        // 1.5 x 2^10 units: added and taken away, it leaves whole units
     const half8_t grid8 = {grid, grid, grid, grid, grid, grid, grid, grid};
     auto tap8 = [&](int f, int p) __attribute__((always_inline)) {
@@ -185,6 +197,8 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
                 taps[f][p ^ tap_key(f)] = half8_t{a[0][i], a[1][i], a[2][i], a[3][i], a[4][i], a[5][i], a[6][i], a[7][i]};
             }
         }
+    }
+    if (r > 0 && !IN64) {
         __syncthreads();
         // WAVES / 2 threads a feature, side by side
         constexpr int kSide = WAVES / 2;
@@ -232,6 +246,10 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
         for (int away = kSide; away < 64; away *= 2) most = max(most, (uint32_t)__shfl_xor((int)most, away, 64));
         if (lane == 0 && most) atomicMax(&longest, most);
     }
+    if constexpr (IN64) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) asm volatile("" :: "v"(early[i]));
+    }
     __syncthreads();
     // (the instruction aligns a subnormal operand as one of 2^-14)
     const float a_norm2 = longest ? __builtin_bit_cast(float, longest) + (float)r * 0x1p-28f : 0.0f;
@@ -253,7 +271,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
         uint32_t words[BITS], sz = 0, open_rows = (1u << max(0, min(16, rows))) - 1;
         half8_t d8[4];
         uint32_t open_delta = 0;                                                // DELTA: pairs of features with an fp16 number that 32 bits leave open, the first pair in bit 15
-        if (!__builtin_amdgcn_readfirstlane(__hip_atomic_load(&straight, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) {   // wave-uniform
+        if (!IN64 && !__builtin_amdgcn_readfirstlane(__hip_atomic_load(&straight, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) {   // wave-uniform
             half8_t w[4], b[2];
             b[0] = branch_rows(8 * q);
             b[1] = branch_rows(kQuantTapStep + 8 * q);
@@ -408,7 +426,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
         // order of the taps matters only where a sum needs more than 53 bits.
         // Many of them: all sixteen at once on the fp64 matrix instruction.  Lane (c, q) supplies tap q of four of feature 32 (c % 4) + 4 t + c / 4 and of row c, and ends up
         // with the features 32 q + 4 t .. + 3 of row c, as above.  (An open row takes a quarter of the time of all sixteen.)
-        const bool many = __builtin_popcount(open_rows) > kFewOpen;
+        const bool many = IN64 || __builtin_popcount(open_rows) > kFewOpen;
         if (many) {
             int lane_here = lane;                                                // (as above)
             asm volatile("" : "+v"(lane_here));
@@ -445,7 +463,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
             for (int t = 0; t < 8; ++t) {
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) R[t][v] = (double)(float)w[t >> 1][4 * (t & 1) + v] - (DELTA ? R[t][v] * (double)tap_back[32 * q + 4 * t + v] : R[t][v]);
+                for (int v = 0; v < 4; ++v) R[t][v] = (double)(float)w[t >> 1][4 * (t & 1) + v] - (DELTA && !IN64 ? R[t][v] * (double)tap_back[32 * q + 4 * t + v] : R[t][v]);
             }
             double lo = R[0][0], hi = R[0][0];
 #pragma unroll
@@ -475,7 +493,7 @@ __global__ __launch_bounds__(64 * WAVES, DELTA ? (WAVES == 8 || STEPS > 4 ? 2 : 
             pack_codes<BITS>(x, words);
             sz = found;
             // (rows of one layer are alike; a wave that sees it late finds the same)
-            if (lane == 0 && __builtin_popcount(open_rows) > 8) __hip_atomic_store(&straight, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (!IN64 && lane == 0 && __builtin_popcount(open_rows) > 8) __hip_atomic_store(&straight, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             open_rows = 0xFFFFu;                                                 // (the others come out as they were)
         }
         // A few: one by one, two features a lane.
@@ -623,11 +641,12 @@ hipError_t launch_quantize(const fbq_desc &d, const uint16_t *W, const uint16_t 
     const int rows = wide ? 128 : 64, blocks = G * ceil_div(d.N, rows);
     const int tiles = d.r > 0 && blocks >= (wide ? 1024 : 2048) ? 2 : 1;
     const dim3 grid(G, ceil_div(d.N, rows * tiles));
-#define FBQ_QUANT(B, D, S, V) hipLaunchKernelGGL((fbq_quantize_kernel<B, D, S, V>), grid, dim3(64 * V), 0, stream, W, At, Bt, qw, scales, zeros, d.N, d.K, d.r, words, D16, gain, tiles)
-#define FBQ_QUANT_R(B, D) do { if (wide) FBQ_QUANT(B, D, 8, 8); \
-                               else if (d.r <= 64) FBQ_QUANT(B, D, 2, 4); else if (d.r <= 128) FBQ_QUANT(B, D, 4, 4); else FBQ_QUANT(B, D, 8, 4); } while (0)
-    if (d.bits == 4) { if (D16) FBQ_QUANT_R(4, true); else FBQ_QUANT_R(4, false); }
-    else { if (D16) FBQ_QUANT_R(3, true); else FBQ_QUANT_R(3, false); }
+    const bool all_in_64 = blocks <= 256;                                        // (a CU each: see the head of the file)
+#define FBQ_QUANT(B, D, S, V, I) hipLaunchKernelGGL((fbq_quantize_kernel<B, D, S, V, I>), grid, dim3(64 * V), 0, stream, W, At, Bt, qw, scales, zeros, d.N, d.K, d.r, words, D16, gain, tiles)
+#define FBQ_QUANT_R(B, D, I) do { if (wide) FBQ_QUANT(B, D, 8, 8, false); \
+                                  else if (d.r <= 64) FBQ_QUANT(B, D, 2, 4, I); else if (d.r <= 128) FBQ_QUANT(B, D, 4, 4, I); else FBQ_QUANT(B, D, 8, 4, I); } while (0)
+    if (d.bits == 4) { if (D16 && all_in_64) FBQ_QUANT_R(4, true, true); else if (D16) FBQ_QUANT_R(4, true, false); else FBQ_QUANT_R(4, false, false); }
+    else { if (D16 && all_in_64) FBQ_QUANT_R(3, true, true); else if (D16) FBQ_QUANT_R(3, true, false); else FBQ_QUANT_R(3, false, false); }
 #undef FBQ_QUANT_R
 #undef FBQ_QUANT
     return hipGetLastError();
