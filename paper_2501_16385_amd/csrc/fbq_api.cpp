@@ -223,6 +223,7 @@ fbq_status check_layer(const fbq_desc *d, int M, const void *x, const void *qwei
     a->y = (uint16_t *)y;
     a->workspace = workspace;
     a->workspace_need = a->split ? fbq_workspace_bytes(d, M) : need;
+    a->unsplit_need = need;
     a->M = M; a->N = d->N; a->K = d->K; a->r = d->r; a->bits = d->bits;
     a->mix_with = nullptr; a->mix_out = nullptr;
     return FBQ_OK;
@@ -346,17 +347,24 @@ static fbq_status linear_group(const fbq_layer_call *calls, const fbq_mix *mix, 
         args[i].mix_with = (const uint16_t *)mix[i].with;
         args[i].mix_out = (uint16_t *)mix[i].out;
     }
+    // A layer whose room for partial sums meets another layer's workspace goes unsplit: what such calls did before K was split, sharing nothing
+    // that they needed, they still do.
+    const auto meet = [&](int i, int j) {
+        return args[i].workspace_need && args[j].workspace_need && overlap(args[i].workspace, args[i].workspace_need, args[j].workspace, args[j].workspace_need);
+    };
+    bool unsplit[kMaxCalls] = {false};
+    for (int i = 0; i < n; ++i)
+        for (int j = 0; j < n; ++j) unsplit[i] = unsplit[i] || (i != j && args[i].split && meet(i, j));
+    for (int i = 0; i < n; ++i) {
+        if (!unsplit[i]) continue;
+        args[i].split = false;
+        args[i].workspace_need = args[i].unsplit_need;
+    }
     // Layers that share a launch carry the same launch tag: two of them writing their hand-over words into the same
     // memory would accept each other's t.  Workspaces must not overlap.
-    for (int i = 0; i < n; ++i) {
-        const size_t ni = args[i].workspace_need;
-        const uintptr_t ai = (uintptr_t)args[i].workspace;
-        for (int j = 0; j < i && ni; ++j) {
-            const size_t nj = args[j].workspace_need;
-            const uintptr_t aj = (uintptr_t)args[j].workspace;
-            if (nj && ai < aj + nj && aj < ai + ni) return FBQ_ERR_WORKSPACE;
-        }
-    }
+    for (int i = 0; i < n; ++i)
+        for (int j = 0; j < i; ++j)
+            if (meet(i, j)) return FBQ_ERR_WORKSPACE;
     if (mix && mix_tensors_overlap(args, n)) return FBQ_ERR_UNSUPPORTED;
     hipError_t e = hipSuccess;
     if (M > kDecodeMaxM) {

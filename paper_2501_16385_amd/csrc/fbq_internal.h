@@ -45,7 +45,8 @@ struct LinearArgs {
     const uint16_t *x;
     uint16_t *y;
     void *workspace;  // see decode_workspace_bytes / small_m_workspace_bytes / prefill_workspace_bytes
-    size_t workspace_need;   // fbq_workspace_bytes of the call (above 64 tokens a search, so looked up once)
+    size_t workspace_need;   // fbq_workspace_bytes of the call (above 64 tokens a search, so looked up once) ...
+    size_t unsplit_need;     // ... and of the same call with K unsplit
     int M, N, K, r, bits;
     const uint16_t *mix_with;   // [M][N] and ...
     uint16_t *mix_out;          // ... null, or [M][N] that the decode launchers write y averaged with mix_with to (see launch_mix)

@@ -112,3 +112,55 @@ def test_grouped_layers_share_a_launch(recorder):
     for call, names in zip(one + two, launches):
         assert len(names) == (1 if call in one else 2), (call, names)
         assert any("few_stream" in n for n in names) == any(N >= 10240 for N in call[3]), (call, names)
+
+
+SPLIT_CHILD = r"""
+import ctypes, json, sys
+sys.path[:0] = [sys.argv[1]]
+import paper_2501_16385_amd as fbq
+lib = fbq.load()
+launched = []
+
+@ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_char_p, ctypes.POINTER(ctypes.c_void_p))
+def on_launch(name, args):
+    launched.append(name.decode())
+    return 0
+
+ctypes.CDLL(None).recorder_set_callback(on_launch)
+out = []
+for M, layers in json.loads(sys.argv[2]):
+    p = lambda i, j: 0x100000000 * (10 * i + j + 2)
+    arr = (fbq.fbq._CLayerCall * len(layers))(*(fbq.fbq._CLayerCall(fbq.Desc(N, K, r, bits).c(), 0x100000000, p(i, 0), p(i, 1), p(i, 2), p(i, 3), p(i, 4), p(i, 5), at, size)
+                                                for i, (N, K, r, bits, at, size) in enumerate(layers)))
+    launched.clear()
+    rc = lib.fbq_linear_group(arr, len(layers), M, None)
+    out.append([rc, [sum(k in n for n in launched) for k in ("few_split_kernel", "few_join_kernel", "small_m", "few_stream")], len(launched)])
+print("RESULT " + json.dumps(out))
+"""
+
+
+def test_room_for_partial_sums_that_meets_another_workspace_is_not_used(recorder):
+    """Workspaces may not overlap in what the layers cannot do without, as ever; where only the room for partial sums would, those layers go unsplit."""
+    import json
+    BIG, AT = 1 << 30, 0x9000000000
+    words = lambda r: 17 * 16 * r * 8
+    split, plain = [1, 1, 0, 0], [0, 0, 1, 0]
+    cases = [
+        # one scratch for two layers that need none; the same for three sets; hand-over areas one behind the other, each with the rest of the arena as its size
+        (16, [(8192, 28672, 0, 4, AT, BIG)] * 2, 0, plain), (48, [(5120, 13824, 0, 3, AT, BIG)] * 2, 0, None),
+        (8, [(4096, 28672, 64, 4, AT, BIG), (8192, 28672, 64, 4, AT + words(64), BIG - words(64))], 0, plain),
+        # a third layer elsewhere keeps its split; a small layer's words inside a split layer's room; one that needs nothing does not count
+        (8, [(4096, 28672, 64, 4, AT, BIG), (8192, 28672, 64, 4, AT + words(64), BIG), (2048, 28672, 64, 4, 2 * AT, BIG)], 0, [1, 1, 1, 0]),
+        (8, [(4096, 28672, 64, 4, AT, BIG), (1024, 28672, 64, 4, AT + (1 << 20), words(64))], 0, [0, 0, 1, 0]),
+        (8, [(4096, 28672, 0, 4, AT, BIG), (1024, 28672, 0, 4, AT, BIG)], 0, [1, 1, 1, 0]),
+        # apart: both split, in one launch
+        (16, [(8192, 28672, 0, 4, AT, BIG), (8192, 28672, 0, 4, 2 * AT, BIG)], 0, split),
+        # and what never went: the same hand-over words, or words that begin inside another layer's
+        (16, [(8192, 28672, 64, 4, AT, BIG)] * 2, 5, [0, 0, 0, 0]), (8, [(4096, 28672, 64, 4, AT, BIG), (4096, 28672, 64, 4, AT + words(64) - 16, BIG)], 5, [0, 0, 0, 0]),
+    ]
+    env = dict(os.environ, LD_PRELOAD=" ".join([recorder] + os.environ.get("LD_PRELOAD", "").split()))
+    res = subprocess.run([sys.executable, "-c", SPLIT_CHILD, ROOT, json.dumps([c[:2] for c in cases])], env=env, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
+    for (M, layers, want_rc, want), (rc, kinds, count) in zip(cases, json.loads(res.stdout.split("RESULT ")[1])):
+        assert rc == want_rc, (M, layers, rc)
+        assert kinds == want if want is not None else kinds[0] == 0 and count > 0, (M, layers, kinds)
