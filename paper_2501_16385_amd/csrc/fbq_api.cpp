@@ -105,21 +105,22 @@ static size_t least_workspace(const fbq_desc *d, int M)
     return handover_reserve(d->K, d->r) + prefill_workspace_bytes(M, d->N, d->K, d->r);      // holds the re-ordered activations even when r == 0
 }
 
-// Room for 16 tokens' partial sums where K is split, whatever the number of sets, and behind it the hand-over words.
-static size_t split_set_bytes(const fbq_desc *d)
+// How K is split for a call (segments 0: not), and the workspace that takes: the hand-over words' room and the partial sums, or what the call needs without.
+static FewSplit split_of(const fbq_desc *d, int M)
 {
-    size_t most = 0;
-    for (int sets = 1; sets <= kMaxSmallGroup; ++sets) most = std::max(most, few_split_bytes(sets, d->N, d->K, d->r, d->bits) / sets);
-    return most + handover_reserve(d->K, d->r);
+    return takes_split(M, d->N, d->K) ? few_split(ceil_div(M, kDecodeMaxM), d->N, d->K, d->r, d->bits) : FewSplit{0, 0};
+}
+static size_t split_workspace(const fbq_desc *d, int M, const FewSplit &f, size_t least)
+{
+    return std::max(least, handover_reserve(d->K, d->r) + few_split_bytes(f, ceil_div(M, kDecodeMaxM), d->N, d->r));
 }
 
 extern "C" size_t fbq_workspace_bytes(const fbq_desc *d, int M)
 {
     const size_t least = least_workspace(d, M);
-    if (fbq_check_desc(d) != FBQ_OK || M < 1 || !takes_split(M, d->N, d->K)) return least;
-    const int sets = (M + kDecodeMaxM - 1) / kDecodeMaxM;
-    if (M <= kDecodeMaxM || takes_sets(M, d->N, d->K)) return least + sets * split_set_bytes(d);   // (as for the sets: so many times that of 16 tokens, where these take it too)
-    return std::max(least, handover_reserve(d->K, d->r) + few_split_bytes(sets, d->N, d->K, d->r, d->bits));
+    if (fbq_check_desc(d) != FBQ_OK || M < 1) return 0;
+    const FewSplit f = split_of(d, M);
+    return f.segments ? split_workspace(d, M, f, least) : least;
 }
 
 // ------------------------------------------------------------------ host-side packing
@@ -212,8 +213,10 @@ fbq_status check_layer(const fbq_desc *d, int M, const void *x, const void *qwei
     if (d->r > 0 && (misaligned(At) || misaligned(Bt))) return FBQ_ERR_ALIGN;
     if (need > 0 && misaligned(workspace)) return FBQ_ERR_ALIGN;
     if (workspace_bytes < need) return FBQ_ERR_WORKSPACE;
-    // (a workspace of the size that was enough before K was split is still accepted, and served without the split)
-    a->split = takes_split(M, d->N, d->K) && workspace && !misaligned(workspace) && workspace_bytes >= fbq_workspace_bytes(d, M);
+    // (a workspace without room for the partial sums is accepted, and served without the split)
+    a->split = split_of(d, M);
+    const size_t whole = a->split.segments ? split_workspace(d, M, a->split, need) : need;
+    if (!workspace || misaligned(workspace) || workspace_bytes < whole) a->split = {0, 0};
     a->qw = (const uint32_t *)qweight;
     a->scales = (const uint16_t *)scales;
     a->zeros = (const uint16_t *)zeros;
@@ -222,7 +225,7 @@ fbq_status check_layer(const fbq_desc *d, int M, const void *x, const void *qwei
     a->x = (const uint16_t *)x;
     a->y = (uint16_t *)y;
     a->workspace = workspace;
-    a->workspace_need = a->split ? fbq_workspace_bytes(d, M) : need;
+    a->workspace_need = a->split.segments ? whole : need;
     a->unsplit_need = need;
     a->M = M; a->N = d->N; a->K = d->K; a->r = d->r; a->bits = d->bits;
     a->mix_with = nullptr; a->mix_out = nullptr;
@@ -245,7 +248,7 @@ static hipError_t launch_prefill(const LinearArgs &call, hipStream_t s)
 hipError_t launch_one(const LinearArgs &a, hipStream_t s)
 {
     if (a.M <= kPerTokenMaxM) return launch_gemv_decode(&a, 1, s);
-    if (a.split) return launch_few_split(&a, 1, s);
+    if (a.split.segments) return launch_few_split(&a, 1, s);
     if (a.M <= kDecodeMaxM) return launch_gemv_small_m(&a, 1, s);
     if (a.M <= kChunkedMaxM && takes_sets(a.M, a.N, a.K)) {
         static_assert(kChunkedMaxM <= kMaxSmallGroup * kDecodeMaxM, "the sets of 16 tokens must fit one grouped launch");
@@ -289,7 +292,7 @@ extern "C" fbq_status fbq_linear_unfused(const fbq_desc *d, int M, const void *x
     hipStream_t s = (hipStream_t)stream;
     LinearArgs main_path = a;                           // the quantized layer without its sub-branch ...
     main_path.r = 0; main_path.At = nullptr; main_path.Bt = nullptr;
-    main_path.split = false;                            // (in one launch)
+    main_path.split = {0, 0};                           // (in one launch)
     hipError_t e = launch_one(main_path, s);
     if (e == hipSuccess && d->r > 0) e = launch_unfused_branch(a, (uint16_t *)workspace, s);   // ... and the sub-branch on top
     return hip_status(e);
@@ -354,10 +357,10 @@ static fbq_status linear_group(const fbq_layer_call *calls, const fbq_mix *mix, 
     };
     bool unsplit[kMaxCalls] = {false};
     for (int i = 0; i < n; ++i)
-        for (int j = 0; j < n; ++j) unsplit[i] = unsplit[i] || (i != j && args[i].split && meet(i, j));
+        for (int j = 0; j < n; ++j) unsplit[i] = unsplit[i] || (i != j && args[i].split.segments && meet(i, j));
     for (int i = 0; i < n; ++i) {
         if (!unsplit[i]) continue;
-        args[i].split = false;
+        args[i].split = {0, 0};
         args[i].workspace_need = args[i].unsplit_need;
     }
     // Layers that share a launch carry the same launch tag: two of them writing their hand-over words into the same
@@ -386,12 +389,12 @@ static fbq_status linear_group(const fbq_layer_call *calls, const fbq_mix *mix, 
         LinearArgs batch[kMaxGroup];
         int nb = 0;
         for (int j = i; j < n && nb < cap; ++j) {
-            if (!done[j] && (few ? args[j].split == args[i].split && small_m_group_compatible(args[i], args[j]) : decode_group_compatible(args[i], args[j]))) {
+            if (!done[j] && (few ? !args[j].split.segments == !args[i].split.segments && small_m_group_compatible(args[i], args[j]) : decode_group_compatible(args[i], args[j]))) {
                 batch[nb++] = args[j];
                 done[j] = true;
             }
         }
-        e = !few ? launch_gemv_decode(batch, nb, s) : batch[0].split ? launch_few_split(batch, nb, s) : launch_gemv_small_m(batch, nb, s);
+        e = !few ? launch_gemv_decode(batch, nb, s) : batch[0].split.segments ? launch_few_split(batch, nb, s) : launch_gemv_small_m(batch, nb, s);
     }
     return hip_status(e);
 }

@@ -412,7 +412,7 @@ hipError_t launch_few_split(const LinearArgs *layers, int n_layers, hipStream_t 
     int blocks = 0, joins = 0;
     for (int i = 0; i < n_layers; ++i) {
         const LinearArgs &a = layers[i];
-        const FewSplit f = few_split(sets, a.N, a.K, a.r, a.bits);
+        const FewSplit f = a.split;
         SplitParams &p = g.layer[i];
         p.qw = a.qw; p.scales = a.scales; p.zeros = a.zeros; p.At = a.At; p.x = a.x;
         p.part = (float4_t *)((char *)a.workspace + handover_reserve(a.K, a.r));

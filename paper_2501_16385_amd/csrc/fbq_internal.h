@@ -36,6 +36,9 @@ int spin_limit();
 // Words per packed row.
 inline size_t row_words(int K, int bits) { return (size_t)K * bits / 32; }
 
+// Segments of K, 0: not split, and the groups each of a block's eight waves takes of one (fbq_few_split.hip).
+struct FewSplit { int segments, share; };
+
 struct LinearArgs {
     const uint32_t *qw;
     const uint16_t *scales;
@@ -50,7 +53,7 @@ struct LinearArgs {
     int M, N, K, r, bits;
     const uint16_t *mix_with;   // [M][N] and ...
     uint16_t *mix_out;          // ... null, or [M][N] that the decode launchers write y averaged with mix_with to (see launch_mix)
-    bool split;                 // 3 to 64 tokens: K is split over blocks (see takes_split), and the workspace has room for it
+    FewSplit split;             // 3 to 64 tokens: how K is split over blocks (see takes_split), where the workspace has room for it
 };
 
 // 3 to 16 tokens: which of the two kernels serves a layer of N rows (for sets of 16 tokens side by side: rows times sets).  Of

@@ -9,7 +9,6 @@ namespace fbq {
 constexpr int kSplitCus = 256;           // (the workspace is sized without a device)
 constexpr int kSplitTapCost = 5;         // a tile of 16 taps in tiles of 16 rows: fp16 against codes of 3 or 4 bits
 
-struct FewSplit { int segments, share; };                                // segments of K, and the groups each of a block's eight waves takes of one
 struct FewSplitRuns { int tap_blocks, taps, row_blocks, units; };        // per segment: blocks for A^T, their tiles of 16 taps, blocks for rows, their units of rows
 
 inline int few_split_unit_rows(int sets) { return sets <= 2 ? 16 : 32; }
@@ -52,10 +51,7 @@ inline FewSplit few_split(int sets, int N, int K, int r, int bits)
 }
 
 // Bytes of partial sums.
-inline size_t few_split_bytes(int sets, int N, int K, int r, int bits)
-{
-    return (size_t)few_split(sets, N, K, r, bits).segments * sets * (ceil_div(N, 16) + ceil_div(r, 16)) * 1024;
-}
+inline size_t few_split_bytes(const FewSplit &f, int sets, int N, int r) { return (size_t)f.segments * sets * (ceil_div(N, 16) + ceil_div(r, 16)) * 1024; }
 
 }  // namespace fbq
 

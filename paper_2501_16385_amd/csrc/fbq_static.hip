@@ -54,6 +54,6 @@ extern "C" fbq_status fbq_linear_static(const fbq_desc *d, int M, const void *x,
     st = scratch_on_current_device(&ws);
     if (st != FBQ_OK) return st;
     a.workspace = ws;
-    a.split = false;                                     // (no room for partial sums)
+    a.split = {0, 0};                                    // (no room for partial sums)
     return hip_status(launch_one(a, (hipStream_t)stream));
 }

@@ -11,7 +11,7 @@ int main()
     while (std::cin >> sets >> N >> K >> r >> bits >> slots) {
         const fbq::FewSplit f = fbq::few_split(sets, N, K, r, bits);
         const fbq::FewSplitRuns u = fbq::few_split_runs(sets, N, r, slots > 0 ? slots : std::max(1, fbq::kSplitCus / f.segments));
-        printf("%d %d %d %d %d %d %zu\n", f.segments, f.share, u.tap_blocks, u.taps, u.row_blocks, u.units, fbq::few_split_bytes(sets, N, K, r, bits));
+        printf("%d %d %d %d %d %d %zu\n", f.segments, f.share, u.tap_blocks, u.taps, u.row_blocks, u.units, fbq::few_split_bytes(f, sets, N, r));
     }
     return 0;
 }

