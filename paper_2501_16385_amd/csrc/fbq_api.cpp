@@ -76,19 +76,30 @@ size_t handover_reserve(int K, int r)
 }
 }  // namespace fbq
 
-// Whether a call of 3 to 64 tokens has its K split over blocks (fbq_few_split.hip) instead of going where it would go otherwise.  us, otherwise / split.
-// Up to 16 tokens: from 14336 activations on and between 2048 and 10240 rows: 28672 -> 2048 INT4, r = 64, 16 tokens 20.8 / 14.6, -> 4096 25.3 / 20.2, -> 8192
-// 42.8 / 34.3; 14336 -> 4096 INT3, 8 tokens 16.3 / 15.2, -> 8192, 16 tokens 21.2 / 21.4; on the other side 11008 -> 4096 INT3, 8 tokens 13.5 / 14.1, 8320 -> 4096, r =
-// 200, 14.4 / 17.6.  (Wider layers stream; narrower ones share launches with them.)
-// 17 to 64: instead of sets of 16 with more than 8192 activations and 25 million codes: 13824 -> 5120 INT4, r = 128, 17 tokens 28.1 / 22.1, 64 40.0 / 26.0; 11008 ->
-// 4096 INT3 at 32 18.3 / 17.8, at 48 23.9 / 19.5; 14336 -> 2000 at 32 14.9 / 14.6; but 8320 -> 1000 at 32 10.7 / 13.4.  Instead of the GEMM from 2048
-// activations on: 4096 -> 28672 INT3 at 48 33.9 / 26.3, 20480 -> 9000 at 64 52.3 / 46.8, 6144 -> 20000 at 64 53.2 / 40.5, 2048 -> 28000 at 64 26.7 / 25.7; but
-// 1024 -> 28672 at 48 20.9 / 21.7, at 64 21.2 / 25.7.
-static bool takes_split(int M, int N, int K)
+// How a call of 3 to 64 tokens has its K split over blocks (fbq_few_split.hip) instead of going where it would go otherwise; segments 0: not at all.  Times of the split
+// over those of the other way, r = 64, INT3 and INT4.
+// Up to 16 tokens, instead of streaming or bursts: above 16384 activations, from 2048 to 10239 rows: 28672 -> 2048 0.62 to 0.72, -> 8192 0.76 to 0.95; 17408 -> 2048 to 10000 0.82 to 1.03; but
+// 16384 -> 2500 1.06 to 1.19, 14336 -> 6000 INT4 1.1.  (Wider layers stream; narrower ones share launches with them.)
+// Instead of sets of 16, above 8192 activations and from 25 million codes on: three and four sets 0.65 to 1.0; two sets where they take four passes, above 12288: 13824 -> 2304 to 8192 0.77 to 0.97; below
+// that from 4600 rows on: 8320 -> 4700 0.82 to 0.90, 10240 -> 5120 0.95 to 1.01, 11008 -> 8192 0.88; but 11008 -> 2304 1.16, -> 4096 1.04; with one or two tokens left over, which the sets take one by one, from 3400: 8320 to 12288
+// -> 3500 0.80 to 0.86, -> 3001 0.88 to 1.03.
+// Instead of the GEMM, from 2048 activations on, up to the rows whose partial sums, written and read once a segment, cost what is saved.  Two sets 44000 rows: 2048 -> 28000 0.82, 34000 0.94, 44000 0.98, 52000 1.08
+// (long rows at any N: 20480 -> 52000 0.57); three sets 46000, less as the segments are less full: 2048 -> 44000 0.98, 52000 1.04; 2176 -> 24000 (full 17/32) 0.97, 28000 1.02, 34000 1.17; 4224 -> 28000 0.93, 44000 1.17;
+// four sets 35000 likewise, 30000 where there is one segment: 2048 -> 28000 0.96, 34000 1.06; 2304 -> 20000 0.94, 28000 1.15; 3072 -> 28000 0.96, 34000 1.1; 4224 -> 24000 1.0, 34000 1.15; 8192 -> 34000 0.84, 64000 1.1.  And
+// 1024 -> 28672 at 48 tokens 20.9 us against 21.7 split.
+static FewSplit split_of(const fbq_desc *d, int M)
 {
-    if (M <= kPerTokenMaxM || M > kChunkedMaxM) return false;
-    if (M <= kDecodeMaxM) return K >= 14336 && N >= 2048 && N < 10240;
-    return takes_sets(M, N, K) ? K > 8192 && (long)N * K >= 25000000L : K >= 2048;
+    const FewSplit none{0, 0};
+    const int N = d->N, K = d->K, G = K / kGroup, sets = ceil_div(M, kDecodeMaxM);
+    if (M <= kPerTokenMaxM || M > kChunkedMaxM) return none;
+    const bool few = M <= kDecodeMaxM, instead_of_sets = !few && takes_sets(M, N, K);
+    if (few ? K <= 16384 || N < 2048 || N >= 10240 : K < (instead_of_sets ? 8193 : 2048) || (instead_of_sets && (long)N * K < 25000000L)) return none;
+    const FewSplit f = few_split(sets, N, K, d->r, d->bits);
+    const double full = G / (8.0 * f.share * f.segments);       // of what the waves could hold, what there is of K
+    if (few) return f;
+    if (instead_of_sets) return sets > 2 || K > 12288 || N >= (M <= kDecodeMaxM + kPerTokenMaxM ? 3400 : 4600) ? f : none;
+    if (sets == 2) return K > 8192 || N <= 44000 ? f : none;
+    return N <= (sets == 3 ? 46000 : K == 2048 ? 30000 : 35000) * full ? f : none;
 }
 
 // What a call cannot do without.
@@ -105,11 +116,7 @@ static size_t least_workspace(const fbq_desc *d, int M)
     return handover_reserve(d->K, d->r) + prefill_workspace_bytes(M, d->N, d->K, d->r);      // holds the re-ordered activations even when r == 0
 }
 
-// How K is split for a call (segments 0: not), and the workspace that takes: the hand-over words' room and the partial sums, or what the call needs without.
-static FewSplit split_of(const fbq_desc *d, int M)
-{
-    return takes_split(M, d->N, d->K) ? few_split(ceil_div(M, kDecodeMaxM), d->N, d->K, d->r, d->bits) : FewSplit{0, 0};
-}
+// The workspace of a split call: the hand-over words' room and the partial sums, or what it needs without the split.
 static size_t split_workspace(const fbq_desc *d, int M, const FewSplit &f, size_t least)
 {
     return std::max(least, handover_reserve(d->K, d->r) + few_split_bytes(f, ceil_div(M, kDecodeMaxM), d->N, d->r));

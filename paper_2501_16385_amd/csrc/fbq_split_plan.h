@@ -39,6 +39,10 @@ inline FewSplit few_split(int sets, int N, int K, int r, int bits)
     for (int segments = least; segments <= least + 2; ++segments) {
         const FewSplit f{segments, ceil_div(G, 8 * segments)};
         if (ceil_div(G, 8 * f.share) != segments) continue;      // (a segment would be empty)
+        // A unit half empty costs what a full one does: 2560 -> 28000 INT4, 64 tokens, in three segments with one group a wave 43.0 us, in two with two 33.6; 10240 -> 5120 INT4, 32 tokens,
+        // five with two 20.6, four with three 19.7.  (Groups dealt out evenly over segments and waves, up to 16 % fewer to the longest, are no better with three and four sets, and with fewer
+        // worse: 8320 -> 8192, 32 tokens, 1.05 of the time of the sets instead of 0.86.)
+        if (2 * f.share <= most && segments > least) continue;
         const FewSplitRuns runs = few_split_runs(sets, N, r, std::max(1, kSplitCus / segments));
         const double rounds = ceil_div(segments * (runs.tap_blocks + runs.row_blocks), kSplitCus);
         const double tile_bytes = 16.0 * 8 * f.share * (16.0 * bits + 4);

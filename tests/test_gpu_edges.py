@@ -6,6 +6,7 @@ import pytest
 
 import fbq_synth
 from helpers import assert_matches_oracle, framed_in_nan, framed_layer, gpu_y, make_oracle_layer
+from few_cases import SETS_OR_GEMM_CASES, SPLIT_CASES
 from oracle import fbq_oracle as orc
 from prefill_cases import CUT_CASES, ORDER_CASES
 
@@ -386,24 +387,10 @@ def test_stream_edges(bits, N, K, r, M):
     assert np.array_equal(y, gpu_y(dev, x_np))
 
 
-SETS_OR_GEMM_CASES = [
-    # N, K, r, M, whether the sets of 16 take it.  The shortest and the longest rows that two and four sets take beyond the GEMM's
-    # old line, and one group of 128 past either
-    (40001, 3072, 40, 17, True), (40001, 2944, 40, 17, False),
-    (20001, 8192, 0, 32, True), (20001, 8320, 0, 32, False),
-    (8543, 8192, 72, 64, True), (8545, 8320, 72, 64, False),
-    # either side of 70 million codes at four sets; three sets; a rank above 128
-    (17089, 4096, 136, 50, True), (17091, 4096, 136, 50, False),
-    (28673, 8192, 16, 18, True), (28673, 8192, 16, 33, False),
-    # one or two tokens left over as a set, and beside two sets
-    (5121, 5120, 24, 33, True), (5121, 5120, 24, 34, True), (4097, 14336, 96, 49, True),
-]
-
-
 @pytest.mark.parametrize("bits", [4, 3])
-@pytest.mark.parametrize("N,K,r,M,sets", SETS_OR_GEMM_CASES)
-def test_sets_or_gemm_edges(bits, N, K, r, M, sets):
-    """Each within the bound of the path that takes it (the sets multiply the codes exactly, the GEMM rounds every weight to fp16: the
+@pytest.mark.parametrize("N,K,r,M,way", SETS_OR_GEMM_CASES)
+def test_sets_or_gemm_edges(bits, N, K, r, M, way):
+    """Each within the bound of the path that takes it (sets and split multiply the codes exactly, the GEMM rounds every weight to fp16: the
     two bounds beside ELEMENT_SLACK), also with a workspace that calls of other token counts have used."""
     import torch
     import paper_2501_16385_amd as fbq
@@ -413,7 +400,7 @@ def test_sets_or_gemm_edges(bits, N, K, r, M, sets):
     del W
     x_np = x.cpu().view(torch.int16).numpy().view(np.float16)
     y = gpu_y(dev, x_np)
-    assert_matches_oracle(y, want, f"INT{bits} {N}x{K} r={r} M={M}", "few" if sets else "prefill")
+    assert_matches_oracle(y, want, f"INT{bits} {N}x{K} r={r} M={M}", "prefill" if way == "gemm" else "few")
     x65 = torch.randn(65, K, device="cuda", generator=g).half()
     ws = torch.zeros(max(fbq.workspace_bytes(dev.desc, m) for m in (65, M, 16, 2)), dtype=torch.uint8, device="cuda")
     for other in (x65, x65[:16], x65[:2], x):
@@ -582,15 +569,6 @@ def test_stream_behind_the_other_entry_points(N, K, r, M, bits):
     assert float(miss) <= 1.5e-3, float(miss)
 
 
-SPLIT_CASES = [
-    # N, K, r, M: one to four sets, a token more or less than whole ones; last segments of one group; odd numbers of scales; a row more than whole
-    # tiles and units; no sub-branch, ranks on both sides of 16, 32 and 128; the shortest and the longest rows
-    (2048, 14336, 8, 3), (2049, 14464, 0, 8), (4099, 28672, 200, 16), (10239, 16384, 40, 9),
-    (3001, 8448, 72, 17), (2100, 14336, 0, 32), (5121, 13824, 136, 33), (3001, 8448, 8, 48), (4097, 14336, 256, 64),
-    (28673, 2048, 16, 50), (28001, 2176, 40, 49), (30001, 2176, 0, 20), (1025, 32768, 24, 63),
-]
-
-
 @pytest.mark.parametrize("bits", [4, 3])
 @pytest.mark.parametrize("N,K,r,M", SPLIT_CASES)
 def test_split_edges(bits, N, K, r, M):
@@ -628,7 +606,7 @@ def test_split_group_average_and_replayed_graph(bits, M):
     from paper_2501_16385_amd.random_layers import random_layer
     g = torch.Generator(device="cuda")
     g.manual_seed(121 + M)
-    K, shapes = 14336, [(2049, 8), (4100, 72), (1000, 16), (2304, 0)]
+    K, shapes = 17408, [(2049, 8), (4100, 72), (1000, 16), (2304, 0)]
     devs = [framed_layer(random_layer(fbq.Desc(N, K, r, bits), g, gain=1.0)) for N, r in shapes]
     x = torch.randn(M, K, device="cuda", generator=g).half()
     with_ = [torch.randn(M, N, device="cuda", generator=g).half() for N, _ in shapes]

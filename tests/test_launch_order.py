@@ -134,7 +134,7 @@ for M, layers in json.loads(sys.argv[2]):
                                                 for i, (N, K, r, bits, at, size) in enumerate(layers)))
     launched.clear()
     rc = lib.fbq_linear_group(arr, len(layers), M, None)
-    out.append([rc, [sum(k in n for n in launched) for k in ("few_split_kernel", "few_join_kernel", "small_m", "few_stream")], len(launched)])
+    out.append([rc, [sum(k in n for n in launched) for k in ("few_split_kernel", "few_join_kernel", "small_m", "few_stream", "fbq_gemm_kernel", "fbq_gemv_kernel")], len(launched)])
 print("RESULT " + json.dumps(out))
 """
 
@@ -144,7 +144,7 @@ def test_room_for_partial_sums_that_meets_another_workspace_is_not_used(recorder
     import json
     BIG, AT = 1 << 30, 0x9000000000
     words = lambda r: 17 * 16 * r * 8
-    split, plain = [1, 1, 0, 0], [0, 0, 1, 0]
+    split, plain = [1, 1, 0, 0], [0, 0, 1, 0]     # few_split, few_join, small_m, few_stream
     cases = [
         # one scratch for two layers that need none; the same for three sets; hand-over areas one behind the other, each with the rest of the arena as its size
         (16, [(8192, 28672, 0, 4, AT, BIG)] * 2, 0, plain), (48, [(5120, 13824, 0, 3, AT, BIG)] * 2, 0, None),
@@ -163,7 +163,7 @@ def test_room_for_partial_sums_that_meets_another_workspace_is_not_used(recorder
     assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
     for (M, layers, want_rc, want), (rc, kinds, count) in zip(cases, json.loads(res.stdout.split("RESULT ")[1])):
         assert rc == want_rc, (M, layers, rc)
-        assert kinds == want if want is not None else kinds[0] == 0 and count > 0, (M, layers, kinds)
+        assert kinds[:4] == want if want is not None else kinds[0] == 0 and count > 0, (M, layers, kinds)
 
 
 def test_a_workspace_with_room_for_the_partial_sums_is_used(recorder):
@@ -181,3 +181,19 @@ def test_a_workspace_with_room_for_the_partial_sums_is_used(recorder):
     assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
     for i, (rc, kinds, _) in enumerate(json.loads(res.stdout.split("RESULT ")[1])):
         assert rc == 0 and kinds[0] == kinds[1] == (1 - i % 2), (cases[i], rc, kinds)
+
+
+def test_which_way_a_call_of_few_tokens_takes(recorder):
+    import json
+    from few_cases import ROUTE_CASES
+    AT = 0x9000000000
+    env = dict(os.environ, LD_PRELOAD=" ".join([recorder] + os.environ.get("LD_PRELOAD", "").split()))
+    for bits in (3, 4):
+        calls = [(M, [(N, K, r, bits, AT, 1 << 32)]) for N, K, r, M, _ in ROUTE_CASES]
+        res = subprocess.run([sys.executable, "-c", SPLIT_CHILD, ROOT, json.dumps(calls)], env=env, capture_output=True, text=True, timeout=300)
+        assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
+        for (N, K, r, M, way), (rc, (split, join, small, stream, gemm, gemv), _) in zip(ROUTE_CASES, json.loads(res.stdout.split("RESULT ")[1])):
+            few = small + stream
+            got = ("split" if split == join == 1 and not few + gemm + gemv else "gemm" if gemm and not few + split + gemv else "gemv" if gemv and not few else
+                   "sets" + ("+gemv" if gemv else "") if few == 1 and M > 16 else "stream" if stream else "burst" if small else "?")
+            assert rc == 0 and got == way, (N, K, r, M, bits, way, got, rc)
