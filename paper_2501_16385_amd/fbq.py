@@ -229,6 +229,21 @@ def upload_layer(p: PackedLayer, device="cuda") -> DeviceLayer:
     return DeviceLayer(p.desc, t(p.qweight), t(p.scales), t(p.zeros), t(p.At), t(p.Bt))
 
 
+def _scratch(d: Desc, M: int, device):
+    """A workspace for one call, or None.  Zeros only where the few-token kernels look for hand-over words (a size that the rows of a layer do not change); what
+    else 3 to 64 tokens keep there, megabytes of partial sums, is written before it is read."""
+    import torch
+    need = workspace_bytes(d, M)
+    if need == 0:
+        return None
+    words = 4 * workspace_bytes(Desc(1, d.K, d.r, d.bits, d.group), 16) if 2 < M <= 64 else need
+    if need <= words:
+        return torch.zeros(need, dtype=torch.uint8, device=device)
+    workspace = torch.empty(need, dtype=torch.uint8, device=device)
+    workspace[:words].zero_()
+    return workspace
+
+
 def linear(layer: DeviceLayer, x, y=None, workspace=None, stream=None):
     """fbq_linear: x [M, K] fp16 device tensor -> y [M, N] fp16 device tensor."""
     d = layer.desc
@@ -237,9 +252,8 @@ def linear(layer: DeviceLayer, x, y=None, workspace=None, stream=None):
         import torch
         if y is None:
             y = torch.empty((M, d.N), dtype=torch.float16, device=x.device)
-        need = 0 if workspace is not None else workspace_bytes(d, M)   # (a workspace that is given is checked by the library)
-        if need:
-            workspace = torch.zeros(need, dtype=torch.uint8, device=x.device)
+        if workspace is None:                           # (one that is given is checked by the library)
+            workspace = _scratch(d, M, x.device)
     if _lib is None:
         load()
     # one token through 4096 x 4096, us a call: 6.1 by way of ctypes' argument objects, 5.0 this way
@@ -263,9 +277,8 @@ def linear_unfused(layer: DeviceLayer, x, y=None, workspace=None, stream=None):
     M = int(x.shape[0])
     if y is None:
         y = torch.empty((M, d.N), dtype=torch.float16, device=x.device)
-    need = workspace_bytes(d, M)
-    if workspace is None and need:
-        workspace = torch.zeros(need, dtype=torch.uint8, device=x.device)
+    if workspace is None:
+        workspace = _scratch(d, M, x.device)
     wbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     rc = load().fbq_linear_unfused(ctypes.byref(d.c()), M, _dev_ptr(x), _dev_ptr(layer.qweight), _dev_ptr(layer.scales),
                                    _dev_ptr(layer.zeros), _dev_ptr(layer.At), _dev_ptr(layer.Bt), _dev_ptr(y), _dev_ptr(workspace),
@@ -305,10 +318,7 @@ def linear_group(layers, xs, ys=None, workspaces=None, stream=None):
     if ys is None:
         ys = [torch.empty((M, l.desc.N), dtype=torch.float16, device=x.device) for l, x in zip(layers, xs)]
     if workspaces is None:
-        workspaces = []
-        for l, x in zip(layers, xs):
-            need = workspace_bytes(l.desc, M)
-            workspaces.append(torch.zeros(need, dtype=torch.uint8, device=x.device) if need else None)
+        workspaces = [_scratch(l.desc, M, x.device) for l, x in zip(layers, xs)]
     arr = make_group(layers, xs, ys, workspaces)
     _check(load().fbq_linear_group(arr, len(layers), M, _stream(stream)), "fbq_linear_group")
     return ys

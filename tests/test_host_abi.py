@@ -261,3 +261,19 @@ def test_linear_refuses_host_tensors_as_before():
     layer = fbq.DeviceLayer(fbq.Desc(128, 128, 0, 4), torch.zeros(128, 16, dtype=torch.int32), *[torch.zeros(128, 1, dtype=torch.int16)] * 2, None, None)
     with pytest.raises(ValueError, match="device tensor"):
         fbq.linear(layer, torch.zeros(1, 128).half(), torch.zeros(1, 128).half(), torch.zeros(64, dtype=torch.uint8), stream=type("S", (), {"cuda_stream": 0}))
+
+
+def test_scratch_of_a_call_is_zero_where_hand_over_words_lie_and_nowhere_else_filled(monkeypatch):
+    """Calls without a workspace of their own: partial sums are megabytes that nobody reads before they are written."""
+    import torch
+    from paper_2501_16385_amd import fbq as binding
+    monkeypatch.setattr(torch, "empty", lambda n, **k: torch.full((n,), 0xAB, **k))
+    for N, K, r, M in [(8192, 28672, 64, 16), (8192, 28672, 0, 16), (131072, 4096, 64, 40), (5120, 13824, 128, 48), (131072, 4096, 64, 64), (4096, 4096, 64, 16), (4096, 4096, 8, 40),
+                       (4096, 4096, 64, 2), (4096, 4096, 0, 2), (4096, 4096, 64, 65)]:
+        d = fbq.Desc(N, K, r, 4)
+        ws, need, words = binding._scratch(d, M, "cpu"), fbq.workspace_bytes(d, M), 4 * 17 * 16 * r * 8
+        assert (ws is None) == (need == 0), (N, K, r, M)
+        if ws is None:
+            continue
+        zeros = need if M <= 2 or M > 64 else min(need, words)
+        assert ws.numel() == need and int(ws[:zeros].count_nonzero()) == 0 and bool((ws[zeros:] == 0xAB).all()), (N, K, r, M)
