@@ -1,7 +1,8 @@
 // The binding's call of fbq_linear for one layer whose result and workspace the caller keeps: collects the pointers of the tensors and calls the
 // library, without the argument objects that ctypes builds (one token through 4096 x 4096: the call took longer than its kernel, 6.1 us; 5.0 this way).
 // It knows nothing of torch: it asks the objects what the binding's Python code asks (is_cuda, is_contiguous(), data_ptr(), numel(),
-// element_size()).  Whatever is not as it should be makes it return None, and the Python code does the call, or raises.
+// element_size()).  Whatever is not as it should be makes it return None, and the Python code does the call, or raises;
+// exceptions that are no `Exception` pass through.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stdint.h>
@@ -67,6 +68,7 @@ static PyObject *linear(PyObject *self, PyObject *const *arg, Py_ssize_t n)
     ok = ok && pointer(arg[3], &p[6]) && pointer(arg[4], &p[7]);
     if (ok && arg[4] != Py_None) ok = number(PyObject_CallMethodNoArgs(arg[4], s_numel), &count) && number(PyObject_CallMethodNoArgs(arg[4], s_element_size), &each);
     if (!ok) {
+        if (PyErr_Occurred() && !PyErr_ExceptionMatches(PyExc_Exception)) return NULL;   // (an interrupt, say: not this call's to drop)
         PyErr_Clear();
         Py_RETURN_NONE;
     }

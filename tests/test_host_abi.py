@@ -252,6 +252,15 @@ def test_native_call_of_linear_hands_over_what_ctypes_would():
                 call(layer(), ws=tensor(2, contiguous=False)), call(layer(At=object())), call(layer(fbq.Desc(-8, 128, 0, 4))), call(layer(fbq.Desc(8.0, 128, 0, 4))),
                 call(layer(), x=tensor(64, shape=())), call(layer(), x=tensor(64, shape=(2.5,))), call(layer(), stream=None), call(NS())):
         assert odd is None and not seen
+    def fails(e):
+        def method():
+            raise e
+        return method
+    assert call(layer(), y=NS(is_cuda=True, is_contiguous=lambda: True, data_ptr=fails(RuntimeError("meta tensor")))) is None
+    for e in (KeyboardInterrupt, SystemExit):           # not dropped on the way to the Python code
+        with pytest.raises(e):
+            call(layer(), y=NS(is_cuda=True, is_contiguous=lambda: True, data_ptr=fails(e())))
+    assert not seen
     with pytest.raises(TypeError):
         _fbq_call.linear(address)
 
