@@ -279,7 +279,8 @@ fbq_status fbq_measure_read_stream(const void *buf, size_t bytes, fbq_stream str
  *
  * fbq_train_workspace_bytes - device scratch for fbq_gram (T tokens) and fbq_train_step: a copy
  *   of X (used where H16_out lies over X) and partial sums, or fp16 copies of the branch, Delta_F, the r-row products
- *   and the partial sums of contractions whose K range is split over blocks (about 4 N K bytes).
+ *   and the partial sums of contractions whose K range is split over blocks (about 4 N K bytes, of which a step leaves 2 N K alone: room for a
+ *   second orientation of Delta_F that it no longer writes is still asked for, so that what is refused does not change).
  *   0 for an invalid descriptor, r < 1 or T < 1.
  *
  * fbq_gram - H16_out [K,K] fp16 = fp16(h_scale * X^T X), accumulated in fp32 on the matrix cores.

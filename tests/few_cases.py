@@ -19,15 +19,15 @@ SETS_OR_GEMM_CASES = [
 ]
 
 SPLIT_CASES = [
-    # one to four sets, a token more or less than whole ones; last segments of one group; odd numbers of scales; a row more than whole
+    # and the way without room for partial sums.  One to four sets, a token more or less than whole ones; last segments of one group; odd numbers of scales; a row more than whole
     # tiles and units; no sub-branch, ranks on both sides of 16, 32 and 128; the shortest and the longest rows
-    (2048, 16512, 8, 3), (2049, 16640, 0, 8), (4099, 28672, 200, 16), (10239, 16512, 40, 9),
-    (4601, 8448, 72, 17), (2100, 14336, 0, 32), (5121, 13824, 136, 33), (3001, 8448, 8, 48), (4097, 14336, 256, 64),
-    (28673, 2048, 16, 50), (18001, 2176, 40, 49), (30001, 2176, 0, 20), (1025, 32768, 24, 63),
+    (2048, 16512, 8, 3, "burst"), (2049, 16640, 0, 8, "burst"), (4099, 28672, 200, 16, "burst"), (10239, 16512, 40, 9, "burst"),
+    (4601, 8448, 72, 17, "sets"), (2100, 14336, 0, 32, "sets"), (5121, 13824, 136, 33, "sets"), (3001, 8448, 8, 48, "sets"), (4097, 14336, 256, 64, "sets"),
+    (28673, 2048, 16, 50, "gemm"), (18001, 2176, 40, 49, "gemm"), (30001, 2176, 0, 20, "gemm"), (1025, 32768, 24, 63, "sets"),
 ]
 
 # further lines of the rule, on the CPU only
-ROUTE_CASES = SETS_OR_GEMM_CASES + [(N, K, r, M, "split") for N, K, r, M in SPLIT_CASES] + [
+ROUTE_CASES = SETS_OR_GEMM_CASES + [(N, K, r, M, "split") for N, K, r, M, _ in SPLIT_CASES] + [
     (2047, 16512, 8, 3, "burst"), (10240, 16512, 8, 3, "stream"), (4096, 16384, 64, 16, "burst"), (4096, 14336, 64, 8, "burst"), (2048, 16512, 8, 2, "gemv"),
     (4599, 8448, 72, 32, "sets"), (4600, 8448, 72, 32, "split"), (3399, 8448, 72, 18, "sets+gemv"), (3400, 8448, 72, 18, "split"), (3400, 8448, 72, 19, "sets"),
     (2304, 12288, 64, 32, "sets"), (2304, 12416, 64, 32, "split"), (1999, 12416, 64, 32, "sets"), (3000, 8320, 8, 48, "sets"), (3100, 8320, 8, 48, "split"),

@@ -73,6 +73,66 @@ def test_quantizer_where_32_bits_leave_rows_open(bits, N, K, r, kind):
     assert np.array_equal(codes[rows], want)
 
 
+def quantize_in_64_bits(W, A, B, bits):
+    """Scales, zeros and codes of W - B A as include/fbq.h defines them, on the GPU in fp64; s and z as fp16 numbers, rounded once."""
+    import torch
+
+    def half_once(d):                                   # by way of an fp32 number rounded to odd
+        f = d.float()
+        u = f.view(torch.int32)
+        u = torch.where(f.double().abs() > d.abs(), u - 1, u)
+        return torch.where(f.double() != d, u | 1, u).view(torch.float32).half()
+    N, K = W.shape
+    qmax = 2 ** bits - 1
+    R = (W.double() - B.double() @ A.double()).view(N, K // 128, 128)
+    lo, hi = R.amin(2), R.amax(2)
+    s = half_once(torch.where(hi > lo, (hi - lo) / qmax, torch.ones_like(hi))).clamp_min(2.0 ** -14)
+    while True:
+        z = half_once(-lo / s.double())
+        off = ~((lo / s.double() + z.double() >= -0.5) & (hi / s.double() + z.double() <= qmax + 0.5)) & (s < 65504)
+        if not bool(off.any()):
+            return s, z, torch.round(R / s.double()[:, :, None] + z.double()[:, :, None]).clamp_(0, qmax).view(N, K).to(torch.uint8)
+        s = torch.where(off, (s.view(torch.int16) + 1).view(torch.float16), s)
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("r", [8, 32, 64, 136, 256])
+@pytest.mark.parametrize("kind", ["one size", "mixed sizes", "cancelling", "subnormal", "one large", "near"])
+def test_codes_where_the_sums_in_32_bits_are_strained(kind, r, bits):
+    """The quantizer decides in 32 bits what a bound on the error of its sums allows; the bound rests on how the fp16 matrix instruction rounds (eight products at a time, operands cut 2^-24
+    below the largest, subnormals aligned as 2^-14).  Eight million elements a case, the branch as large as the weights or larger, so that hundreds lie within the bound of a rounding
+    boundary and as many just outside: products of one size and of sizes 2^24 apart, sums that cancel, subnormal operands, one product far above the rest.  Every word as in 64 bits."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    N, K = 2048, 4096
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1000 * r + bits)
+    rand = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    power = lambda lo, hi, *s: 2.0 ** torch.randint(lo, hi + 1, s, device="cuda", generator=g)
+    A, B = rand(r, K) * 0.1, rand(N, r) * 0.1
+    if kind == "one size":
+        A, B = torch.sign(A) * (1 + torch.rand(r, K, device="cuda", generator=g) * 2.0 ** -9) * 0.1, torch.sign(B) * 0.1
+    elif kind == "mixed sizes":
+        A, B = A * power(-12, 0, r, K), B * power(-12, 0, N, r)
+    elif kind == "cancelling":
+        A[1::2], B[:, 1::2] = A[::2] * (1 + rand(r // 2, K) * 2.0 ** -9), -B[:, ::2]
+    elif kind == "subnormal":
+        A, B = A * power(-18, -10, r, K), B * power(-6, 12, N, r)
+    elif kind == "one large":
+        A[r // 2] *= 64.0
+        B[:, r // 2] *= 64.0
+    A, B = A.half(), B.half()
+    sigma = B.double() @ A.double()
+    W = (sigma + (0.02 if kind == "near" else 1.0) * sigma.std() * rand(N, K)).half()
+    d = fbq.Desc(N, K, r, bits)
+    dev = fbq.quantize_feedback(d, W, A.view(torch.int16), B.view(torch.int16))
+    s, z, q = quantize_in_64_bits(W, A, B, bits)
+    assert torch.equal(dev.scales.view(torch.float16), s)
+    assert torch.equal(dev.zeros.view(torch.float16), z)
+    off = fbq.unpack_codes(dev) != q
+    assert not bool(off.any()), (int(off.sum()), off.nonzero()[:5].tolist())
+
+
 def quantize_group_by_the_book(R, qmax):
     """Scale, zero and codes of one group as include/fbq.h defines them, the scale stepped through every fp16 number: extremes that
     ignore NaN, comparisons that a NaN fails, clamping that turns a NaN into code 0."""
@@ -570,10 +630,12 @@ def test_stream_behind_the_other_entry_points(N, K, r, M, bits):
 
 
 @pytest.mark.parametrize("bits", [4, 3])
-@pytest.mark.parametrize("N,K,r,M", SPLIT_CASES)
-def test_split_edges(bits, N, K, r, M):
+@pytest.mark.parametrize("N,K,r,M,otherwise", SPLIT_CASES)
+def test_split_edges(bits, N, K, r, M, otherwise):
     """Against 64 bits, with the bound of exactly multiplied codes, on a workspace whose every byte was part of a NaN; the same bits again; and,
-    without the room that the split needs, within the bound of the path that serves such a workspace."""
+    without the room that the split needs, within the bound of the path that serves such a workspace: hand-over words are enough where the few-token kernels do, and
+    nothing less than the GEMM's own workspace where that does."""
+    import ctypes
     import torch
     import paper_2501_16385_amd as fbq
     dev, W, g = framed_random_layer(N, K, r, bits, 111 + N + M)
@@ -587,14 +649,52 @@ def test_split_edges(bits, N, K, r, M):
         fbq.linear(dev, x, y, ws)
     assert_matches_oracle(ys[0].cpu().numpy(), want, f"INT{bits} {N}x{K} r={r} M={M}", "few")
     assert torch.equal(ys[0], ys[1])
-    words = 17 * 16 * r * 8                              # hand-over words of 16 tokens
-    small = torch.zeros(-(-M // 16) * words, dtype=torch.uint8, device="cuda") if r else None
-    try:
-        fbq.linear_group([dev], [x], ys=[ys[1]], workspaces=[small])
-    except fbq.FbqError:
-        assert M > 16                                    # (where the GEMM would serve it, which needs more)
-    else:
-        assert_matches_oracle(ys[1].cpu().numpy(), want, f"INT{bits} {N}x{K} r={r} M={M}, smaller workspace", "few")
+    ptr = lambda t: None if t is None else t.data_ptr()
+
+    def given(size):
+        small = framed_in_nan(torch.zeros(size, dtype=torch.uint8, device="cuda")) if size else None
+        ys[1].fill_(float("nan"))
+        return fbq.load().fbq_linear(ctypes.byref(dev.desc.c()), M, x.data_ptr(), ptr(dev.qweight), ptr(dev.scales), ptr(dev.zeros), ptr(dev.At), ptr(dev.Bt),
+                                     ys[1].data_ptr(), ptr(small), size, torch.cuda.current_stream().cuda_stream)
+
+    words = -(-M // 16) * 17 * 16 * r * 8                # hand-over words of 16 tokens each
+    if otherwise == "gemm":
+        # activations in tiles, scales and zeros by group are the least that the GEMM keeps; its plan's partial sums may come on top
+        assert given(words) == (5 if words else 1) and given(4 * 17 * 16 * r * 8 + 2 * M * K) == 5
+        low, high = 4 * 17 * 16 * r * 8 + 2 * M * K, need    # refused, accepted
+        while high - low > 1:
+            low, high = (low, (low + high) // 2) if given((low + high) // 2) == 0 else ((low + high) // 2, high)
+        words = high
+    elif words:
+        assert given(words - 1) == 5
+    assert given(words) == 0
+    torch.cuda.synchronize()
+    assert_matches_oracle(ys[1].cpu().numpy(), want, f"INT{bits} {N}x{K} r={r} M={M}, smaller workspace", "prefill" if otherwise == "gemm" else "few")
+
+
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("N,K,r", [(2050, 16640, 64), (19001, 4096, 40)])
+def test_one_workspace_for_split_and_other_calls(bits, N, K, r):
+    """One workspace, zero-filled once, for calls of every kind: what a split call keeps lies behind the hand-over words of the others, and each gives what it gives by itself."""
+    import torch
+    import paper_2501_16385_amd as fbq
+    dev, W, g = framed_random_layer(N, K, r, bits, 131 + N)
+    counts = [40, 5, 1, 64, 70, 16, 2, 17, 48, 33, 9]
+    ws = torch.zeros(max(fbq.workspace_bytes(dev.desc, M) for M in counts), dtype=torch.uint8, device="cuda")
+    front = 4 * 17 * 16 * r * 8
+    splits = 0
+    for M in counts:
+        x = torch.randn(M, K, device="cuda", generator=g).half()
+        alone = fbq.linear(dev, x)
+        before = ws[:front].clone()
+        y = fbq.linear(dev, x, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(y, alone), M
+        assert_matches_oracle(y.cpu().numpy(), (x.double() @ W.T).cpu().numpy(), f"INT{bits} {N}x{K} r={r} M={M}", "prefill" if M > 64 else "few" if M > 2 else "gemv")
+        if fbq.workspace_bytes(dev.desc, M) > front:     # split, or the GEMM
+            splits += M <= 64
+            assert torch.equal(ws[:front], before), M
+    assert splits >= 4
 
 
 @pytest.mark.parametrize("bits", [4, 3])

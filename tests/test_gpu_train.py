@@ -180,8 +180,8 @@ def test_reconstruction_loop_lowers_the_loss_and_keeps_the_bound():
 
 
 @pytest.mark.parametrize("bits,N,K,r", [(3, 4100, 4096, 8), (4, 2100, 2048, 72), (4, 1030, 4096, 136), (3, 4100, 4096, 72), (4, 70, 256, 200), (3, 129, 128, 128)])
-def test_delta_in_both_orientations_at_the_quantizers_block_shapes(bits, N, K, r):
-    """Blocks of four and eight waves, of one and two row tiles, rows past the last: the gradients, which see Delta_F in both orientations,
+def test_gradients_at_the_quantizers_block_shapes(bits, N, K, r):
+    """Blocks of four and eight waves, of one and two row tiles, rows past the last: the gradients, one of which contracts Delta_F over its rows and the other over its columns,
     against 64 bits from the step's own layer.  Three roundings to fp16 of 2^-11 each, as above: 2e-3."""
     g = torch.Generator(device="cuda")
     g.manual_seed(N + r)
@@ -325,3 +325,49 @@ def test_every_element_of_delta_is_that_of_64_bits(bits, N, K, r, kind):
     want = (256.0 * (R.view(N, K // 128, 128) - s * (fbq.unpack_codes(plain).view(N, K // 128, 128) - z))).view(N, K).float().half()
     off = stored_delta(st) != want
     assert not bool(off.any()), (int(off.sum()), off.nonzero()[:5].tolist())
+
+
+@pytest.mark.parametrize("bits,N,K,r", [(4, 1000, 1024, 64), (3, 65, 384, 200), (4, 4100, 512, 8), (3, 300, 4096, 128)])
+def test_step_stays_inside_the_workspace_asked_for(bits, N, K, r):
+    """A workspace of exactly that size, between guard bytes, holds all that a step writes; a larger one gives the same bits."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(23 + N)
+    rand = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    d, W, At, Bt = fbq.Desc(N, K, r, bits), (rand(N, K) * 0.02).half(), rand(r, K) * 0.01, rand(N, r) * 0.01
+    H16 = fbq.gram(d, rand(300, K).half(), 1.0 / 256)
+    need, guard = fbq.train_workspace_bytes(d, 1), 4096
+    results = []
+    for room in (need, 2 * need):
+        st = fbq.train_state(d, At.clone(), Bt.clone())
+        whole = torch.full((room + 2 * guard,), 0xA5, dtype=torch.uint8, device="cuda")
+        st.workspace = whole[guard:guard + room]
+        fbq.train_step(st, W, H16, 1.0 / 256, 1e-4)
+        assert bool((whole[:guard] == 0xA5).all()) and bool((whole[guard + need:] == 0xA5).all())
+        results.append([st.layer.qweight, st.layer.scales, st.layer.zeros, st.grad_At, st.grad_Bt, st.At32, st.Bt32, st.loss])
+    assert all(torch.equal(a, b) for a, b in zip(*results))
+    st.workspace = whole[guard:guard + need - 1]
+    with pytest.raises(fbq.FbqError, match="workspace"):
+        fbq.train_step(st, W, H16, 1.0 / 256, 1e-4)
+
+
+def test_gram_over_its_activations_in_a_replayed_graph():
+    """H written over X goes by way of a copy of X, also in a captured graph: every replay on new activations gives what an eager call gives, with eager work in between."""
+    K, T = 384, 1000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(29)
+    d = fbq.Desc(128, K, 8, 4)
+    both = torch.zeros(T * K, dtype=torch.float16, device="cuda")
+    ws = torch.empty(fbq.train_workspace_bytes(d, T), dtype=torch.uint8, device="cuda")
+    call = lambda: fbq.load().fbq_gram(ctypes.byref(d.c()), T, both.data_ptr(), 1.0 / 16, both.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert call() == 0
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        assert call() == 0
+    for _ in range(4):
+        X = torch.randint(-3, 4, (T, K), device="cuda", generator=g).half()
+        want = fbq.gram(d, X, 1.0 / 16)
+        both.copy_(X.flatten())
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(both[: K * K].view(K, K), want)

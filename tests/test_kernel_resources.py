@@ -60,6 +60,27 @@ def test_streaming_instances_have_their_registers_and_a_cu_each(kernels):
         assert 80 * 1024 < k[".group_segment_fixed_size"] <= 160 * 1024, n
 
 
+def test_split_instances_have_their_registers_and_a_cu_each(kernels):
+    """As the streaming kernel's: two waves per SIMD without scratch memory, and more than half of the LDS, since the plan counts one block per CU."""
+    split = {n: k for n, k in kernels.items() if "fbq_few_split_kernel<" in n}
+    assert len(split) == 10                                         # 2 bit widths x (1 set of up to 8 and up to 16 tokens, 2, 3, 4 sets)
+    for n, k in split.items():
+        assert k[".vgpr_count"] <= 256 and k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, n
+        assert 80 * 1024 < k[".group_segment_fixed_size"] <= 160 * 1024, n
+
+
+def test_quantizer_instances_have_their_registers(kernels):
+    """No scratch memory, and the waves a SIMD that the launch bounds ask for wherever the LDS allows them: four without Delta_F, three with (two above rank 128)."""
+    quant = {n: k for n, k in kernels.items() if "fbq_quantize_kernel<" in n}
+    assert len(quant) == 22                                         # 2 bit widths x (4 shapes with and without Delta_F, 3 in fp64 with it)
+    for n, k in quant.items():
+        delta, steps, waves = re.search(r"<\d, (\w+), (\d), (\d)", n).groups()
+        assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, n
+        blocks = 160 * 1024 // k[".group_segment_fixed_size"]       # of `waves` waves on four SIMDs
+        wanted = min(blocks * int(waves) // 4, 4 if delta == "false" else 2 if steps == "8" else 3)
+        assert k[".vgpr_count"] <= 512 // wanted // 8 * 8, (n, k[".vgpr_count"], wanted)
+
+
 def test_inline_assembly_declares_the_scalar_register_it_overwrites():
     """M0 belongs to the compiler: a statement that moves an LDS address into it without saying so would silently change
     whatever value the compiler keeps there."""
