@@ -637,7 +637,9 @@ hipError_t launch_quantize(const fbq_desc &d, const uint16_t *W, const uint16_t 
     // room for two blocks at most (11008 x 4096 INT4, r = 200: 125 us with four, 96 with eight), unless those are too few to go round.
     // Tiles a block: two, which halves the work of getting At into LDS (r = 64, INT3, 11008 x 4096: 55 us with one tile, 50 with two, 49 with three),
     // where the GPU is full with them; one without a sub-branch (30, 32, 33 us: blocks that start in the order of the rows read memory best).
-    const bool wide = d.r > 128 && G * ceil_div(d.N, 128) >= 256;
+    // (Not with Delta_F, either, where such blocks go round once and a little: r = 200, 5000 x 1024, 320 blocks, the kernel 67.3 us with eight waves, 62.7 with four; with 384 blocks a step 124.0 and 125.8.)
+    const int wide_blocks = G * ceil_div(d.N, 128);
+    const bool wide = d.r > 128 && wide_blocks >= 256 && !(D16 && wide_blocks > 256 && wide_blocks < 352);
     const int rows = wide ? 128 : 64, blocks = G * ceil_div(d.N, rows);
     const int tiles = d.r > 0 && blocks >= (wide ? 1024 : 2048) ? 2 : 1;
     const dim3 grid(G, ceil_div(d.N, rows * tiles));
