@@ -84,8 +84,8 @@ size_t fbq_packed_bytes(const fbq_desc *d);
  * re-ordered for the matrix cores (M rows of K fp16), scales and zeros by group (K/g rows of N words, N rounded up
  * to 256), t as two fp16 halves and its partial sums, and, where the launch splits K over blocks, fp32 partial
  * outputs (up to 8 x M x N); not 0 even when r == 0.  0 for an invalid descriptor or M < 1.
- * 3 <= M <= 64 where K is split over blocks (see fbq_linear): also room for the fp32 partial sums, K segments x token
- * rows x N, not 0 even when r == 0.  A workspace without that room, as large as the hand-over words (or, where the sets of 16
+ * 3 <= M <= 64 where K is split over blocks (see fbq_linear): room for the hand-over words of 64 tokens, and behind it the fp32 partial sums, K segments x
+ * tokens (a multiple of 16) x (N + r), not 0 even when r == 0.  A workspace without that room, as large as the hand-over words (or, where the sets of 16
  * would not serve the call, the path of M > 64) ask for - NULL where that is 0 - is accepted too; the call then goes unsplit, with the same error bound
  * or that path's and other last bits.
  * The size is NOT monotonic in M (fewer tokens can mean more K slices or a K split with partial outputs): a workspace
@@ -118,8 +118,9 @@ fbq_status fbq_pack(const fbq_desc *d, const uint8_t *codes, const uint16_t *sca
  * down-projection; 17 <= M <= 64 is the same launch with the sets of 16 tokens side by side (the packed words are read
  * once per 16 tokens and the codes multiplied exactly; one or two tokens left over go through the GEMV
  * or, in larger layers, are a set too; a layer so large that reading it two to four times costs far more takes the path
- * of M > 64 instead).  With long rows (up to 16 tokens from 14336 activations on in layers of 2048 to 10239 rows, with more above 8192
- * and in those large layers) K is split over blocks that take all tokens of the call at once, and a second launch adds up.  M > 64 runs the fp16 MFMA GEMM after a pass that
+ * of M > 64 instead).  With long rows (up to 16 tokens above 16384 activations in layers
+ * of 2048 to 10239 rows, 17 to 64 above 8192) and in large layers of 17 to 64 tokens that the sets do not serve, K is split over blocks that take all tokens of the call
+ * at once, and a second launch adds up.  M > 64 runs the fp16 MFMA GEMM after a pass that
  * re-orders x and a separate down-projection; a layer with too few output tiles to fill the GPU has
  * its K range split over up to 8 blocks per tile, summed in fp32 by a last small launch.
  *   x         device [M, K] fp16             qweight, scales, zeros, At, Bt: device, layout above
@@ -127,7 +128,8 @@ fbq_status fbq_pack(const fbq_desc *d, const uint8_t *codes, const uint16_t *sca
  *   workspace device, >= fbq_workspace_bytes(d, M) bytes (may be NULL when that is 0).  Zero-fill it
  *             once after allocating it; after that it needs no care between calls, on any stream
  *             and under graph replay: every launch marks what it writes with its own identity.
- *             Calls that may run concurrently must not share a workspace.
+ *             Calls that may run concurrently must not share a workspace (layers without a sub-branch
+ *             included: where K is split they keep partial sums there).
  * Errors: FBQ_ERR_NULL, _SHAPE, _UNSUPPORTED, _ALIGN, _WORKSPACE before any launch; FBQ_ERR_HIP.
  * Up to 16 tokens the blocks that use t wait a bounded number of polls (32768, about 10 ms) for the
  * blocks of the same launch that compute it, then compute their share themselves (same results, slower;
@@ -146,6 +148,7 @@ fbq_status fbq_linear(const fbq_desc *d, int M, const void *x, const void *qweig
  *   Arguments as for fbq_linear, without workspace and workspace_bytes.  M <= 16 only: larger token
  *   counts need scratch that grows with M, N and K and are refused with FBQ_ERR_UNSUPPORTED;
  *   FBQ_ERR_WORKSPACE if the layer's scratch would not fit the array (it always fits for r <= 256).
+ *   Where fbq_linear splits K over blocks this call does not: as with a workspace without room for the partial sums, its last bits differ from fbq_linear's there.
  *   All calls on one GPU share that GPU's array, on whatever stream: calls that may overlap in time on
  *   one GPU race on it and must be ordered by the caller.  Nothing needs clearing between calls (the
  *   array starts zeroed and every launch marks what it writes with its own identity).
@@ -189,10 +192,12 @@ typedef struct {
  * same bits and K that read the SAME x (the same pointer) and all have a sub-branch (or all have
  * none) share one launch, up to 4 layers (two launches where layers of 10240 rows and 40 million codes or more, which have
  * a kernel of their own, come with smaller ones and K is below 2048 or above 12288, or above 4096 with smaller ones that fill
- * the GPU by themselves).  Anything else, and every layer when M > 16, is launched on its own.
+ * the GPU by themselves).  Layers whose K fbq_linear splits over blocks share two launches with each other and none with the rest: beside others of the same x, which takes K above
+ * 16384 and rows on both sides of 2048 or 10240, they cost a launch or two more than unsplit ({8192, 1024} x 28672 INT4, 16 tokens: 49.7 us, 40.9 with workspaces of the
+ * size of the hand-over words, which leave them unsplit).  Anything else, and every layer when M > 16, is launched on its own.
  *   calls host array of n layers (read during the call only); M tokens, the same for all layers
  * Errors: those of fbq_linear for any layer, and FBQ_ERR_WORKSPACE if the workspaces of two layers
- * overlap, reported before ANY launch.
+ * overlap in what they cannot do without, reported before ANY launch (a layer whose room for partial sums meets another's workspace goes unsplit).
  */
 fbq_status fbq_linear_group(const fbq_layer_call *calls, int n, int M, fbq_stream stream);
 
@@ -232,7 +237,9 @@ fbq_status fbq_unpack_codes(const fbq_desc *d, const void *qweight, uint8_t *cod
 /*
  * fbq_quantize_feedback - the step before the path: the feedback quantizer Q(W - Sigma) of
  * Sec. 4.1 / Alg. 1 (forward line), group-wise asymmetric round-to-nearest, computed on the GPU
- * in fp64 and written straight into the device layout.  Per row and group: mn, mx of
+ * and written straight into the device layout.  The result is that of fp64: rows of a group that 32-bit sums with a bound on their error leave
+ * open are done again in fp64, at about 1.2 times the time of fp64 throughout where that is nearly all of them (weights on half steps, or so far from zero
+ * that |z| is above 1024).  Per row and group: mn, mx of
  * R = W - Sigma; s = fp16((mx - mn)/qmax) (1 if the group is constant, never below the smallest
  * normal fp16); z = fp16(-mn/s); s is stepped to the next fp16 until both ends of the range lie
  * within half a step of [0, qmax]; q = clamp(round_half_even(R/s + z), 0, qmax).

@@ -1,4 +1,4 @@
-// What the two kernels for 3 to 16 tokens share (device code): matrix-core helpers, the order of the activations, the
+// What the kernels for 3 to 64 tokens share (device code): matrix-core helpers, the order of the activations, the
 // down-projection inside the launch and its hand-over.
 #ifndef FBQ_FEW_TOKENS_H
 #define FBQ_FEW_TOKENS_H

@@ -53,7 +53,7 @@ struct LinearArgs {
     int M, N, K, r, bits;
     const uint16_t *mix_with;   // [M][N] and ...
     uint16_t *mix_out;          // ... null, or [M][N] that the decode launchers write y averaged with mix_with to (see launch_mix)
-    FewSplit split;             // 3 to 64 tokens: how K is split over blocks (see takes_split), where the workspace has room for it
+    FewSplit split;             // 3 to 64 tokens: how K is split over blocks (see split_of), where the workspace has room for it
 };
 
 // 3 to 16 tokens: which of the two kernels serves a layer of N rows (for sets of 16 tokens side by side: rows times sets).  Of

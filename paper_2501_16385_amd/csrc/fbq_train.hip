@@ -353,9 +353,9 @@ static GemmArgs gemm_args(const uint16_t *A, int Mr, int lda, const uint16_t *B,
 // rounds.  Few tiles: the contraction is split over blocks - for free where only the dot product is wanted (it is linear in
 // G), through fp32 partial tiles and a summing launch otherwise.
 // Bound: matrix cores; 4096 x 4096 in us, the whole square in 128-row tiles staged through registers / this: H over 2048 tokens
-// 103 / 41, the loss over 4096 rows 196 / 71 (both 34 and 69 GFLOP of the triangle: 0.84 and 0.97 PFLOP/s).
-// H used to be taken from a transposed copy of X, 7 us more at this size (46.4 / 40.6 for all of H, 128 features over some tokens 18.0 / 15.6); the
-// turned reads are twice as many instructions for the same bytes and cost nothing beside the matrix instructions.
+// 103 / 41, the loss over 4096 rows 196 / 74 (34 and 69 GFLOP of the triangle: 0.84 and 0.93 PFLOP/s).
+// H used to be taken from a transposed copy of X, 7 us more at this size (46.4 / 40.6 for all of H, 128 features over some tokens 18.0 / 15.6), and the loss from a second, transposed Delta_F.  The
+// turned reads are twice as many instructions for the same bytes and cost the loss 4 us (70.6 / 74.6 on one box), of the 13 that writing Delta_F twice cost the quantizer.
 // Other sizes leave the last round emptier and keep the gain; H with that transpose, the square / this: 3072 features, 4096 tokens
 // 152 / 66 (136 tiles); 5120, 2048 185 / 81 (378); 8192, 512 168 / 80 (946); 11008, 4096 1362 / 493 (1711).
 constexpr int kSyTile = 192, kSyWave = 96, kSyStages = 3;

@@ -197,3 +197,43 @@ def test_which_way_a_call_of_few_tokens_takes(recorder):
             got = ("split" if split == join == 1 and not few + gemm + gemv else "gemm" if gemm and not few + split + gemv else "gemv" if gemv and not few else
                    "sets" + ("+gemv" if gemv else "") if few == 1 and M > 16 else "stream" if stream else "burst" if small else "?")
             assert rc == 0 and got == way, (N, K, r, M, bits, way, got, rc)
+
+
+QUANT_CHILD = r"""
+import ctypes, json, re, sys
+sys.path[:0] = [sys.argv[1]]
+import paper_2501_16385_amd as fbq
+lib = fbq.load()
+launched = []
+
+@ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_char_p, ctypes.POINTER(ctypes.c_void_p))
+def on_launch(name, args):
+    launched.append(name.decode())
+    return 0
+
+ctypes.CDLL(None).recorder_set_callback(on_launch)
+p = lambda i: 0x100000000 * (i + 1)
+out = []
+for step, N, K, r in json.loads(sys.argv[2]):
+    d = fbq.Desc(N, K, r, 4)
+    launched.clear()
+    if step:
+        assert lib.fbq_train_step(ctypes.byref(d.c()), p(0), p(1), 1.0, p(2), p(3), 0.0, *(p(i) for i in range(4, 11)), None, p(11), fbq.train_workspace_bytes(d, 1), None) == 0
+    else:
+        assert lib.fbq_quantize_feedback(ctypes.byref(d.c()), p(0), p(1), p(2), p(3), p(4), p(5), None) == 0
+    out += [list(map(int, re.search(r"fbq_quantize_kernelILi4ELb(\d)ELi(\d)ELi(\d)ELb(\d)", n).groups())) for n in launched if "fbq_quantize_kernel" in n]
+print("RESULT " + json.dumps(out))
+"""
+
+
+def test_which_instance_of_the_quantizer_a_layer_takes(recorder):
+    """With Delta_F, steps of 32 taps, waves a block, in fp64 throughout: a block a CU or less; by rank; eight waves above rank 128 where they fill the GPU, and with Delta_F not
+    where they go round once and a little."""
+    import json
+    want = {(1, 1000, 1024, 64): [1, 2, 4, 1], (1, 2048, 1024, 128): [1, 4, 4, 1], (1, 2049, 1024, 64): [1, 2, 4, 0], (1, 2049, 1024, 72): [1, 4, 4, 0], (1, 1000, 1024, 200): [1, 8, 4, 1],
+            (1, 2048, 2048, 200): [1, 8, 8, 0], (1, 2049, 2048, 200): [1, 8, 4, 0], (1, 5000, 1024, 200): [1, 8, 4, 0], (1, 2816, 2048, 200): [1, 8, 8, 0], (1, 1920, 2048, 200): [1, 8, 4, 0],
+            (0, 1000, 1024, 64): [0, 2, 4, 0], (0, 5000, 1024, 200): [0, 8, 8, 0], (0, 1000, 1024, 200): [0, 8, 4, 0], (0, 1000, 1024, 0): [0, 2, 4, 0]}
+    env = dict(os.environ, LD_PRELOAD=" ".join([recorder] + os.environ.get("LD_PRELOAD", "").split()))
+    res = subprocess.run([sys.executable, "-c", QUANT_CHILD, ROOT, json.dumps(list(want))], env=env, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
+    assert json.loads(res.stdout.split("RESULT ")[1]) == list(want.values())
