@@ -16,6 +16,8 @@ SETS_OR_GEMM_CASES = [
     (5121, 5120, 24, 33, "sets+gemv"), (5121, 5120, 24, 34, "sets"), (2601, 8320, 96, 49, "sets"),
     # the GEMM at the shortest rows, at rows that fill little of two segments, and where a split is one segment
     (40001, 1920, 40, 33, "gemm"), (19001, 2176, 24, 50, "gemm"), (30001, 2048, 136, 64, "gemm"), (25001, 2176, 0, 48, "gemm"),
+    # long rows that a first form of the rule split, and four sets of which one has one token
+    (2048, 14336, 8, 3, "burst"), (2049, 14464, 0, 8, "burst"), (10239, 16384, 40, 9, "burst"), (3001, 8448, 72, 17, "sets+gemv"), (28001, 2176, 40, 49, "gemm"), (4097, 14336, 96, 49, "split"),
 ]
 
 SPLIT_CASES = [
